@@ -23,11 +23,13 @@ extern "C" {
  * quantize, 1 = vectorised quantize, 2 = element-wise copy, 3 = vectorised copy,
  * 4 = vectorised quantize of one whole bucket of 4096 or 8192 elements, 5 = the short end
  * of a layer (less than a chunk of 2048 elements) with power-of-two buckets, 6 = whole buckets
- * of a size that is no power of two, at most a chunk in all (streamed row by row; only the ragged
- * end of such a layer and sizes above the chunk take the generic kind 0).
+ * of a size that is no power of two, at most a chunk in all (the ragged end of such a layer and
+ * sizes above the chunk are kind 0; kinds 0, 5 and 6 run through the same code if they hold at most a
+ * chunk).
  * Every element of every non-empty layer lies in exactly one tile and tiles never
  * cross layers (paper Sec. 4.1).  This is the table of one chunk per vectorised
- * tile that most calls walk: cgx_quantize on a binary16 gradient of 2^24 elements
+ * tile that the statistics walk.  The other calls cut pass-through layers into tiles of 1024
+ * elements instead of 8192, a reduction also cuts buckets longer than a chunk, and cgx_quantize on a binary16 gradient of 2^24 elements
  * or more, and the fused reduce + requantize on 2^27 elements or more, join 2
  * consecutive chunks of a layer into one tile (same bytes out; a wave's set-up is
  * spread over more input).  At most `capacity` records

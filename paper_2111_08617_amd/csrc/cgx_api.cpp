@@ -24,6 +24,7 @@ struct CachedPlan {
     uint64_t digest = 0;        // hash of (off, bits, layer_buckets): compared before the arrays themselves
     int chunk = 0;              // elements per chunk of the kernels that walk this table
     int chunks_per_tile = 0;
+    cgx::TableUse use = cgx::kStatistics;
     std::vector<int64_t> off;
     std::vector<uint8_t> bits;
     std::vector<int32_t> layer_buckets;   // empty: `bucket` for every layer; else the table holds the
@@ -32,9 +33,8 @@ struct CachedPlan {
     cgx::PlanShape shape;
     int64_t n_tiles = 0;
     int64_t plan_tiles = 0;     // tiles of the whole plan: n_tiles, or the sum over the launches of a layered plan
-    bool odd_tiles = false;     // some vectorised quantized tile starts on an odd element index
+    bool odd_tiles = false;     // some quantized tile starts on an odd element index
     bool aligned_tiles = true;  // every vectorised quantized tile starts on a 16-byte boundary of the buffer
-    bool many_tails = false;    // the reduce kernel with the masked path for short ends of layers pays (see get_plan)
     Tile *d_tiles = nullptr;
     // per-layer numbering of the tiles (for the statistics): slot of every tile, first slot of every layer
     uint32_t *d_slots = nullptr;
@@ -189,7 +189,7 @@ uint64_t plan_digest(int32_t L, const int64_t *off, const uint8_t *bits, const i
 // and a table that does not exist yet is not built during a capture (that would allocate and copy
 // synchronously in the middle of it): the call fails with CGX_ERR_CAPTURE and records nothing.
 int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
-             int chunks_per_tile, PlanRef *out, const int32_t *layer_buckets = nullptr, bool with_copies = true)
+             int chunks_per_tile, cgx::TableUse use, PlanRef *out, const int32_t *layer_buckets = nullptr, bool with_copies = true)
 {
     const uint64_t digest = plan_digest(L, off, bits, layer_buckets);       // before the lock is taken
     std::lock_guard<std::mutex> lock(g_mutex);
@@ -200,7 +200,7 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     if (!capturing) (void)hipGetLastError();       // a refused query (legacy stream beside a capture) is not this call's error
     for (const auto &p : g_plans) {
         if (p->digest == digest && p->device == device && p->bucket == bucket && p->dt == dt &&
-            p->chunk == chunk && p->chunks_per_tile == chunks_per_tile && p->bits.size() == size_t(L) &&
+            p->chunk == chunk && p->chunks_per_tile == chunks_per_tile && p->use == use && p->bits.size() == size_t(L) &&
             p->with_copies == with_copies && p->layer_buckets.size() == (layer_buckets ? size_t(L) : 0) &&
             (!layer_buckets || L == 0 ||
              std::memcmp(p->layer_buckets.data(), layer_buckets, sizeof(int32_t) * size_t(L)) == 0) &&
@@ -223,6 +223,7 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     plan->dt = dt;
     plan->chunk = chunk;
     plan->chunks_per_tile = chunks_per_tile;
+    plan->use = use;
     plan->off.assign(off, off + L + 1);
     plan->bits.assign(bits, bits + L);
     if (layer_buckets) plan->layer_buckets.assign(layer_buckets, layer_buckets + L);
@@ -231,12 +232,13 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     std::vector<Tile> tiles;
     std::vector<uint32_t> slots;
     std::vector<int64_t> layer_first;
-    cgx::build_tiles(L, off, bits, bucket, dt, chunk, chunks_per_tile, tiles, &slots, &layer_first, layer_buckets,
-                     with_copies);
+    const bool numbered = use == cgx::kStatistics;
+    cgx::build_tiles(L, off, bits, bucket, dt, chunk, chunks_per_tile, tiles, numbered ? &slots : nullptr,
+                     numbered ? &layer_first : nullptr, layer_buckets, with_copies, use);
     if (tiles.size() > size_t(0xffffffffu)) return CGX_ERR_SIZE;
     plan->n_tiles = int64_t(tiles.size());
     plan->plan_tiles = plan->n_tiles;
-    if (layer_buckets) {
+    if (layer_buckets && numbered) {
         // The per-layer statistics number the tiles of the WHOLE plan layer by layer; this table
         // holds one launch's share of them, so its tiles take their numbers in that common order.
         std::vector<int64_t> common(size_t(L) + 1, 0);
@@ -259,16 +261,11 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
         plan->plan_tiles = common[size_t(L)];
     }
     for (const Tile &t : tiles)
-        if ((cgx::is_streamed_kind(cgx::tile_kind(t)) || cgx::tile_kind(t) == cgx::kQuantTail) && (t.elem0 & 1))
+        if (cgx::is_quantized_kind(cgx::tile_kind(t)) && (t.elem0 & 1))
             plan->odd_tiles = true;
     for (const Tile &t : tiles)
         if (cgx::is_vector_kind(cgx::tile_kind(t)) && (t.elem0 * (dt == CGX_F16 ? 2 : 4)) % 16 != 0)
             plan->aligned_tiles = false;
-    int64_t tails = 0;
-    for (const Tile &t : tiles) tails += cgx::tile_kind(t) == cgx::kQuantTail;
-    // One short end that goes through the generic path is a chain of dependent round trips,
-    // bucket after bucket: hidden in a long launch, it outlasts the rest of a short one.
-    plan->many_tails = tails > 0 && (plan->n_tiles < 16384 || tails * 512 >= plan->n_tiles);
     if (!upload(&plan->d_tiles, tiles) || !upload(&plan->d_slots, slots) ||
         !upload(&plan->d_layer_first, layer_first)) {
         free_plan(*plan);
@@ -291,12 +288,12 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
 // The tables of all launches of a call, looked up before its first launch: a call that fails for a
 // missing table (CGX_ERR_CAPTURE) has then queued nothing.
 int get_plans(hipStream_t stream, const std::vector<Launch> &launches, int32_t L, const int64_t *off,
-              const uint8_t *bits, int dt, int chunk, int chunks_per_tile, const int32_t *layer_buckets,
+              const uint8_t *bits, int dt, int chunk, int chunks_per_tile, cgx::TableUse use, const int32_t *layer_buckets,
               std::vector<PlanRef> *out)
 {
     out->resize(launches.size());
     for (size_t i = 0; i < launches.size(); i++) {
-        const int rc = get_plan(stream, L, off, bits, launches[i].bucket, dt, chunk, chunks_per_tile, &(*out)[i],
+        const int rc = get_plan(stream, L, off, bits, launches[i].bucket, dt, chunk, chunks_per_tile, use, &(*out)[i],
                                 layer_buckets, launches[i].with_copies);
         if (rc != CGX_OK) return rc;
     }
@@ -334,7 +331,7 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
     const std::vector<Launch> launches = launches_of(buckets, L, off, bits, chunk);
     std::vector<PlanRef> plans;
     rc = get_plans(static_cast<hipStream_t>(stream), launches, L, off, bits, dt, chunk, tile_length(kQuantizeCall, dt, n),
-                   buckets.per_layer, &plans);
+                   cgx::kWholeBuckets, buckets.per_layer, &plans);
     if (rc != CGX_OK) return rc;
     for (size_t i = 0; i < launches.size(); i++) {
         const Launch &launch = launches[i];
@@ -374,7 +371,7 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
     const std::vector<Launch> launches = launches_of(buckets, L, off, bits, chunk);
     std::vector<PlanRef> plans;
     rc = get_plans(static_cast<hipStream_t>(stream), launches, L, off, bits, dt, chunk,
-                   tile_length(kOtherCall, dt, n), buckets.per_layer, &plans);
+                   tile_length(kOtherCall, dt, n), cgx::kPieces, buckets.per_layer, &plans);
     if (rc != CGX_OK) return rc;
     const auto launch_reduce = chunk == cgx::kDefaultChunk ? cgx::launch_dequant_reduce_g4 : cgx::launch_dequant_reduce_g2;
     for (size_t li = 0; li < launches.size(); li++) {
@@ -398,7 +395,7 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
             // writer gains.  A decompression's stores go through at system scope whatever the size.
             const bool small = int64_t(n) * (out_dt == CGX_F16 ? 2 : 4) <= launch_config().keep_sums_max_bytes;
             const int policy = decompression ? cgx::kStoreThrough : small ? cgx::kStoreKeep : cgx::kStoreStream;
-            const hipError_t e = launch_reduce(scheme, peers, k, dt, plan->d_tiles, plan->n_tiles, plan->many_tails,
+            const hipError_t e = launch_reduce(scheme, peers, k, dt, plan->d_tiles, plan->n_tiles,
                                                launch.bucket, init, init_dt, out, out_dt, policy, launch_config(),
                                                static_cast<hipStream_t>(stream));
             if (e != hipSuccess) return CGX_ERR_HIP;
@@ -431,10 +428,10 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
     for (const Launch &launch : launches_of(buckets, L, layer_offsets, bits_per_layer, cgx::kDefaultChunk)) {
         PlanRef in, out;
         rc = get_plan(static_cast<hipStream_t>(stream), L, layer_offsets, bits_per_layer, launch.bucket, dt,
-                      cgx::kDefaultChunk, tile_length(kFusedCall, dt, n), &in, buckets.per_layer, launch.with_copies);
+                      cgx::kDefaultChunk, tile_length(kFusedCall, dt, n), cgx::kWholeBuckets, &in, buckets.per_layer, launch.with_copies);
         if (rc != CGX_OK) return rc;
         rc = get_plan(static_cast<hipStream_t>(stream), L, layer_offsets, bits_per_layer, launch.bucket, CGX_F32,
-                      cgx::kDefaultChunk, tile_length(kFusedCall, dt, n), &out, buckets.per_layer, launch.with_copies);
+                      cgx::kDefaultChunk, tile_length(kFusedCall, dt, n), cgx::kWholeBuckets, &out, buckets.per_layer, launch.with_copies);
         if (rc != CGX_OK) return rc;
         if (in->n_tiles != out->n_tiles) return CGX_ERR_SIZE;     // cannot happen: same tiling for both layouts
         const hipError_t e = cgx::launch_dequant_reduce_requantize(
@@ -480,7 +477,7 @@ int sqerrors_impl(int scheme, const void *grad, const void *packed, const void *
     const std::vector<Launch> launches = launches_of(buckets, L, off, bits, cgx::kDefaultChunk);
     std::vector<PlanRef> plans;
     rc = get_plans(static_cast<hipStream_t>(stream), launches, L, off, bits, dt, cgx::kDefaultChunk,
-                   tile_length(kOtherCall, dt, n), buckets.per_layer, &plans);
+                   tile_length(kOtherCall, dt, n), cgx::kStatistics, buckets.per_layer, &plans);
     if (rc != CGX_OK) return rc;
     for (const PlanRef &plan : plans)
         if (workspace_bytes < size_t(plan->plan_tiles) * sizeof(double)) return CGX_ERR_SIZE;
@@ -763,7 +760,7 @@ int cgx_layer_sqnorms(const void *buf, int64_t n, int32_t L, const int64_t *laye
     if (misaligned(buf) || misaligned(workspace) || (reinterpret_cast<uintptr_t>(sqnorm) & 7u)) return CGX_ERR_ALIGN;
     PlanRef plan;
     rc = get_plan(static_cast<hipStream_t>(stream), L, layer_offsets, zeros.data(), 32, int(dt), cgx::kDefaultChunk,
-                  tile_length(kOtherCall, int(dt), n), &plan);
+                  tile_length(kOtherCall, int(dt), n), cgx::kStatistics, &plan);
     if (rc != CGX_OK) return rc;
     if (workspace_bytes < size_t(plan->n_tiles) * sizeof(double)) return CGX_ERR_SIZE;
     const hipError_t e = cgx::launch_layer_sqnorms(buf, int(dt), plan->d_tiles, plan->d_slots, plan->n_tiles,

@@ -402,17 +402,24 @@ __device__ __forceinline__ void flush_stage(const uint4v *stage, uint4v *dst, in
 //                  eight bytes per byte they read (cgx_dequantize).  An arithmetic-free kernel in that mix
 //                  sustains 0.61 of the HBM peak with non-temporal loads and stores, 0.75 with ordinary
 //                  loads and these stores (8 KB per wave), and 0.91 with 4 KB per wave
-__device__ __forceinline__ void flush_stage_to_elements(const uint4v *stage, uint4u2 *dst, int vecs, int lane, int policy)
+// at(v): where vector v sits in the staging area.
+template <typename At>
+__device__ __forceinline__ void flush_stage_to_elements(const uint4v *stage, uint4u2 *dst, int vecs, int lane, int policy, At at)
 {
     if (policy == kStoreKeep) {
         for (int v = lane; v < vecs; v += kWave)
-            asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(dst + v), "v"(stage[v]) : "memory");
+            asm volatile("global_store_dwordx4 %0, %1, off sc1" : : "v"(dst + v), "v"(stage[at(v)]) : "memory");
     } else if (policy == kStoreThrough) {
         for (int v = lane; v < vecs; v += kWave)
-            asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt" : : "v"(dst + v), "v"(stage[v]) : "memory");
+            asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1 nt" : : "v"(dst + v), "v"(stage[at(v)]) : "memory");
     } else {
-        for (int v = lane; v < vecs; v += kWave) __builtin_nontemporal_store(stage[v], dst + v);
+        for (int v = lane; v < vecs; v += kWave) __builtin_nontemporal_store(stage[at(v)], dst + v);
     }
+}
+
+__device__ __forceinline__ void flush_stage_to_elements(const uint4v *stage, uint4u2 *dst, int vecs, int lane, int policy)
+{
+    flush_stage_to_elements(stage, dst, vecs, lane, policy, [](int v) { return v; });
 }
 
 // One 16-byte vector per lane from global memory straight into LDS, without passing
@@ -436,6 +443,13 @@ __device__ __forceinline__ void load_to_lds16_cached(const uint4v *gptr, uint4v 
 __device__ __forceinline__ void wait_vector_memory()
 {
     __builtin_amdgcn_s_waitcnt(0x0f70);
+}
+
+// Waits until this wave's LDS reads have delivered (s_waitcnt lgkmcnt(0)): an area that asynchronous loads
+// fill next has then been read.
+__device__ __forceinline__ void wait_lds_reads()
+{
+    __builtin_amdgcn_s_waitcnt(0xc07f);
 }
 
 // b bytes holding 8 codes into the LDS staging area at a multiple of b bytes: exactly b bytes
@@ -513,49 +527,123 @@ struct LaneMap {
     __device__ __forceinline__ int group(int r) const { return e_lane + r * row; }
 };
 
-// The short end of a layer (fewer elements than a chunk, whole buckets and possibly a ragged last
-// one) goes through the chunk code with the missing elements masked.
-struct TailShape {
-    int count;       // elements of the tile
-    int buckets;     // its buckets (the last one may be short)
-    int nvecs;       // 16-byte vectors of its packed bytes (the layer's zero padding included)
-    template <int BITS>
-    __device__ __forceinline__ static TailShape of(const Tile &tile, int bucket)
-    {
-        TailShape t;
-        t.count = int(tile.count);
-        t.buckets = (t.count + bucket - 1) / bucket;
-        t.nvecs = ((t.count * BITS + 7) / 8 + 15) / 16;
-        return t;
-    }
-    // how many of the 8 elements of the group that starts at chunk element e exist
-    __device__ __forceinline__ int valid(int e) const { return count - e >= 8 ? 8 : count - e > 0 ? count - e : 0; }
-};
-
-// A tile of whole buckets of a size that is no power of two (kQuantAny): held row by row, group Gi = 64 r +
-// lane of the tile's count / 8 groups of 8 elements is group r of lane `lane`; a bucket is bucket / 8
-// consecutive groups.
-struct AnyShape {
-    int groups;      // groups of 8 elements in the tile
-    int gb;          // groups per bucket
-    int m;           // buckets in the tile (at most 21: the smallest such bucket is 96)
-    uint32_t inv;    // ceil(2^16 / gb): (Gi * inv) >> 16 == Gi / gb for Gi < 256 and gb <= 256 (checked exhaustively)
-    __device__ __forceinline__ AnyShape(const Tile &tile, int bucket)
-    {
-        groups = int(tile.count >> 3);
-        gb = bucket >> 3;
-        m = int(tile.count) / bucket;
-        inv = (65536u + uint32_t(gb) - 1u) / uint32_t(gb);
-    }
-    __device__ __forceinline__ int bucket_of(int Gi) const { return int((uint32_t(Gi) * inv) >> 16); }
-};
-
-// One dword per lane from global memory straight into LDS: lane l's dword lands at lds_base + 4 * l.
-__device__ __forceinline__ void load_to_lds4(const uint32_t *gptr, uint32_t *lds_base)
+// All element pairs of the tile share the upper 32 bits of their pair index: the generator's key is uniform over it.
+__device__ __forceinline__ bool one_key_block(const Tile &tile)
 {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)gptr,
-                                     (__attribute__((address_space(3))) void *)lds_base, 4, 0, 2 /* nt */);
+    return uint32_t((uint64_t(tile.elem0) >> 1) >> 32) == uint32_t((uint64_t(tile.elem0 + tile.count - 1) >> 1) >> 32);
 }
+
+// A run: at most a chunk of consecutive elements of one layer, with buckets of any size, whole or ragged (the short
+// ends of layers, and everything whose bucket size is no power of two).  Such a tile used to be bound by the number of
+// dependent round trips of its one wave (row order with two peers staged at a time; ragged ends element by element):
+// a fused step over 20 M binary16 elements, buckets of 160, ragged layers, 4 peers, 85 us then and 26 us in lane order;
+// 43 M elements, buckets of 96, 8 bits, 113 and 49 us.  Lane l holds the 8 G elements from 8 G l
+// on.  Bucket sizes are multiples of 32, so all of them belong to one bucket: a lane keeps one scale and one entry of
+// meta per peer, as in the bucket-major mapping, and a bucket is bucket / (8 G) consecutive lanes.  A run that is a
+// piece of a bucket longer than the chunk lies in its bucket 0.
+struct Run {
+    int count;       // elements
+    int lanes;       // lanes per bucket
+    int buckets;     // buckets (the last one may be short)
+    int bi;          // bucket of this lane (lanes past the end: the last bucket)
+    int left;        // elements from this lane's first one to the end (any sign)
+    __device__ __forceinline__ Run(int count_, int bucket, int lane) : count(count_)
+    {
+        lanes = bucket / (8 * G);
+        // (l + 0.5) / lanes lies at least 0.5 / lanes from every whole number: the approximate reciprocal is exact enough
+        const float inv = __builtin_amdgcn_rcpf(float(lanes));
+        const int last = int((float((count - 1) / (8 * G)) + 0.5f) * inv);
+        buckets = __builtin_amdgcn_readfirstlane(last) + 1;
+        bi = int((float(lane) + 0.5f) * inv);
+        bi = bi < buckets ? bi : buckets - 1;
+        left = count - lane * (8 * G);
+    }
+    // how many of the 8 elements of group r exist
+    __device__ __forceinline__ int valid(int r) const { return left - 8 * r >= 8 ? 8 : left - 8 * r > 0 ? left - 8 * r : 0; }
+};
+
+// Where 16-byte vector v of a run sits in LDS, PER_LANE vectors per lane: within blocks of PER_LANE vectors the order
+// is permuted so that 16 neighbouring lanes that each access "their" vector c touch 16 different bank groups (in plain
+// order they would touch 16 / PER_LANE of them).  Its own inverse.
+template <int PER_LANE>
+__device__ __forceinline__ int run_slot(int v)
+{
+    return v ^ ((v >> 4) & (PER_LANE - 1));
+}
+
+// The elements of a run on their way from the buffer into lane order: rows of whole 16-byte vectors (consecutive
+// across lanes, at any element alignment), through LDS.  issue() queues the loads, finish() waits for them;
+// elements that do not exist are 0.  The LDS area holds a chunk as stored.
+template <int DT>
+struct RunLoad {
+    static constexpr int kPerVec = DT == CGX_F16 ? 8 : 4;            // elements per vector
+    static constexpr int kRows = kChunk / kPerVec / kWave;           // loads
+    static constexpr int kPerLane = 8 * G / kPerVec;                 // vectors a lane owns
+    uint4v raw[kRows];
+    uint32_t rest;                                                   // one of the elements behind the last whole vector
+    __device__ __forceinline__ void issue(const void *buf, int64_t elem0, int count, int lane)
+    {
+        using Vec = std::conditional_t<DT == CGX_F16, uint4u2, uint4u4>;
+        const uint8_t *first = static_cast<const uint8_t *>(buf) + elem0 * (16 / kPerVec);
+        const Vec *src = reinterpret_cast<const Vec *>(first);
+        const int whole = count / kPerVec;
+#pragma unroll
+        for (int k = 0; k < kRows; k++) {
+            raw[k] = uint4v{0u, 0u, 0u, 0u};
+            if (k * kWave + lane < whole) raw[k] = __builtin_nontemporal_load(src + k * kWave + lane);
+        }
+        rest = 0;
+        const int e = whole * kPerVec + lane;
+        if (lane < kPerVec && e < count)
+            rest = DT == CGX_F16 ? uint32_t(reinterpret_cast<const uint16_t *>(first)[e]) : reinterpret_cast<const uint32_t *>(first)[e];
+    }
+    // waits for the loads and parks the run in LDS
+    __device__ __forceinline__ void park(int count, int lane, uint4v *stage) const
+    {
+#pragma unroll
+        for (int k = 0; k < kRows; k++) stage[run_slot<kPerLane>(k * kWave + lane)] = raw[k];
+        const int whole = count / kPerVec;
+        wave_lds_fence();
+        if (lane < kPerVec && whole * kPerVec + lane < count) {      // into the vector that was staged as zeros
+            uint4v *last = stage + run_slot<kPerLane>(whole);
+            if (DT == CGX_F16)
+                reinterpret_cast<uint16_t *>(last)[lane] = uint16_t(rest);
+            else
+                reinterpret_cast<uint32_t *>(last)[lane] = rest;
+        }
+        wave_lds_fence();
+    }
+    // group r of this lane
+    __device__ __forceinline__ static void group(const uint4v *stage, int lane, int r, float (&x)[8])
+    {
+#pragma unroll
+        for (int c = 0; c < 8 / kPerVec; c++) {
+            const uint4v v = stage[run_slot<kPerLane>(lane * kPerLane + r * (8 / kPerVec) + c)];
+            if (DT == CGX_F16) {
+                const half8v h = __builtin_bit_cast(half8v, v);
+#pragma unroll
+                for (int j = 0; j < 8; j++) x[j] = float(h[j]);
+            } else {
+                const float4v f = __builtin_bit_cast(float4v, v);
+#pragma unroll
+                for (int j = 0; j < 4; j++) x[4 * c + j] = f[j];
+            }
+        }
+    }
+    // the area is filled anew right after this
+    __device__ __forceinline__ static void release()
+    {
+        wait_lds_reads();
+        wave_lds_fence();
+    }
+    __device__ __forceinline__ void finish(int count, int lane, uint4v *stage, float (&x)[G][8]) const
+    {
+        park(count, lane, stage);
+#pragma unroll
+        for (int r = 0; r < G; r++) group(stage, lane, r, x[r]);
+        release();
+    }
+};
 
 // Runs CALL with BITS = bits as a constant (kNormSign has no 1-bit codes: the entry points
 // reject such plans, and nothing is instantiated for them).

@@ -260,167 +260,137 @@ __device__ __forceinline__ void quantize_wide(const void *__restrict__ grad, uin
     }
 }
 
-// x holds the tile's elements in the chunk mapping, 0 where there is none -> meta and codes.
-template <int SCHEME, int BITS, bool ODD>
-__device__ __forceinline__ void quantize_tail_regs(const float (&x)[G][8], const TailShape &shape, const LaneMap &map,
-                                                   int lane, int64_t first, uint32_t key, float *__restrict__ meta,
-                                                   uint8_t *__restrict__ out, uint4v *stage)
+// The codes of a lane's groups of a run (8 * BITS bits each, group after group) into LDS, G * BITS bytes per lane.
+// The area starts on 16 bytes.
+template <int BITS>
+__device__ __forceinline__ void stage_run_codes(uint8_t *area, const uint64_t (&codes)[G], int lane)
 {
-    constexpr uint32_t kLevels = top_level<SCHEME>(BITS);
+    if constexpr (G == 4) {
+        // 32 codes are BITS whole dwords
+        constexpr int kAlign = BITS % 4 == 0 ? 16 : BITS % 2 == 0 ? 8 : 4;
+        uint32_t w[BITS + 2] = {};
+#pragma unroll
+        for (int r = 0; r < G; r++) {
+            const int d = r * BITS / 4, shift = r * BITS % 4 * 8;
+            w[d] |= uint32_t(codes[r] << shift);
+            w[d + 1] |= uint32_t((codes[r] << shift) >> 32);
+            if (shift && BITS > 4) w[d + 2] |= uint32_t(codes[r] >> (64 - shift));
+        }
+        __builtin_memcpy(__builtin_assume_aligned(area + lane * (4 * BITS), kAlign), w, 4 * BITS);
+    } else {
+#pragma unroll
+        for (int r = 0; r < G; r++) stage_codes<BITS>(area + (lane * G + r) * BITS, codes[r]);
+    }
+}
+
+// LDS a wave needs to quantize a run of storage type DT: the chunk as stored; later its codes with 16 bytes of
+// padding, an extent per lane and a scale per bucket.
+template <int DT>
+constexpr int kRunStageBytes = kChunk * (DT == CGX_F16 ? 2 : 4) > kChunk + 16 + 2 * kWave * 8 ? kChunk * (DT == CGX_F16 ? 2 : 4)
+                                                                                              : kChunk + 16 + 2 * kWave * 8;
+
+// Extent (kNormSign: +0 and the largest magnitude) of the elements of a run that a lane holds; nothing: the neutral one.
+template <int SCHEME>
+__device__ __forceinline__ float2 run_extent(const float (&x)[G][8], const Run &run)
+{
     // kNormSign: the zeros of the missing elements are neutral for the largest magnitude
     float mn = SCHEME == kNormSign ? 0.0f : __builtin_inff(), mx = SCHEME == kNormSign ? 0.0f : -__builtin_inff();
+    if (SCHEME == kNormSign || run.left >= 8 * G) {
+        lane_extent<SCHEME>(x, mn, mx);
+    } else {
 #pragma unroll
-    for (int r = 0; r < G; r++) {
-        const int v = shape.valid(map.group(r));
+        for (int r = 0; r < G; r++) {
+            const int v = run.valid(r);
 #pragma unroll
-        for (int j = 0; j < 8; j++) {
-            if (SCHEME == kNormSign) {
-                mx = __builtin_fmaxf(mx, __builtin_fabsf(x[r][j]));
-            } else {
+            for (int j = 0; j < 8; j++) {
                 mn = __builtin_fminf(mn, j < v ? x[r][j] : __builtin_inff());
                 mx = __builtin_fmaxf(mx, j < v ? x[r][j] : -__builtin_inff());
             }
         }
     }
-    if (SCHEME == kNormSign)
-        group_max(mx, map.lg, lane);
-    else
-        group_minmax(mn, mx, map.lg, lane);
-    const Scale s = bucket_scale(mn, mx, int(kLevels));
-    if (map.lp == 0 && map.bi < shape.buckets) store_meta<SCHEME>(meta, map.bi, s);
-#pragma unroll
-    for (int r = 0; r < G; r++) {
-        const int v = shape.valid(map.group(r));
-        const uint32_t pair0 = uint32_t(uint64_t(first + map.group(r)) >> 1);
-        uint64_t codes = encode_group<SCHEME, BITS, ODD>(x[r], s, pair0, key, uint32_t(first) & 1u);
-        codes &= v == 8 ? ~uint64_t(0) : (uint64_t(1) << (v * BITS)) - 1u;       // nothing past the layer's end
-        stage_codes<BITS>(reinterpret_cast<uint8_t *>(stage) + (map.group(r) >> 3) * BITS, codes);
-    }
-    // every group of the chunk has been staged (zeros past the end), so whole vectors can leave:
-    // they carry the zero padding of the layer's segment with them
-    wave_lds_fence();
-    flush_stage(stage, reinterpret_cast<uint4v *>(out), shape.nvecs, lane);
-    wave_lds_fence();
+    return make_float2(mn, mx);
 }
 
-template <int SCHEME, int DT, int BITS, bool ODD>
-__device__ __forceinline__ void quantize_tail(const void *__restrict__ grad, uint8_t *__restrict__ packed,
-                                              float *__restrict__ meta, const Tile &tile, int bucket,
-                                              uint32_t seed_lo, uint32_t seed_hi, int lane, uint4v *stage)
-{
-    const LaneMap map(tile, bucket, lane);
-    const TailShape shape = TailShape::of<BITS>(tile, bucket);
-    const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
-    float x[G][8];
-#pragma unroll
-    for (int r = 0; r < G; r++) {
-        const int e = map.group(r), v = shape.valid(e);
-        if (v == 8) {
-            load8<DT>(grad, tile.elem0 + e, x[r]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; j++) x[r][j] = j < v ? load_elem<DT>(grad, tile.elem0 + e + j) : 0.0f;
-        }
-    }
-    quantize_tail_regs<SCHEME, BITS, ODD>(x, shape, map, lane, tile.elem0, key,
-                                          meta + kMetaFloats<SCHEME> * tile.bucket0, packed + tile.packed_off, stage);
-}
-
-// LDS a wave needs for a tile of kind kQuantAny: its codes, a minimum and a maximum per group, a scale per bucket.
-constexpr int kAnyStageBytes = kChunk + 2 * (kChunk / 8) * 4 + kWave * 8;
-
-// x holds the tile row by row (zeros where there is no group) -> meta of its buckets and its packed codes.
-// The scale of a bucket comes from a per-group minimum / maximum parked in LDS: the lanes are split into
-// groups of P (a power of two, 64 / P >= buckets), each of which folds the entries of one bucket.
+// The run's codes under a scale per lane: staged, then sent out with `pad` zero bytes behind them.  out is a multiple
+// of 4 bytes, and so is the number of bytes written: a run starts a multiple of 32 codes into its segment of the
+// stream and either ends one or is padded to the segment's 16 bytes.
 template <int SCHEME, int BITS, bool ODD>
-__device__ __forceinline__ void quantize_any_regs(const float (&x)[G][8], const AnyShape &shape, const Tile &tile,
-                                                  uint32_t key, float *__restrict__ meta, uint8_t *__restrict__ out,
-                                                  uint4v *stage, int lane)
+__device__ __forceinline__ void encode_run(const float (&x)[G][8], const Run &run, const Scale &s, int lane, int64_t first,
+                                           uint32_t key, uint8_t *__restrict__ out, uint32_t pad, uint4v *stage)
+{
+    uint8_t *area = reinterpret_cast<uint8_t *>(stage);
+    uint64_t codes[G];
+#pragma unroll
+    for (int r = 0; r < G; r++) {
+        const uint32_t pair0 = uint32_t(uint64_t(first + (lane * G + r) * 8) >> 1);
+        codes[r] = encode_group<SCHEME, BITS, ODD>(x[r], s, pair0, key, uint32_t(first) & 1u);
+        const int v = run.valid(r);
+        codes[r] &= v == 8 ? ~uint64_t(0) : (uint64_t(1) << (v * BITS)) - 1u;       // nothing past the end
+        // one group after the other: together they cost the kernel registers that every path of it then pays
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    stage_run_codes<BITS>(area, codes, lane);
+    if (lane < 4) reinterpret_cast<uint32_t *>(area + kChunk * BITS / 8)[lane] = 0;      // padding behind a full chunk
+    wave_lds_fence();
+    const int bytes = (run.count * BITS + 7) / 8 + int(pad), vecs = bytes / 16;
+    for (int v = lane; v < vecs; v += kWave) __builtin_nontemporal_store(stage[v], reinterpret_cast<uint4u4 *>(out) + v);
+    if (lane < (bytes & 15) / 4) reinterpret_cast<uint32_t *>(out)[vecs * 4 + lane] = reinterpret_cast<const uint32_t *>(area)[vecs * 4 + lane];
+    wave_lds_fence();
+}
+
+// x holds a run (zeros where there is no element) -> meta of its buckets and its packed codes.  The scale of a
+// bucket comes from an extent per lane parked in LDS: the lanes are split into sets of P (a power of two,
+// 64 / P >= buckets > 32 / P, so a lane folds at most two entries), each of which folds the extents of one bucket.
+template <int SCHEME, int BITS, bool ODD>
+__device__ __forceinline__ void quantize_run_regs(const float (&x)[G][8], const Run &run, int lane, int64_t first, uint32_t key,
+                                                  float *__restrict__ meta, uint8_t *__restrict__ out, uint32_t pad, uint4v *stage)
 {
     constexpr uint32_t kLevels = top_level<SCHEME>(BITS);
-    uint8_t *codes = reinterpret_cast<uint8_t *>(stage);
-    float *gmn = reinterpret_cast<float *>(codes + kChunk), *gmx = gmn + kChunk / 8;
-    float2 *scales = reinterpret_cast<float2 *>(gmx + kChunk / 8);
-#pragma unroll
-    for (int r = 0; r < G; r++) {
-        const int Gi = r * kWave + lane;
-        float mn = SCHEME == kNormSign ? 0.0f : x[r][0], mx = SCHEME == kNormSign ? 0.0f : x[r][0];
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            if (SCHEME == kNormSign) {
-                mx = __builtin_fmaxf(mx, __builtin_fabsf(x[r][j]));
-            } else {
-                mn = __builtin_fminf(mn, x[r][j]);
-                mx = __builtin_fmaxf(mx, x[r][j]);
-            }
-        }
-        if (Gi < shape.groups) {
-            gmn[Gi] = mn;
-            gmx[Gi] = mx;
-        }
-    }
+    float2 *extents = reinterpret_cast<float2 *>(reinterpret_cast<uint8_t *>(stage) + kChunk + 16), *scales = extents + kWave;
+    extents[lane] = run_extent<SCHEME>(x, run);
     wave_lds_fence();
-    const int lgP = 31 - __builtin_clz(uint32_t(kWave / shape.m));      // floor(log2(64 / buckets))
-    const int bucket_of_lane = lane >> lgP, part = lane & ((1 << lgP) - 1);
+    const int lgP = run.buckets > 1 ? __builtin_clz(uint32_t(run.buckets - 1)) - 26 : 6, P = 1 << lgP;
+    const int bucket = lane >> lgP, part = lane & (P - 1), entry = bucket * run.lanes + part;
     float mn = SCHEME == kNormSign ? 0.0f : __builtin_inff(), mx = SCHEME == kNormSign ? 0.0f : -__builtin_inff();
-    if (bucket_of_lane < shape.m) {
-        for (int g = part; g < shape.gb; g += 1 << lgP) {
-            if (SCHEME != kNormSign) mn = __builtin_fminf(mn, gmn[bucket_of_lane * shape.gb + g]);
-            mx = __builtin_fmaxf(mx, gmx[bucket_of_lane * shape.gb + g]);
-        }
+    if (part < run.lanes && entry < kWave) {
+        const float2 e = extents[entry];
+        mn = e.x, mx = e.y;
+    }
+    if (part + P < run.lanes && entry + P < kWave) {
+        const float2 e = extents[entry + P];
+        if (SCHEME != kNormSign) mn = min_plain(mn, e.x);
+        mx = max_plain(mx, e.y);
     }
     if (SCHEME == kNormSign)
         group_max(mx, lgP, lane);
     else
         group_minmax(mn, mx, lgP, lane);
-    if (bucket_of_lane < shape.m && part == 0) {
-        const Scale s = bucket_scale(mn, mx, int(kLevels));
-        store_meta<SCHEME>(meta, uint32_t(bucket_of_lane), s);
-        scales[bucket_of_lane] = make_float2(s.mn, s.inv16);
+    const Scale of_set = bucket_scale(mn, mx, int(kLevels));
+    if (part == 0 && bucket < run.buckets) {
+        store_meta<SCHEME>(meta, uint32_t(bucket), of_set);
+        scales[bucket] = make_float2(of_set.mn, of_set.inv16);
     }
     wave_lds_fence();
-#pragma unroll
-    for (int r = 0; r < G; r++) {
-        const int Gi = r * kWave + lane;
-        if (Gi < shape.groups) {
-            const float2 sc = scales[shape.bucket_of(Gi)];
-            const Scale s{0.0f, sc.x, sc.y};
-            const uint32_t pair0 = uint32_t(uint64_t(tile.elem0 + int64_t(Gi) * 8) >> 1);
-            stage_codes<BITS>(codes + Gi * BITS, encode_group<SCHEME, BITS, ODD>(x[r], s, pair0, key, uint32_t(tile.elem0) & 1u));
-        }
-    }
-    wave_lds_fence();
-    // the tile's codes are groups * BITS bytes, a multiple of 4, at a multiple of 4 in the stream
-    const int dwords = shape.groups * BITS / 4;
-    uint32_t *dst = reinterpret_cast<uint32_t *>(out);
-    for (int v = lane; v < dwords; v += kWave) stream_store(dst + v, reinterpret_cast<const uint32_t *>(codes)[v]);
-    if (uint32_t(lane) < tile.pad) out[shape.groups * BITS + lane] = 0;        // the layer's zero padding
-    wave_lds_fence();
+    const float2 own = scales[run.bi];
+    encode_run<SCHEME, BITS, ODD>(x, run, Scale{0.0f, own.x, own.y}, lane, first, key, out, pad, stage);
 }
 
 template <int SCHEME, int DT, int BITS, bool ODD>
-__device__ __forceinline__ void quantize_any(const void *__restrict__ grad, uint8_t *__restrict__ packed,
+__device__ __forceinline__ void quantize_run(const void *__restrict__ grad, uint8_t *__restrict__ packed,
                                              float *__restrict__ meta, const Tile &tile, int bucket,
                                              uint32_t seed_lo, uint32_t seed_hi, int lane, uint4v *stage)
 {
-    const AnyShape shape(tile, bucket);
+    const Run run(int(tile.count), bucket, lane);
     const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
+    RunLoad<DT> load;
+    load.issue(grad, tile.elem0, run.count, lane);
     float x[G][8];
-#pragma unroll
-    for (int r = 0; r < G; r++) {
-        const int Gi = r * kWave + lane;
-        if (Gi < shape.groups) {
-            load8<DT>(grad, tile.elem0 + int64_t(Gi) * 8, x[r]);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; j++) x[r][j] = 0.0f;
-        }
-    }
-    quantize_any_regs<SCHEME, BITS, ODD>(x, shape, tile, key, meta + kMetaFloats<SCHEME> * tile.bucket0,
-                                         packed + tile.packed_off, stage, lane);
+    load.finish(run.count, lane, stage, x);
+    quantize_run_regs<SCHEME, BITS, ODD>(x, run, lane, tile.elem0, key, meta + kMetaFloats<SCHEME> * tile.bucket0,
+                                         packed + tile.packed_off, tile.pad, stage);
 }
 
-// Any bucket size, any alignment, ragged last bucket: one bucket at a time, two passes.
+// What no other path takes (a tile across two key blocks of the generator): one bucket at a time, two passes.
 // value(j) gives element j of the tile (called twice per element).  With BATCH the values
 // of a pass are fetched 8 at a time so that plain loads overlap; without it (value() is
 // itself a reduction over the peers) they are taken one by one.
@@ -508,8 +478,17 @@ __device__ __forceinline__ void copy_tile(const void *__restrict__ grad, uint8_t
     uint32_t done = 0;
     if (fast) {
         const uint32_t vecs = bytes / 16;
-        for (uint32_t v = lane; v < vecs; v += kWave)
-            reinterpret_cast<uint4v *>(dst)[v] = reinterpret_cast<const uint4u2 *>(src)[v];
+        // all loads of a tile (kCopyPiece elements) in flight together
+        constexpr int kLoads = kCopyPiece * S / 16 / kWave;
+        for (uint32_t v0 = lane; v0 < vecs; v0 += kLoads * kWave) {
+            uint4v raw[kLoads];
+#pragma unroll
+            for (int u = 0; u < kLoads; u++)
+                if (v0 + u * kWave < vecs) raw[u] = reinterpret_cast<const uint4u2 *>(src)[v0 + u * kWave];
+#pragma unroll
+            for (int u = 0; u < kLoads; u++)
+                if (v0 + u * kWave < vecs) reinterpret_cast<uint4v *>(dst)[v0 + u * kWave] = raw[u];
+        }
         done = vecs * 16;
     } else if (DT == CGX_F16) {
         for (uint32_t e = lane; e < tile.count; e += kWave)

@@ -114,30 +114,60 @@ __device__ __forceinline__ void codes_to_scaled_float(uint64_t v, float (&f)[8])
     }
 }
 
+// The codes of a lane's G groups of a run, group r's 8 in the low 8 * BITS bits of v[r] (bits above are unspecified).
+// codes: the run's first code in LDS, a multiple of 4 bytes, of 8 at 2 and 6 bits and of 16 at 4 and 8 bits (a run
+// starts a multiple of 32 codes into its layer).
+template <int BITS>
+__device__ __forceinline__ void run_codes(const uint8_t *codes, int lane, uint64_t (&v)[G])
+{
+    if constexpr (G == 4) {
+        // 32 codes are BITS whole dwords
+        constexpr int kAlign = BITS % 4 == 0 ? 16 : BITS % 2 == 0 ? 8 : 4;
+        uint32_t w[BITS + 2];
+        __builtin_memcpy(w, __builtin_assume_aligned(codes + lane * (4 * BITS), kAlign), 4 * BITS);
+        w[BITS] = w[BITS + 1] = 0;
+#pragma unroll
+        for (int r = 0; r < G; r++) {
+            const int d = r * BITS / 4, shift = r * BITS % 4 * 8;
+            const uint32_t lo = shift ? __builtin_amdgcn_alignbit(w[d + 1], w[d], shift) : w[d];
+            const uint32_t hi = BITS <= 4 ? 0u : shift ? __builtin_amdgcn_alignbit(w[d + 2], w[d + 1], shift) : w[d + 1];
+            v[r] = (uint64_t(hi) << 32) | lo;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < G; r++) v[r] = staged_codes<BITS>(codes, (lane * G + r) * BITS);
+    }
+}
+
 // Folds peers w0 .. w0+WB-1 into acc.  Each peer's share of the chunk (kChunk*BITS/8 bytes)
 // is fetched as whole 16-byte vectors, consecutive across lanes, directly into the wave's
 // LDS staging area, and read back by the lanes that own the codes.
-// TAIL: the chunk is the short end of a layer; only its first nvecs 16-byte vectors exist in the
-// packed streams (what lies behind them in LDS is stale, and so are the sums of elements past
-// the end: the caller drops them).
+// RUN: the chunk is a run (code_off unused).  Its codes start on a multiple of 4 bytes only; the vectors that
+// cover them are fetched (nvecs of them from the 16-byte boundary at or before in_off: they stay inside the layer's
+// segment, which starts and ends on 16 bytes).  What lies behind the run's end in LDS is stale, and so are the
+// sums of elements past the end: the caller drops them.
 // PAIRED: the two-per-instruction conversion above; the result says whether every peer's unit allowed it:
 // if not, acc holds garbage and the caller forms the sums again without PAIRED.
-template <int SCHEME, int BITS, int WB, bool TAIL, bool PAIRED, typename Peers>
+template <int BITS>
+constexpr int kRunLead = BITS % 4 == 0 ? 0 : 16;      // bytes between that boundary and the first code, at most 12
+
+template <int SCHEME, int BITS, int WB, bool RUN, bool PAIRED, typename Peers>
 __device__ __forceinline__ bool reduce_peers(Peers &peers, int w0, int64_t in_off, uint32_t g,
                                              const int (&code_off)[G], float (&acc)[G][8], uint4v *stage,
                                              int lane, int nvecs)
 {
-    constexpr int kBytes = kChunk * BITS / 8;        // per peer
+    constexpr int kBytes = kChunk * BITS / 8 + (RUN ? kRunLead<BITS> : 0);        // per peer
     constexpr int kVecs = kBytes / 16;
     constexpr int kPerLane = (kVecs + kWave - 1) / kWave;
+    const int lead = RUN && kRunLead<BITS> ? int(in_off & 15) : 0;
     float2 m[WB];
 #pragma unroll
     for (int i = 0; i < WB; i++) {
-        const uint4v *in = reinterpret_cast<const uint4v *>(peers.packed[w0 + i] + in_off);
+        const uint4v *in = reinterpret_cast<const uint4v *>(peers.packed[w0 + i] + (in_off - lead));
 #pragma unroll
         for (int k = 0; k < kPerLane; k++) {
             const int v = lane + k * kWave;
-            if (TAIL ? v < nvecs : (kVecs % kWave == 0 || v < kVecs)) {
+            if (RUN ? v < nvecs : (kVecs % kWave == 0 || v < kVecs)) {
                 // a block of one peer is what a decompression (W = 1) consists of: ordinary loads there
                 if (WB == 1)
                     load_to_lds16_cached(in + v, stage + i * kVecs + k * kWave);
@@ -149,7 +179,7 @@ __device__ __forceinline__ bool reduce_peers(Peers &peers, int w0, int64_t in_of
     }
     wait_vector_memory();
     wave_lds_fence();
-    const uint8_t *codes = reinterpret_cast<const uint8_t *>(stage);
+    const uint8_t *codes = reinterpret_cast<const uint8_t *>(stage) + lead;
     bool usable = true;
 #pragma unroll
     for (int i = 0; i < WB; i++) {
@@ -157,13 +187,20 @@ __device__ __forceinline__ bool reduce_peers(Peers &peers, int w0, int64_t in_of
             usable = usable && paired_usable(m[i]);
             m[i].x *= kPairedScale;
         }
+        uint64_t run[G];
+        if constexpr (RUN) run_codes<BITS>(codes + i * kBytes, lane, run);
 #pragma unroll
         for (int r = 0; r < G; r++) {
             float f[8];
-            if constexpr (PAIRED && kPairedConversion<SCHEME, BITS>)
-                codes_to_scaled_float<BITS>(staged_codes<BITS>(codes + i * kBytes, code_off[r]), f);
+            uint64_t v;
+            if constexpr (RUN)
+                v = run[r];
             else
-                codes_to_float<SCHEME, BITS>(staged_codes<BITS>(codes + i * kBytes, code_off[r]), f);
+                v = staged_codes<BITS>(codes + i * kBytes, code_off[r]);
+            if constexpr (PAIRED && kPairedConversion<SCHEME, BITS>)
+                codes_to_scaled_float<BITS>(v, f);
+            else
+                codes_to_float<SCHEME, BITS>(v, f);
 #pragma unroll
             for (int j = 0; j < 8; j++) acc[r][j] = __fadd_rn(acc[r][j], decode<SCHEME>(f[j], m[i]));
         }
@@ -174,28 +211,45 @@ __device__ __forceinline__ bool reduce_peers(Peers &peers, int w0, int64_t in_of
     return __builtin_amdgcn_ballot_w64(!usable) == 0;
 }
 
+// peers staged together: 8 if their packed bytes fit the staging area (one chunk of sums,
+// kChunk * 4 bytes), else 4; the odd widths take 4 (their two or three dwords per group
+// and peer are all in flight together: at 8 peers the 3-bit path alone raised the fused
+// kernel from 106 to 125 registers, which cost every other width up to 50 % there)
+template <int BITS>
+constexpr int kPeerBlock = (kStagedOverRead<BITS> != 0 || 8 * (kChunk * BITS / 8) > kChunk * 4) ? 4 : 8;
+
 // Sum over the W peers of one chunk's dequantized values, added to acc in peer order.
 // PAIRED: as in reduce_peers; false is returned when the sums have to be formed again without it.
-template <int SCHEME, int BITS, bool TAIL = false, bool PAIRED = false, typename Peers>
+template <int SCHEME, int BITS, bool PAIRED = false, typename Peers>
 __device__ __forceinline__ bool reduce_chunk(Peers &peers, int W, int64_t in_off, uint32_t g,
-                                             const LaneMap &map, float (&acc)[G][8], uint4v *stage, int lane,
-                                             int nvecs = 0)
+                                             const LaneMap &map, float (&acc)[G][8], uint4v *stage, int lane)
 {
-    // peers staged together: 8 if their packed bytes fit the staging area (one chunk of sums,
-    // kChunk * 4 bytes), else 4; the odd widths take 4 (their two or three dwords per group
-    // and peer are all in flight together: at 8 peers the 3-bit path alone raised the fused
-    // kernel from 106 to 125 registers, which cost every other width up to 50 % there)
     constexpr int kBytes = kChunk * BITS / 8;
-    constexpr bool kOddWidth = kStagedOverRead<BITS> != 0;
-    constexpr int kWide = (kOddWidth || 8 * kBytes > kChunk * 4) ? 4 : 8;
-    static_assert(kWide * kBytes + kStagedOverRead<BITS> <= kChunk * 4, "staging area too small");
+    static_assert(kPeerBlock<BITS> * kBytes + kStagedOverRead<BITS> <= kChunk * 4, "staging area too small");
     int code_off[G];
 #pragma unroll
     for (int r = 0; r < G; r++) code_off[r] = (map.group(r) >> 3) * BITS;
     bool good = true;
-    for_peer_blocks<kWide>(W, [&](int w0, auto wb) {
-        good &= reduce_peers<SCHEME, BITS, decltype(wb)::value, TAIL, PAIRED>(peers, w0, in_off, g, code_off, acc, stage,
-                                                                             lane, nvecs);
+    for_peer_blocks<kPeerBlock<BITS>>(W, [&](int w0, auto wb) {
+        good &= reduce_peers<SCHEME, BITS, decltype(wb)::value, false, PAIRED>(peers, w0, in_off, g, code_off, acc, stage,
+                                                                              lane, 0);
+    });
+    return good;
+}
+
+// The same for a run whose codes start at byte in_off and whose first bucket is bucket0.
+template <int SCHEME, int BITS, bool PAIRED = false, typename Peers>
+__device__ __forceinline__ bool reduce_run(Peers &peers, int W, int64_t in_off, uint32_t bucket0, const Run &run,
+                                           float (&acc)[G][8], uint4v *stage, int lane)
+{
+    constexpr int kBytes = kChunk * BITS / 8 + kRunLead<BITS>;
+    static_assert(kPeerBlock<BITS> * kBytes + (G == 4 ? 0 : kStagedOverRead<BITS>) <= kChunk * 4, "staging area too small");
+    const int nvecs = (int(in_off & 15) + (run.count * BITS + 7) / 8 + 15) / 16;
+    const int unused[G] = {};
+    bool good = true;
+    for_peer_blocks<kPeerBlock<BITS>>(W, [&](int w0, auto wb) {
+        good &= reduce_peers<SCHEME, BITS, decltype(wb)::value, true, PAIRED>(peers, w0, in_off, bucket0 + uint32_t(run.bi), unused,
+                                                                             acc, stage, lane, nvecs);
     });
     return good;
 }
@@ -305,148 +359,52 @@ __device__ __forceinline__ void reduce_fast(Peers &peers, int W, const SumIo &io
     }
 }
 
-// Sums of the short end of a layer, in the chunk mapping: acc[r][j] is valid for j < valid(group r).
+// Sums of a run: start values come in and sums go out as whole 16-byte vectors, consecutive across lanes, through the
+// staging area; the elements behind the last whole vector one by one.
 template <int SCHEME, int BITS, typename Peers>
-__device__ __forceinline__ void reduce_tail_regs(Peers &peers, int W, const Tile &tile,
-                                                 const TailShape &shape, const LaneMap &map, float (&acc)[G][8],
-                                                 uint4v *stage, int lane)
+__device__ __forceinline__ void reduce_run_tile(Peers &peers, int W, const SumIo &io, const Tile &tile,
+                                                int bucket, int lane, uint4v *stage)
 {
-    // lanes past the last bucket read its meta (and produce sums nobody uses)
-    const int bi = map.bi < shape.buckets ? map.bi : shape.buckets - 1;
-    reduce_chunk<SCHEME, BITS, true>(peers, W, tile.packed_off, tile.bucket0 + uint32_t(bi), map, acc, stage, lane,
-                                     shape.nvecs);
-}
-
-// Start values come in and sums go out through the staging area, element by element over the
-// elements that exist (coalesced; light on registers).
-template <int SCHEME, int BITS, typename Peers>
-__device__ __forceinline__ void reduce_tail(Peers &peers, int W, const SumIo &io, const Tile &tile,
-                                            int bucket, int lane, uint4v *stage)
-{
-    const LaneMap map(tile, bucket, lane);
-    const TailShape shape = TailShape::of<BITS>(tile, bucket);
-    float *staged = reinterpret_cast<float *>(stage);
-    for (int e = lane; e < kChunk; e += kWave) staged[e] = e < shape.count ? init1(io, tile.elem0 + e) : -0.0f;
-    wave_lds_fence();
+    const Run run(int(tile.count), bucket, lane);
     float acc[G][8];
-#pragma unroll
-    for (int r = 0; r < G; r++) {
-        const float4v *p = reinterpret_cast<const float4v *>(staged + map.group(r));
-        const float4v a = p[0], b = p[1];
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            acc[r][j] = a[j];
-            acc[r][4 + j] = b[j];
-        }
+    if (!io.init) {
+        clear_sums(acc);
+    } else if (io.init_dt == CGX_F16) {
+        RunLoad<CGX_F16> load;
+        load.issue(io.init, tile.elem0, run.count, lane);
+        load.finish(run.count, lane, stage, acc);
+    } else {
+        RunLoad<CGX_F32> load;
+        load.issue(io.init, tile.elem0, run.count, lane);
+        load.finish(run.count, lane, stage, acc);
     }
-    wave_lds_fence();
-    reduce_tail_regs<SCHEME, BITS>(peers, W, tile, shape, map, acc, stage, lane);
-#pragma unroll
-    for (int r = 0; r < G; r++) {
-        float4v *p = reinterpret_cast<float4v *>(staged + map.group(r));
-        p[0] = float4v{acc[r][0], acc[r][1], acc[r][2], acc[r][3]};
-        p[1] = float4v{acc[r][4], acc[r][5], acc[r][6], acc[r][7]};
-    }
-    wave_lds_fence();
-    for (int e = lane; e < shape.count; e += kWave) store1(io, tile.elem0 + e, staged[e]);
-    wave_lds_fence();
-}
-
-// Sums of a tile of whole buckets of a size that is no power of two (kQuantAny), row by row: acc[r] belongs to
-// group Gi = 64 r + lane (valid for Gi < shape.groups).  Two peers at a time: their codes (a multiple of 4
-// bytes at a multiple of 4 in the stream) and the meta of the tile's buckets go straight into LDS, one dword
-// per lane and instruction.
-template <int SCHEME, int BITS, typename Peers>
-__device__ __forceinline__ void reduce_any_regs(Peers &peers, int W, const Tile &tile, const AnyShape &shape,
-                                                float (&acc)[G][8], uint4v *stage, int lane)
-{
-    constexpr int kPeerBytes = kChunk * BITS / 8 + 16 + kWave * 8;      // codes (+ over-read), unit[64], offset[64]
-    static_assert(2 * kPeerBytes <= kChunk * 4, "staging area too small");
-    constexpr int kMetaAt = kChunk * BITS / 8 + 16;
-    const int dwords = shape.groups * BITS / 4;
-    uint8_t *area = reinterpret_cast<uint8_t *>(stage);
-    for_peer_blocks<2>(W, [&](int w0, auto wb) {
-        constexpr int WB = decltype(wb)::value;
-#pragma unroll
-        for (int i = 0; i < WB; i++) {
-            const uint32_t *in = reinterpret_cast<const uint32_t *>(peers.packed[w0 + i] + tile.packed_off);
-            uint32_t *codes = reinterpret_cast<uint32_t *>(area + i * kPeerBytes);
-            for (int v0 = 0; v0 < dwords; v0 += kWave)
-                if (v0 + lane < dwords) load_to_lds4(in + v0 + lane, codes + v0);
-            // meta of bucket j of the tile: lane j fetches it (kMinMax: unit and minimum, two dwords)
-            const uint32_t *m = reinterpret_cast<const uint32_t *>(peers.meta[w0 + i]) + size_t(kMetaFloats<SCHEME>) * tile.bucket0;
-            uint32_t *unit = reinterpret_cast<uint32_t *>(area + i * kPeerBytes + kMetaAt);
-            if (lane < shape.m) {
-                load_to_lds4(m + kMetaFloats<SCHEME> * lane, unit);
-                if (SCHEME != kNormSign) load_to_lds4(m + kMetaFloats<SCHEME> * lane + 1, unit + kWave);
-            }
-        }
-        wait_vector_memory();
-        wave_lds_fence();
-#pragma unroll
-        for (int i = 0; i < WB; i++) {
-            const uint8_t *codes = area + i * kPeerBytes;
-            const float *unit = reinterpret_cast<const float *>(area + i * kPeerBytes + kMetaAt);
-#pragma unroll
-            for (int r = 0; r < G; r++) {
-                const int Gi = r * kWave + lane;
-                if (Gi < shape.groups) {
-                    const int j = shape.bucket_of(Gi);
-                    const float2 m = make_float2(unit[j], SCHEME == kNormSign ? 0.0f : unit[kWave + j]);
-                    float f[8];
-                    codes_to_float<SCHEME, BITS>(staged_codes<BITS>(codes, Gi * BITS), f);
-#pragma unroll
-                    for (int k = 0; k < 8; k++) acc[r][k] = __fadd_rn(acc[r][k], decode<SCHEME>(f[k], m));
-                }
-            }
-        }
-        wave_lds_fence();
-    });
-}
-
-template <int SCHEME, int BITS, typename Peers>
-__device__ __forceinline__ void reduce_any(Peers &peers, int W, const SumIo &io, const Tile &tile, int bucket,
-                                           int lane, uint4v *stage)
-{
-    const AnyShape shape(tile, bucket);
-    float acc[G][8];
-#pragma unroll
-    for (int r = 0; r < G; r++) {
-        const int Gi = r * kWave + lane;
-        if (Gi < shape.groups) {
-            init8(io, tile.elem0 + int64_t(Gi) * 8, acc[r]);
-        } else {
-#pragma unroll
-            for (int k = 0; k < 8; k++) acc[r][k] = -0.0f;
-        }
-    }
-    reduce_any_regs<SCHEME, BITS>(peers, W, tile, shape, acc, stage, lane);
-    // the sums leave through LDS as whole vectors: count is a multiple of 32 elements
+    reduce_run<SCHEME, BITS>(peers, W, tile.packed_off, tile.bucket0, run, acc, stage, lane);
     if (io.out_dt == CGX_F16) {
 #pragma unroll
         for (int r = 0; r < G; r++) {
-            const int Gi = r * kWave + lane;
             half8v h;
 #pragma unroll
-            for (int k = 0; k < 8; k++) h[k] = _Float16(acc[r][k]);
-            if (Gi < shape.groups) reinterpret_cast<half8v *>(stage)[Gi] = h;
+            for (int j = 0; j < 8; j++) h[j] = _Float16(acc[r][j]);
+            stage[run_slot<G>(lane * G + r)] = __builtin_bit_cast(uint4v, h);
         }
         wave_lds_fence();
-        flush_stage_to_elements(stage, reinterpret_cast<uint4u2 *>(reinterpret_cast<_Float16 *>(io.out) + tile.elem0),
-                                shape.groups, lane, io.keep);
+        const int vecs = run.count / 8, e = vecs * 8 + lane;
+        _Float16 *out = reinterpret_cast<_Float16 *>(io.out) + tile.elem0;
+        flush_stage_to_elements(stage, reinterpret_cast<uint4u2 *>(out), vecs, lane, io.keep, run_slot<G>);
+        if (e < run.count) out[e] = reinterpret_cast<const _Float16 *>(stage + run_slot<G>(vecs))[lane];
     } else {
 #pragma unroll
         for (int r = 0; r < G; r++) {
-            const int Gi = r * kWave + lane;
-            if (Gi < shape.groups) {
-                float4v *p = reinterpret_cast<float4v *>(stage) + 2 * Gi;
-                p[0] = float4v{acc[r][0], acc[r][1], acc[r][2], acc[r][3]};
-                p[1] = float4v{acc[r][4], acc[r][5], acc[r][6], acc[r][7]};
-            }
+            stage[run_slot<2 * G>(lane * 2 * G + 2 * r)] =
+                __builtin_bit_cast(uint4v, (float4v{acc[r][0], acc[r][1], acc[r][2], acc[r][3]}));
+            stage[run_slot<2 * G>(lane * 2 * G + 2 * r + 1)] =
+                __builtin_bit_cast(uint4v, (float4v{acc[r][4], acc[r][5], acc[r][6], acc[r][7]}));
         }
         wave_lds_fence();
-        flush_stage_to_elements(stage, reinterpret_cast<uint4u2 *>(reinterpret_cast<float *>(io.out) + tile.elem0),
-                                2 * shape.groups, lane, io.keep);
+        const int vecs = run.count / 4, e = vecs * 4 + lane;
+        float *out = reinterpret_cast<float *>(io.out) + tile.elem0;
+        flush_stage_to_elements(stage, reinterpret_cast<uint4u2 *>(out), vecs, lane, io.keep, run_slot<2 * G>);
+        if (e < run.count) out[e] = reinterpret_cast<const float *>(stage + run_slot<2 * G>(vecs))[lane];
     }
     wave_lds_fence();
 }
@@ -484,14 +442,6 @@ __device__ __forceinline__ float generic_sum(Peers &peers, int W, const Tile &ti
         }
     });
     return acc;
-}
-
-// Any bucket size, any alignment, ragged tiles: one element per lane and pass.
-template <int SCHEME, typename Peers>
-__device__ __forceinline__ void reduce_slow(Peers &peers, int W, const SumIo &io, const Tile &tile, int bucket, int lane)
-{
-    for (uint32_t j = lane; j < tile.count; j += kWave)
-        store1(io, tile.elem0 + j, generic_sum<SCHEME>(peers, W, tile, bucket, j, init1(io, tile.elem0 + j)));
 }
 
 // Ordered sum over the peers of 8 consecutive elements of a pass-through tile (16-byte

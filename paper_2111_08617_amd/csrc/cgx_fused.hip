@@ -23,7 +23,7 @@ __device__ __forceinline__ void fused_fast(Peers &peers, int W, const Tile &tile
         clear_sums(acc);
         const int64_t in_off = tile.packed_off + int64_t(c) * (kChunk * BITS / 8);
         const uint32_t g = tile.bucket0 + c * buckets_per_chunk + map.bi;
-        if (!reduce_chunk<SCHEME, BITS, false, true>(peers, W, in_off, g, map, acc, stage, lane)) {
+        if (!reduce_chunk<SCHEME, BITS, true>(peers, W, in_off, g, map, acc, stage, lane)) {
             // a unit of 2^118 or more (or none at all): once more with the plain conversion
             clear_sums(acc);
             reduce_chunk<SCHEME, BITS>(peers, W, in_off, g, map, acc, stage, lane);
@@ -74,45 +74,32 @@ __device__ __forceinline__ void fused_wide(Peers &peers, int W, const Tile &tile
     }
 }
 
-// The short end of a layer: masked sums feed the masked quantizer.
+// A run: its sums feed the quantizer in the same lane order.
 template <int SCHEME, int BITS, bool ODD, typename Peers>
-__device__ __forceinline__ void fused_tail(Peers &peers, int W, const Tile &tile, int64_t out_off, int bucket,
-                                           uint32_t seed_lo, uint32_t seed_hi, uint8_t *__restrict__ packed_out,
-                                           float *__restrict__ meta_out, int lane, uint4v *stage)
-{
-    const LaneMap map(tile, bucket, lane);
-    const TailShape shape = TailShape::of<BITS>(tile, bucket);
-    const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
-    float acc[G][8];
-    clear_sums(acc);
-    reduce_tail_regs<SCHEME, BITS>(peers, W, tile, shape, map, acc, stage, lane);
-#pragma unroll
-    for (int r = 0; r < G; r++) {
-        const int v = shape.valid(map.group(r));
-#pragma unroll
-        for (int j = 0; j < 8; j++)
-            if (j >= v) acc[r][j] = 0.0f;            // stale LDS bytes decoded to anything
-    }
-    quantize_tail_regs<SCHEME, BITS, ODD>(acc, shape, map, lane, tile.elem0, key,
-                                          meta_out + kMetaFloats<SCHEME> * tile.bucket0, packed_out + out_off, stage);
-}
-
-// Whole buckets of a size that is no power of two: the row-by-row sums feed the row-by-row quantizer.
-template <int SCHEME, int BITS, bool ODD, typename Peers>
-__device__ __forceinline__ void fused_any(Peers &peers, int W, const Tile &tile, int64_t out_off, uint32_t out_pad,
+__device__ __forceinline__ void fused_run(Peers &peers, int W, const Tile &tile, int64_t out_off, uint32_t out_pad,
                                           int bucket, uint32_t seed_lo, uint32_t seed_hi,
                                           uint8_t *__restrict__ packed_out, float *__restrict__ meta_out, int lane,
                                           uint4v *stage)
 {
-    const AnyShape shape(tile, bucket);
+    const Run run(int(tile.count), bucket, lane);
     const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
     float acc[G][8];
     clear_sums(acc);
-    reduce_any_regs<SCHEME, BITS>(peers, W, tile, shape, acc, stage, lane);
-    Tile out = tile;                                 // the same elements and buckets at their place in the output stream
-    out.pad = out_pad;
-    quantize_any_regs<SCHEME, BITS, ODD>(acc, shape, out, key, meta_out + kMetaFloats<SCHEME> * tile.bucket0,
-                                         packed_out + out_off, stage, lane);
+    if (!reduce_run<SCHEME, BITS, true>(peers, W, tile.packed_off, tile.bucket0, run, acc, stage, lane)) {
+        clear_sums(acc);
+        reduce_run<SCHEME, BITS>(peers, W, tile.packed_off, tile.bucket0, run, acc, stage, lane);
+    }
+    if (run.left < 8 * G) {
+#pragma unroll
+        for (int r = 0; r < G; r++) {
+            const int v = run.valid(r);
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                if (j >= v) acc[r][j] = 0.0f;        // stale LDS bytes decoded to anything
+        }
+    }
+    quantize_run_regs<SCHEME, BITS, ODD>(acc, run, lane, tile.elem0, key, meta_out + kMetaFloats<SCHEME> * tile.bucket0,
+                                         packed_out + out_off, out_pad, stage);
 }
 
 // tiles_in follows the layout of the chunks (storage type dt), tiles_out that of the
@@ -161,15 +148,10 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ 
                 CGX_FOR_BITS(tile_bits(tile), (fused_fast<SCHEME, BITS, ODD>(peers, W, tile, out_off, bucket, seed_lo,
                                                                          seed_hi, packed_out, meta_out, lane, stage)))
             }
-        } else if (kind == kQuantTail) {
-            CGX_FOR_BITS(tile_bits(tile), (fused_tail<SCHEME, BITS, ODD>(peers, W, tile, out_off, bucket, seed_lo,
-                                                                         seed_hi, packed_out, meta_out, lane, stage)))
-        } else if (!WIDE && kind == kQuantAny) {
-            if constexpr (!WIDE) {
-                CGX_FOR_BITS(tile_bits(tile), (fused_any<SCHEME, BITS, ODD>(peers, W, tile, out_off, out_pad, bucket, seed_lo,
-                                                                            seed_hi, packed_out, meta_out, lane, stage)))
-            }
-        } else if (kind == kQuantSlow || kind == kQuantAny) {
+        } else if (is_quantized_kind(kind) && tile.count <= uint32_t(kChunk) && one_key_block(tile)) {
+            CGX_FOR_BITS(tile_bits(tile), (fused_run<SCHEME, BITS, ODD>(peers, W, tile, out_off, out_pad, bucket, seed_lo,
+                                                                        seed_hi, packed_out, meta_out, lane, stage)))
+        } else if (is_quantized_kind(kind)) {
             quantize_generic<SCHEME, false>(
                 [&](uint32_t j) { return generic_sum<SCHEME>(peers, W, tile, bucket, j, -0.0f); },
                 packed_out + out_off, meta_out, tile, out_pad, bucket, seed_lo, seed_hi, lane);

@@ -55,15 +55,12 @@ enum StorePolicy { kStoreStream = 0, kStoreKeep = 1, kStoreThrough = 2 };
 // store_policy (StorePolicy): the result is streamed (non-temporal), written through at device scope (it then stays
 // in the memory-side cache if it is small enough; the caller decides by size), or written through at system scope,
 // non-temporal (calls that mostly write: a decompression).
-// many_tails: the short ends of layers are a real share of the plan's tiles (the kernel then
-// takes them through the masked chunk path instead of the generic one).
+// tiles: a table whose quantized tiles hold at most a chunk each (TableUse kPieces).
 // (two builds: chunks of 1024 elements, which a decompression takes, and of 2048)
 hipError_t launch_dequant_reduce_g2(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles, int64_t n_tiles,
-                                 bool many_tails,
                                  int32_t bucket, const void *init, int init_dt, void *out, int out_dt,
                                  int store_policy, const LaunchConfig &cfg, hipStream_t stream);
 hipError_t launch_dequant_reduce_g4(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles, int64_t n_tiles,
-                                 bool many_tails,
                                  int32_t bucket, const void *init, int init_dt, void *out, int out_dt,
                                  int store_policy, const LaunchConfig &cfg, hipStream_t stream);
 

@@ -74,7 +74,7 @@ static inline bool same_key_block(int64_t e0, int64_t count)
 
 void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
                  int chunks_per_tile, std::vector<Tile> &tiles, std::vector<uint32_t> *slots,
-                 std::vector<int64_t> *layer_first, const int32_t *layer_buckets, bool with_copies)
+                 std::vector<int64_t> *layer_first, const int32_t *layer_buckets, bool with_copies, TableUse use)
 {
     tiles.clear();
     if (layer_first) layer_first->assign(size_t(L) + 1, 0);
@@ -106,11 +106,12 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
         const bool aligned = true;
         const size_t first_tile = tiles.size();
         if (b == 0) {
-            for (int64_t j = 0; j < len; j += kCopyTile) {
+            const int64_t piece = use == kStatistics ? kCopyTile : kCopyPiece;
+            for (int64_t j = 0; j < len; j += piece) {
                 Tile t{};
                 t.elem0 = first + j;
                 t.packed_off = int64_t(seg + uint64_t(j) * S);
-                t.count = uint32_t(len - j < kCopyTile ? len - j : kCopyTile);
+                t.count = uint32_t(len - j < piece ? len - j : piece);
                 t.info = uint32_t(kCopyFast) << 4;
                 tiles.push_back(t);
             }
@@ -133,6 +134,21 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
                     c += k;
                 }
                 j = full_chunks * kChunk;
+            } else if (own_bucket > kChunk && use == kPieces) {
+                // the chunks of every bucket, the last one of a bucket or of the layer shorter if need be
+                while (j < len) {
+                    const int64_t in_bucket = own_bucket - j % own_bucket, left = len - j;
+                    const int64_t most = in_bucket < left ? in_bucket : left, k = most < kChunk ? most : kChunk;
+                    const bool whole = wide_bucket && k == kChunk;
+                    Tile t{};
+                    t.elem0 = first + j;
+                    t.packed_off = int64_t(seg + uint64_t(j) * b / 8);
+                    t.bucket0 = uint32_t(bucket0 + uint64_t(j) / own_bucket);
+                    t.count = uint32_t(k);
+                    t.info = uint32_t(b) | uint32_t(whole ? kQuantWide : kQuantSlow) << 4 | (whole ? 6u << 8 : 0u) | size_bits;
+                    tiles.push_back(t);
+                    j += k;
+                }
             } else if (wide_bucket && aligned) {
                 // one tile per whole bucket: its scale needs all of it (lanes-per-bucket field: the whole wave)
                 const int64_t full = len / own_bucket;

@@ -26,21 +26,31 @@ namespace cgx {
 // 4 groups = 2048 elements) and walks a tile table built for that size: a vectorised tile is a
 // whole number of chunks.
 constexpr int chunk_of(int groups) { return 64 * 8 * groups; }
-// Elements per pass-through tile.
+// Elements per pass-through tile of the statistics (and of the tables of cgx_plan_tiles).
 constexpr int kCopyTile = 8192;
+// Elements per pass-through tile of the other kernels: a wave moves what its loads can have in flight together.  A
+// longer tile is a chain of round trips that outlasts the rest of a short launch (a reduce of 7.6 M elements with 124
+// layers, 8 peers, and the requantize of its sums: 36.1 us with pieces of 2048, 33.8 us with 1024).
+constexpr int kCopyPiece = 1024;
+
+// What walks a tile table.  The statistics keep one partial sum per tile (their workspace is sized by that table).
+// The quantizers need whole buckets; a reduction does not, so buckets longer than a chunk are cut into chunks
+// for it, one tile each.
+enum TableUse { kStatistics = 0, kWholeBuckets = 1, kPieces = 2 };
 
 enum TileKind : uint32_t {
-    kQuantSlow = 0,  // any bucket size, any alignment, ragged last bucket
+    kQuantSlow = 0,  // none of the others: a ragged end, a longer bucket, or a tile across two of the generator's key blocks
     kQuantFast = 1,  // power-of-two bucket <= chunk, whole chunks
     kCopyFast = 3,   // pass-through, 16-byte vectors
     kQuantWide = 4,  // one whole power-of-two bucket longer than a chunk (4096, 8192)
-    kQuantTail = 5,  // power-of-two bucket <= chunk, the last tile of a layer, shorter than a chunk
+    kQuantTail = 5,  // power-of-two bucket <= chunk, the last tile of a layer, shorter than a chunk (run as a kQuantAny)
     kQuantAny = 6    // whole buckets of a size that is no power of two (a multiple of 32, at most a chunk in all)
 };
 
 // Chunk-shaped quantized tiles (whole chunks of the bucket-major or row-by-row mapping).
 CGX_HOST_DEVICE inline bool is_vector_kind(uint32_t kind) { return kind == kQuantFast || kind == kQuantWide; }
-// Tiles that stream (everything else costs several dependent memory round trips and goes first in the table).
+CGX_HOST_DEVICE inline bool is_quantized_kind(uint32_t kind) { return kind != kCopyFast; }
+// Tiles that make up the bulk of a plan (the others go first in the table).
 CGX_HOST_DEVICE inline bool is_streamed_kind(uint32_t kind) { return is_vector_kind(kind) || kind == kQuantAny; }
 
 struct Tile {               // 32 bytes, read by the kernels with scalar loads
@@ -97,6 +107,6 @@ PlanShape plan_shape(int32_t L, const int64_t *off, const uint8_t *bits, int32_t
 void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
                  int chunks_per_tile, std::vector<Tile> &tiles, std::vector<uint32_t> *slots = nullptr,
                  std::vector<int64_t> *layer_first = nullptr, const int32_t *layer_buckets = nullptr,
-                 bool with_copies = true);
+                 bool with_copies = true, TableUse use = kStatistics);
 
 }  // namespace cgx

@@ -4,13 +4,6 @@
 namespace cgx {
 namespace {
 
-// TAILS: the short ends of layers take the masked chunk path.  The kernel with that path is
-// about 1 % slower on plans that hardly use it (and, when it was added, needed one register
-// more than the kernel's occupancy allows).  Without it a short end goes through the generic
-// path, a chain of dependent round trips for one tile: hidden behind the rest of a long launch,
-// it outlasts a short one (6 % of a 25 us launch with a single short end).  The host asks for
-// it when there is a short end and the plan has fewer than 16384 tiles, or when short ends are
-// at least 1/512 of the tiles.
 // The arguments as the kernarg segment lays them out (each at its natural alignment, in order): gives the
 // offset of the peers' table behind the scalars.
 struct ReduceArguments {
@@ -23,7 +16,7 @@ struct ReduceArguments {
     PeerPtrs peers;
 };
 
-template <int SCHEME, bool TAILS>
+template <int SCHEME>
 __global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__ tiles, int64_t n_tiles, int W, int dt,
                                                          const void *init, void *out, int init_dt, int out_dt,
                                                          int keep, const PeerPtrs peers_argument)
@@ -50,15 +43,8 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__
         const uint32_t kind = tile_kind(tile);
         if (is_vector_kind(kind)) {      // a wide tile is chunks of one bucket: kChunk / bucket == 0 below
             CGX_FOR_BITS(tile_bits(tile), (reduce_fast<SCHEME, BITS>(peers, W, io, tile, bucket, lane, stage)))
-        } else if (TAILS && kind == kQuantTail) {
-            if constexpr (TAILS) {
-                CGX_FOR_BITS(tile_bits(tile),
-                             (reduce_tail<SCHEME, BITS>(peers_in_memory, W, io, tile, bucket, lane, stage)))
-            }
-        } else if (kind == kQuantAny) {
-            CGX_FOR_BITS(tile_bits(tile), (reduce_any<SCHEME, BITS>(peers_in_memory, W, io, tile, bucket, lane, stage)))
-        } else if (kind == kQuantSlow || kind == kQuantTail) {
-            reduce_slow<SCHEME>(peers_in_memory, W, io, tile, bucket, lane);
+        } else if (is_quantized_kind(kind)) {
+            CGX_FOR_BITS(tile_bits(tile), (reduce_run_tile<SCHEME, BITS>(peers_in_memory, W, io, tile, bucket, lane, stage)))
         } else if (dt == CGX_F16) {
             reduce_copy<CGX_F16>(peers_in_memory, W, io, tile.elem0, tile, kind == kCopyFast, lane);
         } else {
@@ -71,16 +57,13 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__
 
 // This file is compiled once per chunk size (CGX_GROUPS = 2 and 4): launch_dequant_reduce_g2, launch_dequant_reduce_g4.
 hipError_t CGX_CONCAT(launch_dequant_reduce_g, CGX_GROUPS)(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles, int64_t n_tiles,
-                                 bool many_tails,
                                  int32_t bucket, const void *init, int init_dt, void *out, int out_dt,
                                  int store_policy, const LaunchConfig &cfg, hipStream_t stream)
 {
     if (n_tiles == 0) return hipSuccess;
     const dim3 grid(grid_for(n_tiles, cfg)), block(kBlock);
     const SumIo io{init, init_dt, out, out_dt, store_policy};
-    const auto kernel = scheme == kSchemeNormSign
-                            ? (many_tails ? reduce_kernel<kNormSign, true> : reduce_kernel<kNormSign, false>)
-                            : (many_tails ? reduce_kernel<kMinMax, true> : reduce_kernel<kMinMax, false>);
+    const auto kernel = scheme == kSchemeNormSign ? reduce_kernel<kNormSign> : reduce_kernel<kMinMax>;
     (void)bucket;
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, tiles, n_tiles, W, dt, io.init, io.out, io.init_dt, io.out_dt, io.keep,
                        peers);

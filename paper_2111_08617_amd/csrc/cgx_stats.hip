@@ -176,9 +176,9 @@ __device__ __forceinline__ double sqerror_fast(const void *__restrict__ grad, Pe
         // (waits for every load of this wave, the gradient's included)
         reduce_chunk<SCHEME, BITS>(chunk, 1, tile.packed_off + int64_t(c) * (kChunk * BITS / 8),
                                    tile.bucket0 + c * buckets_per_chunk + map.bi, map, v, stage, lane);
-        if constexpr (VIA_LDS) {
 #pragma unroll
-            for (int r = 0; r < G; r++) {
+        for (int r = 0; r < G; r++) {
+            if constexpr (VIA_LDS) {
                 if (DT == CGX_F16) {
                     const half8v h = *reinterpret_cast<const half8v *>(reinterpret_cast<const _Float16 *>(x_stage) + map.group(r));
 #pragma unroll
@@ -193,15 +193,48 @@ __device__ __forceinline__ double sqerror_fast(const void *__restrict__ grad, Pe
                     }
                 }
             }
-            wave_lds_fence();                // before the next chunk overwrites the area
-        }
-#pragma unroll
-        for (int r = 0; r < G; r++)
 #pragma unroll
             for (int j = 0; j < 8; j++) {
                 const double d = double(x[r][j]) - double(v[r][j]);
                 s += d * d;
             }
+            // one group after the other (registers)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (VIA_LDS) wave_lds_fence();                // before the next chunk overwrites the area
+    }
+    return s;
+}
+
+// Squared error of any other quantized tile: run by run (one, unless the bucket is longer than a chunk).
+template <int SCHEME, int DT, int BITS, typename Peers>
+__device__ __forceinline__ double sqerror_runs(const void *__restrict__ grad, Peers &chunk, const Tile &tile, int bucket,
+                                               int lane, uint4v *stage, uint4v *x_stage)
+{
+    double s = 0.0;
+    for (int j0 = 0; j0 < int(tile.count); j0 += kChunk) {
+        const int count = int(tile.count) - j0 < kChunk ? int(tile.count) - j0 : kChunk;
+        const Run run(count, bucket, lane);
+        float v[G][8];
+        clear_sums(v);
+        reduce_run<SCHEME, BITS>(chunk, 1, tile.packed_off + int64_t(j0) * BITS / 8, tile.bucket0, run, v, stage, lane);
+        // (in flight together with the codes, the gradient would cost the kernel 25 registers more)
+        RunLoad<DT> load;
+        load.issue(grad, tile.elem0 + j0, count, lane);
+        load.park(count, lane, x_stage);
+#pragma unroll
+        for (int r = 0; r < G; r++) {
+            float x[8];
+            load.group(x_stage, lane, r, x);
+            const int valid = run.valid(r);
+#pragma unroll
+            for (int j = 0; j < 8; j++) {
+                const double d = double(x[j]) - double(v[r][j]);
+                if (j < valid) s += d * d;
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        load.release();
     }
     return s;
 }
@@ -222,11 +255,14 @@ __global__ __launch_bounds__(kBlock) void sqerror_kernel(const PeerPtrs chunk_ar
     constexpr int kPerWave = VIA_LDS ? kErrorChunkVecs + kErrorCodeVecs : kErrorChunkVecs;
     __shared__ uint4v stage_all[kWavesPerBlock][kPerWave];
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-    const int lane = int(threadIdx.x) & 63;
+    int lane_of_wave = int(threadIdx.x) & 63;
     uint4v *x_stage = stage_all[wave];
     uint4v *stage = VIA_LDS ? x_stage + kErrorChunkVecs : x_stage;
     const int64_t stride = int64_t(gridDim.x) * kWavesPerBlock;
     for (int64_t t = int64_t(blockIdx.x) * kWavesPerBlock + wave; t < n_tiles; t += stride) {
+        // opaque once per tile, as in the reduce kernel: nothing that depends on the lane alone stays in registers
+        asm volatile("" : "+v"(lane_of_wave));
+        const int lane = lane_of_wave;
         const Tile tile = tiles[t];
         const int bucket = tile_bucket(tile);
         const uint32_t kind = tile_kind(tile);
@@ -234,12 +270,8 @@ __global__ __launch_bounds__(kBlock) void sqerror_kernel(const PeerPtrs chunk_ar
         if (is_vector_kind(kind)) {
             CGX_FOR_BITS(tile_bits(tile),
                          (s = sqerror_fast<SCHEME, DT, BITS, VIA_LDS>(grad, chunk, tile, bucket, lane, stage, x_stage)))
-        } else if (kind == kQuantSlow || kind == kQuantTail || kind == kQuantAny) {
-            for (uint32_t j = lane; j < tile.count; j += kWave) {
-                const double d = double(load_elem<DT>(grad, tile.elem0 + j)) -
-                                 double(generic_sum<SCHEME>(chunk, 1, tile, bucket, j, -0.0f));
-                s += d * d;
-            }
+        } else if (is_quantized_kind(kind)) {
+            CGX_FOR_BITS(tile_bits(tile), (s = sqerror_runs<SCHEME, DT, BITS>(grad, chunk, tile, bucket, lane, stage, x_stage)))
         }
         s = wave_sum(s);
         if (lane == 0) partial[slots[t]] = s;

@@ -751,3 +751,28 @@ def test_thousands_of_small_layers(torch, oracle, dt):
     w = wl.Workload("small_layers", [(int(s),) for s in sizes], bits, 256, dt, 2, 4242, wl._normal,
                     np.exp(rng.normal(-3, 1, 4000)))
     full_cycle(torch, oracle, w, W=2, what="4000 layers")
+
+
+@pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("bucket", [32, 96, 160, 640, 992, 1024, 1056, 2016, 2048, 2080, 4096, 8160])
+def test_layer_lengths_around_every_edge_of_a_run(torch, oracle, bucket, dt):
+    """Layers whose ends fall next to an element group, a lane, a bucket and a chunk of either size, and pass-through
+    layers next to a copy piece, with the widths in turn; W = 9 takes a block of 8 (or 4) peers and one more.  The same
+    chunks are then added to a local term of either type.  (bit-exact: codes, scales and ordered sums are fixed)"""
+    edges = [1, 7, 8, 9, 15, 17, 31, 33, bucket - 1, bucket + 1, 2 * bucket + 31, 1023, 1025, 1024 + 16, 2047, 2049, 2048 + 33,
+             4096 + 5, 6 * bucket + 8]
+    bits = [1 + i % 8 for i in range(len(edges))] + [0, 4, 0, 3, 0, 6]
+    sizes = edges + [1023, bucket, 1025, bucket + 4, 3, 5 * bucket - 1]
+    w = wl.Workload("edges", [(s,) for s in sizes], np.array(bits, np.uint8), bucket, dt, 9, 9000 + bucket, wl._normal,
+                    np.linspace(0.01, 2.0, len(sizes)))
+    full_cycle(torch, oracle, w, W=9, what=f"edges B={bucket}")
+    plan = cgx.Plan(w.offsets, w.bits, w.bucket, w.dt)
+    chunks = [oracle.quantize(w.gradient(p), w.offsets, w.bits, bucket, w.quant_seed(p), dt) for p in range(3)]
+    total = torch.full((w.n + 16,), 5.0, device="cuda")
+    cgx.cgx_dequant_reduce_add(dev(torch, w.gradient(7)), dt, [dev(torch, c[0]) for c in chunks],
+                               [dev(torch, c[1].reshape(-1)) for c in chunks], plan, total)
+    torch.cuda.synchronize()
+    ref = oracle.dequant_reduce([c[0] for c in chunks], [c[1] for c in chunks], w.offsets, w.bits, bucket, dt,
+                                local=w.gradient(7))
+    out = total.cpu().numpy()
+    assert (out[w.n:] == 5.0).all() and np.array_equal(out[:w.n].view(np.uint32), ref["sum32"].view(np.uint32))
