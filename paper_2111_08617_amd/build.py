@@ -14,7 +14,8 @@ SOURCES = [("cgx_plan.cpp", "cgx_plan", []), ("cgx_api.cpp", "cgx_api", []), ("c
            ("cgx_quantize.hip", "cgx_quantize_g2", ["-DCGX_GROUPS=2"]),
            ("cgx_quantize.hip", "cgx_quantize_g4", ["-DCGX_GROUPS=4"]),
            ("cgx_reduce.hip", "cgx_reduce_g2", ["-DCGX_GROUPS=2"]),
-           ("cgx_reduce.hip", "cgx_reduce_g4", ["-DCGX_GROUPS=4"]), ("cgx_fused.hip", "cgx_fused", []), ("cgx_stats.hip", "cgx_stats", []),
+           ("cgx_reduce.hip", "cgx_reduce_g4", ["-DCGX_GROUPS=4"]), ("cgx_fused.hip", "cgx_fused", []), ("cgx_wide.hip", "cgx_wide", []),
+           ("cgx_stats.hip", "cgx_stats", []),
            ("cgx_probe.hip", "cgx_probe", [])]
 
 # -ffp-contract=off: the code decision is binary32 without fused operations.

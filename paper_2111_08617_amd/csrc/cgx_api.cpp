@@ -118,15 +118,27 @@ enum CallKind { kQuantizeCall, kFusedCall, kOtherCall };
 // per wave than with 8 KB, and the quantizer follows it: 0.74 -> 0.78 of the HBM peak on 1.3 G
 // elements); on binary16 a chunk of 2048 elements is 4 KB already.  The reduce, fused and statistics
 // kernels take 2048 (a peer's codes of a chunk then fill a whole load instruction at 4 bits).
-// Bucket sizes between 1024 and 2048 take the quantizer of 2048-element chunks also on binary32 (one bucket per
-// chunk, vectorised or streamed; with chunks of 1024 such a bucket is a two-pass tile or a generic one).
-int chunk_length(CallKind call, int dt, const Buckets &buckets)
+// A call with a bucket of more than 1024 elements takes the quantizer of 2048-element chunks also on binary32: such a
+// bucket fits its chunk or a block of its waves (cgx_wide.hip).  The whole call takes it, one launch for all sizes
+// up to 2048 instead of two (ResNet-50 with sizes by layer length, 128 / 512 / 2048: 36 us of quantizing in two launches
+// of 1024-element chunks, in which a bucket of 2048 is read twice,
+// 26 us in one launch of 2048-element chunks).
+int chunk_length(CallKind call, int dt, int32_t longest)
 {
+    if (call != kQuantizeCall || longest > cgx::chunk_of(2)) return cgx::kDefaultChunk;
     const int forced = launch_config().quantize_groups;
-    if (call != kQuantizeCall) return cgx::kDefaultChunk;
     if (forced > 0) return cgx::chunk_of(forced);
-    const bool long_buckets = !buckets.per_layer && buckets.uniform > 1024 && buckets.uniform <= 2048;
-    return cgx::chunk_of(dt == CGX_F32 && !long_buckets ? 2 : 4);
+    return cgx::chunk_of(dt == CGX_F32 ? 2 : 4);
+}
+
+// The longest bucket size of a call (of its quantized layers, if they have their own).
+int32_t longest_bucket(const Buckets &buckets, int32_t L, const int64_t *off, const uint8_t *bits)
+{
+    if (!buckets.per_layer) return buckets.uniform;
+    int32_t longest = 0;
+    for (int32_t l = 0; l < L; l++)
+        if (bits[l] != 0 && off[l + 1] > off[l] && buckets.per_layer[l] > longest) longest = buckets.per_layer[l];
+    return longest;
 }
 
 int tile_length(CallKind call, int dt, int64_t n)
@@ -326,7 +338,8 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
     const cgx::PlanShape shape = cgx::plan_shape(L, off, bits, buckets.uniform, dt, buckets.per_layer);
     if (!grad || !packed || (shape.meta_bytes && !meta)) return CGX_ERR_NULL;
     if (misaligned(grad) || misaligned(packed) || misaligned(meta)) return CGX_ERR_ALIGN;
-    const int chunk = chunk_length(kQuantizeCall, dt, buckets);
+    const int32_t longest = longest_bucket(buckets, L, off, bits);
+    const int chunk = chunk_length(kQuantizeCall, dt, longest);
     const auto launch_quantize = chunk == cgx::chunk_of(2) ? cgx::launch_quantize_g2 : cgx::launch_quantize_g4;
     const std::vector<Launch> launches = launches_of(buckets, L, off, bits, chunk);
     std::vector<PlanRef> plans;
@@ -336,9 +349,12 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
     for (size_t i = 0; i < launches.size(); i++) {
         const Launch &launch = launches[i];
         const PlanRef &plan = plans[i];
-        const hipError_t e = launch_quantize(scheme, grad, dt, plan->d_tiles, plan->n_tiles, plan->odd_tiles,
-                                                  plan->aligned_tiles, launch.bucket, seed, packed, meta, launch_config(),
-                                                  static_cast<hipStream_t>(stream));
+        const hipError_t e =
+            cgx::mapping_of(launch.bucket, chunk) == cgx::kMapWide
+                ? cgx::launch_quantize_wide(scheme, grad, dt, plan->d_tiles, plan->n_tiles, plan->odd_tiles, longest,
+                                            seed, packed, meta, launch_config(), static_cast<hipStream_t>(stream))
+                : launch_quantize(scheme, grad, dt, plan->d_tiles, plan->n_tiles, plan->odd_tiles, plan->aligned_tiles,
+                                  launch.bucket, seed, packed, meta, launch_config(), static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;
@@ -434,9 +450,15 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
                       cgx::kDefaultChunk, tile_length(kFusedCall, dt, n), cgx::kWholeBuckets, &out, buckets.per_layer, launch.with_copies);
         if (rc != CGX_OK) return rc;
         if (in->n_tiles != out->n_tiles) return CGX_ERR_SIZE;     // cannot happen: same tiling for both layouts
-        const hipError_t e = cgx::launch_dequant_reduce_requantize(
-            scheme, peers, W, dt, in->d_tiles, out->d_tiles, in->n_tiles, in->odd_tiles, launch.bucket, seed,
-            packed_out, meta_out, launch_config(), static_cast<hipStream_t>(stream));
+        const hipError_t e =
+            cgx::mapping_of(launch.bucket, cgx::kDefaultChunk) == cgx::kMapWide
+                ? cgx::launch_dequant_reduce_requantize_wide(scheme, peers, W, dt, in->d_tiles, out->d_tiles, in->n_tiles,
+                                                             in->odd_tiles, longest_bucket(buckets, L, layer_offsets, bits_per_layer),
+                                                             seed, packed_out, meta_out, launch_config(),
+                                                             static_cast<hipStream_t>(stream))
+                : cgx::launch_dequant_reduce_requantize(scheme, peers, W, dt, in->d_tiles, out->d_tiles, in->n_tiles,
+                                                        in->odd_tiles, seed, packed_out, meta_out, launch_config(),
+                                                        static_cast<hipStream_t>(stream));
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;

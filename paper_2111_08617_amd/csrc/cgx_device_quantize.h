@@ -221,45 +221,6 @@ __device__ __forceinline__ void quantize_fast_rows(const void *__restrict__ grad
     }
 }
 
-// A tile that is one whole bucket of 2 or 4 chunks: a first pass over the chunks finds the
-// scale, a second one reads them again (from the caches: 16 or 32 KB read a moment ago) and
-// cuts the codes.  Row-by-row mapping (LaneMap with the whole wave as one bucket).
-template <int SCHEME, int DT, int BITS, bool ODD>
-__device__ __forceinline__ void quantize_wide(const void *__restrict__ grad, uint8_t *__restrict__ packed,
-                                              float *__restrict__ meta, const Tile &tile, int bucket,
-                                              uint32_t seed_lo, uint32_t seed_hi, int lane, uint4v *stage)
-{
-    constexpr uint32_t kLevels = top_level<SCHEME>(BITS);
-    const LaneMap map(tile, bucket, lane);
-    const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
-    const int chunks = int(tile.count / kChunk);
-    float mn = SCHEME == kNormSign ? 0.0f : __builtin_inff(), mx = SCHEME == kNormSign ? 0.0f : -__builtin_inff();
-    for (int c = 0; c < chunks; c++) {
-        float x[G][8];
-#pragma unroll
-        for (int r = 0; r < G; r++) {
-            Raw8<DT> raw;
-            raw.load_keep(grad, tile.elem0 + int64_t(c) * kChunk + map.group(r));   // read again below
-            raw.widen(x[r]);
-        }
-        lane_extent<SCHEME>(x, mn, mx);
-    }
-    if (SCHEME == kNormSign)
-        group_max(mx, 6, lane);
-    else
-        group_minmax(mn, mx, 6, lane);
-    const Scale s = bucket_scale(mn, mx, int(kLevels));
-    if (lane == 0) store_meta<SCHEME>(meta, tile.bucket0, s);
-    for (int c = 0; c < chunks; c++) {
-        const int64_t first = tile.elem0 + int64_t(c) * kChunk;
-        float x[G][8];
-#pragma unroll
-        for (int r = 0; r < G; r++) load8<DT>(grad, first + map.group(r), x[r]);
-        encode_chunk<SCHEME, BITS, ODD>(x, s, map, first, key, packed + tile.packed_off + int64_t(c) * (kChunk * BITS / 8),
-                                   stage, lane);
-    }
-}
-
 // The codes of a lane's groups of a run (8 * BITS bits each, group after group) into LDS, G * BITS bytes per lane.
 // The area starts on 16 bytes.
 template <int BITS>
@@ -315,9 +276,12 @@ __device__ __forceinline__ float2 run_extent(const float (&x)[G][8], const Run &
 // of 4 bytes, and so is the number of bytes written: a run starts a multiple of 32 codes into its segment of the
 // stream and either ends one or is padded to the segment's 16 bytes.
 template <int SCHEME, int BITS, bool ODD>
-__device__ __forceinline__ void encode_run(const float (&x)[G][8], const Run &run, const Scale &s, int lane, int64_t first,
+__device__ __forceinline__ void encode_run(const float (&x)[G][8], const Run &run, Scale s, int lane, int64_t first,
                                            uint32_t key, uint8_t *__restrict__ out, uint32_t pad, uint4v *stage)
 {
+    // What the widths have in common (draws, positions between the levels) is not computed ahead of the choice of a
+    // width: it would take 50 registers.
+    asm volatile("" : "+v"(lane), "+v"(s.inv16) : "i"(BITS));
     uint8_t *area = reinterpret_cast<uint8_t *>(stage);
     uint64_t codes[G];
 #pragma unroll
@@ -466,8 +430,9 @@ __device__ __forceinline__ void quantize_generic(Value value, uint8_t *__restric
     }
 }
 
-// Pass-through tile of the quantize kernel: verbatim copy, then the layer's zero padding.
-template <int DT>
+// Pass-through tile of the quantize kernels: verbatim copy, then the layer's zero padding.  WIDTH lanes work on it, this
+// one is number `lane`.
+template <int DT, int WIDTH = kWave>
 __device__ __forceinline__ void copy_tile(const void *__restrict__ grad, uint8_t *__restrict__ packed, const Tile &tile,
                           bool fast, int lane)
 {
@@ -479,27 +444,27 @@ __device__ __forceinline__ void copy_tile(const void *__restrict__ grad, uint8_t
     if (fast) {
         const uint32_t vecs = bytes / 16;
         // all loads of a tile (kCopyPiece elements) in flight together
-        constexpr int kLoads = kCopyPiece * S / 16 / kWave;
-        for (uint32_t v0 = lane; v0 < vecs; v0 += kLoads * kWave) {
+        constexpr int kLoads = kCopyPiece * S / 16 / WIDTH > 0 ? kCopyPiece * S / 16 / WIDTH : 1;
+        for (uint32_t v0 = lane; v0 < vecs; v0 += kLoads * WIDTH) {
             uint4v raw[kLoads];
 #pragma unroll
             for (int u = 0; u < kLoads; u++)
-                if (v0 + u * kWave < vecs) raw[u] = reinterpret_cast<const uint4u2 *>(src)[v0 + u * kWave];
+                if (v0 + u * WIDTH < vecs) raw[u] = reinterpret_cast<const uint4u2 *>(src)[v0 + u * WIDTH];
 #pragma unroll
             for (int u = 0; u < kLoads; u++)
-                if (v0 + u * kWave < vecs) reinterpret_cast<uint4v *>(dst)[v0 + u * kWave] = raw[u];
+                if (v0 + u * WIDTH < vecs) reinterpret_cast<uint4v *>(dst)[v0 + u * WIDTH] = raw[u];
         }
         done = vecs * 16;
     } else if (DT == CGX_F16) {
-        for (uint32_t e = lane; e < tile.count; e += kWave)
+        for (uint32_t e = lane; e < tile.count; e += WIDTH)
             reinterpret_cast<uint16_t *>(dst)[e] = reinterpret_cast<const uint16_t *>(src)[e];
         done = bytes;
     } else {
-        for (uint32_t e = lane; e < tile.count; e += kWave)
+        for (uint32_t e = lane; e < tile.count; e += WIDTH)
             reinterpret_cast<uint32_t *>(dst)[e] = reinterpret_cast<const uint32_t *>(src)[e];
         done = bytes;
     }
-    for (uint32_t k = done + lane; k < bytes + tile.pad; k += kWave) dst[k] = k < bytes ? src[k] : uint8_t(0);
+    for (uint32_t k = done + lane; k < bytes + tile.pad; k += WIDTH) dst[k] = k < bytes ? src[k] : uint8_t(0);
 }
 
 }  // namespace

@@ -264,6 +264,44 @@ __device__ __forceinline__ void clear_sums(float (&acc)[G][8])
         for (int j = 0; j < 8; j++) acc[r][j] = -0.0f;
 }
 
+// acc = the sums of a run over the W peers, with the paired conversion where the units allow it.
+template <int SCHEME, int BITS, typename Peers>
+__device__ __forceinline__ void sum_run(Peers &peers, int W, int64_t in_off, uint32_t bucket0, const Run &run,
+                                        float (&acc)[G][8], uint4v *stage, int lane)
+{
+    clear_sums(acc);
+    if (!reduce_run<SCHEME, BITS, true>(peers, W, in_off, bucket0, run, acc, stage, lane)) {
+        // a unit of 2^118 or more (or none at all): once more with the plain conversion
+        clear_sums(acc);
+        reduce_run<SCHEME, BITS>(peers, W, in_off, bucket0, run, acc, stage, lane);
+    }
+}
+
+// The sums of a run's missing elements (stale LDS bytes decoded to anything) become 0.
+__device__ __forceinline__ void clear_missing(float (&acc)[G][8], const Run &run)
+{
+    if (run.left < 8 * G) {
+#pragma unroll
+        for (int r = 0; r < G; r++) {
+            const int v = run.valid(r);
+#pragma unroll
+            for (int j = 0; j < 8; j++)
+                if (j >= v) acc[r][j] = 0.0f;
+        }
+    }
+}
+
+// The fused kernels' arguments as the kernarg segment lays them out: offset of the peers' table behind the scalars.
+struct FusedArguments {
+    const Tile *tiles_in, *tiles_out;
+    int64_t n_tiles;
+    int W, dt;
+    uint32_t seed_lo, seed_hi;
+    uint8_t *packed_out;
+    float *meta_out;
+    PeerPtrs peers;
+};
+
 // What a reduction starts from and where it goes: element e of the tile's buffer is
 // init[e] (binary32 or binary16; init == nullptr: nothing) and is written to out[e]
 // (binary32, or binary16 rounded to nearest even).
@@ -481,19 +519,19 @@ __device__ __forceinline__ float copy_sum1(Peers &peers, int W, const Tile &tile
 }
 
 // Pass-through tile of the reduce kernels: plain ordered sum of the stored values; element j
-// of the tile starts from / goes to position e0 + j of io.
-template <int DT, typename Peers>
+// of the tile starts from / goes to position e0 + j of io.  WIDTH lanes work on it, this one is number `lane`.
+template <int DT, int WIDTH = kWave, typename Peers>
 __device__ __forceinline__ void reduce_copy(Peers &peers, int W, const SumIo &io, int64_t e0, const Tile &tile, bool fast,
                             int lane)
 {
     const uint32_t groups = fast ? tile.count / 8 : 0;
-    for (uint32_t g = lane; g < groups; g += kWave) {
+    for (uint32_t g = lane; g < groups; g += WIDTH) {
         float acc[8];
         init8(io, e0 + int64_t(g) * 8, acc);
         copy_sum8<DT>(peers, W, tile, g, acc);
         store8(io, e0 + int64_t(g) * 8, acc);
     }
-    for (uint32_t j = groups * 8 + lane; j < tile.count; j += kWave)
+    for (uint32_t j = groups * 8 + lane; j < tile.count; j += WIDTH)
         store1(io, e0 + j, copy_sum1<DT>(peers, W, tile, j, init1(io, e0 + j)));
 }
 

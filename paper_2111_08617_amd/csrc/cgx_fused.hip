@@ -34,46 +34,6 @@ __device__ __forceinline__ void fused_fast(Peers &peers, int W, const Tile &tile
     }
 }
 
-// A tile that is one whole bucket of 2 or 4 chunks: the sums are formed twice, once for the
-// scale and once for the codes (they would not fit the registers, and the chunks' bytes come
-// from the caches the second time).
-template <int SCHEME, int BITS, bool ODD, typename Peers>
-__device__ __forceinline__ void fused_wide(Peers &peers, int W, const Tile &tile, int64_t out_off,
-                                           int bucket, uint32_t seed_lo, uint32_t seed_hi,
-                                           uint8_t *__restrict__ packed_out, float *__restrict__ meta_out,
-                                           int lane, uint4v *stage)
-{
-    constexpr uint32_t kLevels = top_level<SCHEME>(BITS);
-    const LaneMap map(tile, bucket, lane);
-    const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
-    const int chunks = int(tile.count / kChunk);
-    float mn = SCHEME == kNormSign ? 0.0f : __builtin_inff(), mx = SCHEME == kNormSign ? 0.0f : -__builtin_inff();
-    Scale s{0.0f, 0.0f, 0.0f};
-    // both passes in one loop, so that the reduction is instantiated once
-    for (int it = 0; it < 2 * chunks; it++) {
-        const bool second = it >= chunks;
-        const int c = second ? it - chunks : it;
-        float acc[G][8];
-        clear_sums(acc);
-        reduce_chunk<SCHEME, BITS>(peers, W, tile.packed_off + int64_t(c) * (kChunk * BITS / 8), tile.bucket0, map,
-                                   acc, stage, lane);
-        if (second) {
-            encode_chunk<SCHEME, BITS, ODD>(acc, s, map, tile.elem0 + int64_t(c) * kChunk, key,
-                                       packed_out + out_off + int64_t(c) * (kChunk * BITS / 8), stage, lane);
-            continue;
-        }
-        lane_extent<SCHEME>(acc, mn, mx);
-        if (c == chunks - 1) {
-            if (SCHEME == kNormSign)
-                group_max(mx, 6, lane);
-            else
-                group_minmax(mn, mx, 6, lane);
-            s = bucket_scale(mn, mx, int(kLevels));
-            if (lane == 0) store_meta<SCHEME>(meta_out, tile.bucket0, s);
-        }
-    }
-}
-
 // A run: its sums feed the quantizer in the same lane order.
 template <int SCHEME, int BITS, bool ODD, typename Peers>
 __device__ __forceinline__ void fused_run(Peers &peers, int W, const Tile &tile, int64_t out_off, uint32_t out_pad,
@@ -84,38 +44,15 @@ __device__ __forceinline__ void fused_run(Peers &peers, int W, const Tile &tile,
     const Run run(int(tile.count), bucket, lane);
     const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
     float acc[G][8];
-    clear_sums(acc);
-    if (!reduce_run<SCHEME, BITS, true>(peers, W, tile.packed_off, tile.bucket0, run, acc, stage, lane)) {
-        clear_sums(acc);
-        reduce_run<SCHEME, BITS>(peers, W, tile.packed_off, tile.bucket0, run, acc, stage, lane);
-    }
-    if (run.left < 8 * G) {
-#pragma unroll
-        for (int r = 0; r < G; r++) {
-            const int v = run.valid(r);
-#pragma unroll
-            for (int j = 0; j < 8; j++)
-                if (j >= v) acc[r][j] = 0.0f;        // stale LDS bytes decoded to anything
-        }
-    }
+    sum_run<SCHEME, BITS>(peers, W, tile.packed_off, tile.bucket0, run, acc, stage, lane);
+    clear_missing(acc, run);
     quantize_run_regs<SCHEME, BITS, ODD>(acc, run, lane, tile.elem0, key, meta_out + kMetaFloats<SCHEME> * tile.bucket0,
                                          packed_out + out_off, out_pad, stage);
 }
 
 // tiles_in follows the layout of the chunks (storage type dt), tiles_out that of the
 // output (binary32 pass-through layers); the two tables list the same tiles in the same order.
-// WIDE: the call's bucket is longer than a chunk (see quantize_kernel's MAP).
-struct FusedArguments {       // the kernarg segment's layout: offset of the peers' table behind the scalars
-    const Tile *tiles_in, *tiles_out;
-    int64_t n_tiles;
-    int W, dt;
-    uint32_t seed_lo, seed_hi;
-    uint8_t *packed_out;
-    float *meta_out;
-    PeerPtrs peers;
-};
-
-template <int SCHEME, bool WIDE, bool ODD>
+template <int SCHEME, bool ODD>
 __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ tiles_in,
                                                         const Tile *__restrict__ tiles_out, int64_t n_tiles, int W,
                                                         int dt, uint32_t seed_lo, uint32_t seed_hi,
@@ -141,13 +78,8 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ 
         const uint32_t out_pad = tiles_out[t].pad;
         const uint32_t kind = tile_kind(tile);
         if (is_vector_kind(kind)) {
-            if constexpr (WIDE) {
-                CGX_FOR_BITS(tile_bits(tile), (fused_wide<SCHEME, BITS, ODD>(peers, W, tile, out_off, bucket, seed_lo,
-                                                                         seed_hi, packed_out, meta_out, lane, stage)))
-            } else {
-                CGX_FOR_BITS(tile_bits(tile), (fused_fast<SCHEME, BITS, ODD>(peers, W, tile, out_off, bucket, seed_lo,
-                                                                         seed_hi, packed_out, meta_out, lane, stage)))
-            }
+            CGX_FOR_BITS(tile_bits(tile), (fused_fast<SCHEME, BITS, ODD>(peers, W, tile, out_off, bucket, seed_lo,
+                                                                     seed_hi, packed_out, meta_out, lane, stage)))
         } else if (is_quantized_kind(kind) && tile.count <= uint32_t(kChunk) && one_key_block(tile)) {
             CGX_FOR_BITS(tile_bits(tile), (fused_run<SCHEME, BITS, ODD>(peers, W, tile, out_off, out_pad, bucket, seed_lo,
                                                                         seed_hi, packed_out, meta_out, lane, stage)))
@@ -171,21 +103,17 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ 
 }  // namespace
 
 hipError_t launch_dequant_reduce_requantize(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
-                                            const Tile *tiles_out, int64_t n_tiles, bool odd_tiles, int32_t bucket,
+                                            const Tile *tiles_out, int64_t n_tiles, bool odd_tiles,
                                             uint64_t seed, void *packed_out, void *meta_out,
                                             const LaunchConfig &cfg, hipStream_t stream)
 {
     if (n_tiles == 0) return hipSuccess;
     const dim3 grid(grid_for(n_tiles, cfg)), block(kBlock);
-    const bool wide = mapping_of(bucket, kChunk) == kMapWide;
     using Kernel = void (*)(const Tile *, const Tile *, int64_t, int, int, uint32_t, uint32_t, uint8_t *, float *,
                             const PeerPtrs);
-    static const Kernel table[2][2][2] = {
-        {{fused_kernel<kMinMax, false, false>, fused_kernel<kMinMax, true, false>},
-         {fused_kernel<kNormSign, false, false>, fused_kernel<kNormSign, true, false>}},
-        {{fused_kernel<kMinMax, false, true>, fused_kernel<kMinMax, true, true>},
-         {fused_kernel<kNormSign, false, true>, fused_kernel<kNormSign, true, true>}}};
-    const Kernel kernel = table[odd_tiles][scheme == kSchemeNormSign][wide];
+    static const Kernel table[2][2] = {{fused_kernel<kMinMax, false>, fused_kernel<kNormSign, false>},
+                                       {fused_kernel<kMinMax, true>, fused_kernel<kNormSign, true>}};
+    const Kernel kernel = table[odd_tiles][scheme == kSchemeNormSign];
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, tiles_in, tiles_out, n_tiles, W, dt, uint32_t(seed),
                        uint32_t(seed >> 32), static_cast<uint8_t *>(packed_out), static_cast<float *>(meta_out), peers);
     return hipGetLastError();

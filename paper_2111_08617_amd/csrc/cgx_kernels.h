@@ -68,9 +68,19 @@ hipError_t launch_dequant_reduce_g4(int scheme, const PeerPtrs &peers, int W, in
 // reaching memory; tiles_in describes the chunks (storage type dt), tiles_out the output
 // (binary32 pass-through); W <= kPeersPerLaunch.
 hipError_t launch_dequant_reduce_requantize(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
-                                            const Tile *tiles_out, int64_t n_tiles, bool odd_tiles, int32_t bucket,
+                                            const Tile *tiles_out, int64_t n_tiles, bool odd_tiles,
                                             uint64_t seed, void *packed_out, void *meta_out,
                                             const LaunchConfig &cfg, hipStream_t stream);
+
+// The same two for buckets longer than a chunk of 2048 elements (tables of class kMapWide at that chunk); longest: the
+// longest bucket of the call.
+hipError_t launch_quantize_wide(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, bool odd_tiles,
+                                int32_t longest, uint64_t seed, void *packed, void *meta, const LaunchConfig &cfg,
+                                hipStream_t stream);
+hipError_t launch_dequant_reduce_requantize_wide(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
+                                                 const Tile *tiles_out, int64_t n_tiles, bool odd_tiles, int32_t longest,
+                                                 uint64_t seed, void *packed_out, void *meta_out, const LaunchConfig &cfg,
+                                                 hipStream_t stream);
 
 // Per-layer squared l2 norms of buf (tiles of a plan whose layers are all pass-through) and
 // of the compression error grad - dequantize(packed, meta) (tiles of the chunk's plan).

@@ -38,9 +38,6 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict
             if constexpr (MAP == kMapRows) {
                 CGX_FOR_BITS(tile_bits(tile), (quantize_fast_rows<SCHEME, DT, BITS, ODD>(grad, packed, meta, tile, bucket,
                                                                                       seed_lo, seed_hi, lane, stage)))
-            } else if constexpr (MAP == kMapWide) {
-                CGX_FOR_BITS(tile_bits(tile), (quantize_wide<SCHEME, DT, BITS, ODD>(grad, packed, meta, tile, bucket,
-                                                                                 seed_lo, seed_hi, lane, stage)))
             } else {
                 CGX_FOR_BITS(tile_bits(tile), (quantize_fast<SCHEME, DT, BITS, ODD, VIA_LDS>(
                                                   grad, packed, meta, tile, bucket, seed_lo, seed_hi, lane, stage)))
@@ -82,8 +79,8 @@ hipError_t CGX_CONCAT(launch_quantize_g, CGX_GROUPS)(int scheme, const void *gra
     const uint32_t seed_lo = uint32_t(seed), seed_hi = uint32_t(seed >> 32);
     using Kernel = void (*)(const void *, const Tile *, int64_t, uint32_t, uint32_t, uint8_t *, float *);
 #define CGX_QUANTIZE_MAPS(S, D, O) \
-    {quantize_kernel<S, D, kMapBuckets, O>, quantize_kernel<S, D, kMapRows, O>, quantize_kernel<S, D, kMapWide, O>}
-    static const Kernel table[2][2][2][3] = {
+    {quantize_kernel<S, D, kMapBuckets, O>, quantize_kernel<S, D, kMapRows, O>}
+    static const Kernel table[2][2][2][2] = {
         {{CGX_QUANTIZE_MAPS(kMinMax, CGX_F32, false), CGX_QUANTIZE_MAPS(kMinMax, CGX_F16, false)},
          {CGX_QUANTIZE_MAPS(kNormSign, CGX_F32, false), CGX_QUANTIZE_MAPS(kNormSign, CGX_F16, false)}},
         {{CGX_QUANTIZE_MAPS(kMinMax, CGX_F32, true), CGX_QUANTIZE_MAPS(kMinMax, CGX_F16, true)},
