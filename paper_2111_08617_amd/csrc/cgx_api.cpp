@@ -378,44 +378,38 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
     if (misaligned(out) || misaligned(local)) return CGX_ERR_ALIGN;
     // A decompression (one chunk, nothing to add to) writes eight bytes per byte it reads; a kernel that only
     // moves bytes in that mix sustains 0.75 of the HBM peak with 8 KB written per wave and 0.91 with 4 KB, so it
-    // takes the kernel of 1024-element chunks (buckets up to 1024 elements; longer ones keep 2048).
+    // takes the kernel of 1024-element chunks (to binary16 2048 elements are 4 KB).
     const bool decompression = W == 1 && !local && launch_config().dequantize_through;
-    const bool short_buckets = !buckets.per_layer && buckets.uniform <= 1024;
     const int forced = launch_config().reduce_groups;
-    const int chunk = forced > 0 ? (short_buckets ? cgx::chunk_of(forced) : cgx::kDefaultChunk)
-                      : decompression && short_buckets && out_dt == CGX_F32 ? cgx::chunk_of(2) : cgx::kDefaultChunk;
-    const std::vector<Launch> launches = launches_of(buckets, L, off, bits, chunk);
-    std::vector<PlanRef> plans;
-    rc = get_plans(static_cast<hipStream_t>(stream), launches, L, off, bits, dt, chunk,
-                   tile_length(kOtherCall, dt, n), cgx::kPieces, buckets.per_layer, &plans);
+    const int chunk = forced > 0 ? cgx::chunk_of(forced)
+                      : decompression && out_dt == CGX_F32 ? cgx::chunk_of(2) : cgx::kDefaultChunk;
+    PlanRef plan;
+    rc = get_plan(static_cast<hipStream_t>(stream), L, off, bits, buckets.uniform, dt, chunk, tile_length(kOtherCall, dt, n),
+                  cgx::kPieces, &plan, buckets.per_layer);
     if (rc != CGX_OK) return rc;
     const auto launch_reduce = chunk == cgx::kDefaultChunk ? cgx::launch_dequant_reduce_g4 : cgx::launch_dequant_reduce_g2;
-    for (size_t li = 0; li < launches.size(); li++) {
-        const Launch &launch = launches[li];
-        const PlanRef &plan = plans[li];
-        // peers are folded in order, kPeersPerLaunch at a time, so the sum order is local, 0, 1, ..., W-1;
-        // a later launch starts from the binary32 result of the one before (W <= kPeersPerLaunch
-        // whenever the output is not binary32: only cgx_dequantize asks for that, with W = 1)
-        for (int w0 = 0; w0 < W; w0 += cgx::kPeersPerLaunch) {
-            const int k = W - w0 < cgx::kPeersPerLaunch ? W - w0 : cgx::kPeersPerLaunch;
-            cgx::PeerPtrs peers{};
-            for (int i = 0; i < k; i++) {
-                peers.packed[i] = static_cast<const uint8_t *>(packed[w0 + i]);
-                peers.meta[i] = static_cast<const float *>(meta[w0 + i]);
-            }
-            const void *init = w0 == 0 ? local : out;
-            const int init_dt = w0 == 0 ? local_dt : CGX_F32;
-            // a result that fits the 256 MB memory-side cache with room to spare is left there for the
-            // call that consumes it (requantize, the optimizer): measured on 102 MB of sums, the reduce
-            // runs 7 % and the requantize after it 10 % faster; on 658 MB the reader loses what the
-            // writer gains.  A decompression's stores go through at system scope whatever the size.
-            const bool small = int64_t(n) * (out_dt == CGX_F16 ? 2 : 4) <= launch_config().keep_sums_max_bytes;
-            const int policy = decompression ? cgx::kStoreThrough : small ? cgx::kStoreKeep : cgx::kStoreStream;
-            const hipError_t e = launch_reduce(scheme, peers, k, dt, plan->d_tiles, plan->n_tiles,
-                                               launch.bucket, init, init_dt, out, out_dt, policy, launch_config(),
-                                               static_cast<hipStream_t>(stream));
-            if (e != hipSuccess) return CGX_ERR_HIP;
+    // peers are folded in order, kPeersPerLaunch at a time, so the sum order is local, 0, 1, ..., W-1;
+    // a later launch starts from the binary32 result of the one before (W <= kPeersPerLaunch
+    // whenever the output is not binary32: only cgx_dequantize asks for that, with W = 1)
+    for (int w0 = 0; w0 < W; w0 += cgx::kPeersPerLaunch) {
+        const int k = W - w0 < cgx::kPeersPerLaunch ? W - w0 : cgx::kPeersPerLaunch;
+        cgx::PeerPtrs peers{};
+        for (int i = 0; i < k; i++) {
+            peers.packed[i] = static_cast<const uint8_t *>(packed[w0 + i]);
+            peers.meta[i] = static_cast<const float *>(meta[w0 + i]);
         }
+        const void *init = w0 == 0 ? local : out;
+        const int init_dt = w0 == 0 ? local_dt : CGX_F32;
+        // a result that fits the 256 MB memory-side cache with room to spare is left there for the
+        // call that consumes it (requantize, the optimizer): measured on 102 MB of sums, the reduce
+        // runs 7 % and the requantize after it 10 % faster; on 658 MB the reader loses what the
+        // writer gains.  A decompression's stores go through at system scope whatever the size.
+        const bool small = int64_t(n) * (out_dt == CGX_F16 ? 2 : 4) <= launch_config().keep_sums_max_bytes;
+        const int policy = decompression ? cgx::kStoreThrough : small ? cgx::kStoreKeep : cgx::kStoreStream;
+        const hipError_t e = launch_reduce(scheme, peers, k, dt, plan->d_tiles, plan->n_tiles,
+                                           init, init_dt, out, out_dt, policy, launch_config(),
+                                           static_cast<hipStream_t>(stream));
+        if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;
 }

@@ -331,10 +331,18 @@ __device__ __forceinline__ float init1(const SumIo &io, int64_t e)
     return io.init_dt == CGX_F16 ? load_elem<CGX_F16>(io.init, e) : load_elem<CGX_F32>(io.init, e);
 }
 
+// A sum rounded to binary16.  The sum is a binary32 number first: with one peer, whose value is a multiply-add, the
+// compiler would otherwise form v_fma_mixlo_f16, which rounds once instead of twice.
+__device__ __forceinline__ _Float16 to_half(float v)
+{
+    asm("" : "+v"(v));
+    return _Float16(v);
+}
+
 __device__ __forceinline__ void store1(const SumIo &io, int64_t e, float v)
 {
     if (io.out_dt == CGX_F16)
-        reinterpret_cast<_Float16 *>(io.out)[e] = _Float16(v);
+        reinterpret_cast<_Float16 *>(io.out)[e] = to_half(v);
     else
         reinterpret_cast<float *>(io.out)[e] = v;
 }
@@ -345,7 +353,7 @@ __device__ __forceinline__ void store8(const SumIo &io, int64_t e, const float (
     if (io.out_dt == CGX_F16) {
         half8v h;
 #pragma unroll
-        for (int j = 0; j < 8; j++) h[j] = _Float16(acc[j]);
+        for (int j = 0; j < 8; j++) h[j] = to_half(acc[j]);
         *reinterpret_cast<half8u *>(reinterpret_cast<_Float16 *>(io.out) + e) = h;
     } else {
         float4u *p = reinterpret_cast<float4u *>(reinterpret_cast<float *>(io.out) + e);
@@ -376,7 +384,7 @@ __device__ __forceinline__ void reduce_fast(Peers &peers, int W, const SumIo &io
             for (int r = 0; r < G; r++) {
                 half8v h;
 #pragma unroll
-                for (int j = 0; j < 8; j++) h[j] = _Float16(acc[r][j]);
+                for (int j = 0; j < 8; j++) h[j] = to_half(acc[r][j]);
                 reinterpret_cast<half8v *>(stage)[map.group(r) >> 3] = h;
             }
             wave_lds_fence();
@@ -422,7 +430,7 @@ __device__ __forceinline__ void reduce_run_tile(Peers &peers, int W, const SumIo
         for (int r = 0; r < G; r++) {
             half8v h;
 #pragma unroll
-            for (int j = 0; j < 8; j++) h[j] = _Float16(acc[r][j]);
+            for (int j = 0; j < 8; j++) h[j] = to_half(acc[r][j]);
             stage[run_slot<G>(lane * G + r)] = __builtin_bit_cast(uint4v, h);
         }
         wave_lds_fence();

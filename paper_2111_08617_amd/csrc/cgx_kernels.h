@@ -58,10 +58,10 @@ enum StorePolicy { kStoreStream = 0, kStoreKeep = 1, kStoreThrough = 2 };
 // tiles: a table whose quantized tiles hold at most a chunk each (TableUse kPieces).
 // (two builds: chunks of 1024 elements, which a decompression takes, and of 2048)
 hipError_t launch_dequant_reduce_g2(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles, int64_t n_tiles,
-                                 int32_t bucket, const void *init, int init_dt, void *out, int out_dt,
+                                 const void *init, int init_dt, void *out, int out_dt,
                                  int store_policy, const LaunchConfig &cfg, hipStream_t stream);
 hipError_t launch_dequant_reduce_g4(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles, int64_t n_tiles,
-                                 int32_t bucket, const void *init, int init_dt, void *out, int out_dt,
+                                 const void *init, int init_dt, void *out, int out_dt,
                                  int store_policy, const LaunchConfig &cfg, hipStream_t stream);
 
 // packed_out / meta_out = quantize(deq_0 + ... + deq_{W-1}) without the binary32 sum ever

@@ -91,7 +91,7 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
         uint64_t payload, buckets;
         const int32_t own_bucket = layer_buckets ? layer_buckets[l] : bucket;
         layer_extent(len, b, own_bucket, dt, payload, buckets);
-        if (b == 0 ? !with_copies : mapping_of(own_bucket, chunk) != launch_mapping) {
+        if (b == 0 ? !with_copies : use != kPieces && mapping_of(own_bucket, chunk) != launch_mapping) {
             seg += round_up16(payload);                           // another launch's layer: only its extent counts
             bucket0 += buckets;
             continue;

@@ -35,7 +35,7 @@ constexpr int kCopyPiece = 1024;
 
 // What walks a tile table.  The statistics keep one partial sum per tile (their workspace is sized by that table).
 // The quantizers need whole buckets; a reduction does not, so buckets longer than a chunk are cut into chunks
-// for it, one tile each.
+// for it, one tile each, and one launch takes buckets of every size.
 enum TableUse { kStatistics = 0, kWholeBuckets = 1, kPieces = 2 };
 
 enum TileKind : uint32_t {
@@ -102,7 +102,7 @@ PlanShape plan_shape(int32_t L, const int64_t *off, const uint8_t *bits, int32_t
 // With layer_buckets (a bucket size per layer) the table holds the tiles of the layers whose
 // bucket size has the lane mapping of `bucket` (mapping_of at this chunk size) only, at their places in the whole
 // plan's streams: a launch runs one kernel instantiation, so such a plan takes one launch per
-// mapping in use (at most three).  The pass-through layers belong to the launch with
+// mapping in use (at most three; a reduction, use = kPieces, one in all).  The pass-through layers belong to the launch with
 // with_copies set.
 void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
                  int chunks_per_tile, std::vector<Tile> &tiles, std::vector<uint32_t> *slots = nullptr,

@@ -16,8 +16,14 @@ struct ReduceArguments {
     PeerPtrs peers;
 };
 
-template <int SCHEME>
-__global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__ tiles, int64_t n_tiles, int W, int dt,
+// SINGLE: a decompression (W = 1, no start values) into storage type OUT, bound by the eight bytes it writes per byte
+// it reads.  It needs half of the reduction's registers and LDS, and twice as many waves then keep stores in
+// flight (54 instead of 123 vector registers at 2048-element chunks; 36 instead of 86 at 1024): 8 shares of 355 M elements
+// to binary16 187 -> 166 us, 268 M elements to binary32 211 -> 186 us, 67 M 44 us either way.
+constexpr int kAnyOut = -1;
+
+template <int SCHEME, int SINGLE>
+__global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__ tiles, int64_t n_tiles, int W_argument, int dt,
                                                          const void *init, void *out, int init_dt, int out_dt,
                                                          int keep, const PeerPtrs peers_argument)
 {
@@ -25,9 +31,12 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__
     // the other kinds index it at run time and read it from the kernarg segment
     const PeerPtrs &peers = peers_argument;
     KernargPeers &peers_in_memory = kernel_argument_peers(offsetof(ReduceArguments, peers));
-    const SumIo io{init, init_dt, out, out_dt, keep};
-    // per-wave staging area: a chunk of binary32 results, or the packed bytes of a block of peers
-    __shared__ uint4v stage_all[kWavesPerBlock][kChunk / 4];
+    constexpr bool kSingle = SINGLE != kAnyOut;
+    const int W = kSingle ? 1 : W_argument;
+    const SumIo io{kSingle ? nullptr : init, init_dt, out, kSingle ? SINGLE : out_dt, kSingle ? int(kStoreThrough) : keep};
+    // per-wave staging area: a chunk of results, or the packed bytes of a block of peers (at 8 bits a chunk of a single
+    // peer takes kChunk bytes, half of its binary16 results)
+    __shared__ uint4v stage_all[kWavesPerBlock][kChunk / (SINGLE == CGX_F16 ? 8 : 4)];
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
     int lane_of_wave = int(threadIdx.x) & 63;
     uint4v *stage = stage_all[wave];
@@ -57,15 +66,20 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__
 
 // This file is compiled once per chunk size (CGX_GROUPS = 2 and 4): launch_dequant_reduce_g2, launch_dequant_reduce_g4.
 hipError_t CGX_CONCAT(launch_dequant_reduce_g, CGX_GROUPS)(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles, int64_t n_tiles,
-                                 int32_t bucket, const void *init, int init_dt, void *out, int out_dt,
+                                 const void *init, int init_dt, void *out, int out_dt,
                                  int store_policy, const LaunchConfig &cfg, hipStream_t stream)
 {
     if (n_tiles == 0) return hipSuccess;
     const dim3 grid(grid_for(n_tiles, cfg)), block(kBlock);
-    const SumIo io{init, init_dt, out, out_dt, store_policy};
-    const auto kernel = scheme == kSchemeNormSign ? reduce_kernel<kNormSign> : reduce_kernel<kMinMax>;
-    (void)bucket;
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, tiles, n_tiles, W, dt, io.init, io.out, io.init_dt, io.out_dt, io.keep,
+    using Kernel = void (*)(const Tile *, int64_t, int, int, const void *, void *, int, int, int, const PeerPtrs);
+    // (a decompression to binary32 runs the build for chunks of 1024 elements, one to binary16 that for 2048: 4 KB of
+    // results per wave either way)
+    constexpr int kSingleOut = kGroups == 2 ? CGX_F32 : CGX_F16;
+    const bool single = store_policy == kStoreThrough && out_dt == kSingleOut;
+    static const Kernel table[2][2] = {{reduce_kernel<kMinMax, kAnyOut>, reduce_kernel<kNormSign, kAnyOut>},
+                                       {reduce_kernel<kMinMax, kSingleOut>, reduce_kernel<kNormSign, kSingleOut>}};
+    const Kernel kernel = table[single && W == 1 && !init][scheme == kSchemeNormSign];
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, tiles, n_tiles, W, dt, init, out, init_dt, out_dt, store_policy,
                        peers);
     return hipGetLastError();
 }
