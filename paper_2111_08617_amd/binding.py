@@ -122,8 +122,55 @@ def status_string(status: int) -> str:
     return lib().cgx_status_string(int(status)).decode()
 
 
-class Plan:
+_native = None
+
+
+def _args():
+    """The extension module that checks tensors (csrc/cgx_tensor_args.cpp); raises if it has not been built."""
+    global _native
+    if _native is None:
+        import torch  # noqa: F401  (the module links against its libraries)
+        try:
+            from . import _cgx_args
+        except ImportError as e:
+            raise FileNotFoundError("_cgx_args.so is missing or does not fit this torch: build it with "
+                                    "`python -m paper_2111_08617_amd.build`") from e
+        _native = _cgx_args
+    return _native
+
+
+class _HostArray:
+    """An array attribute of a plan: stored next to its address (numpy makes a new object per look-up of that)."""
+
+    def __set_name__(self, owner, name):
+        self.name, self.address = "_" + name, "_" + name + "_address"
+
+    def __get__(self, plan, owner=None):
+        return self if plan is None else plan.__dict__[self.name]
+
+    def __set__(self, plan, array):
+        plan.__dict__[self.name] = array
+        plan.__dict__[self.address] = array.ctypes.data
+
+
+class _HostArrays:
+    """Copies and pickles of a plan take the arrays, never their addresses."""
+
+    def __getstate__(self):
+        return {k: v for k, v in self.__dict__.items() if not k.endswith("_address")}
+
+    def __setstate__(self, state):
+        for k, v in state.items():
+            if isinstance(v, np.ndarray):
+                setattr(self, k.lstrip("_"), v)
+            else:
+                self.__dict__[k] = v
+
+
+class Plan(_HostArrays):
     """Host arrays of a plan, kept alive and contiguous for the C calls."""
+
+    offsets, bits = _HostArray(), _HostArray()
 
     def __init__(self, layer_offsets, bits_per_layer, bucket: int, dt: int = F32):
         self.offsets = np.ascontiguousarray(layer_offsets, dtype=np.int64)
@@ -137,11 +184,13 @@ class Plan:
 
     @property
     def args(self):
-        return (self.n, self.L, self.offsets.ctypes.data, self.bits.ctypes.data, self.bucket)
+        return (self.n, self.L, self._offsets_address, self._bits_address, self.bucket)
 
 
-class LayeredPlan:
+class LayeredPlan(_HostArrays):
     """A plan with a bucket size per layer (the cgx_layered_* calls)."""
+
+    offsets, bits, buckets = _HostArray(), _HostArray(), _HostArray()
 
     def __init__(self, layer_offsets, bits_per_layer, buckets_per_layer, dt: int = F32):
         self.offsets = np.ascontiguousarray(layer_offsets, dtype=np.int64)
@@ -155,7 +204,7 @@ class LayeredPlan:
 
     @property
     def args(self):
-        return (self.n, self.L, self.offsets.ctypes.data, self.bits.ctypes.data, self.buckets.ctypes.data)
+        return (self.n, self.L, self._offsets_address, self._bits_address, self._buckets_address)
 
 
 def _check(status: int, where: str) -> None:
@@ -165,12 +214,17 @@ def _check(status: int, where: str) -> None:
 
 def _stream(stream) -> int:
     if stream is None:
+        # the current stream of the current device, as torch.cuda.current_stream() but without an object around it
         import torch
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return int(torch.cuda.current_stream().cuda_stream)
     return int(getattr(stream, "cuda_stream", stream))
 
 
 _TORCH_DTYPES = {F32: "float32", F16: "float16"}
+#: element types by the numbers the extension module knows
+_TYPE_CODES = {None: 0, "float32": 1, "float16": 2, "float64": 3}
 
 
 _dtype_objects = {}
@@ -187,6 +241,10 @@ def _device_buffer(t, what, nbytes: int, dtype: str = None) -> int:
     """Address of a device tensor after the checks the C ABI cannot make (it sees no sizes): a contiguous
     device tensor of the expected element type holding at least nbytes bytes.  Raises ValueError.
     `what` names the argument in the message (a string, or a tuple of parts joined only when needed)."""
+    address = (_native or _args()).address(t, nbytes, _TYPE_CODES[dtype])
+    if address is not None:
+        return address
+    # whatever is no plain tensor, and whatever fails a check
     try:
         ok = t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype is _torch_dtype(dtype)) and \
             t.numel() * t.element_size() >= nbytes
@@ -223,6 +281,9 @@ def _chunk(packed, meta, what, packed_bytes: int, meta_bytes: int):
 
 
 def _peers(packed: Sequence, meta: Sequence, what: str, packed_bytes: int, meta_bytes: int):
+    tables = (_native or _args()).tables(packed, meta, packed_bytes, meta_bytes) if meta_bytes else None
+    if tables is not None:
+        return len(packed), *tables
     W = len(packed)
     if len(meta) != W:
         raise ValueError("as many meta tensors as packed tensors")
@@ -235,9 +296,12 @@ def _peers(packed: Sequence, meta: Sequence, what: str, packed_bytes: int, meta_
 def _sizes_of(plan, qsgd: bool = False, dt: int = None) -> Tuple[int, int]:
     """(packed_bytes, meta_bytes) of a Plan or LayeredPlan, for either quantizer, optionally at another storage type."""
     dt = plan.dt if dt is None else dt
-    cache = plan.__dict__.setdefault("_sizes", {})           # a plan's arrays are not changed after construction
-    if (qsgd, dt) in cache:
-        return cache[(qsgd, dt)]
+    cache = plan.__dict__.get("_sizes")                      # a plan's arrays are not changed after construction
+    if cache is None:
+        cache = plan.__dict__["_sizes"] = {}
+    known = cache.get((qsgd, dt))
+    if known is not None:
+        return known
     pb, mb = ctypes.c_size_t(), ctypes.c_size_t()
     if isinstance(plan, LayeredPlan):
         fn, name = (lib().cgx_qsgd_layered_sizes, "cgx_qsgd_layered_sizes") if qsgd else \
@@ -450,7 +514,7 @@ def cgx_layer_sqnorms(buf, plan: Plan, sqnorm, workspace, stream=None) -> None:
     b = _elements(buf, "cgx_layer_sqnorms: buf", plan.n, plan.dt)
     out = _device_buffer(sqnorm, "cgx_layer_sqnorms: sqnorm", 8 * plan.L, "float64")
     ws = _device_buffer(workspace, "cgx_layer_sqnorms: workspace", 0)   # sized check: in the library
-    _check(lib().cgx_layer_sqnorms(b, plan.n, plan.L, plan.offsets.ctypes.data, plan.dt, out, ws,
+    _check(lib().cgx_layer_sqnorms(b, plan.n, plan.L, plan._offsets_address, plan.dt, out, ws,
                                    workspace.numel() * workspace.element_size(), _stream(stream)), "cgx_layer_sqnorms")
 
 

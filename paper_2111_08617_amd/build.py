@@ -8,6 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcgx.so")
+ARGS = os.path.join(HERE, "_cgx_args.so")
 OBJ = os.path.join(HERE, "_build")
 # (source, object name, extra flags): the quantize kernel is built for chunks of 1024 and of 2048 elements
 SOURCES = [("cgx_plan.cpp", "cgx_plan", []), ("cgx_api.cpp", "cgx_api", []), ("cgx_adaptive.cpp", "cgx_adaptive", []),
@@ -47,8 +48,25 @@ def build(verbose: bool = False, extra=(), jobs: int = 8) -> str:
         subprocess.run(cmd, check=True, cwd=CSRC)
         return obj
 
-    with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(SOURCES)))) as pool:
+    def compile_args(_):
+        # the binding's tensor checks: host code against torch's headers
+        import sysconfig
+
+        import torch
+        from torch.utils.cpp_extension import include_paths
+        libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+        cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+               *(f"-I{d}" for d in (*include_paths(), sysconfig.get_paths()["include"])),
+               os.path.join(CSRC, "cgx_tensor_args.cpp"), "-o", ARGS, f"-L{libs}", "-ltorch_python", "-ltorch_cpu", "-lc10",
+               f"-Wl,-rpath,{libs}"]
+        if verbose:
+            print(" ".join(cmd))
+        subprocess.run(cmd, check=True, cwd=CSRC)
+
+    with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(SOURCES) + 1))) as pool:
+        args = pool.submit(compile_args, None)
         objs = list(pool.map(compile_one, SOURCES))
+        args.result()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     if verbose:
         print(" ".join(cmd))

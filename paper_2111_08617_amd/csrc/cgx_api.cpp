@@ -2,6 +2,7 @@
 // the per-plan tile table cache, and kernel launches on the caller's stream.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <cstring>
 #include <memory>
@@ -33,6 +34,7 @@ struct CachedPlan {
     cgx::PlanShape shape;
     int64_t n_tiles = 0;
     int64_t plan_tiles = 0;     // tiles of the whole plan: n_tiles, or the sum over the launches of a layered plan
+    bool one_bit_layers = false;
     bool odd_tiles = false;     // some quantized tile starts on an odd element index
     bool aligned_tiles = true;  // every vectorised quantized tile starts on a 16-byte boundary of the buffer
     Tile *d_tiles = nullptr;
@@ -195,6 +197,67 @@ uint64_t plan_digest(int32_t L, const int64_t *off, const uint8_t *bits, const i
     return h;
 }
 
+// What identifies a tile table.
+struct PlanKey {
+    int32_t L;
+    const int64_t *off;
+    const uint8_t *bits;
+    int32_t bucket;
+    int dt, chunk, chunks_per_tile;
+    cgx::TableUse use;
+    const int32_t *layer_buckets;
+    bool with_copies;
+    uint64_t digest;
+};
+
+// The cached table of a key, or nothing (g_mutex is held).  A table found during a stream capture is pinned, see get_plan.
+PlanRef cached_plan(const PlanKey &k, int device, bool capturing)
+{
+    for (const auto &p : g_plans) {
+        if (p->digest == k.digest && p->device == device && p->bucket == k.bucket && p->dt == k.dt && p->chunk == k.chunk &&
+            p->chunks_per_tile == k.chunks_per_tile && p->use == k.use && p->bits.size() == size_t(k.L) &&
+            p->with_copies == k.with_copies && p->layer_buckets.size() == (k.layer_buckets ? size_t(k.L) : 0) &&
+            (!k.layer_buckets || k.L == 0 ||
+             std::memcmp(p->layer_buckets.data(), k.layer_buckets, sizeof(int32_t) * size_t(k.L)) == 0) &&
+            std::memcmp(p->bits.data(), k.bits, size_t(k.L)) == 0 &&
+            std::memcmp(p->off.data(), k.off, sizeof(int64_t) * (size_t(k.L) + 1)) == 0) {
+            p->last_use = ++g_clock;
+            if (capturing) p->pinned = true;
+            return p;
+        }
+    }
+    return nullptr;
+}
+
+bool is_capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    const bool capturing = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
+    if (!capturing) (void)hipGetLastError();       // a refused query (legacy stream beside a capture) is not this call's error
+    return capturing;
+}
+
+// The table of a plan with one bucket size that an earlier call has checked and built, found by the arrays' contents;
+// such a call needs neither the checks of the layer table nor its sizes again (2 us at 300 layers).  Nothing
+// is found for arguments that those checks would refuse: tables exist for checked plans only, and 1-bit layers
+// are left to them under the norm-and-sign quantizer.
+PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const int64_t *off, const uint8_t *bits,
+                   const Buckets &buckets, int dt, int chunk, int chunks_per_tile, cgx::TableUse use)
+{
+    // (what the checks find out without reading the arrays keeps them unread)
+    if (buckets.per_layer || L <= 0 || n <= 0 || !off || !bits || (dt != CGX_F32 && dt != CGX_F16) || buckets.uniform < 32 ||
+        buckets.uniform > 8192 || buckets.uniform % 32 || off[L] != n)
+        return nullptr;
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return nullptr;
+    const PlanKey key{L, off, bits, buckets.uniform, dt, chunk, chunks_per_tile, use, nullptr, true,
+                      plan_digest(L, off, bits, nullptr)};
+    const bool capturing = is_capturing(stream);
+    std::lock_guard<std::mutex> lock(g_mutex);
+    const PlanRef plan = cached_plan(key, device, capturing);
+    return plan && scheme == cgx::kSchemeNormSign && plan->one_bit_layers ? nullptr : plan;
+}
+
 // Finds or builds the device-resident tile table of a (valid) plan for a call on `stream`.
 // A graph that is being captured keeps the raw table pointers of the launches recorded into it, so a table
 // found during a capture is pinned for the life of the library (never the one dropped for a new plan),
@@ -207,23 +270,10 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     std::lock_guard<std::mutex> lock(g_mutex);
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return CGX_ERR_HIP;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    const bool capturing = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
-    if (!capturing) (void)hipGetLastError();       // a refused query (legacy stream beside a capture) is not this call's error
-    for (const auto &p : g_plans) {
-        if (p->digest == digest && p->device == device && p->bucket == bucket && p->dt == dt &&
-            p->chunk == chunk && p->chunks_per_tile == chunks_per_tile && p->use == use && p->bits.size() == size_t(L) &&
-            p->with_copies == with_copies && p->layer_buckets.size() == (layer_buckets ? size_t(L) : 0) &&
-            (!layer_buckets || L == 0 ||
-             std::memcmp(p->layer_buckets.data(), layer_buckets, sizeof(int32_t) * size_t(L)) == 0) &&
-            std::memcmp(p->bits.data(), bits, size_t(L)) == 0 &&
-            std::memcmp(p->off.data(), off, sizeof(int64_t) * (size_t(L) + 1)) == 0) {
-            p->last_use = ++g_clock;
-            if (capturing) p->pinned = true;
-            *out = p;
-            return CGX_OK;
-        }
-    }
+    const bool capturing = is_capturing(stream);
+    *out = cached_plan(PlanKey{L, off, bits, bucket, dt, chunk, chunks_per_tile, use, layer_buckets, with_copies, digest}, device,
+                       capturing);
+    if (*out) return CGX_OK;
     if (capturing) return CGX_ERR_CAPTURE;
     std::shared_ptr<CachedPlan> plan(new CachedPlan, [](CachedPlan *p) {
         free_plan(*p);
@@ -240,6 +290,7 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     plan->bits.assign(bits, bits + L);
     if (layer_buckets) plan->layer_buckets.assign(layer_buckets, layer_buckets + L);
     plan->with_copies = with_copies;
+    plan->one_bit_layers = std::find(bits, bits + L, uint8_t(1)) != bits + L;
     plan->shape = cgx::plan_shape(L, off, bits, bucket, dt, layer_buckets);
     std::vector<Tile> tiles;
     std::vector<uint32_t> slots;
@@ -332,29 +383,41 @@ int check_plan(int scheme, int64_t n, int32_t L, const int64_t *off, const uint8
 int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int64_t *off, const uint8_t *bits,
                   const Buckets &buckets, uint64_t seed, int dt, void *packed, void *meta, void *stream)
 {
-    int rc = check_plan(scheme, n, L, off, bits, buckets, dt);
-    if (rc != CGX_OK) return rc;
-    if (n == 0) return CGX_OK;
-    const cgx::PlanShape shape = cgx::plan_shape(L, off, bits, buckets.uniform, dt, buckets.per_layer);
+    const hipStream_t queue = static_cast<hipStream_t>(stream);
+    int32_t longest = buckets.uniform;
+    int chunk = chunk_length(kQuantizeCall, dt, longest);
+    const int per_tile = tile_length(kQuantizeCall, dt, n);
+    const PlanRef known = known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile, cgx::kWholeBuckets);
+    cgx::PlanShape shape;
+    if (known) {
+        shape = known->shape;
+    } else {
+        const int rc = check_plan(scheme, n, L, off, bits, buckets, dt);
+        if (rc != CGX_OK) return rc;
+        if (n == 0) return CGX_OK;
+        shape = cgx::plan_shape(L, off, bits, buckets.uniform, dt, buckets.per_layer);
+    }
     if (!grad || !packed || (shape.meta_bytes && !meta)) return CGX_ERR_NULL;
     if (misaligned(grad) || misaligned(packed) || misaligned(meta)) return CGX_ERR_ALIGN;
-    const int32_t longest = longest_bucket(buckets, L, off, bits);
-    const int chunk = chunk_length(kQuantizeCall, dt, longest);
-    const auto launch_quantize = chunk == cgx::chunk_of(2) ? cgx::launch_quantize_g2 : cgx::launch_quantize_g4;
-    const std::vector<Launch> launches = launches_of(buckets, L, off, bits, chunk);
+    std::vector<Launch> launches;
     std::vector<PlanRef> plans;
-    rc = get_plans(static_cast<hipStream_t>(stream), launches, L, off, bits, dt, chunk, tile_length(kQuantizeCall, dt, n),
-                   cgx::kWholeBuckets, buckets.per_layer, &plans);
-    if (rc != CGX_OK) return rc;
-    for (size_t i = 0; i < launches.size(); i++) {
-        const Launch &launch = launches[i];
-        const PlanRef &plan = plans[i];
+    if (!known) {
+        longest = longest_bucket(buckets, L, off, bits);
+        chunk = chunk_length(kQuantizeCall, dt, longest);
+        launches = launches_of(buckets, L, off, bits, chunk);
+        const int rc = get_plans(queue, launches, L, off, bits, dt, chunk, per_tile, cgx::kWholeBuckets, buckets.per_layer, &plans);
+        if (rc != CGX_OK) return rc;
+    }
+    const auto launch_quantize = chunk == cgx::chunk_of(2) ? cgx::launch_quantize_g2 : cgx::launch_quantize_g4;
+    for (size_t i = 0; i < (known ? 1 : launches.size()); i++) {
+        const CachedPlan &plan = known ? *known : *plans[i];
+        const int32_t bucket = known ? buckets.uniform : launches[i].bucket;
         const hipError_t e =
-            cgx::mapping_of(launch.bucket, chunk) == cgx::kMapWide
-                ? cgx::launch_quantize_wide(scheme, grad, dt, plan->d_tiles, plan->n_tiles, plan->odd_tiles, longest,
-                                            seed, packed, meta, launch_config(), static_cast<hipStream_t>(stream))
-                : launch_quantize(scheme, grad, dt, plan->d_tiles, plan->n_tiles, plan->odd_tiles, plan->aligned_tiles,
-                                  launch.bucket, seed, packed, meta, launch_config(), static_cast<hipStream_t>(stream));
+            cgx::mapping_of(bucket, chunk) == cgx::kMapWide
+                ? cgx::launch_quantize_wide(scheme, grad, dt, plan.d_tiles, plan.n_tiles, plan.odd_tiles, longest, seed, packed,
+                                            meta, launch_config(), queue)
+                : launch_quantize(scheme, grad, dt, plan.d_tiles, plan.n_tiles, plan.odd_tiles, plan.aligned_tiles, bucket, seed,
+                                  packed, meta, launch_config(), queue);
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;
@@ -365,28 +428,34 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
                 const int64_t *off, const uint8_t *bits, const Buckets &buckets, int dt, const void *local,
                 int local_dt, bool want_local, void *out, int out_dt, void *stream)
 {
-    int rc = check_plan(scheme, n, L, off, bits, buckets, dt);
-    if (rc != CGX_OK) return rc;
+    // A decompression (one chunk, nothing to add to) writes eight bytes per byte it reads; a kernel that only
+    // moves bytes in that mix sustains 0.75 of the HBM peak with 8 KB written per wave and 0.91 with 4 KB, so it
+    // takes the kernel of 1024-element chunks (to binary16 2048 elements are 4 KB).
+    const bool decompression = W == 1 && !want_local && launch_config().dequantize_through;
+    const int forced = launch_config().reduce_groups;
+    const int chunk = forced > 0 ? cgx::chunk_of(forced)
+                      : decompression && out_dt == CGX_F32 ? cgx::chunk_of(2) : cgx::kDefaultChunk;
+    const int per_tile = tile_length(kOtherCall, dt, n);
+    const hipStream_t queue = static_cast<hipStream_t>(stream);
+    PlanRef plan = known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile, cgx::kPieces);
+    if (!plan) {
+        const int rc = check_plan(scheme, n, L, off, bits, buckets, dt);
+        if (rc != CGX_OK) return rc;
+    }
     if (W < 1 || W > CGX_MAX_PEERS) return CGX_ERR_PEERS;
     if (n == 0) return CGX_OK;
-    const cgx::PlanShape shape = cgx::plan_shape(L, off, bits, buckets.uniform, dt, buckets.per_layer);
+    const cgx::PlanShape shape =
+        plan ? plan->shape : cgx::plan_shape(L, off, bits, buckets.uniform, dt, buckets.per_layer);
     if (!packed || !meta || !out || (want_local && !local)) return CGX_ERR_NULL;
     for (int w = 0; w < W; w++) {
         if (!packed[w] || (shape.meta_bytes && !meta[w])) return CGX_ERR_NULL;
         if (misaligned(packed[w]) || misaligned(meta[w])) return CGX_ERR_ALIGN;
     }
     if (misaligned(out) || misaligned(local)) return CGX_ERR_ALIGN;
-    // A decompression (one chunk, nothing to add to) writes eight bytes per byte it reads; a kernel that only
-    // moves bytes in that mix sustains 0.75 of the HBM peak with 8 KB written per wave and 0.91 with 4 KB, so it
-    // takes the kernel of 1024-element chunks (to binary16 2048 elements are 4 KB).
-    const bool decompression = W == 1 && !local && launch_config().dequantize_through;
-    const int forced = launch_config().reduce_groups;
-    const int chunk = forced > 0 ? cgx::chunk_of(forced)
-                      : decompression && out_dt == CGX_F32 ? cgx::chunk_of(2) : cgx::kDefaultChunk;
-    PlanRef plan;
-    rc = get_plan(static_cast<hipStream_t>(stream), L, off, bits, buckets.uniform, dt, chunk, tile_length(kOtherCall, dt, n),
-                  cgx::kPieces, &plan, buckets.per_layer);
-    if (rc != CGX_OK) return rc;
+    if (!plan) {
+        const int rc = get_plan(queue, L, off, bits, buckets.uniform, dt, chunk, per_tile, cgx::kPieces, &plan, buckets.per_layer);
+        if (rc != CGX_OK) return rc;
+    }
     const auto launch_reduce = chunk == cgx::kDefaultChunk ? cgx::launch_dequant_reduce_g4 : cgx::launch_dequant_reduce_g2;
     // peers are folded in order, kPeersPerLaunch at a time, so the sum order is local, 0, 1, ..., W-1;
     // a later launch starts from the binary32 result of the one before (W <= kPeersPerLaunch
@@ -407,8 +476,7 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
         const bool small = int64_t(n) * (out_dt == CGX_F16 ? 2 : 4) <= launch_config().keep_sums_max_bytes;
         const int policy = decompression ? cgx::kStoreThrough : small ? cgx::kStoreKeep : cgx::kStoreStream;
         const hipError_t e = launch_reduce(scheme, peers, k, dt, plan->d_tiles, plan->n_tiles,
-                                           init, init_dt, out, out_dt, policy, launch_config(),
-                                           static_cast<hipStream_t>(stream));
+                                           init, init_dt, out, out_dt, policy, launch_config(), queue);
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;
@@ -418,12 +486,23 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
                const int64_t *layer_offsets, const uint8_t *bits_per_layer, const Buckets &buckets, int dt,
                uint64_t seed, void *packed_out, void *meta_out, void *stream)
 {
-    int rc = check_plan(scheme, n, L, layer_offsets, bits_per_layer, buckets, dt);
-    if (rc != CGX_OK) return rc;
+    const hipStream_t queue = static_cast<hipStream_t>(stream);
+    const int per_tile = tile_length(kFusedCall, dt, n);
+    // tables of the chunks and of the output, which lays out its pass-through layers as binary32
+    const PlanRef known_in = known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt, cgx::kDefaultChunk,
+                                        per_tile, cgx::kWholeBuckets);
+    const PlanRef known_out = dt == CGX_F32 || !known_in ? known_in
+                                                         : known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets,
+                                                                      CGX_F32, cgx::kDefaultChunk, per_tile, cgx::kWholeBuckets);
+    const bool known = known_in && known_out;
+    if (!known) {
+        const int rc = check_plan(scheme, n, L, layer_offsets, bits_per_layer, buckets, dt);
+        if (rc != CGX_OK) return rc;
+    }
     if (W < 1 || W > CGX_MAX_FUSED_PEERS) return CGX_ERR_PEERS;
     if (n == 0) return CGX_OK;
     const cgx::PlanShape shape =
-        cgx::plan_shape(L, layer_offsets, bits_per_layer, buckets.uniform, dt, buckets.per_layer);
+        known ? known_in->shape : cgx::plan_shape(L, layer_offsets, bits_per_layer, buckets.uniform, dt, buckets.per_layer);
     if (!packed || !meta || !packed_out || (shape.meta_bytes && !meta_out)) return CGX_ERR_NULL;
     for (int w = 0; w < W; w++) {
         if (!packed[w] || (shape.meta_bytes && !meta[w])) return CGX_ERR_NULL;
@@ -435,14 +514,18 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
         peers.packed[i] = static_cast<const uint8_t *>(packed[i]);
         peers.meta[i] = static_cast<const float *>(meta[i]);
     }
-    for (const Launch &launch : launches_of(buckets, L, layer_offsets, bits_per_layer, cgx::kDefaultChunk)) {
-        PlanRef in, out;
-        rc = get_plan(static_cast<hipStream_t>(stream), L, layer_offsets, bits_per_layer, launch.bucket, dt,
-                      cgx::kDefaultChunk, tile_length(kFusedCall, dt, n), cgx::kWholeBuckets, &in, buckets.per_layer, launch.with_copies);
-        if (rc != CGX_OK) return rc;
-        rc = get_plan(static_cast<hipStream_t>(stream), L, layer_offsets, bits_per_layer, launch.bucket, CGX_F32,
-                      cgx::kDefaultChunk, tile_length(kFusedCall, dt, n), cgx::kWholeBuckets, &out, buckets.per_layer, launch.with_copies);
-        if (rc != CGX_OK) return rc;
+    const std::vector<Launch> launches = known ? std::vector<Launch>{{buckets.uniform, true}}
+                                               : launches_of(buckets, L, layer_offsets, bits_per_layer, cgx::kDefaultChunk);
+    for (const Launch &launch : launches) {
+        PlanRef in = known_in, out = known_out;
+        if (!known) {
+            int rc = get_plan(queue, L, layer_offsets, bits_per_layer, launch.bucket, dt, cgx::kDefaultChunk, per_tile,
+                              cgx::kWholeBuckets, &in, buckets.per_layer, launch.with_copies);
+            if (rc != CGX_OK) return rc;
+            rc = get_plan(queue, L, layer_offsets, bits_per_layer, launch.bucket, CGX_F32, cgx::kDefaultChunk, per_tile,
+                          cgx::kWholeBuckets, &out, buckets.per_layer, launch.with_copies);
+            if (rc != CGX_OK) return rc;
+        }
         if (in->n_tiles != out->n_tiles) return CGX_ERR_SIZE;     // cannot happen: same tiling for both layouts
         const hipError_t e =
             cgx::mapping_of(launch.bucket, cgx::kDefaultChunk) == cgx::kMapWide

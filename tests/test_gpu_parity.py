@@ -776,3 +776,33 @@ def test_layer_lengths_around_every_edge_of_a_run(torch, oracle, bucket, dt):
                                 local=w.gradient(7))
     out = total.cpu().numpy()
     assert (out[w.n:] == 5.0).all() and np.array_equal(out[:w.n].view(np.uint32), ref["sum32"].view(np.uint32))
+
+
+def test_a_cached_plan_does_not_excuse_bad_arguments(torch, oracle):
+    """Tables are found by the contents of the layer table before it is checked: what the checks refuse stays refused when
+    a table of almost the same call exists."""
+    import ctypes
+    off, bits = np.array([0, 2048, 5000], np.int64), np.array([4, 1], np.uint8)
+    x = np.linspace(-1, 1, 5000).astype(np.float32)
+    gp, gm = gpu_quantize(torch, x, off, bits, 128, 3, wl.F32)
+    op, om = oracle.quantize(x, off, bits, 128, 3, wl.F32)
+    assert_same_chunk(gp, gm, op, om, "cached")
+    L, g = cgx.lib(), dev(torch, x)
+    out = torch.zeros(8192, dtype=torch.uint8, device="cuda")
+    meta = torch.zeros(512, device="cuda")
+
+    def quantize(fn, n=5000, layers=2, bucket=128, dt=0, grad=g.data_ptr(), packed=out.data_ptr()):
+        return fn(grad, n, layers, off.ctypes.data, bits.ctypes.data, bucket, 3, dt, packed, meta.data_ptr(), None)
+
+    assert quantize(L.cgx_quantize) == 0
+    assert quantize(L.cgx_quantize, n=4999) == -2 and quantize(L.cgx_quantize, layers=1) == -2
+    assert quantize(L.cgx_quantize, bucket=100) == -5 and quantize(L.cgx_quantize, dt=7) == -7
+    assert quantize(L.cgx_quantize, grad=None) == -1 and quantize(L.cgx_quantize, packed=out.data_ptr() + 4) == -9
+    assert quantize(L.cgx_qsgd_quantize) == -4                       # a 1-bit layer
+    one = (ctypes.c_void_p * 1)(out.data_ptr())
+    m = (ctypes.c_void_p * 1)(meta.data_ptr())
+    total = torch.zeros(5000, device="cuda")
+    args = (5000, 2, off.ctypes.data, bits.ctypes.data, 128, 0, total.data_ptr(), None)
+    assert L.cgx_dequant_reduce(one, m, 1, *args) == 0
+    assert L.cgx_dequant_reduce(one, m, 0, *args) == -6 and L.cgx_qsgd_dequant_reduce(one, m, 1, *args) == -4
+    torch.cuda.synchronize()

@@ -478,3 +478,17 @@ def test_group_to_bucket_lookup_by_multiply_and_shift_is_exact():
     for gb in range(1, 257):
         inv = (65536 + gb - 1) // gb
         assert np.array_equal((G * np.uint64(inv)) >> np.uint64(16), G // np.uint64(gb)), gb
+
+
+def test_copies_of_a_plan_point_at_their_own_arrays():
+    """The binding keeps the addresses of a plan's arrays; copies, pickles and replaced arrays must not inherit them."""
+    import copy
+    import pickle
+    off, bits = np.array([0, 100, 300], np.int64), np.array([4, 2], np.uint8)
+    for plan in (cgx.Plan(off, bits, 128), cgx.LayeredPlan(off, bits, np.array([64, 128], np.int32))):
+        for other in (copy.deepcopy(plan), pickle.loads(pickle.dumps(plan)), copy.copy(plan)):
+            assert other.args[2] == other.offsets.ctypes.data and other.args[3] == other.bits.ctypes.data
+            assert isinstance(plan, cgx.Plan) or other.args[4] == other.buckets.ctypes.data
+            assert np.array_equal(other.offsets, off) and other.n == 300 and other.dt == plan.dt
+        plan.bits = np.array([8, 8], np.uint8)
+        assert plan.args[3] == plan.bits.ctypes.data
