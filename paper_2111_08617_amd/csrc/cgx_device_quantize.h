@@ -138,23 +138,37 @@ __device__ __forceinline__ void quantize_chunk_rows(const float (&x)[G][8], int 
     wave_lds_fence();
 }
 
-// A chunk that starts on a 16-byte boundary, fetched through the wave's LDS area: every load
-// instruction moves 1 KB of consecutive bytes straight into LDS (no registers held while in
-// flight), and each lane then reads its groups from there.  Read into registers directly, a
-// lane's 32 consecutive bytes come from two instructions that each cover every other 16 bytes
-// of 2 KB; a kernel that only moves bytes loses 5 to 9 % of its rate with that pattern.
+// A chunk fetched through the wave's LDS area, so that every load instruction takes 1 KB of consecutive bytes; each lane
+// then reads its groups from there.  Read into registers directly, a lane's 32 consecutive bytes come from two
+// instructions that each cover every other 16 bytes of 2 KB; a kernel that only moves bytes loses 5 to 9 % of its
+// rate with that pattern.  ALIGNED: the chunk starts on a 16-byte boundary and the loads go straight into LDS (no
+// registers held while in flight).  Otherwise they pass through registers, at the alignment of an element: for
+// binary32 (quantize of 67 M elements in ragged layers, us: 4 bit, buckets of 512, 56.5 read directly and 52.4 this way,
+// 52 where the layers are aligned; 2 bit, 128, 64.4 and 51.2; 4 bit, 32, 61.4 and 55.5).  A lane's 8 binary16
+// elements are one vector, so that type has no such pattern to avoid.
 // The area must hold the chunk as stored (kChunk elements of DT).
-template <int DT>
-__device__ __forceinline__ void chunk_through_lds(const void *__restrict__ grad, int64_t first, const LaneMap &map,
+template <int DT, bool ALIGNED, typename Map>
+__device__ __forceinline__ void chunk_through_lds(const void *__restrict__ grad, int64_t first, const Map &map,
                                                   float (&x)[G][8], uint4v *stage, int lane)
 {
     constexpr int S = DT == CGX_F16 ? 2 : 4;
     constexpr int kVecs = kChunk * S / 16;
     static_assert(kVecs % kWave == 0, "whole load instructions");
-    const uint4v *src = reinterpret_cast<const uint4v *>(reinterpret_cast<const uint8_t *>(grad) + first * S);
+    const uint8_t *at = reinterpret_cast<const uint8_t *>(grad) + first * S;
+    if constexpr (ALIGNED) {
+        const uint4v *src = reinterpret_cast<const uint4v *>(at);
 #pragma unroll
-    for (int k = 0; k < kVecs / kWave; k++) load_to_lds16(src + k * kWave + lane, stage + k * kWave);
-    wait_vector_memory();
+        for (int k = 0; k < kVecs / kWave; k++) load_to_lds16(src + k * kWave + lane, stage + k * kWave);
+        wait_vector_memory();
+    } else {
+        using Vec = std::conditional_t<DT == CGX_F16, uint4u2, uint4u4>;
+        const Vec *src = reinterpret_cast<const Vec *>(at);
+        uint4v raw[kVecs / kWave];
+#pragma unroll
+        for (int k = 0; k < kVecs / kWave; k++) raw[k] = __builtin_nontemporal_load(src + k * kWave + lane);
+#pragma unroll
+        for (int k = 0; k < kVecs / kWave; k++) stage[k * kWave + lane] = raw[k];
+    }
     wave_lds_fence();
 #pragma unroll
     for (int r = 0; r < G; r++) {
@@ -189,8 +203,8 @@ __device__ __forceinline__ void quantize_fast(const void *__restrict__ grad, uin
     for (int c = 0; c < chunks; c++) {
         const int64_t first = tile.elem0 + int64_t(c) * kChunk;
         float x[G][8];
-        if constexpr (VIA_LDS) {
-            chunk_through_lds<DT>(grad, first, map, x, stage, lane);
+        if constexpr (VIA_LDS || DT == CGX_F32) {
+            chunk_through_lds<DT, VIA_LDS>(grad, first, map, x, stage, lane);
         } else {
 #pragma unroll
             for (int r = 0; r < G; r++) load8<DT>(grad, first + map.group(r), x[r]);
@@ -200,6 +214,12 @@ __device__ __forceinline__ void quantize_fast(const void *__restrict__ grad, uin
                                      packed + tile.packed_off + int64_t(c) * (kChunk * BITS / 8), stage);
     }
 }
+
+// Row-by-row mapping: group r of a lane is elements [512 r + 8 lane, + 8) of the chunk.
+struct RowMap {
+    int lane;
+    __device__ __forceinline__ int group(int r) const { return r * (kWave * 8) + lane * 8; }
+};
 
 // quantize_fast for buckets of 32 or 64 elements (row-by-row mapping).
 template <int SCHEME, int DT, int BITS, bool ODD>
@@ -213,8 +233,12 @@ __device__ __forceinline__ void quantize_fast_rows(const void *__restrict__ grad
     for (int c = 0; c < chunks; c++) {
         const int64_t first = tile.elem0 + int64_t(c) * kChunk;
         float x[G][8];
+        if constexpr (DT == CGX_F32) {
+            chunk_through_lds<DT, false>(grad, first, RowMap{lane}, x, stage, lane);
+        } else {
 #pragma unroll
-        for (int r = 0; r < G; r++) load8<DT>(grad, first + r * (kWave * 8) + lane * 8, x[r]);
+            for (int r = 0; r < G; r++) load8<DT>(grad, first + RowMap{lane}.group(r), x[r]);
+        }
         quantize_chunk_rows<SCHEME, BITS, ODD>(x, bucket, lane, first, key,
                                           meta + kMetaFloats<SCHEME> * (tile.bucket0 + c * buckets_per_chunk),
                                           packed + tile.packed_off + int64_t(c) * (kChunk * BITS / 8), stage);
