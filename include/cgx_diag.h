@@ -28,11 +28,12 @@ extern "C" {
  * chunk).
  * Every element of every non-empty layer lies in exactly one tile and tiles never
  * cross layers (paper Sec. 4.1).  This is the table of one chunk per vectorised
- * tile that the statistics walk.  The other calls cut pass-through layers into tiles of 1024
- * elements instead of 8192, a reduction also cuts buckets longer than a chunk, and cgx_quantize on a binary16 gradient of 2^24 elements
- * or more, and the fused reduce + requantize on 2^27 elements or more, join 2
- * consecutive chunks of a layer into one tile (same bytes out; a wave's set-up is
- * spread over more input).  At most `capacity` records
+ * tile that the statistics walk.  The other calls cut pass-through layers into
+ * tiles of 1024 elements instead of 8192, and a reduction also cuts buckets longer
+ * than a chunk; cgx_quantize on a binary16 gradient of 2^24 elements or more, and the
+ * fused reduce + requantize on 2^27 elements or more, join 2 consecutive chunks of a
+ * layer into one tile (same bytes out; a wave's set-up is spread over more
+ * input).  At most `capacity` records
  * are written; *n_tiles receives the full count.  Pure host computation.
  */
 int cgx_plan_tiles(int64_t n, int32_t L, const int64_t *layer_offsets, const uint8_t *bits_per_layer,
@@ -42,8 +43,9 @@ int cgx_plan_tiles(int64_t n, int32_t L, const int64_t *layer_offsets, const uin
  * The same table for kernels whose chunk is chunk_elements (1024 or 2048; CGX_ERR_SIZE otherwise).
  * cgx_plan_tiles gives the table of 2048-element chunks, which the reduce, fused and statistics
  * kernels and the binary16 quantizer walk; cgx_quantize on binary32 input, cgx_requantize and
- * cgx_dequantize to binary32 walk the table of 1024-element chunks (buckets of 2048 elements are then one-bucket tiles of
- * kind 4, like those of 4096 and 8192).
+ * cgx_dequantize to binary32 walk the table of 1024-element chunks, unless a call that quantizes has a
+ * bucket of more than 1024 elements (in this table buckets of 2048 are one-bucket tiles of kind 4, like those
+ * of 4096 and 8192).
  */
 int cgx_plan_tiles_chunk(int64_t n, int32_t L, const int64_t *layer_offsets, const uint8_t *bits_per_layer,
                          int32_t bucket, cgx_dtype dt, int32_t chunk_elements, void *tiles_out /* host */,

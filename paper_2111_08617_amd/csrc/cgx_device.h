@@ -547,16 +547,17 @@ struct Run {
     int buckets;     // buckets (the last one may be short)
     int bi;          // bucket of this lane (lanes past the end: the last bucket)
     int left;        // elements from this lane's first one to the end (any sign)
-    __device__ __forceinline__ Run(int count_, int bucket, int lane) : count(count_)
+    // own: groups of 8 elements a lane holds, G or (the quantizer's short runs) fewer
+    __device__ __forceinline__ Run(int count_, int bucket, int lane, int own = G) : count(count_)
     {
-        lanes = bucket / (8 * G);
+        lanes = bucket / (8 * own);
         // (l + 0.5) / lanes lies at least 0.5 / lanes from every whole number: the approximate reciprocal is exact enough
         const float inv = __builtin_amdgcn_rcpf(float(lanes));
-        const int last = int((float((count - 1) / (8 * G)) + 0.5f) * inv);
+        const int last = int((float((count - 1) / (8 * own)) + 0.5f) * inv);
         buckets = __builtin_amdgcn_readfirstlane(last) + 1;
         bi = int((float(lane) + 0.5f) * inv);
         bi = bi < buckets ? bi : buckets - 1;
-        left = count - lane * (8 * G);
+        left = count - lane * (8 * own);
     }
     // how many of the 8 elements of group r exist
     __device__ __forceinline__ int valid(int r) const { return left - 8 * r >= 8 ? 8 : left - 8 * r > 0 ? left - 8 * r : 0; }
@@ -613,12 +614,13 @@ struct RunLoad {
         }
         wave_lds_fence();
     }
-    // group r of this lane
+    // group r of this lane, of OWN
+    template <int OWN = G>
     __device__ __forceinline__ static void group(const uint4v *stage, int lane, int r, float (&x)[8])
     {
 #pragma unroll
         for (int c = 0; c < 8 / kPerVec; c++) {
-            const uint4v v = stage[run_slot<kPerLane>(lane * kPerLane + r * (8 / kPerVec) + c)];
+            const uint4v v = stage[run_slot<kPerLane>((lane * OWN + r) * (8 / kPerVec) + c)];
             if (DT == CGX_F16) {
                 const half8v h = __builtin_bit_cast(half8v, v);
 #pragma unroll
@@ -636,11 +638,12 @@ struct RunLoad {
         wait_lds_reads();
         wave_lds_fence();
     }
-    __device__ __forceinline__ void finish(int count, int lane, uint4v *stage, float (&x)[G][8]) const
+    template <int OWN>
+    __device__ __forceinline__ void finish(int count, int lane, uint4v *stage, float (&x)[OWN][8]) const
     {
         park(count, lane, stage);
 #pragma unroll
-        for (int r = 0; r < G; r++) group(stage, lane, r, x[r]);
+        for (int r = 0; r < OWN; r++) group<OWN>(stage, lane, r, x[r]);
         release();
     }
 };

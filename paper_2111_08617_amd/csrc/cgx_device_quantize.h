@@ -37,11 +37,11 @@ __device__ __forceinline__ uint64_t encode_group(const float (&x)[8], const Scal
 }
 
 // Minimum and maximum (kNormSign: +0 and the largest magnitude) of a lane's chunk, folded into mn / mx.
-template <int SCHEME>
-__device__ __forceinline__ void lane_extent(const float (&x)[G][8], float &mn, float &mx)
+template <int SCHEME, int OWN>
+__device__ __forceinline__ void lane_extent(const float (&x)[OWN][8], float &mn, float &mx)
 {
 #pragma unroll
-    for (int r = 0; r < G; r++)
+    for (int r = 0; r < OWN; r++)
 #pragma unroll
         for (int j = 0; j < 8; j++) {
             if (SCHEME == kNormSign) {
@@ -245,17 +245,17 @@ __device__ __forceinline__ void quantize_fast_rows(const void *__restrict__ grad
     }
 }
 
-// The codes of a lane's groups of a run (8 * BITS bits each, group after group) into LDS, G * BITS bytes per lane.
+// The codes of a lane's groups of a run (8 * BITS bits each, group after group) into LDS, OWN * BITS bytes per lane.
 // The area starts on 16 bytes.
-template <int BITS>
-__device__ __forceinline__ void stage_run_codes(uint8_t *area, const uint64_t (&codes)[G], int lane)
+template <int BITS, int OWN>
+__device__ __forceinline__ void stage_run_codes(uint8_t *area, const uint64_t (&codes)[OWN], int lane)
 {
-    if constexpr (G == 4) {
+    if constexpr (OWN == 4) {
         // 32 codes are BITS whole dwords
         constexpr int kAlign = BITS % 4 == 0 ? 16 : BITS % 2 == 0 ? 8 : 4;
         uint32_t w[BITS + 2] = {};
 #pragma unroll
-        for (int r = 0; r < G; r++) {
+        for (int r = 0; r < OWN; r++) {
             const int d = r * BITS / 4, shift = r * BITS % 4 * 8;
             w[d] |= uint32_t(codes[r] << shift);
             w[d + 1] |= uint32_t((codes[r] << shift) >> 32);
@@ -264,7 +264,7 @@ __device__ __forceinline__ void stage_run_codes(uint8_t *area, const uint64_t (&
         __builtin_memcpy(__builtin_assume_aligned(area + lane * (4 * BITS), kAlign), w, 4 * BITS);
     } else {
 #pragma unroll
-        for (int r = 0; r < G; r++) stage_codes<BITS>(area + (lane * G + r) * BITS, codes[r]);
+        for (int r = 0; r < OWN; r++) stage_codes<BITS>(area + (lane * OWN + r) * BITS, codes[r]);
     }
 }
 
@@ -275,16 +275,16 @@ constexpr int kRunStageBytes = kChunk * (DT == CGX_F16 ? 2 : 4) > kChunk + 16 + 
                                                                                               : kChunk + 16 + 2 * kWave * 8;
 
 // Extent (kNormSign: +0 and the largest magnitude) of the elements of a run that a lane holds; nothing: the neutral one.
-template <int SCHEME>
-__device__ __forceinline__ float2 run_extent(const float (&x)[G][8], const Run &run)
+template <int SCHEME, int OWN>
+__device__ __forceinline__ float2 run_extent(const float (&x)[OWN][8], const Run &run)
 {
     // kNormSign: the zeros of the missing elements are neutral for the largest magnitude
     float mn = SCHEME == kNormSign ? 0.0f : __builtin_inff(), mx = SCHEME == kNormSign ? 0.0f : -__builtin_inff();
-    if (SCHEME == kNormSign || run.left >= 8 * G) {
+    if (SCHEME == kNormSign || run.left >= 8 * OWN) {
         lane_extent<SCHEME>(x, mn, mx);
     } else {
 #pragma unroll
-        for (int r = 0; r < G; r++) {
+        for (int r = 0; r < OWN; r++) {
             const int v = run.valid(r);
 #pragma unroll
             for (int j = 0; j < 8; j++) {
@@ -299,18 +299,18 @@ __device__ __forceinline__ float2 run_extent(const float (&x)[G][8], const Run &
 // The run's codes under a scale per lane: staged, then sent out with `pad` zero bytes behind them.  out is a multiple
 // of 4 bytes, and so is the number of bytes written: a run starts a multiple of 32 codes into its segment of the
 // stream and either ends one or is padded to the segment's 16 bytes.
-template <int SCHEME, int BITS, bool ODD>
-__device__ __forceinline__ void encode_run(const float (&x)[G][8], const Run &run, Scale s, int lane, int64_t first,
+template <int SCHEME, int BITS, bool ODD, int OWN>
+__device__ __forceinline__ void encode_run(const float (&x)[OWN][8], const Run &run, Scale s, int lane, int64_t first,
                                            uint32_t key, uint8_t *__restrict__ out, uint32_t pad, uint4v *stage)
 {
     // What the widths have in common (draws, positions between the levels) is not computed ahead of the choice of a
     // width: it would take 50 registers.
     asm volatile("" : "+v"(lane), "+v"(s.inv16) : "i"(BITS));
     uint8_t *area = reinterpret_cast<uint8_t *>(stage);
-    uint64_t codes[G];
+    uint64_t codes[OWN];
 #pragma unroll
-    for (int r = 0; r < G; r++) {
-        const uint32_t pair0 = uint32_t(uint64_t(first + (lane * G + r) * 8) >> 1);
+    for (int r = 0; r < OWN; r++) {
+        const uint32_t pair0 = uint32_t(uint64_t(first + (lane * OWN + r) * 8) >> 1);
         codes[r] = encode_group<SCHEME, BITS, ODD>(x[r], s, pair0, key, uint32_t(first) & 1u);
         const int v = run.valid(r);
         codes[r] &= v == 8 ? ~uint64_t(0) : (uint64_t(1) << (v * BITS)) - 1u;       // nothing past the end
@@ -318,7 +318,7 @@ __device__ __forceinline__ void encode_run(const float (&x)[G][8], const Run &ru
         __builtin_amdgcn_sched_barrier(0);
     }
     stage_run_codes<BITS>(area, codes, lane);
-    if (lane < 4) reinterpret_cast<uint32_t *>(area + kChunk * BITS / 8)[lane] = 0;      // padding behind a full chunk
+    if (lane < 4) reinterpret_cast<uint32_t *>(area + kWave * OWN * BITS)[lane] = 0;      // padding behind the last lane's codes
     wave_lds_fence();
     const int bytes = (run.count * BITS + 7) / 8 + int(pad), vecs = bytes / 16;
     for (int v = lane; v < vecs; v += kWave) __builtin_nontemporal_store(stage[v], reinterpret_cast<uint4u4 *>(out) + v);
@@ -329,8 +329,8 @@ __device__ __forceinline__ void encode_run(const float (&x)[G][8], const Run &ru
 // x holds a run (zeros where there is no element) -> meta of its buckets and its packed codes.  The scale of a
 // bucket comes from an extent per lane parked in LDS: the lanes are split into sets of P (a power of two,
 // 64 / P >= buckets > 32 / P, so a lane folds at most two entries), each of which folds the extents of one bucket.
-template <int SCHEME, int BITS, bool ODD>
-__device__ __forceinline__ void quantize_run_regs(const float (&x)[G][8], const Run &run, int lane, int64_t first, uint32_t key,
+template <int SCHEME, int BITS, bool ODD, int OWN>
+__device__ __forceinline__ void quantize_run_regs(const float (&x)[OWN][8], const Run &run, int lane, int64_t first, uint32_t key,
                                                   float *__restrict__ meta, uint8_t *__restrict__ out, uint32_t pad, uint4v *stage)
 {
     constexpr uint32_t kLevels = top_level<SCHEME>(BITS);
@@ -363,19 +363,26 @@ __device__ __forceinline__ void quantize_run_regs(const float (&x)[G][8], const 
     encode_run<SCHEME, BITS, ODD>(x, run, Scale{0.0f, own.x, own.y}, lane, first, key, out, pad, stage);
 }
 
-template <int SCHEME, int DT, int BITS, bool ODD>
+// OWN: groups a lane holds.  A wave pays for them whether or not all its lanes have elements.
+template <int SCHEME, int DT, int BITS, bool ODD, int OWN = G>
 __device__ __forceinline__ void quantize_run(const void *__restrict__ grad, uint8_t *__restrict__ packed,
                                              float *__restrict__ meta, const Tile &tile, int bucket,
                                              uint32_t seed_lo, uint32_t seed_hi, int lane, uint4v *stage)
 {
-    const Run run(int(tile.count), bucket, lane);
+    const Run run(int(tile.count), bucket, lane, OWN);
     const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
     RunLoad<DT> load;
     load.issue(grad, tile.elem0, run.count, lane);
-    float x[G][8];
+    float x[OWN][8];
     load.finish(run.count, lane, stage, x);
     quantize_run_regs<SCHEME, BITS, ODD>(x, run, lane, tile.elem0, key, meta + kMetaFloats<SCHEME> * tile.bucket0,
                                          packed + tile.packed_off, tile.pad, stage);
+}
+
+// A run that 24 elements per lane hold, with a bucket size of which 24 is a divisor (a lane stays within a bucket).
+__device__ __forceinline__ bool three_groups_hold(const Tile &tile, int bucket)
+{
+    return tile.count <= uint32_t(kWave * 24) && tile.count > uint32_t(kWave * 16) && bucket % 24 == 0;
 }
 
 // What no other path takes (a tile across two key blocks of the generator): one bucket at a time, two passes.
