@@ -139,42 +139,45 @@ def _args():
     return _native
 
 
-class _HostArray:
-    """An array attribute of a plan: stored next to its address (numpy makes a new object per look-up of that)."""
+class _HostPlan:
+    """What Plan and LayeredPlan share: the host arrays of a plan, kept alive and contiguous for the C calls, and the
+    arguments of these calls (`args`), formed once: numpy makes a new object per look-up of an address."""
 
-    def __set_name__(self, owner, name):
-        self.name, self.address = "_" + name, "_" + name + "_address"
+    #: attribute -> element type the C calls read
+    _ARRAYS = {}
 
-    def __get__(self, plan, owner=None):
-        return self if plan is None else plan.__dict__[self.name]
+    def __setattr__(self, name, value):
+        if name in self._ARRAYS:
+            value = np.ascontiguousarray(value, dtype=self._ARRAYS[name])
+        self.__dict__[name] = value
+        self.__dict__.pop("_args", None)
 
-    def __set__(self, plan, array):
-        plan.__dict__[self.name] = array
-        plan.__dict__[self.address] = array.ctypes.data
-
-
-class _HostArrays:
-    """Copies and pickles of a plan take the arrays, never their addresses."""
-
+    # copies and pickles take the attributes, not what was derived from them
     def __getstate__(self):
-        return {k: v for k, v in self.__dict__.items() if not k.endswith("_address")}
+        return {k: v for k, v in self.__dict__.items() if k != "_args"}
 
     def __setstate__(self, state):
         for k, v in state.items():
-            if isinstance(v, np.ndarray):
-                setattr(self, k.lstrip("_"), v)
-            else:
-                self.__dict__[k] = v
+            # (a state may hold the arrays under a name with an underscore in front)
+            self.__dict__[k[1:] if k[1:] in self._ARRAYS and k[0] == "_" else k] = v
+
+    @property
+    def args(self):
+        known = self.__dict__.get("_args")
+        if known is None:
+            sizes = self.buckets.ctypes.data if "buckets" in self._ARRAYS else self.bucket
+            known = self.__dict__["_args"] = (self.n, self.L, self.offsets.ctypes.data, self.bits.ctypes.data, sizes)
+        return known
 
 
-class Plan(_HostArrays):
+class Plan(_HostPlan):
     """Host arrays of a plan, kept alive and contiguous for the C calls."""
 
-    offsets, bits = _HostArray(), _HostArray()
+    _ARRAYS = {"offsets": np.int64, "bits": np.uint8}
 
     def __init__(self, layer_offsets, bits_per_layer, bucket: int, dt: int = F32):
-        self.offsets = np.ascontiguousarray(layer_offsets, dtype=np.int64)
-        self.bits = np.ascontiguousarray(bits_per_layer, dtype=np.uint8)
+        self.offsets = layer_offsets
+        self.bits = bits_per_layer
         if self.offsets.ndim != 1 or self.bits.ndim != 1 or self.offsets.size != self.bits.size + 1:
             raise ValueError("layer_offsets must have one more entry than bits_per_layer")
         self.bucket = int(bucket)
@@ -182,29 +185,21 @@ class Plan(_HostArrays):
         self.n = int(self.offsets[-1])
         self.L = int(self.bits.size)
 
-    @property
-    def args(self):
-        return (self.n, self.L, self._offsets_address, self._bits_address, self.bucket)
 
-
-class LayeredPlan(_HostArrays):
+class LayeredPlan(_HostPlan):
     """A plan with a bucket size per layer (the cgx_layered_* calls)."""
 
-    offsets, bits, buckets = _HostArray(), _HostArray(), _HostArray()
+    _ARRAYS = {"offsets": np.int64, "bits": np.uint8, "buckets": np.int32}
 
     def __init__(self, layer_offsets, bits_per_layer, buckets_per_layer, dt: int = F32):
-        self.offsets = np.ascontiguousarray(layer_offsets, dtype=np.int64)
-        self.bits = np.ascontiguousarray(bits_per_layer, dtype=np.uint8)
-        self.buckets = np.ascontiguousarray(buckets_per_layer, dtype=np.int32)
+        self.offsets = layer_offsets
+        self.bits = bits_per_layer
+        self.buckets = buckets_per_layer
         if self.offsets.ndim != 1 or self.offsets.size != self.bits.size + 1 or self.buckets.shape != self.bits.shape:
             raise ValueError("one bits and one bucket entry per layer, one more layer offset")
         self.dt = int(dt)
         self.n = int(self.offsets[-1])
         self.L = int(self.bits.size)
-
-    @property
-    def args(self):
-        return (self.n, self.L, self._offsets_address, self._bits_address, self._buckets_address)
 
 
 def _check(status: int, where: str) -> None:
@@ -514,7 +509,7 @@ def cgx_layer_sqnorms(buf, plan: Plan, sqnorm, workspace, stream=None) -> None:
     b = _elements(buf, "cgx_layer_sqnorms: buf", plan.n, plan.dt)
     out = _device_buffer(sqnorm, "cgx_layer_sqnorms: sqnorm", 8 * plan.L, "float64")
     ws = _device_buffer(workspace, "cgx_layer_sqnorms: workspace", 0)   # sized check: in the library
-    _check(lib().cgx_layer_sqnorms(b, plan.n, plan.L, plan._offsets_address, plan.dt, out, ws,
+    _check(lib().cgx_layer_sqnorms(b, *plan.args[:3], plan.dt, out, ws,
                                    workspace.numel() * workspace.element_size(), _stream(stream)), "cgx_layer_sqnorms")
 
 

@@ -492,3 +492,19 @@ def test_copies_of_a_plan_point_at_their_own_arrays():
             assert np.array_equal(other.offsets, off) and other.n == 300 and other.dt == plan.dt
         plan.bits = np.array([8, 8], np.uint8)
         assert plan.args[3] == plan.bits.ctypes.data
+
+
+def test_copies_of_a_plan_keep_attributes_a_program_added():
+    """Copies and pickles of a plan leave out what the binding derived, and nothing else: a program's own attributes
+    travel under their own names.  States with the arrays under the names they once had are read as well."""
+    import copy
+    import pickle
+    for plan in (cgx.Plan([0, 100, 300], [4, 2], 128), cgx.LayeredPlan([0, 100, 300], [4, 2], [64, 128])):
+        plan._weights, plan.weights_address, plan.note = np.arange(3), "kept", "mine"
+        for other in (copy.copy(plan), copy.deepcopy(plan), pickle.loads(pickle.dumps(plan))):
+            assert np.array_equal(other._weights, np.arange(3)) and not hasattr(other, "weights")
+            assert other.weights_address == "kept" and other.note == "mine"
+        old = type(plan).__new__(type(plan))
+        old.__setstate__({("_" + k if k in ("offsets", "bits", "buckets") else k): v for k, v in plan.__getstate__().items()})
+        assert old.args[:2] == plan.args[:2] and np.array_equal(old.offsets, plan.offsets) and np.array_equal(old.bits, plan.bits)
+        assert old.args[2:4] == (old.offsets.ctypes.data, old.bits.ctypes.data)
