@@ -145,19 +145,26 @@ class _HostPlan:
 
     #: attribute -> element type the C calls read
     _ARRAYS = {}
+    #: attributes formed from the others: the arguments of the C calls, sizes of streams (_sizes_of)
+    _DERIVED = ("_args", "_sizes")
 
     def __setattr__(self, name, value):
         if name in self._ARRAYS:
             value = np.ascontiguousarray(value, dtype=self._ARRAYS[name])
         self.__dict__[name] = value
-        self.__dict__.pop("_args", None)
+        if name == "offsets" and value.ndim == 1 and value.size:
+            self.__dict__["n"], self.__dict__["L"] = int(value[-1]), int(value.size) - 1
+        for derived in self._DERIVED:
+            self.__dict__.pop(derived, None)
 
     # copies and pickles take the attributes, not what was derived from them
     def __getstate__(self):
-        return {k: v for k, v in self.__dict__.items() if k != "_args"}
+        return {k: v for k, v in self.__dict__.items() if k not in self._DERIVED}
 
     def __setstate__(self, state):
         for k, v in state.items():
+            if k in self._DERIVED:
+                continue
             # (a state may hold the arrays under a name with an underscore in front)
             self.__dict__[k[1:] if k[1:] in self._ARRAYS and k[0] == "_" else k] = v
 
@@ -165,6 +172,8 @@ class _HostPlan:
     def args(self):
         known = self.__dict__.get("_args")
         if known is None:
+            if any(getattr(self, name).size != self.L + (name == "offsets") for name in self._ARRAYS):
+                raise ValueError("the arrays of a plan must fit its layer count: an entry per layer, one more layer offset")
             sizes = self.buckets.ctypes.data if "buckets" in self._ARRAYS else self.bucket
             known = self.__dict__["_args"] = (self.n, self.L, self.offsets.ctypes.data, self.bits.ctypes.data, sizes)
         return known
@@ -291,19 +300,23 @@ def _peers(packed: Sequence, meta: Sequence, what: str, packed_bytes: int, meta_
 def _sizes_of(plan, qsgd: bool = False, dt: int = None) -> Tuple[int, int]:
     """(packed_bytes, meta_bytes) of a Plan or LayeredPlan, for either quantizer, optionally at another storage type."""
     dt = plan.dt if dt is None else dt
-    cache = plan.__dict__.get("_sizes")                      # a plan's arrays are not changed after construction
-    if cache is None:
-        cache = plan.__dict__["_sizes"] = {}
-    known = cache.get((qsgd, dt))
-    if known is not None:
-        return known
+    args = plan.args
+    known = plan.__dict__.get("_sizes")
+    # the sizes belong to contents: a program may also write into the arrays of a plan it keeps
+    if known is None or not (_native or _args()).unchanged(known[0]):
+        contents = [(getattr(plan, name).ctypes.data, getattr(plan, name).tobytes()) for name in plan._ARRAYS]
+        known = plan.__dict__["_sizes"] = (tuple(x for pair in contents for x in pair), {})
+    cache = known[1]
+    sizes = cache.get((qsgd, dt))
+    if sizes is not None:
+        return sizes
     pb, mb = ctypes.c_size_t(), ctypes.c_size_t()
     if isinstance(plan, LayeredPlan):
         fn, name = (lib().cgx_qsgd_layered_sizes, "cgx_qsgd_layered_sizes") if qsgd else \
             (lib().cgx_layered_sizes, "cgx_layered_sizes")
     else:
         fn, name = (lib().cgx_qsgd_sizes, "cgx_qsgd_sizes") if qsgd else (lib().cgx_sizes, "cgx_sizes")
-    _check(fn(*plan.args, dt, ctypes.byref(pb), ctypes.byref(mb)), name)
+    _check(fn(*args, dt, ctypes.byref(pb), ctypes.byref(mb)), name)
     cache[(qsgd, dt)] = (int(pb.value), int(mb.value))
     return cache[(qsgd, dt)]
 

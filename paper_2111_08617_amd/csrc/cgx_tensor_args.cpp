@@ -3,9 +3,11 @@
 // Written against the Python objects a check costs half a microsecond per tensor, and a reduction of 8 chunks has 17 of
 // them: with the rest of the marshalling 20 us per call where the launch itself takes 3.  A tensor that fails a check
 // (or is anything but a plain tensor with storage) is reported as such and looked at again in Python, which words
-// the error.
+// the error.  The module also tells whether the arrays of a plan still hold what a size was worked out from.
 #define PY_SSIZE_T_CLEAN
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <cstring>
 
 namespace {
 
@@ -76,9 +78,31 @@ PyObject *tables(PyObject *, PyObject *const *args, Py_ssize_t n)
     return Py_BuildValue("(y#y#)", reinterpret_cast<const char *>(packed), bytes, reinterpret_cast<const char *>(meta), bytes);
 }
 
+// unchanged((address, bytes, address, bytes, ...)) -> whether the memory at every address still holds the bytes beside it
+PyObject *unchanged(PyObject *, PyObject *pairs)
+{
+    if (!PyTuple_Check(pairs) || PyTuple_GET_SIZE(pairs) % 2) {
+        PyErr_SetString(PyExc_TypeError, "unchanged((address, bytes, ...))");
+        return nullptr;
+    }
+    for (Py_ssize_t i = 0; i < PyTuple_GET_SIZE(pairs); i += 2) {
+        const void *at = PyLong_AsVoidPtr(PyTuple_GET_ITEM(pairs, i));
+        if (PyErr_Occurred()) return nullptr;
+        PyObject *held = PyTuple_GET_ITEM(pairs, i + 1);
+        if (!PyBytes_Check(held)) {
+            PyErr_SetString(PyExc_TypeError, "unchanged((address, bytes, ...))");
+            return nullptr;
+        }
+        const size_t bytes = size_t(PyBytes_GET_SIZE(held));
+        if (bytes && std::memcmp(at, PyBytes_AS_STRING(held), bytes) != 0) Py_RETURN_FALSE;
+    }
+    Py_RETURN_TRUE;
+}
+
 PyMethodDef methods[] = {
     {"address", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(address)), METH_FASTCALL, nullptr},
     {"tables", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(tables)), METH_FASTCALL, nullptr},
+    {"unchanged", unchanged, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_cgx_args", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

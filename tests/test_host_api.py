@@ -508,3 +508,48 @@ def test_copies_of_a_plan_keep_attributes_a_program_added():
         old.__setstate__({("_" + k if k in ("offsets", "bits", "buckets") else k): v for k, v in plan.__getstate__().items()})
         assert old.args[:2] == plan.args[:2] and np.array_equal(old.offsets, plan.offsets) and np.array_equal(old.bits, plan.bits)
         assert old.args[2:4] == (old.offsets.ctypes.data, old.bits.ctypes.data)
+
+
+@pytest.mark.parametrize("how", ["replaced", "written in place", "on a copy", "bucket size"])
+def test_sizes_follow_the_contents_of_a_plan(lib, how):
+    """The buffers of a call are checked against the plan's sizes: those must be the sizes of what the plan holds at the
+    call, or a chunk that was large enough before a change of widths is accepted and written past its end."""
+    import copy
+    for plan in (cgx.Plan([0, 100, 300], [4, 2], 128), cgx.LayeredPlan([0, 100, 300], [4, 2], [128, 128])):
+        layered = isinstance(plan, cgx.LayeredPlan)
+        before = {(q, dt): cgx._sizes_of(plan, q, dt) for q in (False, True) for dt in (wl.F32, wl.F16)}
+        if how == "on a copy":
+            original, plan = plan, copy.copy(plan)
+        if how == "written in place":
+            plan.bits[:] = 8
+        elif how == "bucket size" and layered:
+            plan.buckets[1] = 32
+        elif how == "bucket size":
+            plan.bucket = 32
+        else:
+            plan.bits = [8, 8]
+        fresh = cgx.LayeredPlan(plan.offsets.copy(), plan.bits.copy(), plan.buckets.copy()) if layered else \
+            cgx.Plan(plan.offsets.copy(), plan.bits.copy(), plan.bucket)
+        for (q, dt), old in before.items():
+            assert cgx._sizes_of(plan, q, dt) == cgx._sizes_of(fresh, q, dt) != old
+            if how == "on a copy":
+                assert cgx._sizes_of(original, q, dt) == old
+
+
+def test_other_layer_offsets_bring_their_own_lengths(lib):
+    """n and L follow replaced offsets; arrays that do not fit each other are refused before their addresses go out."""
+    for plan in (cgx.Plan([0, 100, 300], [4, 2], 128), cgx.LayeredPlan([0, 100, 300], [4, 2], [128, 128])):
+        cgx._sizes_of(plan)
+        plan.offsets = [0, 50, 400]
+        assert (plan.n, plan.L) == (400, 2) and plan.args[0] == 400
+        assert cgx._sizes_of(plan)[0] == 32 + 96                     # 25 and 88 bytes of codes, each padded to 16
+        plan.offsets = np.array([0, 64, 128, 256], np.int32)
+        assert plan.offsets.dtype == np.int64
+        with pytest.raises(ValueError, match="layer count"):
+            plan.args
+        with pytest.raises(ValueError, match="layer count"):
+            cgx._sizes_of(plan)
+        plan.bits = [4, 4, 0]
+        if isinstance(plan, cgx.LayeredPlan):
+            plan.buckets = [32, 32, 32]
+        assert plan.args[:2] == (256, 3) and cgx._sizes_of(plan)[0] == 32 + 32 + 512
