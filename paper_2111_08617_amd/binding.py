@@ -8,6 +8,7 @@ CPU fallback: a missing library raises.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Sequence, Tuple
 
@@ -146,7 +147,7 @@ class _HostPlan:
     #: attribute -> element type the C calls read
     _ARRAYS = {}
     #: attributes formed from the others: the arguments of the C calls, sizes of streams (_sizes_of)
-    _DERIVED = ("_args", "_sizes")
+    _DERIVED = ("args", "_sizes")
 
     def __setattr__(self, name, value):
         if name in self._ARRAYS:
@@ -168,15 +169,12 @@ class _HostPlan:
             # (a state may hold the arrays under a name with an underscore in front)
             self.__dict__[k[1:] if k[1:] in self._ARRAYS and k[0] == "_" else k] = v
 
-    @property
+    @functools.cached_property
     def args(self):
-        known = self.__dict__.get("_args")
-        if known is None:
-            if any(getattr(self, name).size != self.L + (name == "offsets") for name in self._ARRAYS):
-                raise ValueError("the arrays of a plan must fit its layer count: an entry per layer, one more layer offset")
-            sizes = self.buckets.ctypes.data if "buckets" in self._ARRAYS else self.bucket
-            known = self.__dict__["_args"] = (self.n, self.L, self.offsets.ctypes.data, self.bits.ctypes.data, sizes)
-        return known
+        if any(getattr(self, name).size != self.L + (name == "offsets") for name in self._ARRAYS):
+            raise ValueError("the arrays of a plan must fit its layer count: an entry per layer, one more layer offset")
+        sizes = self.buckets.ctypes.data if "buckets" in self._ARRAYS else self.bucket
+        return self.n, self.L, self.offsets.ctypes.data, self.bits.ctypes.data, sizes
 
 
 class Plan(_HostPlan):
@@ -300,10 +298,10 @@ def _peers(packed: Sequence, meta: Sequence, what: str, packed_bytes: int, meta_
 def _sizes_of(plan, qsgd: bool = False, dt: int = None) -> Tuple[int, int]:
     """(packed_bytes, meta_bytes) of a Plan or LayeredPlan, for either quantizer, optionally at another storage type."""
     dt = plan.dt if dt is None else dt
-    args = plan.args
     known = plan.__dict__.get("_sizes")
     # the sizes belong to contents: a program may also write into the arrays of a plan it keeps
     if known is None or not (_native or _args()).unchanged(known[0]):
+        plan.args                                                # (refuses arrays that do not fit each other)
         contents = [(getattr(plan, name).ctypes.data, getattr(plan, name).tobytes()) for name in plan._ARRAYS]
         known = plan.__dict__["_sizes"] = (tuple(x for pair in contents for x in pair), {})
     cache = known[1]
@@ -316,7 +314,7 @@ def _sizes_of(plan, qsgd: bool = False, dt: int = None) -> Tuple[int, int]:
             (lib().cgx_layered_sizes, "cgx_layered_sizes")
     else:
         fn, name = (lib().cgx_qsgd_sizes, "cgx_qsgd_sizes") if qsgd else (lib().cgx_sizes, "cgx_sizes")
-    _check(fn(*args, dt, ctypes.byref(pb), ctypes.byref(mb)), name)
+    _check(fn(*plan.args, dt, ctypes.byref(pb), ctypes.byref(mb)), name)
     cache[(qsgd, dt)] = (int(pb.value), int(mb.value))
     return cache[(qsgd, dt)]
 
