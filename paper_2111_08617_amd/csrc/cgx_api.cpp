@@ -157,6 +157,18 @@ int tile_length(CallKind call, int dt, int64_t n)
 
 bool misaligned(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
 
+// Pointers (and chunks) that no check of a call can refuse.  Only such calls take the quick look-up of a table
+// (known_plan): it asks the stream whether it captures and pins what it finds for a capture, and a call that is refused
+// must leave both alone.
+bool plain(const void *p) { return p && !misaligned(p); }
+bool plain_chunks(const void *const *packed, const void *const *meta, int32_t W, int32_t most)
+{
+    if (W < 1 || W > most || !packed || !meta) return false;
+    for (int32_t w = 0; w < W; w++)
+        if (!plain(packed[w]) || !plain(meta[w])) return false;
+    return true;
+}
+
 // One launch per lane mapping in use (a launch runs one kernel instantiation; the bucket size
 // itself travels in the tile descriptors), named by the smallest bucket size of that mapping;
 // the first launch also carries the pass-through layers.
@@ -398,7 +410,9 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
     int32_t longest = buckets.uniform;
     int chunk = chunk_length(kQuantizeCall, dt, longest);
     const int per_tile = tile_length(kQuantizeCall, dt, n);
-    const PlanRef known = known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile, cgx::kWholeBuckets);
+    const PlanRef known = plain(grad) && plain(packed) && plain(meta)
+                              ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile, cgx::kWholeBuckets)
+                              : nullptr;
     cgx::PlanShape shape;
     if (known) {
         shape = known->shape;
@@ -448,7 +462,9 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
                       : decompression && out_dt == CGX_F32 ? cgx::chunk_of(2) : cgx::kDefaultChunk;
     const int per_tile = tile_length(kOtherCall, dt, n);
     const hipStream_t queue = static_cast<hipStream_t>(stream);
-    PlanRef plan = known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile, cgx::kPieces);
+    PlanRef plan = plain_chunks(packed, meta, W, CGX_MAX_PEERS) && plain(out) && (!want_local || plain(local))
+                       ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile, cgx::kPieces)
+                       : nullptr;
     if (!plan) {
         const int rc = check_plan(scheme, n, L, off, bits, buckets, dt);
         if (rc != CGX_OK) return rc;
@@ -500,8 +516,10 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
     const hipStream_t queue = static_cast<hipStream_t>(stream);
     const int per_tile = tile_length(kFusedCall, dt, n);
     // tables of the chunks and of the output, which lays out its pass-through layers as binary32
-    const PlanRef known_in = known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt, cgx::kDefaultChunk,
-                                        per_tile, cgx::kWholeBuckets);
+    const PlanRef known_in = plain_chunks(packed, meta, W, CGX_MAX_FUSED_PEERS) && plain(packed_out) && plain(meta_out)
+                                 ? known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt,
+                                              cgx::kDefaultChunk, per_tile, cgx::kWholeBuckets)
+                                 : nullptr;
     const PlanRef known_out = dt == CGX_F32 || !known_in ? known_in
                                                          : known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets,
                                                                       CGX_F32, cgx::kDefaultChunk, per_tile, cgx::kWholeBuckets);

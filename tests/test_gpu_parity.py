@@ -698,6 +698,37 @@ def test_captured_graph_survives_any_number_of_later_plans(torch, oracle):
     assert np.array_equal(spare[0].cpu().numpy()[:sp.size], sp)
 
 
+def test_a_refused_call_pins_no_table(torch, oracle):
+    """A table is pinned for the graphs that read it.  A call that is refused for a bad argument during a capture records
+    nothing, so it pins nothing: its plan's table is dropped like any other once enough plans have followed."""
+    x = np.linspace(-1, 1, 9000).astype(np.float32)
+    off, bits = np.array([0, 4096, 9000], np.int64), np.array([4, 3], np.uint8)
+    gpu_quantize(torch, x, off, bits, 512, 3, wl.F32)                  # the table exists
+    L, g = cgx.lib(), dev(torch, x)
+    out, meta = torch.zeros(16384, dtype=torch.uint8, device="cuda"), torch.zeros(512, device="cuda")
+
+    def quantize(stream, packed):
+        return L.cgx_quantize(g.data_ptr(), 9000, 2, off.ctypes.data, bits.ctypes.data, 512, 3, 0, packed, meta.data_ptr(),
+                              stream.cuda_stream)
+
+    def captured(packed):
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=side):
+            out.fill_(0)
+            status = quantize(side, packed)
+        torch.cuda.synchronize()
+        return status
+
+    assert captured(out.data_ptr() + 4) == -9 and captured(None) == -1
+    for k in range(70):
+        cut = 1024 + 8 * k
+        gpu_quantize(torch, x, np.array([0, cut, x.size], np.int64), np.array([2, 4], np.uint8), 128, k, wl.F32)
+    assert captured(out.data_ptr()) == -11                             # dropped meanwhile
+    gpu_quantize(torch, x, off, bits, 512, 3, wl.F32)
+    assert captured(out.data_ptr()) == 0
+
+
 def test_calls_from_several_host_threads_and_streams(torch, oracle):
     """The plan cache is shared by host threads; concurrent calls on separate streams with
     separate outputs give the same bytes as a single call."""
