@@ -38,9 +38,8 @@
  *   which allocates device memory and copies synchronously; later calls with the
  *   same plan only queue kernels.  (cgx_quantize on binary32 input and
  *   cgx_requantize, cgx_quantize on binary16 gradients of 2^24 elements or more,
- *   the fused call on 2^27 or more, the per-layer statistics, and reductions
- *   where a bucket is longer than 2048 elements or the layers have their own
- *   sizes, keep tables of their own beside the one the other calls share.)  At most 64 tables are kept: when a 65th arrives
+ *   and the fused call on 2^27 or more, keep tables of their own beside the one
+ *   the other calls share.)  At most 64 tables are kept: when a 65th arrives
  *   the least recently used one is freed, which waits for the device;
  *   cgx_shutdown() frees them all.
  *   A call on a stream that is capturing a graph records its launches into the

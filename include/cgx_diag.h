@@ -28,9 +28,9 @@ extern "C" {
  * chunk).
  * Every element of every non-empty layer lies in exactly one tile and tiles never
  * cross layers (paper Sec. 4.1).  This is the table of one chunk per vectorised
- * tile that the statistics walk.  The other calls cut pass-through layers into
- * tiles of 1024 elements instead of 8192, and a reduction also cuts buckets longer
- * than a chunk; cgx_quantize on a binary16 gradient of 2^24 elements or more, and the
+ * tile that the norm statistic walks.  The other calls cut pass-through layers into
+ * tiles of 1024 elements instead of 8192, and a reduction gives every chunk of a
+ * bucket longer than one to a wave of its own; cgx_quantize on a binary16 gradient of 2^24 elements or more, and the
  * fused reduce + requantize on 2^27 elements or more, join 2 consecutive chunks of a
  * layer into one tile (same bytes out; a wave's set-up is spread over more
  * input).  At most `capacity` records
@@ -117,7 +117,8 @@ int cgx_issue_probe(int32_t form, int32_t blocks, int32_t iterations, void *out,
 /*
  * Launch-shape overrides, for the tests and for measurements.  The library reads these
  * environment variables once, at its first call; none of them changes a byte of any result (the
- * parity tests run the same inputs under several settings and compare digests):
+ * parity tests run the same inputs under several settings and compare digests), except that
+ * CGX_CHUNKS_PER_TILE regroups the binary64 additions of the per-layer errors:
  *   CGX_CHUNKS_PER_TILE=k   every vectorised tile holds up to k chunks (default: chosen per call)
  *   CGX_MAX_BLOCKS=k        persistent grids of at most k blocks (default: one wave per tile)
  *   CGX_QUANTIZE_GROUPS=2|4 chunk size of every quantize call: 1024 or 2048 elements (default:

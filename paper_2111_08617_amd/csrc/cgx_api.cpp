@@ -25,18 +25,17 @@ struct CachedPlan {
     uint64_t digest = 0;        // hash of (off, bits, layer_buckets): compared before the arrays themselves
     int chunk = 0;              // elements per chunk of the kernels that walk this table
     int chunks_per_tile = 0;
-    cgx::TableUse use = cgx::kStatistics;
+    int copy_tile = 0;          // elements per tile of a pass-through layer
     std::vector<int64_t> off;
     std::vector<uint8_t> bits;
-    std::vector<int32_t> layer_buckets;   // empty: `bucket` for every layer; else the table holds the
-    bool with_copies = true;              // layers of size `bucket` (and the pass-through ones if with_copies)
+    std::vector<int32_t> layer_buckets;   // empty: `bucket` for every layer
     // content
     cgx::PlanShape shape;
+    std::vector<cgx::TablePart> parts;
     int64_t n_tiles = 0;
-    int64_t plan_tiles = 0;     // tiles of the whole plan: n_tiles, or the sum over the launches of a layered plan
+    int64_t stats_tiles = 0;    // partial sums that a workspace of the statistics holds
+    cgx::ReduceTiles reduce;    // the tiles as a reduction walks them
     bool one_bit_layers = false;
-    bool odd_tiles = false;     // some quantized tile starts on an odd element index
-    bool aligned_tiles = true;  // every vectorised quantized tile starts on a 16-byte boundary of the buffer
     Tile *d_tiles = nullptr;
     // per-layer numbering of the tiles (for the statistics): slot of every tile, first slot of every layer
     uint32_t *d_slots = nullptr;
@@ -169,29 +168,6 @@ bool plain_chunks(const void *const *packed, const void *const *meta, int32_t W,
     return true;
 }
 
-// One launch per lane mapping in use (a launch runs one kernel instantiation; the bucket size
-// itself travels in the tile descriptors), named by the smallest bucket size of that mapping;
-// the first launch also carries the pass-through layers.
-struct Launch {
-    int32_t bucket;
-    bool with_copies;
-};
-std::vector<Launch> launches_of(const Buckets &b, int32_t L, const int64_t *off, const uint8_t *bits, int chunk)
-{
-    if (!b.per_layer) return {{b.uniform, true}};
-    int32_t smallest[3] = {0, 0, 0};
-    for (int32_t l = 0; l < L; l++)
-        if (bits[l] != 0 && off[l + 1] > off[l]) {
-            int32_t &s = smallest[cgx::mapping_of(b.per_layer[l], chunk)];
-            if (s == 0 || b.per_layer[l] < s) s = b.per_layer[l];
-        }
-    std::vector<Launch> out;
-    for (int32_t s : smallest)
-        if (s != 0) out.push_back({s, out.empty()});
-    if (out.empty()) out.push_back({32, true});         // pass-through layers only
-    return out;
-}
-
 // A 64-bit digest of the plan's arrays, eight bytes at a time (multiply and xor-shift per word): a look-up
 // compares this one word per cached plan and the arrays themselves only on a match.
 uint64_t plan_digest(int32_t L, const int64_t *off, const uint8_t *bits, const int32_t *layer_buckets)
@@ -212,22 +188,14 @@ uint64_t plan_digest(int32_t L, const int64_t *off, const uint8_t *bits, const i
     return h;
 }
 
-// Where no bucket is longer than a chunk, a reduction's table is the quantizers': one serves both.
-cgx::TableUse shared_use(cgx::TableUse use, int32_t bucket, int chunk, const int32_t *layer_buckets)
-{
-    return use == cgx::kPieces && !layer_buckets && bucket <= chunk ? cgx::kWholeBuckets : use;
-}
-
 // What identifies a tile table.
 struct PlanKey {
     int32_t L;
     const int64_t *off;
     const uint8_t *bits;
     int32_t bucket;
-    int dt, chunk, chunks_per_tile;
-    cgx::TableUse use;
+    int dt, chunk, chunks_per_tile, copy_tile;
     const int32_t *layer_buckets;
-    bool with_copies;
     uint64_t digest;
 };
 
@@ -236,8 +204,8 @@ PlanRef cached_plan(const PlanKey &k, int device, bool capturing)
 {
     for (const auto &p : g_plans) {
         if (p->digest == k.digest && p->device == device && p->bucket == k.bucket && p->dt == k.dt && p->chunk == k.chunk &&
-            p->chunks_per_tile == k.chunks_per_tile && p->use == k.use && p->bits.size() == size_t(k.L) &&
-            p->with_copies == k.with_copies && p->layer_buckets.size() == (k.layer_buckets ? size_t(k.L) : 0) &&
+            p->chunks_per_tile == k.chunks_per_tile && p->copy_tile == k.copy_tile && p->bits.size() == size_t(k.L) &&
+            p->layer_buckets.size() == (k.layer_buckets ? size_t(k.L) : 0) &&
             (!k.layer_buckets || k.L == 0 ||
              std::memcmp(p->layer_buckets.data(), k.layer_buckets, sizeof(int32_t) * size_t(k.L)) == 0) &&
             std::memcmp(p->bits.data(), k.bits, size_t(k.L)) == 0 &&
@@ -263,7 +231,7 @@ bool is_capturing(hipStream_t stream)
 // is found for arguments that those checks would refuse: tables exist for checked plans only, and 1-bit layers
 // are left to them under the norm-and-sign quantizer.
 PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const int64_t *off, const uint8_t *bits,
-                   const Buckets &buckets, int dt, int chunk, int chunks_per_tile, cgx::TableUse use)
+                   const Buckets &buckets, int dt, int chunk, int chunks_per_tile)
 {
     // (what the checks find out without reading the arrays keeps them unread)
     if (buckets.per_layer || L <= 0 || n <= 0 || !off || !bits || (dt != CGX_F32 && dt != CGX_F16) || buckets.uniform < 32 ||
@@ -271,8 +239,7 @@ PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const i
         return nullptr;
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return nullptr;
-    const PlanKey key{L, off, bits, buckets.uniform, dt, chunk, chunks_per_tile,
-                      shared_use(use, buckets.uniform, chunk, nullptr), nullptr, true,
+    const PlanKey key{L, off, bits, buckets.uniform, dt, chunk, chunks_per_tile, cgx::kCopyPiece, nullptr,
                       plan_digest(L, off, bits, nullptr)};
     const bool capturing = is_capturing(stream);
     std::lock_guard<std::mutex> lock(g_mutex);
@@ -285,17 +252,20 @@ PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const i
 // found during a capture is pinned for the life of the library (never the one dropped for a new plan),
 // and a table that does not exist yet is not built during a capture (that would allocate and copy
 // synchronously in the middle of it): the call fails with CGX_ERR_CAPTURE and records nothing.
-int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
-             int chunks_per_tile, cgx::TableUse use, PlanRef *out, const int32_t *layer_buckets = nullptr, bool with_copies = true)
+// built (may be null): whether the table is a new one.
+int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *bits, const Buckets &buckets, int dt, int chunk,
+             int chunks_per_tile, PlanRef *out, int copy_tile = cgx::kCopyPiece, bool *built = nullptr)
 {
-    use = shared_use(use, bucket, chunk, layer_buckets);
+    const int32_t bucket = buckets.uniform;
+    const int32_t *layer_buckets = buckets.per_layer;
     const uint64_t digest = plan_digest(L, off, bits, layer_buckets);       // before the lock is taken
     std::lock_guard<std::mutex> lock(g_mutex);
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return CGX_ERR_HIP;
     const bool capturing = is_capturing(stream);
-    *out = cached_plan(PlanKey{L, off, bits, bucket, dt, chunk, chunks_per_tile, use, layer_buckets, with_copies, digest}, device,
+    *out = cached_plan(PlanKey{L, off, bits, bucket, dt, chunk, chunks_per_tile, copy_tile, layer_buckets, digest}, device,
                        capturing);
+    if (built) *built = !*out;
     if (*out) return CGX_OK;
     if (capturing) return CGX_ERR_CAPTURE;
     std::shared_ptr<CachedPlan> plan(new CachedPlan, [](CachedPlan *p) {
@@ -308,55 +278,28 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     plan->dt = dt;
     plan->chunk = chunk;
     plan->chunks_per_tile = chunks_per_tile;
-    plan->use = use;
+    plan->copy_tile = copy_tile;
     plan->off.assign(off, off + L + 1);
     plan->bits.assign(bits, bits + L);
     if (layer_buckets) plan->layer_buckets.assign(layer_buckets, layer_buckets + L);
-    plan->with_copies = with_copies;
     plan->one_bit_layers = std::find(bits, bits + L, uint8_t(1)) != bits + L;
     plan->shape = cgx::plan_shape(L, off, bits, bucket, dt, layer_buckets);
-    std::vector<Tile> tiles;
-    std::vector<uint32_t> slots;
-    std::vector<int64_t> layer_first;
-    const bool numbered = use == cgx::kStatistics;
-    cgx::build_tiles(L, off, bits, bucket, dt, chunk, chunks_per_tile, tiles, numbered ? &slots : nullptr,
-                     numbered ? &layer_first : nullptr, layer_buckets, with_copies, use);
-    if (tiles.size() > size_t(0xffffffffu)) return CGX_ERR_SIZE;
-    plan->n_tiles = int64_t(tiles.size());
-    plan->plan_tiles = plan->n_tiles;
-    if (layer_buckets && numbered) {
-        // The per-layer statistics number the tiles of the WHOLE plan layer by layer; this table
-        // holds one launch's share of them, so its tiles take their numbers in that common order.
-        std::vector<int64_t> common(size_t(L) + 1, 0);
-        for (const Launch &other : launches_of(Buckets{bucket, layer_buckets}, L, off, bits, chunk)) {
-            std::vector<Tile> their_tiles;
-            std::vector<uint32_t> their_slots;
-            std::vector<int64_t> their_first;
-            cgx::build_tiles(L, off, bits, other.bucket, dt, chunk, chunks_per_tile, their_tiles, &their_slots, &their_first,
-                             layer_buckets, other.with_copies);
-            for (int32_t l = 0; l < L; l++) common[size_t(l) + 1] += their_first[size_t(l) + 1] - their_first[size_t(l)];
-        }
-        for (int32_t l = 0; l < L; l++) common[size_t(l) + 1] += common[size_t(l)];
-        if (common[size_t(L)] > int64_t(0xffffffffu)) return CGX_ERR_SIZE;
-        for (uint32_t &slot : slots) {
-            const size_t l = size_t(std::upper_bound(layer_first.begin(), layer_first.end(), int64_t(slot)) -
-                                    layer_first.begin()) - 1;
-            slot = uint32_t(common[l] + (int64_t(slot) - layer_first[l]));
-        }
-        layer_first = common;
-        plan->plan_tiles = common[size_t(L)];
-    }
-    for (const Tile &t : tiles)
-        if (cgx::is_quantized_kind(cgx::tile_kind(t)) && (t.elem0 & 1))
-            plan->odd_tiles = true;
-    for (const Tile &t : tiles)
-        if (cgx::is_vector_kind(cgx::tile_kind(t)) && (t.elem0 * (dt == CGX_F16 ? 2 : 4)) % 16 != 0)
-            plan->aligned_tiles = false;
-    if (!upload(&plan->d_tiles, tiles) || !upload(&plan->d_slots, slots) ||
-        !upload(&plan->d_layer_first, layer_first)) {
+    // (the statistics walk tables of the default chunk length in tiles of one chunk)
+    const bool numbered = chunk == cgx::kDefaultChunk && chunks_per_tile == tile_length(kOtherCall, dt, off[L]);
+    cgx::PlanTable table = cgx::build_table(L, off, bits, bucket, dt, chunk, chunks_per_tile, numbered, layer_buckets, copy_tile);
+    if (table.tiles.size() > size_t(0xffffffffu) || table.stats_tiles > int64_t(0xffffffffu)) return CGX_ERR_SIZE;
+    plan->n_tiles = int64_t(table.tiles.size());
+    plan->stats_tiles = table.stats_tiles;
+    const int64_t narrow = table.narrow(chunk), wide = plan->n_tiles - narrow;
+    const int pieces = table.pieces(chunk);
+    if (pieces > 1 && wide * pieces >= cgx::kMostPieces) return CGX_ERR_SIZE;
+    if (!upload(&plan->d_tiles, table.tiles) || !upload(&plan->d_slots, table.slots) ||
+        !upload(&plan->d_layer_first, numbered ? table.layer_first : std::vector<int64_t>())) {
         free_plan(*plan);
         return CGX_ERR_HIP;
     }
+    plan->reduce = cgx::ReduceTiles{plan->d_tiles, narrow + wide * pieces, uint32_t(narrow), uint32_t(pieces)};
+    plan->parts = std::move(table.parts);
     plan->last_use = ++g_clock;
     if (g_plans.size() >= kMaxPlans) {
         // drop the least recently used table that no captured graph reads (if all are pinned the cache grows)
@@ -368,21 +311,6 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     }
     *out = plan;
     g_plans.push_back(std::move(plan));
-    return CGX_OK;
-}
-
-// The tables of all launches of a call, looked up before its first launch: a call that fails for a
-// missing table (CGX_ERR_CAPTURE) has then queued nothing.
-int get_plans(hipStream_t stream, const std::vector<Launch> &launches, int32_t L, const int64_t *off,
-              const uint8_t *bits, int dt, int chunk, int chunks_per_tile, cgx::TableUse use, const int32_t *layer_buckets,
-              std::vector<PlanRef> *out)
-{
-    out->resize(launches.size());
-    for (size_t i = 0; i < launches.size(); i++) {
-        const int rc = get_plan(stream, L, off, bits, launches[i].bucket, dt, chunk, chunks_per_tile, use, &(*out)[i],
-                                layer_buckets, launches[i].with_copies);
-        if (rc != CGX_OK) return rc;
-    }
     return CGX_OK;
 }
 
@@ -407,15 +335,14 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
                   const Buckets &buckets, uint64_t seed, int dt, void *packed, void *meta, void *stream)
 {
     const hipStream_t queue = static_cast<hipStream_t>(stream);
-    int32_t longest = buckets.uniform;
-    int chunk = chunk_length(kQuantizeCall, dt, longest);
+    int chunk = chunk_length(kQuantizeCall, dt, buckets.uniform);
     const int per_tile = tile_length(kQuantizeCall, dt, n);
-    const PlanRef known = plain(grad) && plain(packed) && plain(meta)
-                              ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile, cgx::kWholeBuckets)
-                              : nullptr;
+    PlanRef plan = plain(grad) && plain(packed) && plain(meta)
+                       ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile)
+                       : nullptr;
     cgx::PlanShape shape;
-    if (known) {
-        shape = known->shape;
+    if (plan) {
+        shape = plan->shape;
     } else {
         const int rc = check_plan(scheme, n, L, off, bits, buckets, dt);
         if (rc != CGX_OK) return rc;
@@ -424,25 +351,20 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
     }
     if (!grad || !packed || (shape.meta_bytes && !meta)) return CGX_ERR_NULL;
     if (misaligned(grad) || misaligned(packed) || misaligned(meta)) return CGX_ERR_ALIGN;
-    std::vector<Launch> launches;
-    std::vector<PlanRef> plans;
-    if (!known) {
-        longest = longest_bucket(buckets, L, off, bits);
-        chunk = chunk_length(kQuantizeCall, dt, longest);
-        launches = launches_of(buckets, L, off, bits, chunk);
-        const int rc = get_plans(queue, launches, L, off, bits, dt, chunk, per_tile, cgx::kWholeBuckets, buckets.per_layer, &plans);
+    if (!plan) {
+        chunk = chunk_length(kQuantizeCall, dt, longest_bucket(buckets, L, off, bits));
+        const int rc = get_plan(queue, L, off, bits, buckets, dt, chunk, per_tile, &plan);
         if (rc != CGX_OK) return rc;
     }
     const auto launch_quantize = chunk == cgx::chunk_of(2) ? cgx::launch_quantize_g2 : cgx::launch_quantize_g4;
-    for (size_t i = 0; i < (known ? 1 : launches.size()); i++) {
-        const CachedPlan &plan = known ? *known : *plans[i];
-        const int32_t bucket = known ? buckets.uniform : launches[i].bucket;
+    for (const cgx::TablePart &part : plan->parts) {
+        const Tile *tiles = plan->d_tiles + part.first;
         const hipError_t e =
-            cgx::mapping_of(bucket, chunk) == cgx::kMapWide
-                ? cgx::launch_quantize_wide(scheme, grad, dt, plan.d_tiles, plan.n_tiles, plan.odd_tiles, longest, seed, packed,
-                                            meta, launch_config(), queue)
-                : launch_quantize(scheme, grad, dt, plan.d_tiles, plan.n_tiles, plan.odd_tiles, plan.aligned_tiles, bucket, seed,
-                                  packed, meta, launch_config(), queue);
+            cgx::mapping_of(part.bucket, chunk) == cgx::kMapWide
+                ? cgx::launch_quantize_wide(scheme, grad, dt, tiles, part.count, part.odd, part.longest, seed, packed, meta,
+                                            launch_config(), queue)
+                : launch_quantize(scheme, grad, dt, tiles, part.count, part.odd, part.aligned, part.bucket, seed, packed, meta,
+                                  launch_config(), queue);
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;
@@ -458,12 +380,12 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
     // takes the kernel of 1024-element chunks (to binary16 2048 elements are 4 KB).
     const bool decompression = W == 1 && !want_local && launch_config().dequantize_through;
     const int forced = launch_config().reduce_groups;
-    const int chunk = forced > 0 ? cgx::chunk_of(forced)
-                      : decompression && out_dt == CGX_F32 ? cgx::chunk_of(2) : cgx::kDefaultChunk;
+    int chunk = forced > 0 ? cgx::chunk_of(forced)
+                : decompression && out_dt == CGX_F32 ? cgx::chunk_of(2) : cgx::kDefaultChunk;
     const int per_tile = tile_length(kOtherCall, dt, n);
     const hipStream_t queue = static_cast<hipStream_t>(stream);
     PlanRef plan = plain_chunks(packed, meta, W, CGX_MAX_PEERS) && plain(out) && (!want_local || plain(local))
-                       ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile, cgx::kPieces)
+                       ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile)
                        : nullptr;
     if (!plan) {
         const int rc = check_plan(scheme, n, L, off, bits, buckets, dt);
@@ -480,7 +402,20 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
     }
     if (misaligned(out) || misaligned(local)) return CGX_ERR_ALIGN;
     if (!plan) {
-        const int rc = get_plan(queue, L, off, bits, buckets.uniform, dt, chunk, per_tile, cgx::kPieces, &plan, buckets.per_layer);
+        bool built = false;
+        int rc = get_plan(queue, L, off, bits, buckets, dt, chunk, per_tile, &plan, cgx::kCopyPiece, &built);
+        // A decompression in chunks of 1024 elements must not need another table than its plan's other calls where a
+        // program captures one of them after having run the other: under a capture it takes their table if its own does
+        // not exist, and when it builds its own for a plan that is quantized in chunks of 2048, it builds theirs too.
+        if (rc == CGX_ERR_CAPTURE && chunk != cgx::kDefaultChunk) {
+            chunk = cgx::kDefaultChunk;
+            rc = get_plan(queue, L, off, bits, buckets, dt, chunk, per_tile, &plan);
+        } else if (rc == CGX_OK && built && chunk != cgx::kDefaultChunk &&
+                   (buckets.per_layer || (dt == CGX_F32 && chunk_length(kQuantizeCall, dt, buckets.uniform) != chunk) ||
+                    buckets.uniform > chunk)) {
+            PlanRef others;
+            rc = get_plan(queue, L, off, bits, buckets, dt, cgx::kDefaultChunk, per_tile, &others);
+        }
         if (rc != CGX_OK) return rc;
     }
     const auto launch_reduce = chunk == cgx::kDefaultChunk ? cgx::launch_dequant_reduce_g4 : cgx::launch_dequant_reduce_g2;
@@ -502,8 +437,8 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
         // writer gains.  A decompression's stores go through at system scope whatever the size.
         const bool small = int64_t(n) * (out_dt == CGX_F16 ? 2 : 4) <= launch_config().keep_sums_max_bytes;
         const int policy = decompression ? cgx::kStoreThrough : small ? cgx::kStoreKeep : cgx::kStoreStream;
-        const hipError_t e = launch_reduce(scheme, peers, k, dt, plan->d_tiles, plan->n_tiles,
-                                           init, init_dt, out, out_dt, policy, launch_config(), queue);
+        const hipError_t e = launch_reduce(scheme, peers, k, dt, plan->reduce, init, init_dt, out, out_dt, policy,
+                                           launch_config(), queue);
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;
@@ -516,14 +451,14 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
     const hipStream_t queue = static_cast<hipStream_t>(stream);
     const int per_tile = tile_length(kFusedCall, dt, n);
     // tables of the chunks and of the output, which lays out its pass-through layers as binary32
-    const PlanRef known_in = plain_chunks(packed, meta, W, CGX_MAX_FUSED_PEERS) && plain(packed_out) && plain(meta_out)
-                                 ? known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt,
-                                              cgx::kDefaultChunk, per_tile, cgx::kWholeBuckets)
-                                 : nullptr;
-    const PlanRef known_out = dt == CGX_F32 || !known_in ? known_in
-                                                         : known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets,
-                                                                      CGX_F32, cgx::kDefaultChunk, per_tile, cgx::kWholeBuckets);
-    const bool known = known_in && known_out;
+    PlanRef in, out;
+    if (plain_chunks(packed, meta, W, CGX_MAX_FUSED_PEERS) && plain(packed_out) && plain(meta_out)) {
+        in = known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt, cgx::kDefaultChunk, per_tile);
+        out = dt == CGX_F32 || !in ? in
+                                   : known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, CGX_F32,
+                                                cgx::kDefaultChunk, per_tile);
+    }
+    const bool known = in && out;
     if (!known) {
         const int rc = check_plan(scheme, n, L, layer_offsets, bits_per_layer, buckets, dt);
         if (rc != CGX_OK) return rc;
@@ -531,7 +466,7 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
     if (W < 1 || W > CGX_MAX_FUSED_PEERS) return CGX_ERR_PEERS;
     if (n == 0) return CGX_OK;
     const cgx::PlanShape shape =
-        known ? known_in->shape : cgx::plan_shape(L, layer_offsets, bits_per_layer, buckets.uniform, dt, buckets.per_layer);
+        known ? in->shape : cgx::plan_shape(L, layer_offsets, bits_per_layer, buckets.uniform, dt, buckets.per_layer);
     if (!packed || !meta || !packed_out || (shape.meta_bytes && !meta_out)) return CGX_ERR_NULL;
     for (int w = 0; w < W; w++) {
         if (!packed[w] || (shape.meta_bytes && !meta[w])) return CGX_ERR_NULL;
@@ -543,28 +478,21 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
         peers.packed[i] = static_cast<const uint8_t *>(packed[i]);
         peers.meta[i] = static_cast<const float *>(meta[i]);
     }
-    const std::vector<Launch> launches = known ? std::vector<Launch>{{buckets.uniform, true}}
-                                               : launches_of(buckets, L, layer_offsets, bits_per_layer, cgx::kDefaultChunk);
-    for (const Launch &launch : launches) {
-        PlanRef in = known_in, out = known_out;
-        if (!known) {
-            int rc = get_plan(queue, L, layer_offsets, bits_per_layer, launch.bucket, dt, cgx::kDefaultChunk, per_tile,
-                              cgx::kWholeBuckets, &in, buckets.per_layer, launch.with_copies);
-            if (rc != CGX_OK) return rc;
-            rc = get_plan(queue, L, layer_offsets, bits_per_layer, launch.bucket, CGX_F32, cgx::kDefaultChunk, per_tile,
-                          cgx::kWholeBuckets, &out, buckets.per_layer, launch.with_copies);
-            if (rc != CGX_OK) return rc;
-        }
-        if (in->n_tiles != out->n_tiles) return CGX_ERR_SIZE;     // cannot happen: same tiling for both layouts
+    if (!known) {
+        int rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, cgx::kDefaultChunk, per_tile, &in);
+        if (rc != CGX_OK) return rc;
+        rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, CGX_F32, cgx::kDefaultChunk, per_tile, &out);
+        if (rc != CGX_OK) return rc;
+    }
+    if (in->n_tiles != out->n_tiles) return CGX_ERR_SIZE;     // cannot happen: same tiling for both layouts
+    for (const cgx::TablePart &part : in->parts) {
+        const Tile *tiles_in = in->d_tiles + part.first, *tiles_out = out->d_tiles + part.first;
         const hipError_t e =
-            cgx::mapping_of(launch.bucket, cgx::kDefaultChunk) == cgx::kMapWide
-                ? cgx::launch_dequant_reduce_requantize_wide(scheme, peers, W, dt, in->d_tiles, out->d_tiles, in->n_tiles,
-                                                             in->odd_tiles, longest_bucket(buckets, L, layer_offsets, bits_per_layer),
-                                                             seed, packed_out, meta_out, launch_config(),
-                                                             static_cast<hipStream_t>(stream))
-                : cgx::launch_dequant_reduce_requantize(scheme, peers, W, dt, in->d_tiles, out->d_tiles, in->n_tiles,
-                                                        in->odd_tiles, seed, packed_out, meta_out, launch_config(),
-                                                        static_cast<hipStream_t>(stream));
+            cgx::mapping_of(part.bucket, cgx::kDefaultChunk) == cgx::kMapWide
+                ? cgx::launch_dequant_reduce_requantize_wide(scheme, peers, W, dt, tiles_in, tiles_out, part.count, part.odd,
+                                                             part.longest, seed, packed_out, meta_out, launch_config(), queue)
+                : cgx::launch_dequant_reduce_requantize(scheme, peers, W, dt, tiles_in, tiles_out, part.count, part.odd, seed,
+                                                        packed_out, meta_out, launch_config(), queue);
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;
@@ -602,20 +530,16 @@ int sqerrors_impl(int scheme, const void *grad, const void *packed, const void *
         (reinterpret_cast<uintptr_t>(sqerr) & 7u))
         return CGX_ERR_ALIGN;
     // every launch leaves its tiles' partial sums in the workspace; the last one adds them up layer by layer
-    const std::vector<Launch> launches = launches_of(buckets, L, off, bits, cgx::kDefaultChunk);
-    std::vector<PlanRef> plans;
-    rc = get_plans(static_cast<hipStream_t>(stream), launches, L, off, bits, dt, cgx::kDefaultChunk,
-                   tile_length(kOtherCall, dt, n), cgx::kStatistics, buckets.per_layer, &plans);
+    PlanRef plan;
+    rc = get_plan(static_cast<hipStream_t>(stream), L, off, bits, buckets, dt, cgx::kDefaultChunk, tile_length(kOtherCall, dt, n),
+                  &plan);
     if (rc != CGX_OK) return rc;
-    for (const PlanRef &plan : plans)
-        if (workspace_bytes < size_t(plan->plan_tiles) * sizeof(double)) return CGX_ERR_SIZE;
-    for (size_t i = 0; i < launches.size(); i++) {
-        const PlanRef &plan = plans[i];
+    if (workspace_bytes < size_t(plan->stats_tiles) * sizeof(double)) return CGX_ERR_SIZE;
+    for (const cgx::TablePart &part : plan->parts) {
         const hipError_t e = cgx::launch_layer_sqerrors(
-            scheme, grad, dt, packed, meta, plan->d_tiles, plan->d_slots, plan->n_tiles, plan->aligned_tiles,
-            plan->d_layer_first, L,
-            static_cast<double *>(workspace), sqerr, launch_config(), static_cast<hipStream_t>(stream),
-            i + 1 == launches.size());
+            scheme, grad, dt, packed, meta, plan->d_tiles + part.first, plan->d_slots + part.first, part.count, part.aligned,
+            plan->d_layer_first, L, static_cast<double *>(workspace), sqerr, launch_config(), static_cast<hipStream_t>(stream),
+            &part == &plan->parts.back());
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;
@@ -766,15 +690,9 @@ int cgx_layered_stats_workspace(int64_t n, int32_t L, const int64_t *layer_offse
     const Buckets buckets{32, buckets_per_layer};
     const int rc = check_plan(cgx::kSchemeMinMax, n, L, layer_offsets, bits_per_layer, buckets, int(dt));
     if (rc != CGX_OK) return rc;
-    size_t tiles_of_plan = 0;
-    for (const Launch &launch : launches_of(buckets, L, layer_offsets, bits_per_layer, cgx::kDefaultChunk)) {
-        std::vector<Tile> tiles;
-        cgx::build_tiles(L, layer_offsets, bits_per_layer, launch.bucket, int(dt), cgx::kDefaultChunk,
-                         tile_length(kOtherCall, int(dt), n),
-                         tiles, nullptr, nullptr, buckets_per_layer, launch.with_copies);
-        tiles_of_plan += tiles.size();
-    }
-    *bytes = tiles_of_plan * sizeof(double);
+    *bytes = size_t(cgx::build_table(L, layer_offsets, bits_per_layer, 32, int(dt), cgx::kDefaultChunk,
+                                     tile_length(kOtherCall, int(dt), n), false, buckets_per_layer)
+                        .stats_tiles) * sizeof(double);
     return CGX_OK;
 }
 
@@ -887,10 +805,10 @@ int cgx_layer_sqnorms(const void *buf, int64_t n, int32_t L, const int64_t *laye
     if (!sqnorm || (n > 0 && (!buf || !workspace))) return CGX_ERR_NULL;
     if (misaligned(buf) || misaligned(workspace) || (reinterpret_cast<uintptr_t>(sqnorm) & 7u)) return CGX_ERR_ALIGN;
     PlanRef plan;
-    rc = get_plan(static_cast<hipStream_t>(stream), L, layer_offsets, zeros.data(), 32, int(dt), cgx::kDefaultChunk,
-                  tile_length(kOtherCall, int(dt), n), cgx::kStatistics, &plan);
+    rc = get_plan(static_cast<hipStream_t>(stream), L, layer_offsets, zeros.data(), Buckets{32, nullptr}, int(dt),
+                  cgx::kDefaultChunk, tile_length(kOtherCall, int(dt), n), &plan, cgx::kCopyTile);
     if (rc != CGX_OK) return rc;
-    if (workspace_bytes < size_t(plan->n_tiles) * sizeof(double)) return CGX_ERR_SIZE;
+    if (workspace_bytes < size_t(plan->stats_tiles) * sizeof(double)) return CGX_ERR_SIZE;
     const hipError_t e = cgx::launch_layer_sqnorms(buf, int(dt), plan->d_tiles, plan->d_slots, plan->n_tiles,
                                                    plan->d_layer_first, L, static_cast<double *>(workspace), sqnorm,
                                                    launch_config(), static_cast<hipStream_t>(stream));

@@ -55,12 +55,12 @@ enum StorePolicy { kStoreStream = 0, kStoreKeep = 1, kStoreThrough = 2 };
 // store_policy (StorePolicy): the result is streamed (non-temporal), written through at device scope (it then stays
 // in the memory-side cache if it is small enough; the caller decides by size), or written through at system scope,
 // non-temporal (calls that mostly write: a decompression).
-// tiles: a table whose quantized tiles hold at most a chunk each (TableUse kPieces).
+// tiles: the whole table of the plan; the tiles of buckets longer than a chunk are shared out over `pieces` waves each.
 // (two builds: chunks of 1024 elements, which a decompression takes, and of 2048)
-hipError_t launch_dequant_reduce_g2(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles, int64_t n_tiles,
+hipError_t launch_dequant_reduce_g2(int scheme, const PeerPtrs &peers, int W, int dt, const ReduceTiles &tiles,
                                  const void *init, int init_dt, void *out, int out_dt,
                                  int store_policy, const LaunchConfig &cfg, hipStream_t stream);
-hipError_t launch_dequant_reduce_g4(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles, int64_t n_tiles,
+hipError_t launch_dequant_reduce_g4(int scheme, const PeerPtrs &peers, int W, int dt, const ReduceTiles &tiles,
                                  const void *init, int init_dt, void *out, int out_dt,
                                  int store_policy, const LaunchConfig &cfg, hipStream_t stream);
 

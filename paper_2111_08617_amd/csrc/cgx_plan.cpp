@@ -74,7 +74,7 @@ static inline bool same_key_block(int64_t e0, int64_t count)
 
 void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
                  int chunks_per_tile, std::vector<Tile> &tiles, std::vector<uint32_t> *slots,
-                 std::vector<int64_t> *layer_first, const int32_t *layer_buckets, bool with_copies, TableUse use)
+                 std::vector<int64_t> *layer_first, const int32_t *layer_buckets, bool with_copies, int copy_tile)
 {
     tiles.clear();
     if (layer_first) layer_first->assign(size_t(L) + 1, 0);
@@ -91,7 +91,7 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
         uint64_t payload, buckets;
         const int32_t own_bucket = layer_buckets ? layer_buckets[l] : bucket;
         layer_extent(len, b, own_bucket, dt, payload, buckets);
-        if (b == 0 ? !with_copies : use != kPieces && mapping_of(own_bucket, chunk) != launch_mapping) {
+        if (b == 0 ? !with_copies : mapping_of(own_bucket, chunk) != launch_mapping) {
             seg += round_up16(payload);                           // another launch's layer: only its extent counts
             bucket0 += buckets;
             continue;
@@ -106,12 +106,11 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
         const bool aligned = true;
         const size_t first_tile = tiles.size();
         if (b == 0) {
-            const int64_t piece = use == kStatistics ? kCopyTile : kCopyPiece;
-            for (int64_t j = 0; j < len; j += piece) {
+            for (int64_t j = 0; j < len; j += copy_tile) {
                 Tile t{};
                 t.elem0 = first + j;
                 t.packed_off = int64_t(seg + uint64_t(j) * S);
-                t.count = uint32_t(len - j < piece ? len - j : piece);
+                t.count = uint32_t(len - j < copy_tile ? len - j : copy_tile);
                 t.info = uint32_t(kCopyFast) << 4;
                 tiles.push_back(t);
             }
@@ -134,21 +133,6 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
                     c += k;
                 }
                 j = full_chunks * kChunk;
-            } else if (own_bucket > kChunk && use == kPieces) {
-                // the chunks of every bucket, the last one of a bucket or of the layer shorter if need be
-                while (j < len) {
-                    const int64_t in_bucket = own_bucket - j % own_bucket, left = len - j;
-                    const int64_t most = in_bucket < left ? in_bucket : left, k = most < kChunk ? most : kChunk;
-                    const bool whole = wide_bucket && k == kChunk;
-                    Tile t{};
-                    t.elem0 = first + j;
-                    t.packed_off = int64_t(seg + uint64_t(j) * b / 8);
-                    t.bucket0 = uint32_t(bucket0 + uint64_t(j) / own_bucket);
-                    t.count = uint32_t(k);
-                    t.info = uint32_t(b) | uint32_t(whole ? kQuantWide : kQuantSlow) << 4 | (whole ? 6u << 8 : 0u) | size_bits;
-                    tiles.push_back(t);
-                    j += k;
-                }
             } else if (wide_bucket && aligned) {
                 // one tile per whole bucket: its scale needs all of it (lanes-per-bucket field: the whole wave)
                 const int64_t full = len / own_bucket;
@@ -200,6 +184,76 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
     for (size_t i = 0; i < order.size(); i++) sorted[i] = tiles[order[i]];
     tiles.swap(sorted);
     if (slots) slots->swap(order);
+}
+
+int64_t PlanTable::narrow(int chunk) const
+{
+    return mapping_of(parts.back().bucket, chunk) == kMapWide ? parts.back().first : int64_t(tiles.size());
+}
+
+int PlanTable::pieces(int chunk) const
+{
+    return mapping_of(parts.back().bucket, chunk) == kMapWide ? (parts.back().longest + chunk - 1) / chunk : 1;
+}
+
+PlanTable build_table(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
+                      int chunks_per_tile, bool numbered, const int32_t *layer_buckets, int copy_tile)
+{
+    PlanTable table;
+    if (layer_buckets) {
+        TablePart of[3];
+        for (int32_t l = 0; l < L; l++)
+            if (bits[l] != 0 && off[l + 1] > off[l]) {
+                TablePart &part = of[mapping_of(layer_buckets[l], chunk)];
+                part.bucket = part.bucket == 0 ? layer_buckets[l] : std::min(part.bucket, layer_buckets[l]);
+                part.longest = std::max(part.longest, layer_buckets[l]);
+            }
+        for (const TablePart &part : of)
+            if (part.bucket != 0) table.parts.push_back(part);
+    }
+    if (table.parts.empty()) {                          // one bucket size, or pass-through layers only
+        table.parts.emplace_back();
+        table.parts[0].bucket = table.parts[0].longest = layer_buckets ? 32 : bucket;
+    }
+    const bool number_copies = copy_tile == kCopyTile;
+    std::vector<int64_t> in_layer(size_t(L) + 1, 0);    // partial sums of layer l - 1, then their running total
+    std::vector<std::vector<uint32_t>> part_slots(table.parts.size());
+    std::vector<std::vector<int64_t>> part_first(table.parts.size());
+    for (size_t k = 0; k < table.parts.size(); k++) {
+        TablePart &part = table.parts[k];
+        std::vector<Tile> tiles;
+        build_tiles(L, off, bits, part.bucket, dt, chunk, chunks_per_tile, tiles, &part_slots[k], &part_first[k], layer_buckets,
+                    k == 0, copy_tile);
+        part.first = int64_t(table.tiles.size());
+        part.count = int64_t(tiles.size());
+        for (const Tile &t : tiles) {
+            part.odd |= is_quantized_kind(tile_kind(t)) && (t.elem0 & 1);
+            part.aligned &= !(is_vector_kind(tile_kind(t)) && (t.elem0 * elem_size(dt)) % 16 != 0);
+        }
+        for (int32_t l = 0; l < L; l++)
+            if (bits[l] != 0 || number_copies) in_layer[size_t(l) + 1] += part_first[k][size_t(l) + 1] - part_first[k][size_t(l)];
+        if (k == 0)
+            table.tiles.swap(tiles);
+        else
+            table.tiles.insert(table.tiles.end(), tiles.begin(), tiles.end());
+    }
+    for (int32_t l = 0; l < L; l++) {
+        table.stats_tiles += bits[l] != 0 ? in_layer[size_t(l) + 1] : (off[l + 1] - off[l] + kCopyTile - 1) / kCopyTile;
+        in_layer[size_t(l) + 1] += in_layer[size_t(l)];
+    }
+    if (!numbered) return table;
+    // a part's own numbers -> numbers over all parts
+    table.slots.reserve(table.tiles.size());
+    for (size_t k = 0; k < table.parts.size(); k++) {
+        std::vector<uint32_t> number(part_slots[k].size(), kNoSlot);
+        for (int32_t l = 0; l < L; l++)
+            if (bits[l] != 0 || number_copies)
+                for (int64_t i = part_first[k][size_t(l)]; i < part_first[k][size_t(l) + 1]; i++)
+                    number[size_t(i)] = uint32_t(in_layer[size_t(l)] + (i - part_first[k][size_t(l)]));
+        for (const uint32_t slot : part_slots[k]) table.slots.push_back(number[slot]);
+    }
+    table.layer_first = std::move(in_layer);
+    return table;
 }
 
 }  // namespace cgx

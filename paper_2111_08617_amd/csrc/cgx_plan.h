@@ -18,6 +18,7 @@
 #else
 #define CGX_HOST_DEVICE
 #endif
+#define CGX_ALWAYS_INLINE inline __attribute__((always_inline))      // a call in a kernel would move its tile to scratch
 
 namespace cgx {
 
@@ -26,17 +27,12 @@ namespace cgx {
 // 4 groups = 2048 elements) and walks a tile table built for that size: a vectorised tile is a
 // whole number of chunks.
 constexpr int chunk_of(int groups) { return 64 * 8 * groups; }
-// Elements per pass-through tile of the statistics (and of the tables of cgx_plan_tiles).
+// Elements per pass-through tile of the norm statistic (and of the tables of cgx_plan_tiles).
 constexpr int kCopyTile = 8192;
 // Elements per pass-through tile of the other kernels: a wave moves what its loads can have in flight together.  A
 // longer tile is a chain of round trips that outlasts the rest of a short launch (a reduce of 7.6 M elements with 124
 // layers, 8 peers, and the requantize of its sums: 36.1 us with pieces of 2048, 33.8 us with 1024).
 constexpr int kCopyPiece = 1024;
-
-// What walks a tile table.  The statistics keep one partial sum per tile (their workspace is sized by that table).
-// The quantizers need whole buckets; a reduction does not, so buckets longer than a chunk are cut into chunks
-// for it, one tile each, and one launch takes buckets of every size.
-enum TableUse { kStatistics = 0, kWholeBuckets = 1, kPieces = 2 };
 
 enum TileKind : uint32_t {
     kQuantSlow = 0,  // none of the others: a ragged end, a longer bucket, or a tile across two of the generator's key blocks
@@ -101,12 +97,79 @@ PlanShape plan_shape(int32_t L, const int64_t *off, const uint8_t *bits, int32_t
 // partial sum per tile and add them up in that order).
 // With layer_buckets (a bucket size per layer) the table holds the tiles of the layers whose
 // bucket size has the lane mapping of `bucket` (mapping_of at this chunk size) only, at their places in the whole
-// plan's streams: a launch runs one kernel instantiation, so such a plan takes one launch per
-// mapping in use (at most three; a reduction, use = kPieces, one in all).  The pass-through layers belong to the launch with
-// with_copies set.
+// plan's streams, and the pass-through layers' with with_copies.
+// copy_tile: elements per pass-through tile (kCopyTile or kCopyPiece).
 void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
                  int chunks_per_tile, std::vector<Tile> &tiles, std::vector<uint32_t> *slots = nullptr,
                  std::vector<int64_t> *layer_first = nullptr, const int32_t *layer_buckets = nullptr,
-                 bool with_copies = true, TableUse use = kStatistics);
+                 bool with_copies = true, int copy_tile = kCopyTile);
+
+// What one launch of a quantizer, the fused kernel or the error statistic walks: a launch runs one kernel
+// instantiation, so a plan whose layers have bucket sizes of several lane mappings takes one per mapping.  The first
+// part also holds the pass-through layers, the part of mapping kMapWide is the last one.
+struct TablePart {
+    int32_t bucket = 0;          // smallest bucket size in use: names the lane mapping
+    int32_t longest = 0;         // longest bucket size in use
+    int64_t first = 0, count = 0;
+    bool odd = false;            // some quantized tile starts on an odd element index
+    bool aligned = true;         // every vectorised quantized tile starts on a 16-byte boundary of the buffer
+};
+
+// The table of a plan, which all calls with the same chunk and tile lengths share: a program that has run one of them
+// may capture any of them.
+struct PlanTable {
+    std::vector<Tile> tiles;
+    std::vector<TablePart> parts;
+    // Per-layer numbering of the tiles that carry a partial sum (see build_tiles): all of them in a table of kCopyTile
+    // pieces; in one of kCopyPiece pieces the quantized ones (a pass-through layer has no error).  Empty unless asked for.
+    std::vector<uint32_t> slots;
+    std::vector<int64_t> layer_first;
+    int64_t stats_tiles = 0;     // tiles in pieces of kCopyTile: partial sums that a workspace of the statistics holds
+
+    // A reduction walks all parts in one launch and needs no whole buckets.  Tiles from `narrow()` on hold one bucket
+    // longer than a chunk each and go to pieces() waves, a chunk of the bucket each.
+    int64_t narrow(int chunk) const;
+    int pieces(int chunk) const;
+};
+constexpr uint32_t kNoSlot = 0xffffffffu;
+PlanTable build_table(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
+                      int chunks_per_tile, bool numbered, const int32_t *layer_buckets = nullptr, int copy_tile = kCopyPiece);
+
+// The tiles of a plan as a reduction walks them: `count` pieces of work, of which the first `narrow` are a tile each and
+// the others, `pieces` (at most 8) per tile, a chunk of a tile.  With pieces == 1, narrow == count.
+struct ReduceTiles {
+    const Tile *tiles = nullptr;
+    int64_t count = 0;
+    uint32_t narrow = 0, pieces = 1;
+};
+constexpr int64_t kMostPieces = int64_t(1) << 29;     // pieces of the tiles behind the narrow ones: see Piece
+
+// Piece of work number t: tile number `tile`, chunk number `piece` of it.
+struct Piece {
+    int64_t tile;
+    uint32_t piece = 0;
+    // ceil(2^32 / pieces): the upper half of its product with a number below kMostPieces is the quotient for up to 8 pieces
+    // (the error of the inverse, at most 7 / 8, times the number stays below 2^32 / 8)
+    static uint32_t inverse(uint32_t pieces) { return pieces > 1 ? uint32_t(((uint64_t(1) << 32) + pieces - 1) / pieces) : 0u; }
+    CGX_HOST_DEVICE CGX_ALWAYS_INLINE Piece(int64_t t, uint32_t narrow, uint32_t pieces, uint32_t inv) : tile(t)
+    {
+        if (t >= int64_t(narrow)) {
+            const uint32_t u = uint32_t(t - int64_t(narrow)), q = uint32_t((uint64_t(u) * inv) >> 32);
+            piece = u - q * pieces;
+            tile = int64_t(narrow) + q;
+        }
+    }
+    // Leaves the piece's share in the tile (one behind the narrow ones); false: there is none.
+    CGX_HOST_DEVICE CGX_ALWAYS_INLINE bool cut(Tile &t, int chunk) const
+    {
+        if (!is_quantized_kind(tile_kind(t))) return piece == 0;
+        const uint32_t at = piece * uint32_t(chunk);
+        if (at >= t.count) return false;
+        t.elem0 += at;
+        t.packed_off += at / 8 * tile_bits(t);
+        t.count = t.count - at < uint32_t(chunk) ? t.count - at : uint32_t(chunk);
+        return true;
+    }
+};
 
 }  // namespace cgx

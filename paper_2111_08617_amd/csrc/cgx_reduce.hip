@@ -13,6 +13,7 @@ struct ReduceArguments {
     const void *init;
     void *out;
     int init_dt, out_dt, keep;
+    uint32_t narrow, pieces, inv_pieces;
     PeerPtrs peers;
 };
 
@@ -25,7 +26,8 @@ constexpr int kAnyOut = -1;
 template <int SCHEME, int SINGLE>
 __global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__ tiles, int64_t n_tiles, int W_argument, int dt,
                                                          const void *init, void *out, int init_dt, int out_dt,
-                                                         int keep, const PeerPtrs peers_argument)
+                                                         int keep, uint32_t narrow, uint32_t pieces, uint32_t inv_pieces,
+                                                         const PeerPtrs peers_argument)
 {
     // the vectorised tiles index the table with constants (it then sits in scalar registers);
     // the other kinds index it at run time and read it from the kernarg segment
@@ -47,7 +49,12 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__
         // stays in registers across all of it
         asm volatile("" : "+v"(lane_of_wave));
         const int lane = lane_of_wave;
-        const Tile tile = tiles[t];
+        // The tiles behind the first `narrow` hold a bucket longer than a chunk each: `pieces` waves take a chunk of it
+        // each (a sum needs no whole bucket).  Per tile of 6144 elements in a wave of its own, reducing 67 M elements of 8
+        // peers took 486 us, and takes 97; buckets of 4096, 99 and 92.
+        const Piece piece(t, narrow, pieces, inv_pieces);
+        Tile tile = tiles[piece.tile];
+        if (t >= int64_t(narrow) && !piece.cut(tile, kChunk)) continue;
         const int bucket = tile_bucket(tile);       // per tile: a launch may mix sizes of one lane mapping
         const uint32_t kind = tile_kind(tile);
         if (is_vector_kind(kind)) {      // a wide tile is chunks of one bucket: kChunk / bucket == 0 below
@@ -65,13 +72,15 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__
 }  // namespace
 
 // This file is compiled once per chunk size (CGX_GROUPS = 2 and 4): launch_dequant_reduce_g2, launch_dequant_reduce_g4.
-hipError_t CGX_CONCAT(launch_dequant_reduce_g, CGX_GROUPS)(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles, int64_t n_tiles,
+hipError_t CGX_CONCAT(launch_dequant_reduce_g, CGX_GROUPS)(int scheme, const PeerPtrs &peers, int W, int dt, const ReduceTiles &tiles,
                                  const void *init, int init_dt, void *out, int out_dt,
                                  int store_policy, const LaunchConfig &cfg, hipStream_t stream)
 {
-    if (n_tiles == 0) return hipSuccess;
-    const dim3 grid(grid_for(n_tiles, cfg)), block(kBlock);
-    using Kernel = void (*)(const Tile *, int64_t, int, int, const void *, void *, int, int, int, const PeerPtrs);
+    if (tiles.count == 0) return hipSuccess;
+    const dim3 grid(grid_for(tiles.count, cfg)), block(kBlock);
+    using Kernel = void (*)(const Tile *, int64_t, int, int, const void *, void *, int, int, int, uint32_t, uint32_t, uint32_t,
+                            const PeerPtrs);
+    const uint32_t narrow = tiles.pieces > 1 ? tiles.narrow : 0xffffffffu;
     // (a decompression to binary32 runs the build for chunks of 1024 elements, one to binary16 that for 2048: 4 KB of
     // results per wave either way)
     constexpr int kSingleOut = kGroups == 2 ? CGX_F32 : CGX_F16;
@@ -79,8 +88,8 @@ hipError_t CGX_CONCAT(launch_dequant_reduce_g, CGX_GROUPS)(int scheme, const Pee
     static const Kernel table[2][2] = {{reduce_kernel<kMinMax, kAnyOut>, reduce_kernel<kNormSign, kAnyOut>},
                                        {reduce_kernel<kMinMax, kSingleOut>, reduce_kernel<kNormSign, kSingleOut>}};
     const Kernel kernel = table[single && W == 1 && !init][scheme == kSchemeNormSign];
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, tiles, n_tiles, W, dt, init, out, init_dt, out_dt, store_policy,
-                       peers);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, tiles.tiles, tiles.count, W, dt, init, out, init_dt, out_dt, store_policy,
+                       narrow, tiles.pieces, Piece::inverse(tiles.pieces), peers);
     return hipGetLastError();
 }
 

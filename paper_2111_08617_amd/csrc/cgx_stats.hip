@@ -266,11 +266,12 @@ __global__ __launch_bounds__(kBlock) void sqerror_kernel(const PeerPtrs chunk_ar
         const Tile tile = tiles[t];
         const int bucket = tile_bucket(tile);
         const uint32_t kind = tile_kind(tile);
-        double s = 0.0;                              // pass-through tiles: no error
+        if (!is_quantized_kind(kind)) continue;      // pass-through tiles: no error, and no partial sum
+        double s = 0.0;
         if (is_vector_kind(kind)) {
             CGX_FOR_BITS(tile_bits(tile),
                          (s = sqerror_fast<SCHEME, DT, BITS, VIA_LDS>(grad, chunk, tile, bucket, lane, stage, x_stage)))
-        } else if (is_quantized_kind(kind)) {
+        } else {
             CGX_FOR_BITS(tile_bits(tile), (s = sqerror_runs<SCHEME, DT, BITS>(grad, chunk, tile, bucket, lane, stage, x_stage)))
         }
         s = wave_sum(s);

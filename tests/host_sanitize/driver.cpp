@@ -2,6 +2,7 @@
 // (validation, sizes, tile tables), its bit-width assigners, and the CPU oracle, on plans with every
 // kind of layer.  Any out-of-bounds access, overflow or misaligned access aborts the run; the
 // invariants checked here make it fail with a message.  Test infrastructure: links the oracle.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -104,6 +105,118 @@ static void check_tiles(const Plan &p, int bucket, int dt, int chunk, int chunks
     for (int64_t i = 0; i < p.n(); i++) CHECK(covered[size_t(i)] == 1);    // the tables together: every element once
 }
 
+// The table that the entry points build and every call of a plan walks: its parts, the numbering of the statistics, and the
+// pieces of a reduction (by the arithmetic that the kernel runs).
+static void check_table(const Plan &p, int bucket, int dt, int chunk, int chunks_per_tile, const int32_t *layer_buckets, int copy_tile)
+{
+    using namespace cgx;
+    const PlanShape shape = plan_shape(p.L(), p.off.data(), p.bits.data(), bucket, dt, layer_buckets);
+    const PlanTable table = build_table(p.L(), p.off.data(), p.bits.data(), bucket, dt, chunk, chunks_per_tile, true, layer_buckets,
+                                        copy_tile);
+    const auto own_bucket = [&](size_t l) { return layer_buckets ? layer_buckets[l] : bucket; };
+    // where every layer's segment of the stream and its first bucket lie
+    std::vector<uint64_t> segment(size_t(p.L()) + 1), first_bucket(size_t(p.L()) + 1);
+    for (size_t l = 0; l < p.bits.size(); l++) {
+        const uint64_t len = uint64_t(p.off[l + 1] - p.off[l]), b = p.bits[l];
+        segment[l + 1] = segment[l] + ((b ? (len * b + 7) / 8 : len * (dt == CGX_F16 ? 2 : 4)) + 15) / 16 * 16;
+        first_bucket[l + 1] = first_bucket[l] + (b ? (len + own_bucket(l) - 1) / own_bucket(l) : 0);
+    }
+    CHECK(segment.back() == shape.packed_bytes && first_bucket.back() == shape.n_buckets);
+    std::vector<int> covered(size_t(p.n()), 0);
+    const auto check_tile = [&](const Tile &tile, bool whole) {
+        CHECK(tile.count > 0 && tile.elem0 >= 0 && tile.elem0 + tile.count <= p.n());
+        for (uint32_t j = 0; j < tile.count; j++) covered[size_t(tile.elem0 + j)]++;
+        size_t l = 0;
+        while (p.off[l + 1] <= tile.elem0) l++;
+        CHECK(tile.elem0 + tile.count <= p.off[l + 1] && tile_bits(tile) == p.bits[l]);
+        const uint64_t in_layer = uint64_t(tile.elem0 - p.off[l]), b = p.bits[l];
+        const uint64_t at = segment[l] + (b ? in_layer * b / 8 : in_layer * (dt == CGX_F16 ? 2 : 4));
+        const uint64_t payload = b ? (uint64_t(tile.count) * b + 7) / 8 : uint64_t(tile.count) * (dt == CGX_F16 ? 2 : 4);
+        CHECK(uint64_t(tile.packed_off) == at && (!b || in_layer * b % 8 == 0));
+        // zero padding behind the last tile of a layer and nowhere else
+        if (whole) CHECK(tile.pad == (tile.elem0 + tile.count == p.off[l + 1] ? segment[l + 1] - at - payload : 0));
+        if (b) {
+            CHECK(tile_bucket(tile) == own_bucket(l) && tile.bucket0 == first_bucket[l] + in_layer / own_bucket(l));
+            CHECK(!whole || in_layer % own_bucket(l) == 0);                 // whole buckets, from the first element of one on
+        } else {
+            CHECK(int(tile.count) <= copy_tile);
+        }
+        return l;
+    };
+    int64_t next = 0;
+    for (size_t k = 0; k < table.parts.size(); k++) {
+        const TablePart &part = table.parts[k];
+        CHECK(part.first == next && (k == 0 || mapping_of(part.bucket, chunk) > mapping_of(table.parts[k - 1].bucket, chunk)));
+        next += part.count;
+        bool odd = false, aligned = true;
+        for (int64_t t = part.first; t < part.first + part.count; t++) {
+            const Tile &tile = table.tiles[size_t(t)];
+            const size_t l = check_tile(tile, true);
+            if (p.bits[l] == 0) {
+                CHECK(k == 0);
+                continue;
+            }
+            CHECK(mapping_of(own_bucket(l), chunk) == mapping_of(part.bucket, chunk));
+            CHECK(own_bucket(l) >= part.bucket && own_bucket(l) <= part.longest);
+            // a block of waves, or one wave, holds the tile
+            if (mapping_of(part.bucket, chunk) == kMapWide) CHECK(int(tile.count) <= own_bucket(l));
+            else CHECK(int(tile.count) <= (tile_kind(tile) == kQuantFast ? chunks_per_tile : 1) * chunk);
+            odd |= tile.elem0 & 1;
+            if (is_vector_kind(tile_kind(tile))) aligned &= tile.elem0 * (dt == CGX_F16 ? 2 : 4) % 16 == 0;
+        }
+        CHECK(odd == part.odd && aligned == part.aligned);
+    }
+    CHECK(next == int64_t(table.tiles.size()));
+    for (int c : covered) CHECK(c == 1);
+    // one number per tile that carries a partial sum, a layer's numbers together and in the order of its elements
+    CHECK(table.slots.size() == table.tiles.size() && table.layer_first.size() == size_t(p.L()) + 1 && table.layer_first[0] == 0);
+    std::vector<int64_t> element(size_t(table.layer_first.back()), -1);
+    int64_t stats = 0;
+    for (size_t l = 0; l < p.bits.size(); l++)
+        stats += p.bits[l] ? table.layer_first[l + 1] - table.layer_first[l] : (p.off[l + 1] - p.off[l] + kCopyTile - 1) / kCopyTile;
+    CHECK(stats == table.stats_tiles && table.layer_first.back() <= stats);
+    for (size_t t = 0; t < table.tiles.size(); t++) {
+        size_t l = 0;
+        while (p.off[l + 1] <= table.tiles[t].elem0) l++;
+        if (p.bits[l] == 0 && copy_tile != kCopyTile) {
+            CHECK(table.slots[t] == kNoSlot);
+            continue;
+        }
+        CHECK(table.slots[t] >= table.layer_first[l] && table.slots[t] < table.layer_first[l + 1] && element[table.slots[t]] == -1);
+        element[table.slots[t]] = table.tiles[t].elem0;
+    }
+    for (size_t s = 0; s < element.size(); s++) CHECK(element[s] >= 0 && (s == 0 || element[s] > element[s - 1]));
+    // a reduction's pieces
+    const int64_t narrow = table.narrow(chunk), wide = int64_t(table.tiles.size()) - narrow;
+    const uint32_t pieces = uint32_t(table.pieces(chunk)), inv = Piece::inverse(pieces);
+    const uint32_t bound = pieces > 1 ? uint32_t(narrow) : 0xffffffffu;
+    CHECK(pieces <= 8);
+    std::fill(covered.begin(), covered.end(), 0);
+    for (int64_t t = 0; t < narrow + wide * pieces; t++) {
+        const Piece piece(t, bound, pieces, inv);
+        CHECK(piece.tile >= 0 && piece.tile < int64_t(table.tiles.size()));
+        Tile tile = table.tiles[size_t(piece.tile)];
+        if (t >= int64_t(bound) && !piece.cut(tile, chunk)) continue;
+        const size_t l = check_tile(tile, false);
+        if (p.bits[l] == 0 || tile_kind(tile) == kQuantFast) continue;
+        CHECK(int(tile.count) <= chunk);
+        if (tile_kind(tile) == kQuantWide) CHECK(int(tile.count) == chunk);
+        if (own_bucket(l) > chunk)                                          // no piece crosses a bucket
+            CHECK((tile.elem0 - p.off[l]) / own_bucket(l) == (tile.elem0 + tile.count - 1 - p.off[l]) / own_bucket(l));
+    }
+    for (int c : covered) CHECK(c == 1);
+}
+
+static void check_piece_division(std::mt19937 &rng)
+{
+    for (uint32_t pieces = 2; pieces <= 8; pieces++)
+        for (int k = 0; k < 200000; k++) {
+            const int64_t u = k < 1000 ? k : k < 2000 ? cgx::kMostPieces - 1 - (k - 1000) : int64_t(rng() % uint64_t(cgx::kMostPieces));
+            const cgx::Piece piece(u + 5, 5, pieces, cgx::Piece::inverse(pieces));
+            CHECK(piece.tile == 5 + u / pieces && piece.piece == u % pieces);
+        }
+}
+
 static void check_oracle(const Plan &p, int bucket, int dt, std::mt19937 &rng)
 {
     std::normal_distribution<float> normal(0.0f, 1.0f);
@@ -181,20 +294,34 @@ static void check_assigners(const Plan &p, std::mt19937 &rng)
 int main()
 {
     std::mt19937 rng(12345);
+    check_piece_division(rng);
     const int buckets[] = {32, 64, 96, 128, 512, 1024, 2048, 4096, 8192, 8160};
     int plans = 0;
     for (int bucket : buckets) {
         const Plan p = edge_plan(bucket, rng);
         for (int dt : {int(CGX_F32), int(CGX_F16)}) {
             for (int chunk : {1024, 2048})
-                for (int cpt : {1, 3}) check_tiles(p, bucket, dt, chunk, cpt, nullptr);
+                for (int cpt : {1, 3}) {
+                    check_tiles(p, bucket, dt, chunk, cpt, nullptr);
+                    for (int copy_tile : {cgx::kCopyTile, cgx::kCopyPiece})
+                        for (int b : {bucket, bucket + 32 <= 8192 ? bucket + 32 : 8000})
+                            check_table(p, b, dt, chunk, cpt, nullptr, copy_tile);
+                }
             check_oracle(p, bucket, dt, rng);
             plans++;
         }
         std::vector<int32_t> per_layer(size_t(p.L()));
         for (auto &b : per_layer) b = buckets[rng() % 10];
         CHECK(cgx::validate_layer_buckets(p.L(), per_layer.data()) == CGX_OK);
-        for (int chunk : {1024, 2048}) check_tiles(p, 32, CGX_F32, chunk, 1, per_layer.data());
+        for (int chunk : {1024, 2048}) {
+            check_tiles(p, 32, CGX_F32, chunk, 1, per_layer.data());
+            for (int dt : {int(CGX_F32), int(CGX_F16)}) check_table(p, 32, dt, chunk, 1, per_layer.data(), cgx::kCopyPiece);
+        }
+        for (auto &b : per_layer) b = b > 1024 ? 1056 + 32 * int(rng() % 224) : 96 * (1 + int(rng() % 10));
+        for (int chunk : {1024, 2048}) check_table(p, 32, CGX_F32, chunk, 1, per_layer.data(), cgx::kCopyPiece);
+        const Plan copies{p.off, std::vector<uint8_t>(p.bits.size(), 0)};
+        check_table(copies, 32, CGX_F32, 2048, 1, per_layer.data(), cgx::kCopyPiece);
+        check_table(copies, bucket, CGX_F16, 2048, 1, nullptr, cgx::kCopyTile);
         check_assigners(p, rng);
     }
     // rejected plans stay rejected without touching anything

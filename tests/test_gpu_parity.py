@@ -559,6 +559,50 @@ def test_result_does_not_depend_on_launch_geometry(torch, oracle):
     assert len(digests) == 1
 
 
+def test_longer_buckets_and_both_types_do_not_depend_on_launch_geometry(torch, oracle):
+    """The same for buckets longer than a chunk, whose blocks and pieces then come round several times with a small grid, for
+    a bucket size per layer, and for binary16, whose chunks are read into registers with CGX_VIA_LDS=0.  The per-layer errors
+    are among the results: their partial sums belong to tiles, so only a change of the tiles themselves
+    (CGX_CHUNKS_PER_TILE, not used here) puts their binary64 additions in another order."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = (
+        "import sys, hashlib, numpy as np, torch; sys.path.insert(0, %r)\n"
+        "from paper_2111_08617_amd import binding as cgx, workloads as wl\n"
+        "h = hashlib.sha256()\n"
+        "off = np.concatenate([[0], np.cumsum([8192 * 5 + 333, 500, 2048 * 24, 6144 * 4 + 31])]); bits = np.array([4, 0, 2, 7], np.uint8)\n"
+        "x = np.random.default_rng(3).standard_normal(int(off[-1]))\n"
+        "for dt, np_dt, t_dt in ((wl.F32, np.float32, torch.float32), (wl.F16, np.float16, torch.float16)):\n"
+        "    g = torch.from_numpy(x.astype(np_dt)).cuda()\n"
+        "    for b in (256, 1088, 2048, 4096, 6144, np.array([8192, 32, 128, 6144], np.int32)):\n"
+        "        layered = not isinstance(b, int)\n"
+        "        plan = (cgx.LayeredPlan if layered else cgx.Plan)(off, bits, b, dt)\n"
+        "        call = lambda name, *a: getattr(cgx, 'cgx_' + ('layered_' if layered else '') + name)(*a)\n"
+        "        pb, mb = call('sizes', plan)\n"
+        "        new = lambda: (torch.zeros(pb + 2048, dtype=torch.uint8, device='cuda'), torch.zeros(mb // 4, device='cuda'))\n"
+        "        (p, m), (fp, fm) = new(), new()\n"
+        "        call('quantize', g, plan, 77, p, m)\n"
+        "        s = torch.zeros(plan.n, device='cuda'); call('dequant_reduce', [p] * 3, [m] * 3, plan, s)\n"
+        "        call('dequant_reduce_requantize', [p] * 3, [m] * 3, plan, 78, fp, fm)\n"
+        "        d32 = torch.zeros(plan.n, device='cuda'); call('dequantize', p, m, plan, wl.F32, d32)\n"
+        "        d16 = torch.zeros(plan.n, dtype=torch.float16, device='cuda'); call('dequantize', p, m, plan, wl.F16, d16)\n"
+        "        e = torch.zeros(4, dtype=torch.float64, device='cuda')\n"
+        "        ws = torch.zeros(call('stats_workspace' if layered else 'layer_stats_workspace', plan) + 16, dtype=torch.uint8, device='cuda')\n"
+        "        call('layer_sqerrors', g, p, m, plan, e, ws); torch.cuda.synchronize()\n"
+        "        for t in (p, m, s, fp, fm, d32, d16, e): h.update(t.cpu().numpy().tobytes())\n"
+        "print(h.hexdigest())\n"
+    ) % root
+    digests = set()
+    for env in ({}, {"CGX_MAX_BLOCKS": "3"}, {"CGX_VIA_LDS": "0"},
+                {"CGX_REDUCE_GROUPS": "2", "CGX_MAX_BLOCKS": "5"}, {"CGX_REDUCE_GROUPS": "4"}):
+        out = subprocess.run([sys.executable, "-c", code], env={**os.environ, **env}, capture_output=True, text=True, timeout=300)
+        assert out.returncode == 0, out.stderr[-2000:]
+        digests.add(out.stdout.strip().splitlines()[-1])
+    assert len(digests) == 1
+
+
 def test_plan_cache_keeps_working_beyond_its_capacity(torch, oracle):
     """More distinct plans than the library caches (64): the least recently used tables are
     dropped and rebuilt on demand, results stay exact."""
@@ -696,6 +740,78 @@ def test_captured_graph_survives_any_number_of_later_plans(torch, oracle):
     torch.cuda.synchronize()
     sp, sm = oracle.quantize(x, never_seen.offsets, bits, 256, 5, wl.F32)
     assert np.array_equal(spare[0].cpu().numpy()[:sp.size], sp)
+
+
+SHARED_TABLES = [
+    # storage type, the calls that share a plan's table: whichever ran first, the others can be captured
+    (wl.F16, ("quantize", "reduce", "errors", "dequantize")),
+    (wl.F32, ("reduce", "fused", "errors")),
+    (wl.F32, ("quantize", "dequantize")),
+]
+
+
+@pytest.mark.parametrize("buckets", [128, 384, 640, 1088, 2048, 4096, 6144, (128, 32, 2048, 6144), (4096, 512, 96, 8192)], ids=str)
+def test_calls_that_share_a_table_can_be_captured_after_one_another(torch, oracle, buckets):
+    """Of the calls that walk the same table of a plan any one may run first; the others can then be captured, record
+    their launches and replay to what they give eagerly.  Every pair, with bucket sizes of every lane mapping, longer
+    than a chunk, and one per layer.  (bit-exact; the statistics too: their order of additions is fixed)"""
+    groups = SHARED_TABLES + ([(wl.F32, ("dequantize", "reduce"))] if not isinstance(buckets, int) or buckets > 1024 else [])
+    layered = not isinstance(buckets, int)
+    x = np.random.default_rng(77).standard_normal(40000).astype(np.float32)
+    serial = 0
+    for dt, calls in groups:
+        g = dev(torch, x.astype(np.float16) if dt == wl.F16 else x)
+        for first in calls:
+            for second in calls:
+                serial += 1
+                # a plan of its own: layer ends that no other pair has
+                off = np.array([0, 7000 + 8 * serial, 8000 + 16 * serial, 21000 + 24 * serial + 5, 40000 - 8 * serial], np.int64)
+                n, bits = int(off[-1]), np.array([4, 0, 3, 8], np.uint8)
+                plan = cgx.LayeredPlan(off, bits, np.array(buckets, np.int32), dt) if layered else cgx.Plan(off, bits, buckets, dt)
+                name = "cgx_layered_" if layered else "cgx_"
+                pb, mb = (cgx.cgx_layered_sizes if layered else cgx.cgx_sizes)(plan)
+                chunk = (oracle.layered_quantize if layered else oracle.quantize)(
+                    (x.astype(np.float16) if dt == wl.F16 else x)[:n], off, bits, plan.buckets if layered else buckets, 5, dt)
+                packed, meta = dev(torch, chunk[0]), dev(torch, chunk[1].reshape(-1))
+                ws = torch.empty((cgx.cgx_layered_stats_workspace(plan) if layered else cgx.cgx_layer_stats_workspace(plan)) + 16,
+                                 dtype=torch.uint8, device="cuda")
+
+                def make(call):
+                    """The call with buffers of its own, and those buffers."""
+                    if call == "quantize":
+                        out = torch.zeros(pb, dtype=torch.uint8, device="cuda"), torch.zeros(mb // 4, device="cuda")
+                        return (lambda: getattr(cgx, name + "quantize")(g[:n], plan, 9, *out)), out
+                    if call == "reduce":
+                        out = (torch.zeros(n, device="cuda"),)
+                        return (lambda: getattr(cgx, name + "dequant_reduce")([packed] * 3, [meta] * 3, plan, *out)), out
+                    if call == "dequantize":
+                        out = (torch.zeros(n, dtype=torch.float16 if dt == wl.F16 else torch.float32, device="cuda"),)
+                        return (lambda: getattr(cgx, name + "dequantize")(packed, meta, plan, dt, *out)), out
+                    if call == "fused":
+                        out = torch.zeros(pb, dtype=torch.uint8, device="cuda"), torch.zeros(mb // 4, device="cuda")
+                        return (lambda: getattr(cgx, name + "dequant_reduce_requantize")([packed] * 3, [meta] * 3, plan, 9, *out)), out
+                    out = (torch.zeros(4, dtype=torch.float64, device="cuda"),)
+                    return (lambda: getattr(cgx, name + "layer_sqerrors")(g[:n], packed, meta, plan, *out, ws)), out
+
+                make(first)[0]()
+                torch.cuda.synchronize()
+                run, out = make(second)
+                side = torch.cuda.Stream()
+                side.wait_stream(torch.cuda.current_stream())
+                graph = torch.cuda.CUDAGraph()
+                with torch.cuda.graph(graph, stream=side):
+                    run()                             # raises CGX_ERR_CAPTURE if the table does not exist
+                eager, want = make(second)
+                eager()
+                torch.cuda.synchronize()
+                for replay in range(2):
+                    for t in out:
+                        t.fill_(7)
+                    torch.cuda.synchronize()
+                    graph.replay()
+                    torch.cuda.synchronize()
+                    for a, b in zip(out, want):
+                        assert a.cpu().numpy().tobytes() == b.cpu().numpy().tobytes(), (dt, first, second, replay)
 
 
 def test_a_refused_call_pins_no_table(torch, oracle):
