@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import functools
 import os
+import warnings
 from typing import Sequence, Tuple
 
 import numpy as np
@@ -123,20 +124,38 @@ def status_string(status: int) -> str:
     return lib().cgx_status_string(int(status)).decode()
 
 
+class _PythonChecks:
+    """What stands in for the extension module: decides nothing, so every tensor is checked in Python."""
+
+    @staticmethod
+    def address(tensor, nbytes, code):
+        return None
+
+    @staticmethod
+    def tables(packed, meta, packed_bytes, meta_bytes):
+        return None
+
+    @staticmethod
+    def unchanged(pairs) -> bool:
+        return all(ctypes.string_at(at, len(held)) == held for at, held in zip(pairs[::2], pairs[1::2]))
+
+
 _native = None
 
 
 def _args():
-    """The extension module that checks tensors (csrc/cgx_tensor_args.cpp); raises if it has not been built."""
+    """The extension module that checks tensors (csrc/cgx_tensor_args.cpp).  Without it the checks are made in Python,
+    which costs a call 5 to 15 us more."""
     global _native
     if _native is None:
         import torch  # noqa: F401  (the module links against its libraries)
         try:
             from . import _cgx_args
+            _native = _cgx_args
         except ImportError as e:
-            raise FileNotFoundError("_cgx_args.so is missing or does not fit this torch: build it with "
-                                    "`python -m paper_2111_08617_amd.build`") from e
-        _native = _cgx_args
+            warnings.warn(f"_cgx_args.so is missing or does not fit this torch ({e}): arguments are checked in Python.  Build "
+                          "it with `python -m paper_2111_08617_amd.build`", RuntimeWarning)
+            _native = _PythonChecks
     return _native
 
 

@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -35,7 +36,9 @@ FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-ffp-contract=o
 
 
 def build(verbose: bool = False, extra=(), jobs: int = 8) -> str:
-    """Compiles every source (in parallel: the kernel files take a minute each) and links."""
+    """Compiles every source (in parallel: the kernel files take a minute each) and links.  The extension module that
+    checks tensors needs g++ and torch's headers besides; without it the library is complete and the binding makes the
+    checks in Python, so a failure there is a warning."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
 
@@ -48,7 +51,7 @@ def build(verbose: bool = False, extra=(), jobs: int = 8) -> str:
         subprocess.run(cmd, check=True, cwd=CSRC)
         return obj
 
-    def compile_args(_):
+    def compile_args():
         # the binding's tensor checks: host code against torch's headers
         import sysconfig
 
@@ -64,13 +67,17 @@ def build(verbose: bool = False, extra=(), jobs: int = 8) -> str:
         subprocess.run(cmd, check=True, cwd=CSRC)
 
     with ThreadPoolExecutor(max_workers=max(1, min(jobs, len(SOURCES) + 1))) as pool:
-        args = pool.submit(compile_args, None)
+        args = pool.submit(compile_args)
         objs = list(pool.map(compile_one, SOURCES))
-        args.result()
+        failure = args.exception()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     if verbose:
         print(" ".join(cmd))
     subprocess.run(cmd, check=True, cwd=CSRC)
+    if failure is not None:
+        if os.path.exists(ARGS):
+            os.remove(ARGS)                      # of other sources, or for another torch
+        warnings.warn(f"_cgx_args.so was not built: {failure}", RuntimeWarning)
     return LIB
 
 

@@ -553,3 +553,55 @@ def test_other_layer_offsets_bring_their_own_lengths(lib):
         if isinstance(plan, cgx.LayeredPlan):
             plan.buckets = [32, 32, 32]
         assert plan.args[:2] == (256, 3) and cgx._sizes_of(plan)[0] == 32 + 32 + 512
+
+
+def test_calls_check_their_arguments_without_the_extension_module(lib, monkeypatch):
+    """The module that checks tensors in native code needs torch's headers to build.  Where it is missing the same checks are
+    made in Python: the calls work, refuse what they refuse, and a warning says so once."""
+    import sys
+
+    class Fake:
+        is_cuda, dtype, device = True, None, "cuda:0"
+        def __init__(self, nbytes): self.nbytes = nbytes
+        def numel(self): return self.nbytes
+        def element_size(self): return 1
+        def is_contiguous(self): return True
+        def data_ptr(self): return 0x1000
+
+    monkeypatch.setattr(cgx, "_native", None)
+    monkeypatch.setitem(sys.modules, cgx.__package__ + "._cgx_args", None)
+    monkeypatch.delattr(sys.modules[cgx.__package__], "_cgx_args", raising=False)
+    with pytest.warns(RuntimeWarning, match="checked in Python"):
+        assert cgx._device_buffer(Fake(64), "buffer", 64) == 0x1000
+    with pytest.raises(ValueError, match="63 bytes"):
+        cgx._device_buffer(Fake(63), "buffer", 64)
+    W, packed, meta = cgx._peers([Fake(64)] * 3, [Fake(64)] * 3, "call", 64, 0)
+    assert W == 3 and list(packed) == [0x1000] * 3 and list(meta) == [0x1000] * 3
+    plan = cgx.Plan([0, 100, 300], [4, 2], 128)
+    before = cgx.cgx_sizes(plan)
+    assert cgx.cgx_sizes(plan) == before
+    plan.bits[:] = 8
+    assert cgx.cgx_sizes(plan) == cgx.cgx_sizes(cgx.Plan([0, 100, 300], [8, 8], 128)) != before
+
+
+def test_the_library_is_built_where_the_extension_module_is_not(monkeypatch, tmp_path):
+    """hipcc alone builds the C library: a failure of the module that needs g++ and torch's headers is a warning, and no
+    module of other sources is left behind."""
+    import subprocess
+
+    from paper_2111_08617_amd import build as cgx_build
+    commands = []
+
+    def run(cmd, **kw):
+        commands.append(cmd)
+        if cmd[0] == "g++":
+            raise subprocess.CalledProcessError(1, cmd)
+
+    for name in ("LIB", "ARGS", "OBJ"):
+        monkeypatch.setattr(cgx_build, name, str(tmp_path / name))
+    (tmp_path / "ARGS").write_bytes(b"stale")
+    monkeypatch.setattr(cgx_build.subprocess, "run", run)
+    with pytest.warns(RuntimeWarning, match="_cgx_args"):
+        assert cgx_build.build() == str(tmp_path / "LIB")
+    assert "-shared" in commands[-1] and str(tmp_path / "LIB") in commands[-1]
+    assert not (tmp_path / "ARGS").exists()
