@@ -550,7 +550,7 @@ struct Run {
     // own: groups of 8 elements a lane holds, G or (the quantizer's short runs) fewer
     __device__ __forceinline__ Run(int count_, int bucket, int lane, int own = G) : count(count_)
     {
-        lanes = bucket / (8 * own);
+        lanes = (bucket + 8 * own - 1) / (8 * own);      // (rounded up only where the run lies in one bucket)
         // (l + 0.5) / lanes lies at least 0.5 / lanes from every whole number: the approximate reciprocal is exact enough
         const float inv = __builtin_amdgcn_rcpf(float(lanes));
         const int last = int((float((count - 1) / (8 * own)) + 0.5f) * inv);

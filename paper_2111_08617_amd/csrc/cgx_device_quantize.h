@@ -379,10 +379,11 @@ __device__ __forceinline__ void quantize_run(const void *__restrict__ grad, uint
                                          packed + tile.packed_off, tile.pad, stage);
 }
 
-// A run that 24 elements per lane hold, with a bucket size of which 24 is a divisor (a lane stays within a bucket).
+// A run that 24 elements per lane hold, none of the lanes across two buckets: its bucket size is a multiple of 24, or it lies
+// in one bucket (as every run of buckets of more than 1024 elements does).
 __device__ __forceinline__ bool three_groups_hold(const Tile &tile, int bucket)
 {
-    return tile.count <= uint32_t(kWave * 24) && tile.count > uint32_t(kWave * 16) && bucket % 24 == 0;
+    return tile.count <= uint32_t(kWave * 24) && tile.count > uint32_t(kWave * 16) && (bucket % 24 == 0 || tile.count <= uint32_t(bucket));
 }
 
 // What no other path takes (a tile across two key blocks of the generator): one bucket at a time, two passes.

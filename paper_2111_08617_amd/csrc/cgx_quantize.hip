@@ -43,8 +43,9 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict
                                                   grad, packed, meta, tile, bucket, seed_lo, seed_hi, lane, stage)))
             }
         } else if (is_quantized_kind(kind) && tile.count <= uint32_t(kChunk) && one_key_block(tile)) {
-            // (one bucket of 1056 ... 1536 elements per tile; quantize of 67 M elements, buckets of 1056: 79.8 us with four
-            // groups per lane, 71.3 with three; binary16 70.5 and 59.3)
+            // (one bucket of 1056 ... 1536 elements per tile: the lanes past its end cost as much as the others.  Quantize of
+            // 67 M elements, us with four groups per lane and with three: binary32, buckets of 1056, 79.8 and 71.3, of 1184,
+            // 73.8 and 64.8; binary16 70.5 and 59.3, 64.4 and 53.2)
             if (G == 4 && MAP == kMapBuckets && three_groups_hold(tile, bucket)) {
                 if constexpr (G == 4 && MAP == kMapBuckets) {
                     CGX_FOR_BITS(tile_bits(tile), (quantize_run<SCHEME, DT, BITS, ODD, 3>(grad, packed, meta, tile, bucket, seed_lo,

@@ -953,3 +953,14 @@ def test_a_cached_plan_does_not_excuse_bad_arguments(torch, oracle):
     assert L.cgx_dequant_reduce(one, m, 1, *args) == 0
     assert L.cgx_dequant_reduce(one, m, 0, *args) == -6 and L.cgx_qsgd_dequant_reduce(one, m, 1, *args) == -4
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("bucket", [1088, 1184, 1504, 2048])
+def test_runs_of_one_bucket_at_24_elements_per_lane(torch, oracle, bucket, dt):
+    """Runs of 1025 to 1536 elements within one bucket, whose size 24 does not divide: the last lane's elements, and lengths
+    on both sides of the range.  (bit-exact)"""
+    sizes = [bucket, bucket - 1, bucket + 1, 1024, 1025, 1031, 1032, 1033, 1535, 1536, 1537, 3 * bucket + 1100, 5 * bucket + 24 * 45 + 7]
+    bits = np.array([4, 3, 8, 2, 5, 7, 6, 1, 4, 2, 3, 4, 8], np.uint8)
+    w = wl.Workload("one bucket", [(s,) for s in sizes], bits, bucket, dt, 3, 500 + bucket, wl._normal, np.linspace(0.02, 1.5, len(sizes)))
+    full_cycle(torch, oracle, w, W=3, what=f"one bucket B={bucket}")
