@@ -124,25 +124,43 @@ enum CallKind { kQuantizeCall, kFusedCall, kOtherCall };
 // up to 2048 instead of two (ResNet-50 with sizes by layer length, 128 / 512 / 2048: 36 us of quantizing in two launches
 // of 1024-element chunks, in which a bucket of 2048 is read twice,
 // 26 us in one launch of 2048-element chunks).
-int chunk_length(CallKind call, int dt, int32_t longest)
+// A chunk takes whole buckets, and lanes without elements cost as much as the others.  Where chunks of 1024 elements spend
+// at least a quarter more lanes than those of 2048 (352, 384, 544 ... 672 and 768 of the multiples of 32), binary32 takes the
+// longer ones.  Measured, 1024 against 2048, us: 67 M elements in buckets of 672 72.6 and 51.2, 384 62.8 and 52.3, 768 63.8
+// and 50.7; 8.4 M 11.4 and 10.6, 10.3 and 10.6, 10.3 and 9.5.  At an eighth or less the longer ones lose on short buffers:
+// buckets of 288 (1.17) 60.6 and 53.2 on 67 M elements, 10.0 and 10.6 on 8.4 M; 224 (1.12) 57.8 and 52.7, 9.6 and 10.7.
+
+// Lanes' worth of elements that the quantizer of `chunk` spends per element of buckets of a size (at most the chunk).
+double lanes_spent(int32_t bucket, int chunk)
 {
-    if (call != kQuantizeCall || longest > cgx::chunk_of(2)) return cgx::kDefaultChunk;
-    const int forced = launch_config().quantize_groups;
-    if (forced > 0) return cgx::chunk_of(forced);
-    // a chunk takes whole buckets: a size of which 1024 elements hold one, and 2048 three (544 ... 672), leaves a
-    // third of the lanes of the shorter chunk without work (67 M elements, buckets of 672: 72.3 -> 53.9 us)
-    if (longest > 512 && longest <= 682 && longest % 32 == 0) return cgx::kDefaultChunk;
-    return cgx::chunk_of(dt == CGX_F32 ? 2 : 4);
+    const int32_t held = chunk / bucket * bucket;
+    // (runs of up to 1536 elements take three groups per lane, see three_groups_hold)
+    const int32_t lanes = chunk == cgx::chunk_of(4) && held <= 1536 && held > 1024 && bucket % 24 == 0 ? 1536 : chunk;
+    return double(lanes) / held;
 }
 
-// The longest bucket size of a call (of its quantized layers, if they have their own).
-int32_t longest_bucket(const Buckets &buckets, int32_t L, const int64_t *off, const uint8_t *bits)
+// Elements per chunk of a quantize call.  The arrays of the (checked) plan are read only where the layers have sizes of
+// their own.
+int quantize_chunk(int dt, const Buckets &buckets, int32_t L, const int64_t *off, const uint8_t *bits)
 {
-    if (!buckets.per_layer) return buckets.uniform;
-    int32_t longest = 0;
-    for (int32_t l = 0; l < L; l++)
-        if (bits[l] != 0 && off[l + 1] > off[l] && buckets.per_layer[l] > longest) longest = buckets.per_layer[l];
-    return longest;
+    const int shorter = cgx::chunk_of(2), longer = cgx::chunk_of(4);
+    double in_shorter = 0.0, in_longer = 0.0;
+    bool too_long = false;
+    const auto add = [&](int64_t elements, int32_t bucket) {
+        too_long |= bucket > shorter;
+        if (bucket <= 0 || too_long) return;
+        in_shorter += double(elements) * lanes_spent(bucket, shorter);
+        in_longer += double(elements) * lanes_spent(bucket, longer);
+    };
+    if (!buckets.per_layer)
+        add(1, buckets.uniform);
+    else
+        for (int32_t l = 0; l < L; l++)
+            if (bits[l] != 0 && off[l + 1] > off[l]) add(off[l + 1] - off[l], buckets.per_layer[l]);
+    const int forced = launch_config().quantize_groups;
+    if (too_long) return longer;
+    if (forced > 0) return cgx::chunk_of(forced);
+    return dt == CGX_F32 && (in_longer == 0.0 || in_shorter < 1.24 * in_longer) ? shorter : longer;
 }
 
 int tile_length(CallKind call, int dt, int64_t n)
@@ -335,7 +353,7 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
                   const Buckets &buckets, uint64_t seed, int dt, void *packed, void *meta, void *stream)
 {
     const hipStream_t queue = static_cast<hipStream_t>(stream);
-    int chunk = chunk_length(kQuantizeCall, dt, buckets.uniform);
+    int chunk = buckets.per_layer ? cgx::kDefaultChunk : quantize_chunk(dt, buckets, L, off, bits);
     const int per_tile = tile_length(kQuantizeCall, dt, n);
     PlanRef plan = plain(grad) && plain(packed) && plain(meta)
                        ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile)
@@ -352,7 +370,7 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
     if (!grad || !packed || (shape.meta_bytes && !meta)) return CGX_ERR_NULL;
     if (misaligned(grad) || misaligned(packed) || misaligned(meta)) return CGX_ERR_ALIGN;
     if (!plan) {
-        chunk = chunk_length(kQuantizeCall, dt, longest_bucket(buckets, L, off, bits));
+        chunk = quantize_chunk(dt, buckets, L, off, bits);
         const int rc = get_plan(queue, L, off, bits, buckets, dt, chunk, per_tile, &plan);
         if (rc != CGX_OK) return rc;
     }
@@ -411,8 +429,8 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
             chunk = cgx::kDefaultChunk;
             rc = get_plan(queue, L, off, bits, buckets, dt, chunk, per_tile, &plan);
         } else if (rc == CGX_OK && built && chunk != cgx::kDefaultChunk &&
-                   (buckets.per_layer || (dt == CGX_F32 && chunk_length(kQuantizeCall, dt, buckets.uniform) != chunk) ||
-                    buckets.uniform > chunk)) {
+                   (buckets.per_layer || buckets.uniform > chunk ||
+                    (dt == CGX_F32 && quantize_chunk(dt, buckets, L, off, bits) != chunk))) {
             PlanRef others;
             rc = get_plan(queue, L, off, bits, buckets, dt, cgx::kDefaultChunk, per_tile, &others);
         }

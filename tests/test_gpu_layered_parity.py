@@ -280,3 +280,15 @@ def test_layered_plans_that_mix_sizes_that_are_no_power_of_two(torch, oracle, se
     if seed < 5:
         w.bits = np.where(w.bits == 1, 2, w.bits).astype(np.uint8)
         qsgd_cycle(torch, oracle, w, buckets, "norm-sign " + what)
+
+
+@pytest.mark.parametrize("short,long,long_part", [(128, 640, 0.05), (128, 640, 0.6), (1024, 352, 0.7), (512, 768, 0.9), (64, 384, 0.5)])
+def test_chunk_size_follows_the_sizes_that_hold_most_elements(torch, oracle, short, long, long_part):
+    """Sizes of which a longer chunk holds more than twice as many buckets, in a small and in a large part of the elements: either
+    chunk size gives the oracle's bytes.  (bit-exact)"""
+    n = 60000
+    cut = int(n * (1 - long_part))
+    sizes = [(cut // 2,), (300,), (cut - cut // 2 + 7,), (n - cut,)]
+    buckets = np.array([short, 32, short, long], np.int32)
+    w = wl.Workload("mix", sizes, np.array([4, 0, 3, 8], np.uint8), 32, wl.F32, 2, 77, wl._normal, np.linspace(0.1, 1.0, 4))
+    cycle(torch, oracle, w, buckets, f"{short}/{long} {long_part}")
