@@ -317,6 +317,16 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
         return CGX_ERR_HIP;
     }
     plan->reduce = cgx::ReduceTiles{plan->d_tiles, narrow + wide * pieces, uint32_t(narrow), uint32_t(pieces)};
+    for (const int type : {CGX_F32, CGX_F16}) {
+        const int64_t in_64 = type == CGX_F16 ? 32 : 16, in_16 = in_64 / 4;
+        int64_t off_64 = 0, off_16 = 0;
+        for (const Tile &t : table.tiles) {
+            off_64 += t.elem0 % in_64 != 0 ? t.count : 0;
+            off_16 += t.elem0 % in_16 != 0 ? t.count : 0;
+        }
+        plan->reduce.off_64_bytes[type] = 2 * off_64 > off[L];
+        plan->reduce.off_16_bytes[type] = 2 * off_16 > off[L];
+    }
     plan->parts = std::move(table.parts);
     plan->last_use = ++g_clock;
     if (g_plans.size() >= kMaxPlans) {

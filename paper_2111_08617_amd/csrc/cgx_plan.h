@@ -141,6 +141,8 @@ struct ReduceTiles {
     const Tile *tiles = nullptr;
     int64_t count = 0;
     uint32_t narrow = 0, pieces = 1;
+    // by storage type of the result: most elements lie in tiles that do not start on 64, on 16 bytes of it
+    bool off_64_bytes[2] = {false, false}, off_16_bytes[2] = {false, false};
 };
 constexpr int64_t kMostPieces = int64_t(1) << 29;     // pieces of the tiles behind the narrow ones: see Piece
 

@@ -87,8 +87,20 @@ hipError_t CGX_CONCAT(launch_dequant_reduce_g, CGX_GROUPS)(int scheme, const Pee
     const bool single = store_policy == kStoreThrough && out_dt == kSingleOut;
     static const Kernel table[2][2] = {{reduce_kernel<kMinMax, kAnyOut>, reduce_kernel<kNormSign, kAnyOut>},
                                        {reduce_kernel<kMinMax, kSingleOut>, reduce_kernel<kNormSign, kSingleOut>}};
-    const Kernel kernel = table[single && W == 1 && !init][scheme == kSchemeNormSign];
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, tiles.tiles, tiles.count, W, dt, init, out, init_dt, out_dt, store_policy,
+    const bool decompression = single && W == 1 && !init;
+    const Kernel kernel = table[decompression][scheme == kSchemeNormSign];
+    // Where the waves' stores do not start on 64 bytes of the result, two waves write into the lines between them, and eight
+    // waves per SIMD have more such lines open than pays: LDS that nothing uses holds the kernel to seven, or six.  With 8, 7,
+    // 6 and 5 waves, us, 4 bits, 268 M elements: to binary32 in layers of odd lengths 268, 234, 232, 242 (codes still in the
+    // memory-side cache 284, 274, 261, 247), on 16 bytes 257, 251, 255, 271 (266, 263, 266, 277); to binary16, odd lengths,
+    // 139, 128, 124, 124 (122, 117, 121, 128).  On 64 bytes eight are the best: 185, 200, 205, 219, unless the codes are in
+    // that cache: 170, 169, 167, 162.
+    const auto lds_for = [](unsigned waves) {
+        return 160 * 1024 / waves / 128 * 128 - unsigned(sizeof(uint4v)) * kWavesPerBlock * kChunk / (kGroups == 2 ? 4 : 8);
+    };
+    const unsigned unused_lds = !decompression || !tiles.off_64_bytes[out_dt]               ? 0
+                                : out_dt == CGX_F32 && tiles.off_16_bytes[out_dt] ? lds_for(6) : lds_for(7);
+    hipLaunchKernelGGL(kernel, grid, block, unused_lds, stream, tiles.tiles, tiles.count, W, dt, init, out, init_dt, out_dt, store_policy,
                        narrow, tiles.pieces, Piece::inverse(tiles.pieces), peers);
     return hipGetLastError();
 }
