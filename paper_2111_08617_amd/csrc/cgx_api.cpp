@@ -17,15 +17,25 @@ namespace {
 
 using cgx::Tile;
 
+// How the tiles of a table are cut.
+struct TableKind {
+    int chunk = 0;              // elements per chunk of the kernels that walk it
+    int chunks_per_tile = 0;
+    int copy_tile = cgx::kCopyPiece;      // elements per tile of a pass-through layer
+    int long_chunk = 0;         // not 0: the chunk of the layers with buckets longer than `chunk`
+    bool operator==(const TableKind &o) const
+    {
+        return chunk == o.chunk && chunks_per_tile == o.chunks_per_tile && copy_tile == o.copy_tile && long_chunk == o.long_chunk;
+    }
+};
+
 struct CachedPlan {
     // identity
     int device = 0;
     int32_t bucket = 0;
     int dt = 0;
     uint64_t digest = 0;        // hash of (off, bits, layer_buckets): compared before the arrays themselves
-    int chunk = 0;              // elements per chunk of the kernels that walk this table
-    int chunks_per_tile = 0;
-    int copy_tile = 0;          // elements per tile of a pass-through layer
+    TableKind kind;
     std::vector<int64_t> off;
     std::vector<uint8_t> bits;
     std::vector<int32_t> layer_buckets;   // empty: `bucket` for every layer
@@ -139,16 +149,23 @@ double lanes_spent(int32_t bucket, int chunk)
     return double(lanes) / held;
 }
 
-// Elements per chunk of a quantize call.  The arrays of the (checked) plan are read only where the layers have sizes of
-// their own.
-int quantize_chunk(int dt, const Buckets &buckets, int32_t L, const int64_t *off, const uint8_t *bits)
+// Chunks of a quantize call (see TableKind).  The arrays of the (checked) plan are read only where the layers have sizes
+// of their own.
+// A binary32 call with buckets of more than 1024 elements in some layers and 100 M elements or more in the others leaves
+// the others to the kernel of the shorter chunks, in a launch of their own.  Layers of 512 with 3 % of 2048, one launch and
+// two, us: 67 M elements 50.9 and 52.8, 134 M 100.8 and 98.1, 268 M 202 and 195, 537 M 405 and 387; half of 2048: 134 M 99.7
+// and 99.9, 268 M 201 and 195.
+struct Chunks {
+    int chunk, long_chunk;
+};
+Chunks quantize_chunks(int dt, const Buckets &buckets, int32_t L, const int64_t *off, const uint8_t *bits)
 {
     const int shorter = cgx::chunk_of(2), longer = cgx::chunk_of(4);
     double in_shorter = 0.0, in_longer = 0.0;
-    bool too_long = false;
+    int64_t short_elements = 0, long_elements = 0;
     const auto add = [&](int64_t elements, int32_t bucket) {
-        too_long |= bucket > shorter;
-        if (bucket <= 0 || too_long) return;
+        (bucket > shorter ? long_elements : short_elements) += elements;
+        if (bucket <= 0 || bucket > shorter) return;
         in_shorter += double(elements) * lanes_spent(bucket, shorter);
         in_longer += double(elements) * lanes_spent(bucket, longer);
     };
@@ -158,9 +175,13 @@ int quantize_chunk(int dt, const Buckets &buckets, int32_t L, const int64_t *off
         for (int32_t l = 0; l < L; l++)
             if (bits[l] != 0 && off[l + 1] > off[l]) add(off[l + 1] - off[l], buckets.per_layer[l]);
     const int forced = launch_config().quantize_groups;
-    if (too_long) return longer;
-    if (forced > 0) return cgx::chunk_of(forced);
-    return dt == CGX_F32 && (in_longer == 0.0 || in_shorter < 1.24 * in_longer) ? shorter : longer;
+    const bool fills_longer = in_longer > 0.0 && in_shorter >= 1.24 * in_longer;
+    if (long_elements > 0) {
+        const bool apart = forced > 0 ? forced == 2 && short_elements > 0 : short_elements >= int64_t(3) << 25 && !fills_longer;
+        return dt == CGX_F32 && apart ? Chunks{shorter, longer} : Chunks{longer, 0};
+    }
+    if (forced > 0) return {cgx::chunk_of(forced), 0};
+    return {dt == CGX_F32 && !fills_longer ? shorter : longer, 0};
 }
 
 int tile_length(CallKind call, int dt, int64_t n)
@@ -212,7 +233,8 @@ struct PlanKey {
     const int64_t *off;
     const uint8_t *bits;
     int32_t bucket;
-    int dt, chunk, chunks_per_tile, copy_tile;
+    int dt;
+    TableKind kind;
     const int32_t *layer_buckets;
     uint64_t digest;
 };
@@ -221,8 +243,8 @@ struct PlanKey {
 PlanRef cached_plan(const PlanKey &k, int device, bool capturing)
 {
     for (const auto &p : g_plans) {
-        if (p->digest == k.digest && p->device == device && p->bucket == k.bucket && p->dt == k.dt && p->chunk == k.chunk &&
-            p->chunks_per_tile == k.chunks_per_tile && p->copy_tile == k.copy_tile && p->bits.size() == size_t(k.L) &&
+        if (p->digest == k.digest && p->device == device && p->bucket == k.bucket && p->dt == k.dt && p->kind == k.kind &&
+            p->bits.size() == size_t(k.L) &&
             p->layer_buckets.size() == (k.layer_buckets ? size_t(k.L) : 0) &&
             (!k.layer_buckets || k.L == 0 ||
              std::memcmp(p->layer_buckets.data(), k.layer_buckets, sizeof(int32_t) * size_t(k.L)) == 0) &&
@@ -249,7 +271,7 @@ bool is_capturing(hipStream_t stream)
 // is found for arguments that those checks would refuse: tables exist for checked plans only, and 1-bit layers
 // are left to them under the norm-and-sign quantizer.
 PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const int64_t *off, const uint8_t *bits,
-                   const Buckets &buckets, int dt, int chunk, int chunks_per_tile)
+                   const Buckets &buckets, int dt, const TableKind &kind)
 {
     // (what the checks find out without reading the arrays keeps them unread)
     if (buckets.per_layer || L <= 0 || n <= 0 || !off || !bits || (dt != CGX_F32 && dt != CGX_F16) || buckets.uniform < 32 ||
@@ -257,8 +279,7 @@ PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const i
         return nullptr;
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return nullptr;
-    const PlanKey key{L, off, bits, buckets.uniform, dt, chunk, chunks_per_tile, cgx::kCopyPiece, nullptr,
-                      plan_digest(L, off, bits, nullptr)};
+    const PlanKey key{L, off, bits, buckets.uniform, dt, kind, nullptr, plan_digest(L, off, bits, nullptr)};
     const bool capturing = is_capturing(stream);
     std::lock_guard<std::mutex> lock(g_mutex);
     const PlanRef plan = cached_plan(key, device, capturing);
@@ -271,8 +292,8 @@ PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const i
 // and a table that does not exist yet is not built during a capture (that would allocate and copy
 // synchronously in the middle of it): the call fails with CGX_ERR_CAPTURE and records nothing.
 // built (may be null): whether the table is a new one.
-int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *bits, const Buckets &buckets, int dt, int chunk,
-             int chunks_per_tile, PlanRef *out, int copy_tile = cgx::kCopyPiece, bool *built = nullptr)
+int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *bits, const Buckets &buckets, int dt,
+             const TableKind &kind, PlanRef *out, bool *built = nullptr)
 {
     const int32_t bucket = buckets.uniform;
     const int32_t *layer_buckets = buckets.per_layer;
@@ -281,8 +302,7 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return CGX_ERR_HIP;
     const bool capturing = is_capturing(stream);
-    *out = cached_plan(PlanKey{L, off, bits, bucket, dt, chunk, chunks_per_tile, copy_tile, layer_buckets, digest}, device,
-                       capturing);
+    *out = cached_plan(PlanKey{L, off, bits, bucket, dt, kind, layer_buckets, digest}, device, capturing);
     if (built) *built = !*out;
     if (*out) return CGX_OK;
     if (capturing) return CGX_ERR_CAPTURE;
@@ -294,22 +314,21 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     plan->device = device;
     plan->bucket = bucket;
     plan->dt = dt;
-    plan->chunk = chunk;
-    plan->chunks_per_tile = chunks_per_tile;
-    plan->copy_tile = copy_tile;
+    plan->kind = kind;
     plan->off.assign(off, off + L + 1);
     plan->bits.assign(bits, bits + L);
     if (layer_buckets) plan->layer_buckets.assign(layer_buckets, layer_buckets + L);
     plan->one_bit_layers = std::find(bits, bits + L, uint8_t(1)) != bits + L;
     plan->shape = cgx::plan_shape(L, off, bits, bucket, dt, layer_buckets);
     // (the statistics walk tables of the default chunk length in tiles of one chunk)
-    const bool numbered = chunk == cgx::kDefaultChunk && chunks_per_tile == tile_length(kOtherCall, dt, off[L]);
-    cgx::PlanTable table = cgx::build_table(L, off, bits, bucket, dt, chunk, chunks_per_tile, numbered, layer_buckets, copy_tile);
+    const bool numbered = kind.chunk == cgx::kDefaultChunk && kind.chunks_per_tile == tile_length(kOtherCall, dt, off[L]);
+    cgx::PlanTable table = cgx::build_table(L, off, bits, bucket, dt, kind.chunk, kind.chunks_per_tile, numbered, layer_buckets,
+                                            kind.copy_tile, kind.long_chunk);
     if (table.tiles.size() > size_t(0xffffffffu) || table.stats_tiles > int64_t(0xffffffffu)) return CGX_ERR_SIZE;
     plan->n_tiles = int64_t(table.tiles.size());
     plan->stats_tiles = table.stats_tiles;
-    const int64_t narrow = table.narrow(chunk), wide = plan->n_tiles - narrow;
-    const int pieces = table.pieces(chunk);
+    const int64_t narrow = table.narrow(), wide = plan->n_tiles - narrow;
+    const int pieces = table.pieces();
     if (pieces > 1 && wide * pieces >= cgx::kMostPieces) return CGX_ERR_SIZE;
     if (!upload(&plan->d_tiles, table.tiles) || !upload(&plan->d_slots, table.slots) ||
         !upload(&plan->d_layer_first, numbered ? table.layer_first : std::vector<int64_t>())) {
@@ -363,10 +382,9 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
                   const Buckets &buckets, uint64_t seed, int dt, void *packed, void *meta, void *stream)
 {
     const hipStream_t queue = static_cast<hipStream_t>(stream);
-    int chunk = buckets.per_layer ? cgx::kDefaultChunk : quantize_chunk(dt, buckets, L, off, bits);
     const int per_tile = tile_length(kQuantizeCall, dt, n);
-    PlanRef plan = plain(grad) && plain(packed) && plain(meta)
-                       ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile)
+    PlanRef plan = !buckets.per_layer && plain(grad) && plain(packed) && plain(meta)
+                       ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, {quantize_chunks(dt, buckets, L, off, bits).chunk, per_tile})
                        : nullptr;
     cgx::PlanShape shape;
     if (plan) {
@@ -380,15 +398,15 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
     if (!grad || !packed || (shape.meta_bytes && !meta)) return CGX_ERR_NULL;
     if (misaligned(grad) || misaligned(packed) || misaligned(meta)) return CGX_ERR_ALIGN;
     if (!plan) {
-        chunk = quantize_chunk(dt, buckets, L, off, bits);
-        const int rc = get_plan(queue, L, off, bits, buckets, dt, chunk, per_tile, &plan);
+        const Chunks chunks = quantize_chunks(dt, buckets, L, off, bits);
+        const int rc = get_plan(queue, L, off, bits, buckets, dt, {chunks.chunk, per_tile, cgx::kCopyPiece, chunks.long_chunk}, &plan);
         if (rc != CGX_OK) return rc;
     }
-    const auto launch_quantize = chunk == cgx::chunk_of(2) ? cgx::launch_quantize_g2 : cgx::launch_quantize_g4;
     for (const cgx::TablePart &part : plan->parts) {
+        const auto launch_quantize = part.chunk == cgx::chunk_of(2) ? cgx::launch_quantize_g2 : cgx::launch_quantize_g4;
         const Tile *tiles = plan->d_tiles + part.first;
         const hipError_t e =
-            cgx::mapping_of(part.bucket, chunk) == cgx::kMapWide
+            cgx::mapping_of(part.bucket, part.chunk) == cgx::kMapWide
                 ? cgx::launch_quantize_wide(scheme, grad, dt, tiles, part.count, part.odd, part.longest, seed, packed, meta,
                                             launch_config(), queue)
                 : launch_quantize(scheme, grad, dt, tiles, part.count, part.odd, part.aligned, part.bucket, seed, packed, meta,
@@ -413,7 +431,7 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
     const int per_tile = tile_length(kOtherCall, dt, n);
     const hipStream_t queue = static_cast<hipStream_t>(stream);
     PlanRef plan = plain_chunks(packed, meta, W, CGX_MAX_PEERS) && plain(out) && (!want_local || plain(local))
-                       ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, chunk, per_tile)
+                       ? known_plan(queue, scheme, n, L, off, bits, buckets, dt, {chunk, per_tile})
                        : nullptr;
     if (!plan) {
         const int rc = check_plan(scheme, n, L, off, bits, buckets, dt);
@@ -431,18 +449,18 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
     if (misaligned(out) || misaligned(local)) return CGX_ERR_ALIGN;
     if (!plan) {
         bool built = false;
-        int rc = get_plan(queue, L, off, bits, buckets, dt, chunk, per_tile, &plan, cgx::kCopyPiece, &built);
+        int rc = get_plan(queue, L, off, bits, buckets, dt, {chunk, per_tile}, &plan, &built);
         // A decompression in chunks of 1024 elements must not need another table than its plan's other calls where a
         // program captures one of them after having run the other: under a capture it takes their table if its own does
         // not exist, and when it builds its own for a plan that is quantized in chunks of 2048, it builds theirs too.
         if (rc == CGX_ERR_CAPTURE && chunk != cgx::kDefaultChunk) {
             chunk = cgx::kDefaultChunk;
-            rc = get_plan(queue, L, off, bits, buckets, dt, chunk, per_tile, &plan);
+            rc = get_plan(queue, L, off, bits, buckets, dt, {chunk, per_tile}, &plan);
         } else if (rc == CGX_OK && built && chunk != cgx::kDefaultChunk &&
                    (buckets.per_layer || buckets.uniform > chunk ||
-                    (dt == CGX_F32 && quantize_chunk(dt, buckets, L, off, bits) != chunk))) {
+                    (dt == CGX_F32 && quantize_chunks(dt, buckets, L, off, bits).chunk != chunk))) {
             PlanRef others;
-            rc = get_plan(queue, L, off, bits, buckets, dt, cgx::kDefaultChunk, per_tile, &others);
+            rc = get_plan(queue, L, off, bits, buckets, dt, {cgx::kDefaultChunk, per_tile}, &others);
         }
         if (rc != CGX_OK) return rc;
     }
@@ -477,14 +495,13 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
                uint64_t seed, void *packed_out, void *meta_out, void *stream)
 {
     const hipStream_t queue = static_cast<hipStream_t>(stream);
-    const int per_tile = tile_length(kFusedCall, dt, n);
+    const TableKind kind{cgx::kDefaultChunk, tile_length(kFusedCall, dt, n)};
     // tables of the chunks and of the output, which lays out its pass-through layers as binary32
     PlanRef in, out;
     if (plain_chunks(packed, meta, W, CGX_MAX_FUSED_PEERS) && plain(packed_out) && plain(meta_out)) {
-        in = known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt, cgx::kDefaultChunk, per_tile);
+        in = known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt, kind);
         out = dt == CGX_F32 || !in ? in
-                                   : known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, CGX_F32,
-                                                cgx::kDefaultChunk, per_tile);
+                                   : known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, CGX_F32, kind);
     }
     const bool known = in && out;
     if (!known) {
@@ -507,16 +524,16 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
         peers.meta[i] = static_cast<const float *>(meta[i]);
     }
     if (!known) {
-        int rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, cgx::kDefaultChunk, per_tile, &in);
+        int rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, kind, &in);
         if (rc != CGX_OK) return rc;
-        rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, CGX_F32, cgx::kDefaultChunk, per_tile, &out);
+        rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, CGX_F32, kind, &out);
         if (rc != CGX_OK) return rc;
     }
     if (in->n_tiles != out->n_tiles) return CGX_ERR_SIZE;     // cannot happen: same tiling for both layouts
     for (const cgx::TablePart &part : in->parts) {
         const Tile *tiles_in = in->d_tiles + part.first, *tiles_out = out->d_tiles + part.first;
         const hipError_t e =
-            cgx::mapping_of(part.bucket, cgx::kDefaultChunk) == cgx::kMapWide
+            cgx::mapping_of(part.bucket, part.chunk) == cgx::kMapWide
                 ? cgx::launch_dequant_reduce_requantize_wide(scheme, peers, W, dt, tiles_in, tiles_out, part.count, part.odd,
                                                              part.longest, seed, packed_out, meta_out, launch_config(), queue)
                 : cgx::launch_dequant_reduce_requantize(scheme, peers, W, dt, tiles_in, tiles_out, part.count, part.odd, seed,
@@ -559,8 +576,8 @@ int sqerrors_impl(int scheme, const void *grad, const void *packed, const void *
         return CGX_ERR_ALIGN;
     // every launch leaves its tiles' partial sums in the workspace; the last one adds them up layer by layer
     PlanRef plan;
-    rc = get_plan(static_cast<hipStream_t>(stream), L, off, bits, buckets, dt, cgx::kDefaultChunk, tile_length(kOtherCall, dt, n),
-                  &plan);
+    rc = get_plan(static_cast<hipStream_t>(stream), L, off, bits, buckets, dt,
+                  {cgx::kDefaultChunk, tile_length(kOtherCall, dt, n)}, &plan);
     if (rc != CGX_OK) return rc;
     if (workspace_bytes < size_t(plan->stats_tiles) * sizeof(double)) return CGX_ERR_SIZE;
     for (const cgx::TablePart &part : plan->parts) {
@@ -834,7 +851,7 @@ int cgx_layer_sqnorms(const void *buf, int64_t n, int32_t L, const int64_t *laye
     if (misaligned(buf) || misaligned(workspace) || (reinterpret_cast<uintptr_t>(sqnorm) & 7u)) return CGX_ERR_ALIGN;
     PlanRef plan;
     rc = get_plan(static_cast<hipStream_t>(stream), L, layer_offsets, zeros.data(), Buckets{32, nullptr}, int(dt),
-                  cgx::kDefaultChunk, tile_length(kOtherCall, int(dt), n), &plan, cgx::kCopyTile);
+                  {cgx::kDefaultChunk, tile_length(kOtherCall, int(dt), n), cgx::kCopyTile}, &plan);
     if (rc != CGX_OK) return rc;
     if (workspace_bytes < size_t(plan->stats_tiles) * sizeof(double)) return CGX_ERR_SIZE;
     const hipError_t e = cgx::launch_layer_sqnorms(buf, int(dt), plan->d_tiles, plan->d_slots, plan->n_tiles,

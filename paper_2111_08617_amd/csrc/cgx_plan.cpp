@@ -74,7 +74,7 @@ static inline bool same_key_block(int64_t e0, int64_t count)
 
 void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
                  int chunks_per_tile, std::vector<Tile> &tiles, std::vector<uint32_t> *slots,
-                 std::vector<int64_t> *layer_first, const int32_t *layer_buckets, bool with_copies, int copy_tile)
+                 std::vector<int64_t> *layer_first, const int32_t *layer_buckets, bool with_copies, int copy_tile, int longer_than)
 {
     tiles.clear();
     if (layer_first) layer_first->assign(size_t(L) + 1, 0);
@@ -91,7 +91,7 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
         uint64_t payload, buckets;
         const int32_t own_bucket = layer_buckets ? layer_buckets[l] : bucket;
         layer_extent(len, b, own_bucket, dt, payload, buckets);
-        if (b == 0 ? !with_copies : mapping_of(own_bucket, chunk) != launch_mapping) {
+        if (b == 0 ? !with_copies : mapping_of(own_bucket, chunk) != launch_mapping || own_bucket <= longer_than) {
             seg += round_up16(payload);                           // another launch's layer: only its extent counts
             bucket0 += buckets;
             continue;
@@ -186,34 +186,39 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
     if (slots) slots->swap(order);
 }
 
-int64_t PlanTable::narrow(int chunk) const
+int64_t PlanTable::narrow() const
 {
-    return mapping_of(parts.back().bucket, chunk) == kMapWide ? parts.back().first : int64_t(tiles.size());
+    return mapping_of(parts.back().bucket, parts.back().chunk) == kMapWide ? parts.back().first : int64_t(tiles.size());
 }
 
-int PlanTable::pieces(int chunk) const
+int PlanTable::pieces() const
 {
-    return mapping_of(parts.back().bucket, chunk) == kMapWide ? (parts.back().longest + chunk - 1) / chunk : 1;
+    const TablePart &last = parts.back();
+    return mapping_of(last.bucket, last.chunk) == kMapWide ? (last.longest + last.chunk - 1) / last.chunk : 1;
 }
 
 PlanTable build_table(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
-                      int chunks_per_tile, bool numbered, const int32_t *layer_buckets, int copy_tile)
+                      int chunks_per_tile, bool numbered, const int32_t *layer_buckets, int copy_tile, int long_chunk)
 {
     PlanTable table;
     if (layer_buckets) {
-        TablePart of[3];
+        TablePart of[2][3];
         for (int32_t l = 0; l < L; l++)
             if (bits[l] != 0 && off[l + 1] > off[l]) {
-                TablePart &part = of[mapping_of(layer_buckets[l], chunk)];
+                const bool longer = long_chunk != 0 && layer_buckets[l] > chunk;
+                TablePart &part = of[longer][mapping_of(layer_buckets[l], longer ? long_chunk : chunk)];
+                part.chunk = longer ? long_chunk : chunk;
                 part.bucket = part.bucket == 0 ? layer_buckets[l] : std::min(part.bucket, layer_buckets[l]);
                 part.longest = std::max(part.longest, layer_buckets[l]);
             }
-        for (const TablePart &part : of)
-            if (part.bucket != 0) table.parts.push_back(part);
+        for (const auto &parts : of)
+            for (const TablePart &part : parts)
+                if (part.bucket != 0) table.parts.push_back(part);
     }
     if (table.parts.empty()) {                          // one bucket size, or pass-through layers only
         table.parts.emplace_back();
         table.parts[0].bucket = table.parts[0].longest = layer_buckets ? 32 : bucket;
+        table.parts[0].chunk = chunk;
     }
     const bool number_copies = copy_tile == kCopyTile;
     std::vector<int64_t> in_layer(size_t(L) + 1, 0);    // partial sums of layer l - 1, then their running total
@@ -222,8 +227,8 @@ PlanTable build_table(int32_t L, const int64_t *off, const uint8_t *bits, int32_
     for (size_t k = 0; k < table.parts.size(); k++) {
         TablePart &part = table.parts[k];
         std::vector<Tile> tiles;
-        build_tiles(L, off, bits, part.bucket, dt, chunk, chunks_per_tile, tiles, &part_slots[k], &part_first[k], layer_buckets,
-                    k == 0, copy_tile);
+        build_tiles(L, off, bits, part.bucket, dt, part.chunk, chunks_per_tile, tiles, &part_slots[k], &part_first[k],
+                    layer_buckets, k == 0, copy_tile, part.chunk == chunk ? 0 : chunk);
         part.first = int64_t(table.tiles.size());
         part.count = int64_t(tiles.size());
         for (const Tile &t : tiles) {

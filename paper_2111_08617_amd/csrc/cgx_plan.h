@@ -98,18 +98,20 @@ PlanShape plan_shape(int32_t L, const int64_t *off, const uint8_t *bits, int32_t
 // With layer_buckets (a bucket size per layer) the table holds the tiles of the layers whose
 // bucket size has the lane mapping of `bucket` (mapping_of at this chunk size) only, at their places in the whole
 // plan's streams, and the pass-through layers' with with_copies.
-// copy_tile: elements per pass-through tile (kCopyTile or kCopyPiece).
+// copy_tile: elements per pass-through tile (kCopyTile or kCopyPiece).  longer_than: quantized layers with buckets of at
+// most this size are left out too.
 void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
                  int chunks_per_tile, std::vector<Tile> &tiles, std::vector<uint32_t> *slots = nullptr,
                  std::vector<int64_t> *layer_first = nullptr, const int32_t *layer_buckets = nullptr,
-                 bool with_copies = true, int copy_tile = kCopyTile);
+                 bool with_copies = true, int copy_tile = kCopyTile, int longer_than = 0);
 
 // What one launch of a quantizer, the fused kernel or the error statistic walks: a launch runs one kernel
 // instantiation, so a plan whose layers have bucket sizes of several lane mappings takes one per mapping.  The first
-// part also holds the pass-through layers, the part of mapping kMapWide is the last one.
+// part also holds the pass-through layers, a part of mapping kMapWide is the last one.
 struct TablePart {
     int32_t bucket = 0;          // smallest bucket size in use: names the lane mapping
     int32_t longest = 0;         // longest bucket size in use
+    int chunk = 0;               // elements per chunk of the kernel that walks it
     int64_t first = 0, count = 0;
     bool odd = false;            // some quantized tile starts on an odd element index
     bool aligned = true;         // every vectorised quantized tile starts on a 16-byte boundary of the buffer
@@ -128,12 +130,15 @@ struct PlanTable {
 
     // A reduction walks all parts in one launch and needs no whole buckets.  Tiles from `narrow()` on hold one bucket
     // longer than a chunk each and go to pieces() waves, a chunk of the bucket each.
-    int64_t narrow(int chunk) const;
-    int pieces(int chunk) const;
+    int64_t narrow() const;
+    int pieces() const;
 };
 constexpr uint32_t kNoSlot = 0xffffffffu;
+// long_chunk (0: none): layers with buckets longer than `chunk` go to parts of their own, for the kernels with chunks of
+// long_chunk elements.
 PlanTable build_table(int32_t L, const int64_t *off, const uint8_t *bits, int32_t bucket, int dt, int chunk,
-                      int chunks_per_tile, bool numbered, const int32_t *layer_buckets = nullptr, int copy_tile = kCopyPiece);
+                      int chunks_per_tile, bool numbered, const int32_t *layer_buckets = nullptr, int copy_tile = kCopyPiece,
+                      int long_chunk = 0);
 
 // The tiles of a plan as a reduction walks them: `count` pieces of work, of which the first `narrow` are a tile each and
 // the others, `pieces` (at most 8) per tile, a chunk of a tile.  With pieces == 1, narrow == count.

@@ -107,12 +107,13 @@ static void check_tiles(const Plan &p, int bucket, int dt, int chunk, int chunks
 
 // The table that the entry points build and every call of a plan walks: its parts, the numbering of the statistics, and the
 // pieces of a reduction (by the arithmetic that the kernel runs).
-static void check_table(const Plan &p, int bucket, int dt, int chunk, int chunks_per_tile, const int32_t *layer_buckets, int copy_tile)
+static void check_table(const Plan &p, int bucket, int dt, int chunk, int chunks_per_tile, const int32_t *layer_buckets, int copy_tile,
+                        int long_chunk = 0)
 {
     using namespace cgx;
     const PlanShape shape = plan_shape(p.L(), p.off.data(), p.bits.data(), bucket, dt, layer_buckets);
     const PlanTable table = build_table(p.L(), p.off.data(), p.bits.data(), bucket, dt, chunk, chunks_per_tile, true, layer_buckets,
-                                        copy_tile);
+                                        copy_tile, long_chunk);
     const auto own_bucket = [&](size_t l) { return layer_buckets ? layer_buckets[l] : bucket; };
     // where every layer's segment of the stream and its first bucket lie
     std::vector<uint64_t> segment(size_t(p.L()) + 1), first_bucket(size_t(p.L()) + 1);
@@ -146,7 +147,10 @@ static void check_table(const Plan &p, int bucket, int dt, int chunk, int chunks
     int64_t next = 0;
     for (size_t k = 0; k < table.parts.size(); k++) {
         const TablePart &part = table.parts[k];
-        CHECK(part.first == next && (k == 0 || mapping_of(part.bucket, chunk) > mapping_of(table.parts[k - 1].bucket, chunk)));
+        CHECK(part.first == next && (part.chunk == chunk || (part.chunk == long_chunk && part.bucket > chunk)));
+        if (k > 0 && part.chunk == table.parts[k - 1].chunk)
+            CHECK(mapping_of(part.bucket, part.chunk) > mapping_of(table.parts[k - 1].bucket, part.chunk));
+        if (k > 0) CHECK(part.chunk >= table.parts[k - 1].chunk);
         next += part.count;
         bool odd = false, aligned = true;
         for (int64_t t = part.first; t < part.first + part.count; t++) {
@@ -156,11 +160,12 @@ static void check_table(const Plan &p, int bucket, int dt, int chunk, int chunks
                 CHECK(k == 0);
                 continue;
             }
-            CHECK(mapping_of(own_bucket(l), chunk) == mapping_of(part.bucket, chunk));
+            CHECK(mapping_of(own_bucket(l), part.chunk) == mapping_of(part.bucket, part.chunk));
             CHECK(own_bucket(l) >= part.bucket && own_bucket(l) <= part.longest);
             // a block of waves, or one wave, holds the tile
-            if (mapping_of(part.bucket, chunk) == kMapWide) CHECK(int(tile.count) <= own_bucket(l));
-            else CHECK(int(tile.count) <= (tile_kind(tile) == kQuantFast ? chunks_per_tile : 1) * chunk);
+            if (mapping_of(part.bucket, part.chunk) == kMapWide) CHECK(int(tile.count) <= own_bucket(l));
+            else CHECK(int(tile.count) <= (tile_kind(tile) == kQuantFast ? chunks_per_tile : 1) * part.chunk);
+            if (long_chunk) CHECK((own_bucket(l) > chunk) == (part.chunk == long_chunk));
             odd |= tile.elem0 & 1;
             if (is_vector_kind(tile_kind(tile))) aligned &= tile.elem0 * (dt == CGX_F16 ? 2 : 4) % 16 == 0;
         }
@@ -186,9 +191,10 @@ static void check_table(const Plan &p, int bucket, int dt, int chunk, int chunks
         element[table.slots[t]] = table.tiles[t].elem0;
     }
     for (size_t s = 0; s < element.size(); s++) CHECK(element[s] >= 0 && (s == 0 || element[s] > element[s - 1]));
+    if (long_chunk) return;                                                 // (no reduction walks such a table)
     // a reduction's pieces
-    const int64_t narrow = table.narrow(chunk), wide = int64_t(table.tiles.size()) - narrow;
-    const uint32_t pieces = uint32_t(table.pieces(chunk)), inv = Piece::inverse(pieces);
+    const int64_t narrow = table.narrow(), wide = int64_t(table.tiles.size()) - narrow;
+    const uint32_t pieces = uint32_t(table.pieces()), inv = Piece::inverse(pieces);
     const uint32_t bound = pieces > 1 ? uint32_t(narrow) : 0xffffffffu;
     CHECK(pieces <= 8);
     std::fill(covered.begin(), covered.end(), 0);
@@ -317,8 +323,10 @@ int main()
             check_tiles(p, 32, CGX_F32, chunk, 1, per_layer.data());
             for (int dt : {int(CGX_F32), int(CGX_F16)}) check_table(p, 32, dt, chunk, 1, per_layer.data(), cgx::kCopyPiece);
         }
+        check_table(p, 32, CGX_F32, 1024, 1, per_layer.data(), cgx::kCopyPiece, 2048);
         for (auto &b : per_layer) b = b > 1024 ? 1056 + 32 * int(rng() % 224) : 96 * (1 + int(rng() % 10));
         for (int chunk : {1024, 2048}) check_table(p, 32, CGX_F32, chunk, 1, per_layer.data(), cgx::kCopyPiece);
+        check_table(p, 32, CGX_F32, 1024, 1, per_layer.data(), cgx::kCopyPiece, 2048);
         const Plan copies{p.off, std::vector<uint8_t>(p.bits.size(), 0)};
         check_table(copies, 32, CGX_F32, 2048, 1, per_layer.data(), cgx::kCopyPiece);
         check_table(copies, bucket, CGX_F16, 2048, 1, nullptr, cgx::kCopyTile);

@@ -595,7 +595,7 @@ def test_longer_buckets_and_both_types_do_not_depend_on_launch_geometry(torch, o
         "print(h.hexdigest())\n"
     ) % root
     digests = set()
-    for env in ({}, {"CGX_MAX_BLOCKS": "3"}, {"CGX_VIA_LDS": "0"},
+    for env in ({}, {"CGX_MAX_BLOCKS": "3"}, {"CGX_VIA_LDS": "0"}, {"CGX_QUANTIZE_GROUPS": "2"},
                 {"CGX_REDUCE_GROUPS": "2", "CGX_MAX_BLOCKS": "5"}, {"CGX_REDUCE_GROUPS": "4"}):
         out = subprocess.run([sys.executable, "-c", code], env={**os.environ, **env}, capture_output=True, text=True, timeout=300)
         assert out.returncode == 0, out.stderr[-2000:]
