@@ -20,7 +20,7 @@ extern "C" {
  *     uint32 elements; uint32 info; uint32 pad_bytes }
  * with info = bits | kind << 4 | log2(lanes per bucket) << 8 | (bucket / 32) << 12 (the last
  * two fields are 0 where they do not apply) and kind 0 = generic
- * quantize, 1 = vectorised quantize, 2 = element-wise copy, 3 = vectorised copy,
+ * quantize, 1 = vectorised quantize, 3 = copy (2 is not used),
  * 4 = vectorised quantize of one whole bucket of 4096 or 8192 elements, 5 = the short end
  * of a layer (less than a chunk of 2048 elements) with power-of-two buckets, 6 = whole buckets
  * of a size that is no power of two, at most a chunk in all (the ragged end of such a layer and
@@ -43,9 +43,10 @@ int cgx_plan_tiles(int64_t n, int32_t L, const int64_t *layer_offsets, const uin
  * The same table for kernels whose chunk is chunk_elements (1024 or 2048; CGX_ERR_SIZE otherwise).
  * cgx_plan_tiles gives the table of 2048-element chunks, which the reduce, fused and statistics
  * kernels and the binary16 quantizer walk; cgx_quantize on binary32 input, cgx_requantize and
- * cgx_dequantize to binary32 walk the table of 1024-element chunks, unless a call that quantizes has a
- * bucket of more than 1024 elements (in this table buckets of 2048 are one-bucket tiles of kind 4, like those
- * of 4096 and 8192).
+ * cgx_dequantize to binary32 walk the table of 1024-element chunks, but a call that quantizes takes 2048 where a
+ * bucket has more than 1024 elements, or where chunks of 1024 would spend a quarter more lanes on the plan's bucket
+ * sizes (352, 384, 544 ... 672 and 768).  (In the table of 1024-element chunks buckets of 2048 are one-bucket
+ * tiles of kind 4, like those of 4096 and 8192.)
  */
 int cgx_plan_tiles_chunk(int64_t n, int32_t L, const int64_t *layer_offsets, const uint8_t *bits_per_layer,
                          int32_t bucket, cgx_dtype dt, int32_t chunk_elements, void *tiles_out /* host */,
@@ -121,17 +122,21 @@ int cgx_issue_probe(int32_t form, int32_t blocks, int32_t iterations, void *out,
  * CGX_CHUNKS_PER_TILE regroups the binary64 additions of the per-layer errors:
  *   CGX_CHUNKS_PER_TILE=k   every vectorised tile holds up to k chunks (default: chosen per call)
  *   CGX_MAX_BLOCKS=k        persistent grids of at most k blocks (default: one wave per tile)
- *   CGX_QUANTIZE_GROUPS=2|4 chunk size of every quantize call: 1024 or 2048 elements (default:
- *                           1024 for binary32 input, 2048 for binary16)
- *   CGX_VIA_LDS=0           the quantizer reads its chunks straight into registers instead of
- *                           through LDS
+ *   CGX_QUANTIZE_GROUPS=2|4 chunk size of the quantize calls: 1024 or 2048 elements (default: 2048 for
+ *                           binary16; for binary32 1024 but for the sizes named at cgx_plan_tiles_chunk).
+ *                           With 2, buckets of more than 1024 elements keep chunks of 2048; the other
+ *                           layers of such a call, if every layer has its own size, take 1024 on binary32
+ *                           (by default from 100 M elements of them on)
+ *   CGX_VIA_LDS=0           the binary16 quantizer and the error statistic read aligned chunks straight into
+ *                           registers instead of through LDS, the binary32 quantizer through registers
+ *                           into LDS instead of straight into it
  *   CGX_KEEP_SUMS_MB=k      the reduce writes results of up to k MB through at device scope so that
  *                           they stay in the memory-side cache (default 128; 0: always streamed)
  *   CGX_QUANTIZE_TILES_PER_WAVE_X4=k  grid of the binary32 quantizer on plans of up to 2^19 tiles: k/4 tiles per
  *                           wave (default 5: four fifths of the waves that one tile each would take; 4: one
  *                           wave per tile)
- *   CGX_REDUCE_GROUPS=2|4   chunk size of every reduce call with buckets of up to 1024 elements: 1024 or 2048
- *                           elements (default: 2048, and 1024 for cgx_dequantize to binary32)
+ *   CGX_REDUCE_GROUPS=2|4   chunk size of every reduce call: 1024 or 2048 elements (default: 2048, and 1024 for
+ *                           cgx_dequantize to binary32)
  *   CGX_DEQUANTIZE_THROUGH=0  cgx_dequantize runs like a reduce of one chunk (2048-element chunks, the
  *                           reduce's store policy) instead of with 1024-element chunks and stores written
  *                           through at system scope

@@ -3,7 +3,8 @@
 //
 // The kernels: bucketed stochastic quantization of a fused gradient buffer (cgx_quantize.hip),
 // dequantize-and-reduce of W compressed chunks (cgx_reduce.hip), the two fused into one pass
-// (cgx_fused.hip), per-layer statistics and the streaming probe (cgx_stats.hip).
+// (cgx_fused.hip), quantizing and fused kernels for buckets longer than a chunk (cgx_wide.hip), per-layer statistics
+// (cgx_stats.hip) and the measurement probes (cgx_probe.hip).
 //
 // One wavefront (64 lanes) owns one tile of the plan.  In the vectorised path a
 // wave takes a chunk of kChunk elements per pass: each lane holds kGroups groups
@@ -333,13 +334,6 @@ struct Raw8<CGX_F32> {
         a = __builtin_nontemporal_load(p);
         b = __builtin_nontemporal_load(p + 1);
     }
-    // the same with ordinary loads: for data that is read again shortly
-    __device__ __forceinline__ void load_keep(const void *buf, int64_t e)
-    {
-        const float4u *p = reinterpret_cast<const float4u *>(reinterpret_cast<const float *>(buf) + e);
-        a = p[0];
-        b = p[1];
-    }
     __device__ __forceinline__ void widen(float (&x)[8]) const
     {
 #pragma unroll
@@ -355,10 +349,6 @@ struct Raw8<CGX_F16> {
     __device__ __forceinline__ void load(const void *buf, int64_t e)
     {
         h = __builtin_nontemporal_load(reinterpret_cast<const half8u *>(reinterpret_cast<const _Float16 *>(buf) + e));
-    }
-    __device__ __forceinline__ void load_keep(const void *buf, int64_t e)
-    {
-        h = *reinterpret_cast<const half8u *>(reinterpret_cast<const _Float16 *>(buf) + e);
     }
     __device__ __forceinline__ void widen(float (&x)[8]) const
     {

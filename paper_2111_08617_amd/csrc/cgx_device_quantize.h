@@ -465,38 +465,25 @@ __device__ __forceinline__ void quantize_generic(Value value, uint8_t *__restric
 // Pass-through tile of the quantize kernels: verbatim copy, then the layer's zero padding.  WIDTH lanes work on it, this
 // one is number `lane`.
 template <int DT, int WIDTH = kWave>
-__device__ __forceinline__ void copy_tile(const void *__restrict__ grad, uint8_t *__restrict__ packed, const Tile &tile,
-                          bool fast, int lane)
+__device__ __forceinline__ void copy_tile(const void *__restrict__ grad, uint8_t *__restrict__ packed, const Tile &tile, int lane)
 {
     constexpr int S = DT == CGX_F16 ? 2 : 4;
     const uint8_t *src = reinterpret_cast<const uint8_t *>(grad) + tile.elem0 * S;
     uint8_t *dst = packed + tile.packed_off;
     const uint32_t bytes = tile.count * S;
-    uint32_t done = 0;
-    if (fast) {
-        const uint32_t vecs = bytes / 16;
-        // all loads of a tile (kCopyPiece elements) in flight together
-        constexpr int kLoads = kCopyPiece * S / 16 / WIDTH > 0 ? kCopyPiece * S / 16 / WIDTH : 1;
-        for (uint32_t v0 = lane; v0 < vecs; v0 += kLoads * WIDTH) {
-            uint4v raw[kLoads];
+    const uint32_t vecs = bytes / 16;
+    // all loads of a tile (kCopyPiece elements) in flight together
+    constexpr int kLoads = kCopyPiece * S / 16 / WIDTH > 0 ? kCopyPiece * S / 16 / WIDTH : 1;
+    for (uint32_t v0 = lane; v0 < vecs; v0 += kLoads * WIDTH) {
+        uint4v raw[kLoads];
 #pragma unroll
-            for (int u = 0; u < kLoads; u++)
-                if (v0 + u * WIDTH < vecs) raw[u] = reinterpret_cast<const uint4u2 *>(src)[v0 + u * WIDTH];
+        for (int u = 0; u < kLoads; u++)
+            if (v0 + u * WIDTH < vecs) raw[u] = reinterpret_cast<const uint4u2 *>(src)[v0 + u * WIDTH];
 #pragma unroll
-            for (int u = 0; u < kLoads; u++)
-                if (v0 + u * WIDTH < vecs) reinterpret_cast<uint4v *>(dst)[v0 + u * WIDTH] = raw[u];
-        }
-        done = vecs * 16;
-    } else if (DT == CGX_F16) {
-        for (uint32_t e = lane; e < tile.count; e += WIDTH)
-            reinterpret_cast<uint16_t *>(dst)[e] = reinterpret_cast<const uint16_t *>(src)[e];
-        done = bytes;
-    } else {
-        for (uint32_t e = lane; e < tile.count; e += WIDTH)
-            reinterpret_cast<uint32_t *>(dst)[e] = reinterpret_cast<const uint32_t *>(src)[e];
-        done = bytes;
+        for (int u = 0; u < kLoads; u++)
+            if (v0 + u * WIDTH < vecs) reinterpret_cast<uint4v *>(dst)[v0 + u * WIDTH] = raw[u];
     }
-    for (uint32_t k = done + lane; k < bytes + tile.pad; k += WIDTH) dst[k] = k < bytes ? src[k] : uint8_t(0);
+    for (uint32_t k = vecs * 16 + lane; k < bytes + tile.pad; k += WIDTH) dst[k] = k < bytes ? src[k] : uint8_t(0);
 }
 
 }  // namespace

@@ -30,8 +30,8 @@ __device__ __forceinline__ void bytes_to_float(uint32_t t, float &b0, float &b1,
 }
 
 // Levels of one group of 8 codes as floats (kNormSign: signed levels).  Of the signed widths
-// only 4 bits takes the byte-wise form: with 2 and 8 bits as well the reduce kernel needs 129
-// to 131 registers, one wave per SIMD less.
+// only 4 bits takes the byte-wise form: with 2 and 8 bits as well the reduce kernel needed 129
+// to 131 registers, one wave per SIMD less, when it had 127 of them (it has 100 now; not measured again since).
 template <int SCHEME, int BITS>
 __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
 {
@@ -79,7 +79,7 @@ __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
     }
 }
 
-// ---- two conversions per instruction (min/max codes of 2 and 4 bits)
+// ---- two conversions per instruction (min/max codes of 4 bits)
 //
 // A code q <= 15 alone in a byte is also the 8-bit float (E4M3) q / 512: the subnormals and the
 // first binade of that format form one linear grid.  v_cvt_pk_f32_fp8 converts two bytes per
@@ -93,25 +93,15 @@ constexpr float kPairedScale = 512.0f;
 // false: unit * 512 would not be finite (or unit is not) and the codes take the plain conversion
 __device__ __forceinline__ bool paired_usable(float2 m) { return __builtin_fabsf(m.x) < 0x1p118f; }
 
-// Levels / 512 of one group of 8 codes.
-template <int BITS>
-__device__ __forceinline__ void codes_to_scaled_float(uint64_t v, float (&f)[8])
+// Levels / 512 of one group of 8 codes of 4 bits.
+__device__ __forceinline__ void codes_to_scaled_float(uint32_t w, float (&f)[8])
 {
     typedef float float2v __attribute__((ext_vector_type(2)));
-    const uint32_t w = uint32_t(v);
-    if (BITS == 4) {
-        const uint32_t even = w & 0x0f0f0f0fu, odd = (w >> 4) & 0x0f0f0f0fu;
-        const float2v e0 = __builtin_amdgcn_cvt_pk_f32_fp8(even, false), e1 = __builtin_amdgcn_cvt_pk_f32_fp8(even, true);
-        const float2v o0 = __builtin_amdgcn_cvt_pk_f32_fp8(odd, false), o1 = __builtin_amdgcn_cvt_pk_f32_fp8(odd, true);
-        f[0] = e0.x, f[2] = e0.y, f[4] = e1.x, f[6] = e1.y;
-        f[1] = o0.x, f[3] = o0.y, f[5] = o1.x, f[7] = o1.y;
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const float2v p = __builtin_amdgcn_cvt_pk_f32_fp8((w >> (2 * j)) & 0x0303u, false);     // codes j and j + 4
-            f[j] = p.x, f[4 + j] = p.y;
-        }
-    }
+    const uint32_t even = w & 0x0f0f0f0fu, odd = (w >> 4) & 0x0f0f0f0fu;
+    const float2v e0 = __builtin_amdgcn_cvt_pk_f32_fp8(even, false), e1 = __builtin_amdgcn_cvt_pk_f32_fp8(even, true);
+    const float2v o0 = __builtin_amdgcn_cvt_pk_f32_fp8(odd, false), o1 = __builtin_amdgcn_cvt_pk_f32_fp8(odd, true);
+    f[0] = e0.x, f[2] = e0.y, f[4] = e1.x, f[6] = e1.y;
+    f[1] = o0.x, f[3] = o0.y, f[5] = o1.x, f[7] = o1.y;
 }
 
 // The codes of a lane's G groups of a run, group r's 8 in the low 8 * BITS bits of v[r] (bits above are unspecified).
@@ -198,7 +188,7 @@ __device__ __forceinline__ bool reduce_peers(Peers &peers, int w0, int64_t in_of
             else
                 v = staged_codes<BITS>(codes + i * kBytes, code_off[r]);
             if constexpr (PAIRED && kPairedConversion<SCHEME, BITS>)
-                codes_to_scaled_float<BITS>(v, f);
+                codes_to_scaled_float(uint32_t(v), f);
             else
                 codes_to_float<SCHEME, BITS>(v, f);
 #pragma unroll
@@ -374,7 +364,8 @@ __device__ __forceinline__ void reduce_fast(Peers &peers, int W, const SumIo &io
         float acc[G][8];
 #pragma unroll
         for (int r = 0; r < G; r++) init8(io, first + map.group(r), acc[r]);
-        // (the plain conversion: this kernel is bound by memory, and the paired one costs it registers)
+        // (the plain conversion: this kernel is bound by memory; the paired one cost it 4 registers and a wave per SIMD when
+        // it had 127, and has not been measured at its present 100)
         reduce_chunk<SCHEME, BITS>(peers, W, tile.packed_off + int64_t(c) * (kChunk * BITS / 8),
                                    tile.bucket0 + c * buckets_per_chunk + map.bi, map, acc, stage, lane);
         // the results leave through LDS as well, so that every store instruction writes 1 KB of
@@ -529,10 +520,9 @@ __device__ __forceinline__ float copy_sum1(Peers &peers, int W, const Tile &tile
 // Pass-through tile of the reduce kernels: plain ordered sum of the stored values; element j
 // of the tile starts from / goes to position e0 + j of io.  WIDTH lanes work on it, this one is number `lane`.
 template <int DT, int WIDTH = kWave, typename Peers>
-__device__ __forceinline__ void reduce_copy(Peers &peers, int W, const SumIo &io, int64_t e0, const Tile &tile, bool fast,
-                            int lane)
+__device__ __forceinline__ void reduce_copy(Peers &peers, int W, const SumIo &io, int64_t e0, const Tile &tile, int lane)
 {
-    const uint32_t groups = fast ? tile.count / 8 : 0;
+    const uint32_t groups = tile.count / 8;
     for (uint32_t g = lane; g < groups; g += WIDTH) {
         float acc[8];
         init8(io, e0 + int64_t(g) * 8, acc);

@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ 
         const int64_t out_off = tiles_out[t].packed_off;
         const uint32_t out_pad = tiles_out[t].pad;
         const uint32_t kind = tile_kind(tile);
-        if (is_vector_kind(kind)) {
+        if (kind == kQuantFast) {
             CGX_FOR_BITS(tile_bits(tile), (fused_fast<SCHEME, BITS, ODD>(peers, W, tile, out_off, bucket, seed_lo,
                                                                      seed_hi, packed_out, meta_out, lane, stage)))
         } else if (is_quantized_kind(kind) && tile.count <= uint32_t(kChunk) && one_key_block(tile)) {
@@ -91,9 +91,9 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ 
             // pass-through: the sum is written as binary32 into the output stream, then its padding
             const SumIo io{nullptr, CGX_F32, packed_out + out_off, CGX_F32, 0};
             if (dt == CGX_F16)
-                reduce_copy<CGX_F16>(peers, W, io, 0, tile, kind == kCopyFast, lane);
+                reduce_copy<CGX_F16>(peers, W, io, 0, tile, lane);
             else
-                reduce_copy<CGX_F32>(peers, W, io, 0, tile, kind == kCopyFast, lane);
+                reduce_copy<CGX_F32>(peers, W, io, 0, tile, lane);
             uint8_t *end = packed_out + out_off + uint64_t(tile.count) * 4;
             if (uint32_t(lane) < out_pad) end[lane] = 0;
         }

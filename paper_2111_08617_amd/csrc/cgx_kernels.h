@@ -1,5 +1,5 @@
-// Launchers of the gfx950 kernels (implemented in cgx_quantize.hip, cgx_reduce.hip, cgx_fused.hip
-// and cgx_stats.hip).
+// Launchers of the gfx950 kernels (implemented in cgx_quantize.hip, cgx_reduce.hip, cgx_fused.hip, cgx_wide.hip,
+// cgx_stats.hip and cgx_probe.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>

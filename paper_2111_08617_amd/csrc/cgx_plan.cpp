@@ -156,11 +156,11 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
                 t.packed_off = int64_t(seg + uint64_t(j) * b / 8);
                 t.bucket0 = uint32_t(bucket0 + uint64_t(j) / own_bucket);
                 t.count = uint32_t(len - j < step ? len - j : step);
-                // the short end of a layer with power-of-two buckets runs through the chunk code, masked
+                // the short end of a layer with power-of-two buckets
                 const bool tail = fast_bucket && j % kChunk == 0 && t.count < uint32_t(kChunk) &&
                                   same_key_block(t.elem0, t.count);
-                // whole buckets of a size that is no power of two, a chunk or less in all: the streamed path
-                // for any bucket size (the ragged end of a layer stays on the generic one)
+                // whole buckets of a size that is no power of two, a chunk or less in all: part of the bulk of a plan.  (Like
+                // short and ragged ends they run as runs, in lane order; the kinds only tell which tiles go first.)
                 const bool any = !tail && !is_pow2(own_bucket) && own_bucket <= kChunk && t.count % uint32_t(own_bucket) == 0 &&
                                  t.count <= uint32_t(kChunk) && same_key_block(t.elem0, t.count);
                 t.info = uint32_t(b) | uint32_t(tail ? kQuantTail : any ? kQuantAny : kQuantSlow) << 4 |
@@ -172,9 +172,8 @@ void build_tiles(int32_t L, const int64_t *off, const uint8_t *bits, int32_t buc
         seg += round_up16(payload);
         bucket0 += buckets;
     }
-    // Waves take tiles in table order.  The generic and pass-through tiles cost several
-    // dependent memory round trips each, so they go first and overlap with the stream
-    // of vectorised tiles instead of forming the tail of the launch.
+    // Waves take tiles in table order.  Short ends, ragged ends and pass-through tiles take as long as a whole chunk or
+    // longer, so they go first and overlap with the stream of vectorised tiles instead of forming the tail of the launch.
     if (layer_first) (*layer_first)[size_t(L)] = int64_t(tiles.size());
     std::vector<uint32_t> order(tiles.size());
     for (size_t i = 0; i < order.size(); i++) order[i] = uint32_t(i);

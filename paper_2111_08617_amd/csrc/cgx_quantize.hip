@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict
         if (t + stride < n_tiles) upcoming = tiles[t + stride];
         const int bucket = tile_bucket(tile);       // per tile: a launch may mix sizes of one lane mapping
         const uint32_t kind = tile_kind(tile);
-        if (is_vector_kind(kind)) {
+        if (kind == kQuantFast) {
             if constexpr (MAP == kMapRows) {
                 CGX_FOR_BITS(tile_bits(tile), (quantize_fast_rows<SCHEME, DT, BITS, ODD>(grad, packed, meta, tile, bucket,
                                                                                       seed_lo, seed_hi, lane, stage)))
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict
                                            packed + tile.packed_off, meta, tile, tile.pad, bucket, seed_lo,
                                            seed_hi, lane);
         } else {
-            copy_tile<DT>(grad, packed, tile, kind == kCopyFast, lane);
+            copy_tile<DT>(grad, packed, tile, lane);
         }
     }
 }

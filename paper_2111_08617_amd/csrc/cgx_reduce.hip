@@ -17,10 +17,12 @@ struct ReduceArguments {
     PeerPtrs peers;
 };
 
-// SINGLE: a decompression (W = 1, no start values) into storage type OUT, bound by the eight bytes it writes per byte
-// it reads.  It needs half of the reduction's registers and LDS, and twice as many waves then keep stores in
-// flight (54 instead of 123 vector registers at 2048-element chunks; 36 instead of 86 at 1024): 8 shares of 355 M elements
-// to binary16 187 -> 166 us, 268 M elements to binary32 211 -> 186 us, 67 M 44 us either way.
+// SINGLE: a decompression (W = 1, no start values) into storage type SINGLE, bound by the eight bytes it writes per byte
+// it reads.  It needs half of the reduction's registers and LDS, and more waves then keep stores in flight (59 instead of 100
+// vector registers at 2048-element chunks, eight waves per SIMD instead of four; 36 instead of 86 at 1024, eight instead of
+// five): 8 shares of 355 M elements to binary16 187 -> 166 us; to binary32, 4 bits, codes from memory, 268 M elements 224 ->
+// 185 us, 67 M 58 -> 49.  (Decompressed again and again from codes that the memory-side cache holds, 162 -> 170 and 43.5 ->
+// 44.5.)
 constexpr int kAnyOut = -1;
 
 template <int SCHEME, int SINGLE>
@@ -62,9 +64,9 @@ __global__ __launch_bounds__(kBlock) void reduce_kernel(const Tile *__restrict__
         } else if (is_quantized_kind(kind)) {
             CGX_FOR_BITS(tile_bits(tile), (reduce_run_tile<SCHEME, BITS>(peers_in_memory, W, io, tile, bucket, lane, stage)))
         } else if (dt == CGX_F16) {
-            reduce_copy<CGX_F16>(peers_in_memory, W, io, tile.elem0, tile, kind == kCopyFast, lane);
+            reduce_copy<CGX_F16>(peers_in_memory, W, io, tile.elem0, tile, lane);
         } else {
-            reduce_copy<CGX_F32>(peers_in_memory, W, io, tile.elem0, tile, kind == kCopyFast, lane);
+            reduce_copy<CGX_F32>(peers_in_memory, W, io, tile.elem0, tile, lane);
         }
     }
 }

@@ -59,7 +59,7 @@ __device__ __forceinline__ double square(float x)
 // elements), formed by the kNormWaves waves of a block: each wave takes kCopyTile / kNormWaves
 // elements (4 KB of binary32: the slice size at which a wave that only reads runs closest to the
 // memory's peak; eight times that per wave reached 0.78 of it).
-// Elements that no 16-byte load may fetch (a tile off the vector grid, or its last few) go to
+// Elements that no 16-byte load may fetch (a tile's last few) go to
 // wave 0, one per lane and pass.
 constexpr int kNormWaves = 8;
 constexpr int kNormBlock = kNormWaves * kWave;
@@ -82,14 +82,14 @@ __device__ __forceinline__ double square_sum16(const uint4v &v)
 }
 
 template <int DT>
-__device__ __forceinline__ double sqnorm_share(const void *__restrict__ buf, const Tile &tile, bool fast, int wave, int lane)
+__device__ __forceinline__ double sqnorm_share(const void *__restrict__ buf, const Tile &tile, int wave, int lane)
 {
     // which lane squares which element does not matter to the sum: every load instruction takes 1 KB of
     // consecutive addresses, 16 bytes per lane
     constexpr uint32_t kPerVec = DT == CGX_F16 ? 8 : 4;
     constexpr int kLoads = kCopyTile / kNormWaves / kPerVec / kWave;       // per lane: 4 (binary32) or 2
     double s = 0.0;
-    const uint32_t vecs = fast ? tile.count / kPerVec : 0;
+    const uint32_t vecs = tile.count / kPerVec;
     const uint32_t v0 = uint32_t(wave) * (kLoads * kWave);
     if (v0 < vecs) {
         // aligned like an element, not like a vector: a layer may start anywhere
@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kNormBlock) void sqnorm_kernel(const void *__restri
     const int lane = int(threadIdx.x) & 63;
     for (int64_t t = blockIdx.x; t < n_tiles; t += gridDim.x) {
         const Tile tile = tiles[t];
-        const double s = wave_sum(sqnorm_share<DT>(buf, tile, tile_kind(tile) == kCopyFast, wave, lane));
+        const double s = wave_sum(sqnorm_share<DT>(buf, tile, wave, lane));
         if (lane == 0) sums[wave] = s;
         __syncthreads();
         if (threadIdx.x == 0) {

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(WAVES * kWave) void quantize_wide_kernel(const void
                 quantize_generic<SCHEME, true>([&](uint32_t j) { return load_elem<DT>(grad, tile.elem0 + j); },
                                                packed + tile.packed_off, meta, tile, tile.pad, bucket, seed_lo, seed_hi, lane);
         } else {
-            copy_tile<DT, WAVES * kWave>(grad, packed, tile, true, int(threadIdx.x));
+            copy_tile<DT, WAVES * kWave>(grad, packed, tile, int(threadIdx.x));
         }
     }
 }
@@ -137,9 +137,9 @@ __global__ __launch_bounds__(WAVES * kWave, 4) void fused_wide_kernel(const Tile
             // pass-through: the sum is written as binary32 into the output stream, then its padding
             const SumIo io{nullptr, CGX_F32, packed_out + out_off, CGX_F32, 0};
             if (dt == CGX_F16)
-                reduce_copy<CGX_F16, WAVES * kWave>(peers, W, io, 0, tile, true, int(threadIdx.x));
+                reduce_copy<CGX_F16, WAVES * kWave>(peers, W, io, 0, tile, int(threadIdx.x));
             else
-                reduce_copy<CGX_F32, WAVES * kWave>(peers, W, io, 0, tile, true, int(threadIdx.x));
+                reduce_copy<CGX_F32, WAVES * kWave>(peers, W, io, 0, tile, int(threadIdx.x));
             uint8_t *end = packed_out + out_off + uint64_t(tile.count) * 4;
             if (threadIdx.x < out_pad) end[threadIdx.x] = 0;
         }

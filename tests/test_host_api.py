@@ -470,14 +470,25 @@ def test_binding_refuses_buffers_the_kernels_would_overrun(lib, monkeypatch):
         cgx.cgx_qsgd_quantize(Fake(5000), plan, 1, Fake(qp, torch.uint8), Fake(qm // 4 - 1), stream=0)
 
 
-def test_group_to_bucket_lookup_by_multiply_and_shift_is_exact():
-    """The kernels that stream buckets of a size that is no power of two find the bucket of group G of a tile
-    as (G * ceil(2^16 / gb)) >> 16, gb = groups of 8 elements per bucket: equal to G // gb for every group of a
-    chunk (G < 256) and every bucket size up to the chunk (gb <= 256)."""
-    G = np.arange(256, dtype=np.uint64)
-    for gb in range(1, 257):
-        inv = (65536 + gb - 1) // gb
-        assert np.array_equal((G * np.uint64(inv)) >> np.uint64(16), G // np.uint64(gb)), gb
+def test_lane_to_bucket_lookup_by_reciprocal_is_exact():
+    """A run finds the bucket of a lane as int((lane + 0.5) * (1 / lanes)) in binary32, lanes per bucket rounded up, with a
+    reciprocal that may be off by a unit in the last place: exact for every bucket size, for 2, 3 and 4 groups of 8 elements
+    per lane, for every lane, and for the last lane with elements.  With 3 groups a run has a size that 24 divides, or
+    lies in one bucket."""
+    lane = np.arange(64, dtype=np.float32) + np.float32(0.5)
+    for bucket in range(32, 8193, 32):
+        for own in (2, 3, 4):
+            per_lane = 8 * own
+            lanes = -(-bucket // per_lane)
+            exact = np.float32(1.0) / np.float32(lanes)
+            whole = bucket % per_lane == 0
+            for inv in (np.nextafter(exact, np.float32(0)), exact, np.nextafter(exact, np.float32(2))):
+                found = (lane * inv).astype(np.float32).astype(np.int64)
+                if whole:
+                    assert np.array_equal(found, np.arange(64) * per_lane // bucket), (bucket, own)
+                else:
+                    # one bucket: every lane that holds some of its elements finds bucket 0
+                    assert own == 3 and (found[:min(lanes, 64)] == 0).all(), (bucket, own)
 
 
 def test_copies_of_a_plan_point_at_their_own_arrays():
