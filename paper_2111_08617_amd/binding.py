@@ -166,14 +166,23 @@ class _HostPlan:
     #: attribute -> element type the C calls read
     _ARRAYS = {}
     #: attributes formed from the others: the arguments of the C calls, sizes of streams (_sizes_of)
-    _DERIVED = ("args", "_sizes")
+    _DERIVED = ("args", "_args_arrays", "_sizes")
 
     def __setattr__(self, name, value):
+        if name == "args":
+            raise AttributeError("args follows from the plan's arrays")
         if name in self._ARRAYS:
             value = np.ascontiguousarray(value, dtype=self._ARRAYS[name])
-        self.__dict__[name] = value
+        super().__setattr__(name, value)
         if name == "offsets" and value.ndim == 1 and value.size:
             self.__dict__["n"], self.__dict__["L"] = int(value[-1]), int(value.size) - 1
+        self._drop_derived()
+
+    def __delattr__(self, name):
+        super().__delattr__(name)
+        self._drop_derived()
+
+    def _drop_derived(self):
         for derived in self._DERIVED:
             self.__dict__.pop(derived, None)
 
@@ -192,6 +201,7 @@ class _HostPlan:
     def args(self):
         if any(getattr(self, name).size != self.L + (name == "offsets") for name in self._ARRAYS):
             raise ValueError("the arrays of a plan must fit its layer count: an entry per layer, one more layer offset")
+        self.__dict__["_args_arrays"] = [getattr(self, name) for name in self._ARRAYS]      # alive as long as their addresses
         sizes = self.buckets.ctypes.data if "buckets" in self._ARRAYS else self.bucket
         return self.n, self.L, self.offsets.ctypes.data, self.bits.ctypes.data, sizes
 

@@ -616,3 +616,27 @@ def test_the_library_is_built_where_the_extension_module_is_not(monkeypatch, tmp
         assert cgx_build.build() == str(tmp_path / "LIB")
     assert "-shared" in commands[-1] and str(tmp_path / "LIB") in commands[-1]
     assert not (tmp_path / "ARGS").exists()
+
+
+def test_attributes_of_a_plan_follow_the_usual_rules(lib):
+    """Arguments derived from a plan's attributes are dropped with any of them; they cannot be assigned, a deleted array is
+    missed and not read from where it was, and a subclass's own properties work."""
+    class Named(cgx.Plan):
+        @property
+        def label(self): return self._label
+        @label.setter
+        def label(self, value): self._label = "plan " + value
+
+    plan = Named([0, 100, 300], [4, 2], 128)
+    plan.label = "a"
+    assert plan.label == "plan a" and plan.args[:2] == (300, 2)
+    with pytest.raises(AttributeError):
+        plan.args = (1, 2)
+    cgx.cgx_sizes(plan)
+    del plan.bits
+    with pytest.raises(AttributeError):
+        plan.args
+    with pytest.raises(AttributeError):
+        cgx.cgx_sizes(plan)
+    plan.bits = [8, 8]
+    assert cgx.cgx_sizes(plan) == cgx.cgx_sizes(cgx.Plan([0, 100, 300], [8, 8], 128))
