@@ -137,7 +137,7 @@ enum CallKind { kQuantizeCall, kFusedCall, kOtherCall };
 // A chunk takes whole buckets, and lanes without elements cost as much as the others.  Where chunks of 1024 elements spend
 // at least a quarter more lanes than those of 2048 (352, 384, 544 ... 672 and 768 of the multiples of 32), binary32 takes the
 // longer ones.  Measured, 1024 against 2048, us: 67 M elements in buckets of 672 72.6 and 51.2, 384 62.8 and 52.3, 768 63.8
-// and 50.7; 8.4 M 11.4 and 10.6, 10.3 and 10.6, 10.3 and 9.5.  At an eighth or less the longer ones lose on short buffers:
+// and 50.7; 8.4 M 11.4 and 10.6, 10.3 and 10.6, 10.3 and 9.5.  Where they save less, the longer ones lose on short buffers:
 // buckets of 288 (1.17) 60.6 and 53.2 on 67 M elements, 10.0 and 10.6 on 8.4 M; 224 (1.12) 57.8 and 52.7, 9.6 and 10.7.
 
 // Lanes' worth of elements that the quantizer of `chunk` spends per element of buckets of a size (at most the chunk).
@@ -244,8 +244,7 @@ PlanRef cached_plan(const PlanKey &k, int device, bool capturing)
 {
     for (const auto &p : g_plans) {
         if (p->digest == k.digest && p->device == device && p->bucket == k.bucket && p->dt == k.dt && p->kind == k.kind &&
-            p->bits.size() == size_t(k.L) &&
-            p->layer_buckets.size() == (k.layer_buckets ? size_t(k.L) : 0) &&
+            p->bits.size() == size_t(k.L) && p->layer_buckets.size() == (k.layer_buckets ? size_t(k.L) : 0) &&
             (!k.layer_buckets || k.L == 0 ||
              std::memcmp(p->layer_buckets.data(), k.layer_buckets, sizeof(int32_t) * size_t(k.L)) == 0) &&
             std::memcmp(p->bits.data(), k.bits, size_t(k.L)) == 0 &&
@@ -336,16 +335,13 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
         return CGX_ERR_HIP;
     }
     plan->reduce = cgx::ReduceTiles{plan->d_tiles, narrow + wide * pieces, uint32_t(narrow), uint32_t(pieces)};
-    for (const int type : {CGX_F32, CGX_F16}) {
-        const int64_t in_64 = type == CGX_F16 ? 32 : 16, in_16 = in_64 / 4;
-        int64_t off_64 = 0, off_16 = 0;
-        for (const Tile &t : table.tiles) {
-            off_64 += t.elem0 % in_64 != 0 ? t.count : 0;
-            off_16 += t.elem0 % in_16 != 0 ? t.count : 0;
-        }
-        plan->reduce.off_64_bytes[type] = 2 * off_64 > off[L];
-        plan->reduce.off_16_bytes[type] = 2 * off_16 > off[L];
-    }
+    int64_t off_grid[4] = {0, 0, 0, 0};               // elements in tiles that start off 4, 8, 16, 32 elements
+    for (const Tile &t : table.tiles)
+        for (int k = 0; k < 4; k++) off_grid[k] += (t.elem0 & ((4 << k) - 1)) != 0 ? t.count : 0;
+    plan->reduce.off_16_bytes[CGX_F32] = 2 * off_grid[0] > off[L];
+    plan->reduce.off_16_bytes[CGX_F16] = 2 * off_grid[1] > off[L];
+    plan->reduce.off_64_bytes[CGX_F32] = 2 * off_grid[2] > off[L];
+    plan->reduce.off_64_bytes[CGX_F16] = 2 * off_grid[3] > off[L];
     plan->parts = std::move(table.parts);
     plan->last_use = ++g_clock;
     if (g_plans.size() >= kMaxPlans) {
@@ -459,8 +455,8 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
         } else if (rc == CGX_OK && built && chunk != cgx::kDefaultChunk &&
                    (buckets.per_layer || buckets.uniform > chunk ||
                     (dt == CGX_F32 && quantize_chunks(dt, buckets, L, off, bits).chunk != chunk))) {
-            PlanRef others;
-            rc = get_plan(queue, L, off, bits, buckets, dt, {cgx::kDefaultChunk, per_tile}, &others);
+            PlanRef others;                           // (this call does without it)
+            if (get_plan(queue, L, off, bits, buckets, dt, {cgx::kDefaultChunk, per_tile}, &others) != CGX_OK) (void)hipGetLastError();
         }
         if (rc != CGX_OK) return rc;
     }
