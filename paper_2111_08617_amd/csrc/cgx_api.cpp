@@ -184,6 +184,8 @@ Chunks quantize_chunks(int dt, const Buckets &buckets, int32_t L, const int64_t 
     return {dt == CGX_F32 && !fills_longer ? shorter : longer, 0};
 }
 
+int draws_of(const cgx::TablePart &part) { return part.odd ? cgx::kDrawsOdd : part.quads ? cgx::kDrawsQuad : cgx::kDrawsEven; }
+
 int tile_length(CallKind call, int dt, int64_t n)
 {
     const int forced = launch_config().chunks_per_tile;
@@ -403,9 +405,9 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
         const Tile *tiles = plan->d_tiles + part.first;
         const hipError_t e =
             cgx::mapping_of(part.bucket, part.chunk) == cgx::kMapWide
-                ? cgx::launch_quantize_wide(scheme, grad, dt, tiles, part.count, part.odd, part.longest, seed, packed, meta,
+                ? cgx::launch_quantize_wide(scheme, grad, dt, tiles, part.count, draws_of(part), part.longest, seed, packed, meta,
                                             launch_config(), queue)
-                : launch_quantize(scheme, grad, dt, tiles, part.count, part.odd, part.aligned, part.bucket, seed, packed, meta,
+                : launch_quantize(scheme, grad, dt, tiles, part.count, draws_of(part), part.aligned, part.bucket, seed, packed, meta,
                                   launch_config(), queue);
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
@@ -530,9 +532,9 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
         const Tile *tiles_in = in->d_tiles + part.first, *tiles_out = out->d_tiles + part.first;
         const hipError_t e =
             cgx::mapping_of(part.bucket, part.chunk) == cgx::kMapWide
-                ? cgx::launch_dequant_reduce_requantize_wide(scheme, peers, W, dt, tiles_in, tiles_out, part.count, part.odd,
+                ? cgx::launch_dequant_reduce_requantize_wide(scheme, peers, W, dt, tiles_in, tiles_out, part.count, draws_of(part),
                                                              part.longest, seed, packed_out, meta_out, launch_config(), queue)
-                : cgx::launch_dequant_reduce_requantize(scheme, peers, W, dt, tiles_in, tiles_out, part.count, part.odd, seed,
+                : cgx::launch_dequant_reduce_requantize(scheme, peers, W, dt, tiles_in, tiles_out, part.count, draws_of(part), seed,
                                                         packed_out, meta_out, launch_config(), queue);
         if (e != hipSuccess) return CGX_ERR_HIP;
     }

@@ -93,15 +93,16 @@ typedef uint4v uint4u4 __attribute__((aligned(4)));
 
 // 32-bit avalanche finalizer (xor-shift 16, odd multiply, xor-shift 15, odd
 // multiply, xor-shift 16).
-__device__ __forceinline__ uint32_t mix32(uint32_t x)
+__device__ __forceinline__ uint32_t mix32_head(uint32_t x) { return x ^ (x >> 16); }
+__device__ __forceinline__ uint32_t mix32_tail(uint32_t x)
 {
-    x ^= x >> 16;
     x *= 0x7feb352dU;
     x ^= x >> 15;
     x *= 0x846ca68bU;
     x ^= x >> 16;
     return x;
 }
+__device__ __forceinline__ uint32_t mix32(uint32_t x) { return mix32_tail(mix32_head(x)); }
 
 // Key of a 2^32-pair block: folds the seed and the upper half of the pair index.
 __device__ __forceinline__ uint32_t rng_key(uint32_t seed_lo, uint32_t seed_hi, uint32_t pair_hi)
@@ -255,20 +256,32 @@ __device__ __forceinline__ Scale bucket_scale(float mn, float mx, int levels)
     return Scale{unit, mn, inv16};
 }
 
-// bits is the code width (only kNormSign uses it, to cut the two's complement code).
+// Position of x above the minimum (kNormSign: of its magnitude above 0), in 1/65536 of a level, truncated.
 template <int SCHEME>
-__device__ __forceinline__ uint32_t code_of(float x, const Scale &s, uint32_t draw, uint32_t levels, int bits)
+__device__ __forceinline__ uint32_t position_of(float x, const Scale &s)
 {
     const float d = SCHEME == kNormSign ? __builtin_fabsf(x) : __fsub_rn(x, s.mn);
-    const float S = __fmul_rn(d, s.inv16);
-    const uint32_t T = uint32_t(S);                 // v_cvt_u32_f32: truncates, saturates
-    const uint32_t q = (T + draw) >> 16;
+    return uint32_t(__fmul_rn(d, s.inv16));         // v_cvt_u32_f32: truncates, saturates
+}
+
+// The code of x from the sum of its position and its draw.
+// bits is the code width (only kNormSign uses it, to cut the two's complement code).
+template <int SCHEME>
+__device__ __forceinline__ uint32_t code_of_sum(float x, uint32_t sum, uint32_t levels, int bits)
+{
+    const uint32_t q = sum >> 16;
     const uint32_t level = q < levels ? q : levels;
     if (SCHEME == kNormSign) {
         const uint32_t neg = uint32_t(__builtin_bit_cast(int32_t, x) >> 31);    // all ones for a set sign bit
         return ((level ^ neg) - neg) & ((1u << bits) - 1u);
     }
     return level;
+}
+
+template <int SCHEME>
+__device__ __forceinline__ uint32_t code_of(float x, const Scale &s, uint32_t draw, uint32_t levels, int bits)
+{
+    return code_of_sum<SCHEME>(x, position_of<SCHEME>(x, s) + draw, levels, bits);
 }
 
 template <int SCHEME>

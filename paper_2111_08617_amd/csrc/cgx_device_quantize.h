@@ -9,31 +9,90 @@ namespace {
 
 // ---------------------------------------------------------------- quantize
 
-// The 8 codes of one group, packed: element j of the group has buffer index
-// 2 * pair0 + odd + j, key = generator key of the tile.  odd (0 or 1, uniform over a tile: groups
-// start 8 elements apart) tells whether the group starts on the upper half of a generator word;
-// then its 8 draws are the 16-bit halves 1..8 of words pair0 .. pair0 + 4 instead of halves
-// 0..7 of words pair0 .. pair0 + 3.  ODD = false: the plan has no such tile (odd == 0 always),
-// and neither the fifth word nor the selection is paid; the host picks the instantiation.
-template <int SCHEME, int BITS, bool ODD>
+// Bytes 2 of a and b (levels above 16 bits of fraction) in bytes 0 and 1, or 2 and 3, of a word of zeros.
+__device__ __forceinline__ uint32_t levels_low(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x0c0c0602u); }
+__device__ __forceinline__ uint32_t levels_high(uint32_t a, uint32_t b) { return __builtin_amdgcn_perm(b, a, 0x06020c0cu); }
+// The same positions, with all bits set where the sign bit of a, b is.
+__device__ __forceinline__ uint32_t signs_low(float a, float b)
+{
+    return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, b), __builtin_bit_cast(uint32_t, a), 0x0c0c0b09u);
+}
+__device__ __forceinline__ uint32_t signs_high(float a, float b)
+{
+    return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, b), __builtin_bit_cast(uint32_t, a), 0x0b090c0cu);
+}
+
+// Codes of BITS bits, one per byte, from levels and sign masks, one per byte.  (level ^ sign) + (sign & 1) within
+// BITS bits: no carry leaves a byte.
+template <int BITS>
+__device__ __forceinline__ uint32_t signed_bytes(uint32_t level, uint32_t sign)
+{
+    constexpr uint32_t kOnes = 0x01010101u, kMask = kOnes * ((1u << BITS) - 1u);
+    return ((level ^ (sign & kMask)) + (sign & kOnes)) & kMask;
+}
+
+// How 2- and 4-bit codes are cut: the levels are gathered byte by byte from the sums of position and draw, two per
+// v_perm_b32, and shifted into place for four codes at once: 7 instructions per 8 codes where a minimum and a shift-or per code
+// are 16 (kNormSign: 21 where cutting the code is 56).  The minimum falls away: up to 7 bits no position exceeds levels * 65536,
+// since x - mn rounds to at most the range and inv16 to at most (1 + 2^-24) of its value, so their product is below
+// levels * 65536 + 1/2 before it is rounded, and that whole number is one that binary32 holds.  (With a NaN in the bucket, whose
+// values are unspecified, a code may run into its neighbours; they are of the same group.)
+//
+// Measured with the draws of kDrawsQuad below, builds in turn on one box, us: binary16 quantize of 355 M elements 156.7 -> 144.9;
+// 25.6 M binary32 elements 20.1 -> 19.9, the fused step of a 13.7 M share of 8 peers 20.2 -> 19.5, norm-and-sign reduce and
+// requantize of it 33.9 -> 32.9.  1.3 G binary32 elements are bound by memory alone and stay at 988.
+
+// The 8 codes of one group, packed: element j of the group has buffer index 2 * pair0 + odd + j, key = generator key of
+// the tile.  odd (0 or 1, uniform over a tile: groups start 8 elements apart) tells whether the group starts on the upper
+// half of a generator word; then its 8 draws are the 16-bit halves 1..8 of words pair0 .. pair0 + 4 instead of halves
+// 0..7 of words pair0 .. pair0 + 3.  DRAWS (Draws, cgx_kernels.h; the host picks the instantiation): kDrawsOdd alone pays for
+// the fifth word and the selection, and kDrawsQuad knows that pair0 is a multiple of 4: no carry leaves its two lowest bits,
+// so the words of its four pairs differ in them alone until the first multiplication.
+template <int SCHEME, int BITS, int DRAWS>
 __device__ __forceinline__ uint64_t encode_group(const float (&x)[8], const Scale &s, uint32_t pair0, uint32_t key,
-                                                 uint32_t odd)
+                                                 uint32_t odd_start)
 {
     constexpr uint32_t kLevels = top_level<SCHEME>(BITS);
     uint32_t word[5];
+    if (DRAWS == kDrawsQuad) {
+        const uint32_t mixed = mix32_head(pair0 ^ key);
 #pragma unroll
-    for (int k = 0; k < 4 + int(ODD); k++) word[k] = mix32((pair0 + k) ^ key);
-    uint64_t acc = 0;
+        for (int k = 0; k < 4; k++) word[k] = mix32_tail(mixed ^ uint32_t(k));
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4 + int(DRAWS == kDrawsOdd); k++) word[k] = mix32((pair0 + k) ^ key);
+    }
+    uint32_t sum[8];                                 // position of the element between the levels, plus its draw
 #pragma unroll
     for (int k = 0; k < 4; k++) {
         // the pair's two draws
-        const uint32_t w = ODD ? __builtin_amdgcn_alignbit(word[k + 1], word[k], 16u * odd) : word[k];
-        const uint64_t q0 = code_of<SCHEME>(x[2 * k], s, w & 0xffffU, kLevels, BITS);
-        const uint64_t q1 = code_of<SCHEME>(x[2 * k + 1], s, w >> 16, kLevels, BITS);
-        acc |= q0 << (2 * k * BITS);
-        acc |= q1 << ((2 * k + 1) * BITS);
+        const uint32_t w = DRAWS == kDrawsOdd ? __builtin_amdgcn_alignbit(word[k + 1], word[k], 16u * odd_start) : word[k];
+        sum[2 * k] = position_of<SCHEME>(x[2 * k], s) + (w & 0xffffU);
+        sum[2 * k + 1] = position_of<SCHEME>(x[2 * k + 1], s) + (w >> 16);
     }
-    return acc;
+    if constexpr (BITS == 4) {
+        uint32_t even = levels_low(sum[0], sum[2]) | levels_high(sum[4], sum[6]);
+        uint32_t odd = levels_low(sum[1], sum[3]) | levels_high(sum[5], sum[7]);
+        if (SCHEME == kNormSign) {
+            even = signed_bytes<4>(even, signs_low(x[0], x[2]) | signs_high(x[4], x[6]));
+            odd = signed_bytes<4>(odd, signs_low(x[1], x[3]) | signs_high(x[5], x[7]));
+        }
+        return even | (odd << 4);
+    } else if constexpr (BITS == 2) {
+        uint32_t low = levels_low(sum[0], sum[4]) | levels_high(sum[1], sum[5]);       // codes 0, 4, 1, 5
+        uint32_t high = levels_low(sum[2], sum[6]) | levels_high(sum[3], sum[7]);      // codes 2, 6, 3, 7
+        if (SCHEME == kNormSign) {
+            low = signed_bytes<2>(low, signs_low(x[0], x[4]) | signs_high(x[1], x[5]));
+            high = signed_bytes<2>(high, signs_low(x[2], x[6]) | signs_high(x[3], x[7]));
+        }
+        const uint32_t t = low | (high << 4);
+        return (t | (t >> 14)) & 0xffffu;
+    } else {
+        uint64_t acc = 0;
+#pragma unroll
+        for (int j = 0; j < 8; j++) acc |= uint64_t(code_of_sum<SCHEME>(x[j], sum[j], kLevels, BITS)) << (j * BITS);
+        return acc;
+    }
 }
 
 // Minimum and maximum (kNormSign: +0 and the largest magnitude) of a lane's chunk, folded into mn / mx.
@@ -54,7 +113,7 @@ __device__ __forceinline__ void lane_extent(const float (&x)[OWN][8], float &mn,
 }
 
 // Codes of a chunk whose elements all take the scale s: staged, then sent out.
-template <int SCHEME, int BITS, bool ODD>
+template <int SCHEME, int BITS, int DRAWS>
 __device__ __forceinline__ void encode_chunk(const float (&x)[G][8], const Scale &s, const LaneMap &map,
                                              int64_t first, uint32_t key, uint8_t *__restrict__ out,
                                              uint4v *stage, int lane)
@@ -63,7 +122,7 @@ __device__ __forceinline__ void encode_chunk(const float (&x)[G][8], const Scale
     for (int r = 0; r < G; r++) {
         const uint32_t pair0 = uint32_t(uint64_t(first + map.group(r)) >> 1);
         stage_codes<BITS>(reinterpret_cast<uint8_t *>(stage) + (map.group(r) >> 3) * BITS,
-                          encode_group<SCHEME, BITS, ODD>(x[r], s, pair0, key, uint32_t(first) & 1u));
+                          encode_group<SCHEME, BITS, DRAWS>(x[r], s, pair0, key, uint32_t(first) & 1u));
     }
     // the chunk's codes leave as whole 16-byte vectors, consecutive across lanes
     wave_lds_fence();
@@ -74,7 +133,7 @@ __device__ __forceinline__ void encode_chunk(const float (&x)[G][8], const Scale
 // One chunk held in registers (x) -> meta of its buckets and its packed codes.
 // first = buffer index of the chunk's first element; key = generator key of the tile.
 // meta_chunk points at the meta of the chunk's first bucket.
-template <int SCHEME, int BITS, bool ODD>
+template <int SCHEME, int BITS, int DRAWS>
 __device__ __forceinline__ void quantize_chunk(const float (&x)[G][8], const LaneMap &map, int lane, int64_t first,
                                                uint32_t key, float *__restrict__ meta_chunk,
                                                uint8_t *__restrict__ out, uint4v *stage)
@@ -88,7 +147,7 @@ __device__ __forceinline__ void quantize_chunk(const float (&x)[G][8], const Lan
         group_minmax(mn, mx, map.lg, lane);
     const Scale s = bucket_scale(mn, mx, int(kLevels));
     if (map.lp == 0) store_meta<SCHEME>(meta_chunk, map.bi, s);
-    encode_chunk<SCHEME, BITS, ODD>(x, s, map, first, key, out, stage, lane);
+    encode_chunk<SCHEME, BITS, DRAWS>(x, s, map, first, key, out, stage, lane);
 }
 
 // The same for buckets of 32 or 64 elements, with the chunk held row by row: group r of lane l
@@ -98,7 +157,7 @@ __device__ __forceinline__ void quantize_chunk(const float (&x)[G][8], const Lan
 // 16 to 64 bytes of each: measured 21 % of the HBM peak at 32-element buckets).  A bucket is
 // bucket / 8 neighbouring lanes of one row; a lane serves four buckets and pays the two
 // divisions four times.
-template <int SCHEME, int BITS, bool ODD>
+template <int SCHEME, int BITS, int DRAWS>
 __device__ __forceinline__ void quantize_chunk_rows(const float (&x)[G][8], int bucket, int lane, int64_t first,
                                                     uint32_t key, float *__restrict__ meta_chunk,
                                                     uint8_t *__restrict__ out, uint4v *stage)
@@ -131,7 +190,7 @@ __device__ __forceinline__ void quantize_chunk_rows(const float (&x)[G][8], int 
         const int e = r * kRow + lane * 8;           // the group's first element within the chunk
         const uint32_t pair0 = uint32_t(uint64_t(first + e) >> 1);
         stage_codes<BITS>(reinterpret_cast<uint8_t *>(stage) + (e >> 3) * BITS,
-                          encode_group<SCHEME, BITS, ODD>(x[r], s, pair0, key, uint32_t(first) & 1u));
+                          encode_group<SCHEME, BITS, DRAWS>(x[r], s, pair0, key, uint32_t(first) & 1u));
     }
     wave_lds_fence();
     flush_stage(stage, reinterpret_cast<uint4v *>(out), kChunk * BITS / 128, lane);
@@ -191,7 +250,7 @@ __device__ __forceinline__ void chunk_through_lds(const void *__restrict__ grad,
 
 // VIA_LDS: every vectorised tile of the plan starts on a 16-byte boundary of the buffer (a property
 // of the tile table; the host picks the instantiation).
-template <int SCHEME, int DT, int BITS, bool ODD, bool VIA_LDS = false>
+template <int SCHEME, int DT, int BITS, int DRAWS, bool VIA_LDS = false>
 __device__ __forceinline__ void quantize_fast(const void *__restrict__ grad, uint8_t *__restrict__ packed,
                                               float *__restrict__ meta, const Tile &tile, int bucket,
                                               uint32_t seed_lo, uint32_t seed_hi, int lane, uint4v *stage)
@@ -209,7 +268,7 @@ __device__ __forceinline__ void quantize_fast(const void *__restrict__ grad, uin
 #pragma unroll
             for (int r = 0; r < G; r++) load8<DT>(grad, first + map.group(r), x[r]);
         }
-        quantize_chunk<SCHEME, BITS, ODD>(x, map, lane, first, key,
+        quantize_chunk<SCHEME, BITS, DRAWS>(x, map, lane, first, key,
                                      meta + kMetaFloats<SCHEME> * (tile.bucket0 + c * buckets_per_chunk),
                                      packed + tile.packed_off + int64_t(c) * (kChunk * BITS / 8), stage);
     }
@@ -222,7 +281,7 @@ struct RowMap {
 };
 
 // quantize_fast for buckets of 32 or 64 elements (row-by-row mapping).
-template <int SCHEME, int DT, int BITS, bool ODD>
+template <int SCHEME, int DT, int BITS, int DRAWS>
 __device__ __forceinline__ void quantize_fast_rows(const void *__restrict__ grad, uint8_t *__restrict__ packed,
                                                    float *__restrict__ meta, const Tile &tile, int bucket,
                                                    uint32_t seed_lo, uint32_t seed_hi, int lane, uint4v *stage)
@@ -239,7 +298,7 @@ __device__ __forceinline__ void quantize_fast_rows(const void *__restrict__ grad
 #pragma unroll
             for (int r = 0; r < G; r++) load8<DT>(grad, first + RowMap{lane}.group(r), x[r]);
         }
-        quantize_chunk_rows<SCHEME, BITS, ODD>(x, bucket, lane, first, key,
+        quantize_chunk_rows<SCHEME, BITS, DRAWS>(x, bucket, lane, first, key,
                                           meta + kMetaFloats<SCHEME> * (tile.bucket0 + c * buckets_per_chunk),
                                           packed + tile.packed_off + int64_t(c) * (kChunk * BITS / 8), stage);
     }
@@ -299,7 +358,7 @@ __device__ __forceinline__ float2 run_extent(const float (&x)[OWN][8], const Run
 // The run's codes under a scale per lane: staged, then sent out with `pad` zero bytes behind them.  out is a multiple
 // of 4 bytes, and so is the number of bytes written: a run starts a multiple of 32 codes into its segment of the
 // stream and either ends one or is padded to the segment's 16 bytes.
-template <int SCHEME, int BITS, bool ODD, int OWN>
+template <int SCHEME, int BITS, int DRAWS, int OWN>
 __device__ __forceinline__ void encode_run(const float (&x)[OWN][8], const Run &run, Scale s, int lane, int64_t first,
                                            uint32_t key, uint8_t *__restrict__ out, uint32_t pad, uint4v *stage)
 {
@@ -311,7 +370,7 @@ __device__ __forceinline__ void encode_run(const float (&x)[OWN][8], const Run &
 #pragma unroll
     for (int r = 0; r < OWN; r++) {
         const uint32_t pair0 = uint32_t(uint64_t(first + (lane * OWN + r) * 8) >> 1);
-        codes[r] = encode_group<SCHEME, BITS, ODD>(x[r], s, pair0, key, uint32_t(first) & 1u);
+        codes[r] = encode_group<SCHEME, BITS, DRAWS>(x[r], s, pair0, key, uint32_t(first) & 1u);
         const int v = run.valid(r);
         codes[r] &= v == 8 ? ~uint64_t(0) : (uint64_t(1) << (v * BITS)) - 1u;       // nothing past the end
         // one group after the other: together they cost the kernel registers that every path of it then pays
@@ -329,7 +388,7 @@ __device__ __forceinline__ void encode_run(const float (&x)[OWN][8], const Run &
 // x holds a run (zeros where there is no element) -> meta of its buckets and its packed codes.  The scale of a
 // bucket comes from an extent per lane parked in LDS: the lanes are split into sets of P (a power of two,
 // 64 / P >= buckets > 32 / P, so a lane folds at most two entries), each of which folds the extents of one bucket.
-template <int SCHEME, int BITS, bool ODD, int OWN>
+template <int SCHEME, int BITS, int DRAWS, int OWN>
 __device__ __forceinline__ void quantize_run_regs(const float (&x)[OWN][8], const Run &run, int lane, int64_t first, uint32_t key,
                                                   float *__restrict__ meta, uint8_t *__restrict__ out, uint32_t pad, uint4v *stage)
 {
@@ -360,11 +419,11 @@ __device__ __forceinline__ void quantize_run_regs(const float (&x)[OWN][8], cons
     }
     wave_lds_fence();
     const float2 own = scales[run.bi];
-    encode_run<SCHEME, BITS, ODD>(x, run, Scale{0.0f, own.x, own.y}, lane, first, key, out, pad, stage);
+    encode_run<SCHEME, BITS, DRAWS>(x, run, Scale{0.0f, own.x, own.y}, lane, first, key, out, pad, stage);
 }
 
 // OWN: groups a lane holds.  A wave pays for them whether or not all its lanes have elements.
-template <int SCHEME, int DT, int BITS, bool ODD, int OWN = G>
+template <int SCHEME, int DT, int BITS, int DRAWS, int OWN = G>
 __device__ __forceinline__ void quantize_run(const void *__restrict__ grad, uint8_t *__restrict__ packed,
                                              float *__restrict__ meta, const Tile &tile, int bucket,
                                              uint32_t seed_lo, uint32_t seed_hi, int lane, uint4v *stage)
@@ -375,7 +434,7 @@ __device__ __forceinline__ void quantize_run(const void *__restrict__ grad, uint
     load.issue(grad, tile.elem0, run.count, lane);
     float x[OWN][8];
     load.finish(run.count, lane, stage, x);
-    quantize_run_regs<SCHEME, BITS, ODD>(x, run, lane, tile.elem0, key, meta + kMetaFloats<SCHEME> * tile.bucket0,
+    quantize_run_regs<SCHEME, BITS, DRAWS>(x, run, lane, tile.elem0, key, meta + kMetaFloats<SCHEME> * tile.bucket0,
                                          packed + tile.packed_off, tile.pad, stage);
 }
 

@@ -8,7 +8,7 @@ namespace {
 // ---------------------------------------------------------------- fused reduce + requantize
 
 // The sums of a chunk never leave the registers: reduce_chunk feeds quantize_chunk.
-template <int SCHEME, int BITS, bool ODD, typename Peers>
+template <int SCHEME, int BITS, int DRAWS, typename Peers>
 __device__ __forceinline__ void fused_fast(Peers &peers, int W, const Tile &tile, int64_t out_off,
                                            int bucket, uint32_t seed_lo, uint32_t seed_hi,
                                            uint8_t *__restrict__ packed_out, float *__restrict__ meta_out,
@@ -28,14 +28,14 @@ __device__ __forceinline__ void fused_fast(Peers &peers, int W, const Tile &tile
             clear_sums(acc);
             reduce_chunk<SCHEME, BITS>(peers, W, in_off, g, map, acc, stage, lane);
         }
-        quantize_chunk<SCHEME, BITS, ODD>(acc, map, lane, tile.elem0 + int64_t(c) * kChunk, key,
+        quantize_chunk<SCHEME, BITS, DRAWS>(acc, map, lane, tile.elem0 + int64_t(c) * kChunk, key,
                                      meta_out + kMetaFloats<SCHEME> * (tile.bucket0 + c * buckets_per_chunk),
                                      packed_out + out_off + int64_t(c) * (kChunk * BITS / 8), stage);
     }
 }
 
 // A run: its sums feed the quantizer in the same lane order.
-template <int SCHEME, int BITS, bool ODD, typename Peers>
+template <int SCHEME, int BITS, int DRAWS, typename Peers>
 __device__ __forceinline__ void fused_run(Peers &peers, int W, const Tile &tile, int64_t out_off, uint32_t out_pad,
                                           int bucket, uint32_t seed_lo, uint32_t seed_hi,
                                           uint8_t *__restrict__ packed_out, float *__restrict__ meta_out, int lane,
@@ -46,13 +46,13 @@ __device__ __forceinline__ void fused_run(Peers &peers, int W, const Tile &tile,
     float acc[G][8];
     sum_run<SCHEME, BITS>(peers, W, tile.packed_off, tile.bucket0, run, acc, stage, lane);
     clear_missing(acc, run);
-    quantize_run_regs<SCHEME, BITS, ODD>(acc, run, lane, tile.elem0, key, meta_out + kMetaFloats<SCHEME> * tile.bucket0,
+    quantize_run_regs<SCHEME, BITS, DRAWS>(acc, run, lane, tile.elem0, key, meta_out + kMetaFloats<SCHEME> * tile.bucket0,
                                          packed_out + out_off, out_pad, stage);
 }
 
 // tiles_in follows the layout of the chunks (storage type dt), tiles_out that of the
 // output (binary32 pass-through layers); the two tables list the same tiles in the same order.
-template <int SCHEME, bool ODD>
+template <int SCHEME, int DRAWS>
 __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ tiles_in,
                                                         const Tile *__restrict__ tiles_out, int64_t n_tiles, int W,
                                                         int dt, uint32_t seed_lo, uint32_t seed_hi,
@@ -78,10 +78,10 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ 
         const uint32_t out_pad = tiles_out[t].pad;
         const uint32_t kind = tile_kind(tile);
         if (kind == kQuantFast) {
-            CGX_FOR_BITS(tile_bits(tile), (fused_fast<SCHEME, BITS, ODD>(peers, W, tile, out_off, bucket, seed_lo,
+            CGX_FOR_BITS(tile_bits(tile), (fused_fast<SCHEME, BITS, DRAWS>(peers, W, tile, out_off, bucket, seed_lo,
                                                                      seed_hi, packed_out, meta_out, lane, stage)))
         } else if (is_quantized_kind(kind) && tile.count <= uint32_t(kChunk) && one_key_block(tile)) {
-            CGX_FOR_BITS(tile_bits(tile), (fused_run<SCHEME, BITS, ODD>(peers, W, tile, out_off, out_pad, bucket, seed_lo,
+            CGX_FOR_BITS(tile_bits(tile), (fused_run<SCHEME, BITS, DRAWS>(peers, W, tile, out_off, out_pad, bucket, seed_lo,
                                                                         seed_hi, packed_out, meta_out, lane, stage)))
         } else if (is_quantized_kind(kind)) {
             quantize_generic<SCHEME, false>(
@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ 
 }  // namespace
 
 hipError_t launch_dequant_reduce_requantize(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
-                                            const Tile *tiles_out, int64_t n_tiles, bool odd_tiles,
+                                            const Tile *tiles_out, int64_t n_tiles, int draws,
                                             uint64_t seed, void *packed_out, void *meta_out,
                                             const LaunchConfig &cfg, hipStream_t stream)
 {
@@ -111,9 +111,10 @@ hipError_t launch_dequant_reduce_requantize(int scheme, const PeerPtrs &peers, i
     const dim3 grid(grid_for(n_tiles, cfg)), block(kBlock);
     using Kernel = void (*)(const Tile *, const Tile *, int64_t, int, int, uint32_t, uint32_t, uint8_t *, float *,
                             const PeerPtrs);
-    static const Kernel table[2][2] = {{fused_kernel<kMinMax, false>, fused_kernel<kNormSign, false>},
-                                       {fused_kernel<kMinMax, true>, fused_kernel<kNormSign, true>}};
-    const Kernel kernel = table[odd_tiles][scheme == kSchemeNormSign];
+    static const Kernel table[3][2] = {{fused_kernel<kMinMax, kDrawsQuad>, fused_kernel<kNormSign, kDrawsQuad>},
+                                       {fused_kernel<kMinMax, kDrawsEven>, fused_kernel<kNormSign, kDrawsEven>},
+                                       {fused_kernel<kMinMax, kDrawsOdd>, fused_kernel<kNormSign, kDrawsOdd>}};
+    const Kernel kernel = table[draws][scheme == kSchemeNormSign];
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, tiles_in, tiles_out, n_tiles, W, dt, uint32_t(seed),
                        uint32_t(seed >> 32), static_cast<uint8_t *>(packed_out), static_cast<float *>(meta_out), peers);
     return hipGetLastError();

@@ -32,16 +32,21 @@ struct LaunchConfig {
     int quantize_tiles_per_wave_x4 = 5;      // quantize: tiles per wave of the grid, in quarters (4: one wave per tile)
 };
 
-// odd_tiles: some vectorised tile starts on an odd element index (the kernels then take the
-// variant that can draw across generator words; a property of the tile table).
+// How the kernels form the draws of a group of 8 elements, a property of the tile table: by where its quantized tiles start.
+enum Draws {
+    kDrawsQuad = 0,      // all on a multiple of 8 elements, i.e. of four generator words
+    kDrawsEven = 1,      // all on an even element index
+    kDrawsOdd = 2        // some on an odd one: these draw across generator words
+};
+
 // aligned_tiles: every vectorised tile starts on a 16-byte boundary of the buffer (its chunks can then be
 // fetched through LDS with whole-line loads).
 // The quantize kernel is built for chunks of 1024 elements (_g2: two groups of 8 per lane) and of 2048
 // (_g4); `tiles` must have been built for that chunk size.
-hipError_t launch_quantize_g2(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, bool odd_tiles,
+hipError_t launch_quantize_g2(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, int draws,
                               bool aligned_tiles, int32_t bucket, uint64_t seed, void *packed, void *meta,
                               const LaunchConfig &cfg, hipStream_t stream);
-hipError_t launch_quantize_g4(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, bool odd_tiles,
+hipError_t launch_quantize_g4(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, int draws,
                               bool aligned_tiles, int32_t bucket, uint64_t seed, void *packed, void *meta,
                               const LaunchConfig &cfg, hipStream_t stream);
 // Chunk size of every other kernel (reduce, fused, statistics).
@@ -68,17 +73,17 @@ hipError_t launch_dequant_reduce_g4(int scheme, const PeerPtrs &peers, int W, in
 // reaching memory; tiles_in describes the chunks (storage type dt), tiles_out the output
 // (binary32 pass-through); W <= kPeersPerLaunch.
 hipError_t launch_dequant_reduce_requantize(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
-                                            const Tile *tiles_out, int64_t n_tiles, bool odd_tiles,
+                                            const Tile *tiles_out, int64_t n_tiles, int draws,
                                             uint64_t seed, void *packed_out, void *meta_out,
                                             const LaunchConfig &cfg, hipStream_t stream);
 
 // The same two for buckets longer than a chunk of 2048 elements (tables of class kMapWide at that chunk); longest: the
 // longest bucket of the call.
-hipError_t launch_quantize_wide(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, bool odd_tiles,
+hipError_t launch_quantize_wide(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, int draws,
                                 int32_t longest, uint64_t seed, void *packed, void *meta, const LaunchConfig &cfg,
                                 hipStream_t stream);
 hipError_t launch_dequant_reduce_requantize_wide(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
-                                                 const Tile *tiles_out, int64_t n_tiles, bool odd_tiles, int32_t longest,
+                                                 const Tile *tiles_out, int64_t n_tiles, int draws, int32_t longest,
                                                  uint64_t seed, void *packed_out, void *meta_out, const LaunchConfig &cfg,
                                                  hipStream_t stream);
 

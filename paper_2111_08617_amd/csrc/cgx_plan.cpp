@@ -232,6 +232,7 @@ PlanTable build_table(int32_t L, const int64_t *off, const uint8_t *bits, int32_
         part.count = int64_t(tiles.size());
         for (const Tile &t : tiles) {
             part.odd |= is_quantized_kind(tile_kind(t)) && (t.elem0 & 1);
+            part.quads &= !(is_quantized_kind(tile_kind(t)) && (t.elem0 & 7));
             part.aligned &= !(is_vector_kind(tile_kind(t)) && (t.elem0 * elem_size(dt)) % 16 != 0);
         }
         for (int32_t l = 0; l < L; l++)

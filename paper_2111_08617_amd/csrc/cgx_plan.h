@@ -114,6 +114,7 @@ struct TablePart {
     int chunk = 0;               // elements per chunk of the kernel that walks it
     int64_t first = 0, count = 0;
     bool odd = false;            // some quantized tile starts on an odd element index
+    bool quads = true;           // every quantized tile starts on a multiple of 8 elements
     bool aligned = true;         // every vectorised quantized tile starts on a 16-byte boundary of the buffer
 };
 

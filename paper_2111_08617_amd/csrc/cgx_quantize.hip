@@ -4,10 +4,10 @@
 namespace cgx {
 namespace {
 
-// ODD: some vectorised tile of the plan starts on an odd element index (see encode_group).
+// DRAWS: where the plan's quantized tiles start (see encode_group).
 // VIA_LDS: every vectorised tile starts on a 16-byte boundary and the bucket-major mapping reads its
-// chunks through LDS (see chunk_through_lds); never together with ODD.
-template <int SCHEME, int DT, int MAP, bool ODD, bool VIA_LDS = false>
+// chunks through LDS (see chunk_through_lds); never with kDrawsOdd, and with kDrawsEven for binary32 only.
+template <int SCHEME, int DT, int MAP, int DRAWS, bool VIA_LDS = false>
 __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict__ grad,
                                                            const Tile *__restrict__ tiles, int64_t n_tiles,
                                                            uint32_t seed_lo, uint32_t seed_hi,
@@ -36,10 +36,10 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict
         const uint32_t kind = tile_kind(tile);
         if (kind == kQuantFast) {
             if constexpr (MAP == kMapRows) {
-                CGX_FOR_BITS(tile_bits(tile), (quantize_fast_rows<SCHEME, DT, BITS, ODD>(grad, packed, meta, tile, bucket,
+                CGX_FOR_BITS(tile_bits(tile), (quantize_fast_rows<SCHEME, DT, BITS, DRAWS>(grad, packed, meta, tile, bucket,
                                                                                       seed_lo, seed_hi, lane, stage)))
             } else {
-                CGX_FOR_BITS(tile_bits(tile), (quantize_fast<SCHEME, DT, BITS, ODD, VIA_LDS>(
+                CGX_FOR_BITS(tile_bits(tile), (quantize_fast<SCHEME, DT, BITS, DRAWS, VIA_LDS>(
                                                   grad, packed, meta, tile, bucket, seed_lo, seed_hi, lane, stage)))
             }
         } else if (is_quantized_kind(kind) && tile.count <= uint32_t(kChunk) && one_key_block(tile)) {
@@ -48,11 +48,11 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict
             // 73.8 and 64.8; binary16 70.5 and 59.3, 64.4 and 53.2)
             if (G == 4 && MAP == kMapBuckets && three_groups_hold(tile, bucket)) {
                 if constexpr (G == 4 && MAP == kMapBuckets) {
-                    CGX_FOR_BITS(tile_bits(tile), (quantize_run<SCHEME, DT, BITS, ODD, 3>(grad, packed, meta, tile, bucket, seed_lo,
+                    CGX_FOR_BITS(tile_bits(tile), (quantize_run<SCHEME, DT, BITS, DRAWS, 3>(grad, packed, meta, tile, bucket, seed_lo,
                                                                                          seed_hi, lane, stage)))
                 }
             } else {
-                CGX_FOR_BITS(tile_bits(tile), (quantize_run<SCHEME, DT, BITS, ODD>(grad, packed, meta, tile, bucket,
+                CGX_FOR_BITS(tile_bits(tile), (quantize_run<SCHEME, DT, BITS, DRAWS>(grad, packed, meta, tile, bucket,
                                                                                      seed_lo, seed_hi, lane, stage)))
             }
         } else if (is_quantized_kind(kind)) {
@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict
 }  // namespace
 
 // This file is compiled once per chunk size (CGX_GROUPS = 2 and 4): launch_quantize_g2, launch_quantize_g4.
-hipError_t CGX_CONCAT(launch_quantize_g, CGX_GROUPS)(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, bool odd_tiles,
+hipError_t CGX_CONCAT(launch_quantize_g, CGX_GROUPS)(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, int draws,
                            bool aligned_tiles, int32_t bucket, uint64_t seed, void *packed, void *meta,
                            const LaunchConfig &cfg, hipStream_t stream)
 {
@@ -90,18 +90,24 @@ hipError_t CGX_CONCAT(launch_quantize_g, CGX_GROUPS)(int scheme, const void *gra
     using Kernel = void (*)(const void *, const Tile *, int64_t, uint32_t, uint32_t, uint8_t *, float *);
 #define CGX_QUANTIZE_MAPS(S, D, O) \
     {quantize_kernel<S, D, kMapBuckets, O>, quantize_kernel<S, D, kMapRows, O>}
-    static const Kernel table[2][2][2][2] = {
-        {{CGX_QUANTIZE_MAPS(kMinMax, CGX_F32, false), CGX_QUANTIZE_MAPS(kMinMax, CGX_F16, false)},
-         {CGX_QUANTIZE_MAPS(kNormSign, CGX_F32, false), CGX_QUANTIZE_MAPS(kNormSign, CGX_F16, false)}},
-        {{CGX_QUANTIZE_MAPS(kMinMax, CGX_F32, true), CGX_QUANTIZE_MAPS(kMinMax, CGX_F16, true)},
-         {CGX_QUANTIZE_MAPS(kNormSign, CGX_F32, true), CGX_QUANTIZE_MAPS(kNormSign, CGX_F16, true)}}};
+#define CGX_QUANTIZE_SCHEMES(O) \
+    {{CGX_QUANTIZE_MAPS(kMinMax, CGX_F32, O), CGX_QUANTIZE_MAPS(kMinMax, CGX_F16, O)}, \
+     {CGX_QUANTIZE_MAPS(kNormSign, CGX_F32, O), CGX_QUANTIZE_MAPS(kNormSign, CGX_F16, O)}}
+    static const Kernel table[3][2][2][2] = {CGX_QUANTIZE_SCHEMES(kDrawsQuad), CGX_QUANTIZE_SCHEMES(kDrawsEven),
+                                             CGX_QUANTIZE_SCHEMES(kDrawsOdd)};
+#undef CGX_QUANTIZE_SCHEMES
 #undef CGX_QUANTIZE_MAPS
-    static const Kernel through_lds[2][2] = {
-        {quantize_kernel<kMinMax, CGX_F32, kMapBuckets, false, true>, quantize_kernel<kMinMax, CGX_F16, kMapBuckets, false, true>},
-        {quantize_kernel<kNormSign, CGX_F32, kMapBuckets, false, true>, quantize_kernel<kNormSign, CGX_F16, kMapBuckets, false, true>}};
-    const bool via_lds = aligned_tiles && !odd_tiles && mapping_of(bucket, kChunk) == kMapBuckets && cfg.via_lds;
-    const Kernel kernel = via_lds ? through_lds[scheme == kSchemeNormSign][dt == CGX_F16]
-                                  : table[odd_tiles][scheme == kSchemeNormSign][dt == CGX_F16][mapping_of(bucket, kChunk)];
+    // (a 16-byte boundary is a multiple of 8 elements of binary16)
+    static const Kernel through_lds[2][2][2] = {
+        {{quantize_kernel<kMinMax, CGX_F32, kMapBuckets, kDrawsQuad, true>, quantize_kernel<kMinMax, CGX_F16, kMapBuckets, kDrawsQuad, true>},
+         {quantize_kernel<kNormSign, CGX_F32, kMapBuckets, kDrawsQuad, true>,
+          quantize_kernel<kNormSign, CGX_F16, kMapBuckets, kDrawsQuad, true>}},
+        {{quantize_kernel<kMinMax, CGX_F32, kMapBuckets, kDrawsEven, true>, nullptr},
+         {quantize_kernel<kNormSign, CGX_F32, kMapBuckets, kDrawsEven, true>, nullptr}}};
+    const bool via_lds = aligned_tiles && draws <= (dt == CGX_F32 ? kDrawsEven : kDrawsQuad) &&
+                         mapping_of(bucket, kChunk) == kMapBuckets && cfg.via_lds;
+    const Kernel kernel = via_lds ? through_lds[draws][scheme == kSchemeNormSign][dt == CGX_F16]
+                                  : table[draws][scheme == kSchemeNormSign][dt == CGX_F16][mapping_of(bucket, kChunk)];
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, grad, tiles, n_tiles, seed_lo, seed_hi,
                        static_cast<uint8_t *>(packed), static_cast<float *>(meta));
     return hipGetLastError();

@@ -55,7 +55,7 @@ __device__ __forceinline__ Scale block_scale(const float (&x)[G][8], const Run &
     return bucket_scale(mn, mx, int(top_level<SCHEME>(bits)));
 }
 
-template <int SCHEME, int DT, bool ODD, int WAVES>
+template <int SCHEME, int DT, int DRAWS, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave) void quantize_wide_kernel(const void *__restrict__ grad, const Tile *__restrict__ tiles,
                                                                 int64_t n_tiles, uint32_t seed_lo, uint32_t seed_hi,
                                                                 uint8_t *__restrict__ packed, float *__restrict__ meta)
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(WAVES * kWave) void quantize_wide_kernel(const void
             const int64_t first = tile.elem0 + share.at;
             const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
             if (share.count > 0)
-                CGX_FOR_BITS(tile_bits(tile), (encode_run<SCHEME, BITS, ODD>(x, run, s, lane, first, key,
+                CGX_FOR_BITS(tile_bits(tile), (encode_run<SCHEME, BITS, DRAWS>(x, run, s, lane, first, key,
                                                                              packed + tile.packed_off + share.at * BITS / 8,
                                                                              share.last ? tile.pad : 0u, stage)))
         } else if (quantized) {
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(WAVES * kWave) void quantize_wide_kernel(const void
     }
 }
 
-template <int SCHEME, bool ODD, int WAVES>
+template <int SCHEME, int DRAWS, int WAVES>
 __global__ __launch_bounds__(WAVES * kWave, 4) void fused_wide_kernel(const Tile *__restrict__ tiles_in,
                                                              const Tile *__restrict__ tiles_out, int64_t n_tiles, int W,
                                                              int dt, uint32_t seed_lo, uint32_t seed_hi,
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(WAVES * kWave, 4) void fused_wide_kernel(const Tile
             const int64_t first = tile.elem0 + share.at;
             const uint32_t key = rng_key(seed_lo, seed_hi, uint32_t((uint64_t(tile.elem0) >> 1) >> 32));
             if (share.count > 0)
-                CGX_FOR_BITS(tile_bits(tile), (encode_run<SCHEME, BITS, ODD>(acc, run, s, lane, first, key,
+                CGX_FOR_BITS(tile_bits(tile), (encode_run<SCHEME, BITS, DRAWS>(acc, run, s, lane, first, key,
                                                                              packed_out + out_off + share.at * BITS / 8,
                                                                              share.last ? out_pad : 0u, stage)))
         } else if (quantized) {
@@ -157,27 +157,27 @@ inline unsigned wide_grid(int64_t n_tiles, const LaunchConfig &cfg)
 
 }  // namespace
 
-hipError_t launch_quantize_wide(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, bool odd_tiles,
+hipError_t launch_quantize_wide(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, int draws,
                                 int32_t longest, uint64_t seed, void *packed, void *meta, const LaunchConfig &cfg,
                                 hipStream_t stream)
 {
     if (n_tiles == 0) return hipSuccess;
     using Kernel = void (*)(const void *, const Tile *, int64_t, uint32_t, uint32_t, uint8_t *, float *);
 #define CGX_WIDE(S, D, O) {quantize_wide_kernel<S, D, O, 2>, quantize_wide_kernel<S, D, O, 4>}
-    static const Kernel table[2][2][2][2] = {{{CGX_WIDE(kMinMax, CGX_F32, false), CGX_WIDE(kMinMax, CGX_F16, false)},
-                                              {CGX_WIDE(kNormSign, CGX_F32, false), CGX_WIDE(kNormSign, CGX_F16, false)}},
-                                             {{CGX_WIDE(kMinMax, CGX_F32, true), CGX_WIDE(kMinMax, CGX_F16, true)},
-                                              {CGX_WIDE(kNormSign, CGX_F32, true), CGX_WIDE(kNormSign, CGX_F16, true)}}};
+#define CGX_WIDE_SCHEMES(O) \
+    {{CGX_WIDE(kMinMax, CGX_F32, O), CGX_WIDE(kMinMax, CGX_F16, O)}, {CGX_WIDE(kNormSign, CGX_F32, O), CGX_WIDE(kNormSign, CGX_F16, O)}}
+    static const Kernel table[3][2][2][2] = {CGX_WIDE_SCHEMES(kDrawsQuad), CGX_WIDE_SCHEMES(kDrawsEven), CGX_WIDE_SCHEMES(kDrawsOdd)};
+#undef CGX_WIDE_SCHEMES
 #undef CGX_WIDE
     const int waves = longest <= 2 * kChunk ? 2 : 4;
-    const Kernel kernel = table[odd_tiles][scheme == kSchemeNormSign][dt == CGX_F16][waves == 4];
+    const Kernel kernel = table[draws][scheme == kSchemeNormSign][dt == CGX_F16][waves == 4];
     hipLaunchKernelGGL(kernel, dim3(wide_grid(n_tiles, cfg)), dim3(waves * kWave), 0, stream, grad, tiles, n_tiles,
                        uint32_t(seed), uint32_t(seed >> 32), static_cast<uint8_t *>(packed), static_cast<float *>(meta));
     return hipGetLastError();
 }
 
 hipError_t launch_dequant_reduce_requantize_wide(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
-                                                 const Tile *tiles_out, int64_t n_tiles, bool odd_tiles, int32_t longest,
+                                                 const Tile *tiles_out, int64_t n_tiles, int draws, int32_t longest,
                                                  uint64_t seed, void *packed_out, void *meta_out, const LaunchConfig &cfg,
                                                  hipStream_t stream)
 {
@@ -185,11 +185,12 @@ hipError_t launch_dequant_reduce_requantize_wide(int scheme, const PeerPtrs &pee
     using Kernel = void (*)(const Tile *, const Tile *, int64_t, int, int, uint32_t, uint32_t, uint8_t *, float *,
                             const PeerPtrs);
 #define CGX_WIDE(S, O) {fused_wide_kernel<S, O, 2>, fused_wide_kernel<S, O, 4>}
-    static const Kernel table[2][2][2] = {{CGX_WIDE(kMinMax, false), CGX_WIDE(kNormSign, false)},
-                                          {CGX_WIDE(kMinMax, true), CGX_WIDE(kNormSign, true)}};
+    static const Kernel table[3][2][2] = {{CGX_WIDE(kMinMax, kDrawsQuad), CGX_WIDE(kNormSign, kDrawsQuad)},
+                                          {CGX_WIDE(kMinMax, kDrawsEven), CGX_WIDE(kNormSign, kDrawsEven)},
+                                          {CGX_WIDE(kMinMax, kDrawsOdd), CGX_WIDE(kNormSign, kDrawsOdd)}};
 #undef CGX_WIDE
     const int waves = longest <= 2 * kChunk ? 2 : 4;
-    const Kernel kernel = table[odd_tiles][scheme == kSchemeNormSign][waves == 4];
+    const Kernel kernel = table[draws][scheme == kSchemeNormSign][waves == 4];
     hipLaunchKernelGGL(kernel, dim3(wide_grid(n_tiles, cfg)), dim3(waves * kWave), 0, stream, tiles_in, tiles_out, n_tiles, W,
                        dt, uint32_t(seed), uint32_t(seed >> 32), static_cast<uint8_t *>(packed_out),
                        static_cast<float *>(meta_out), peers);

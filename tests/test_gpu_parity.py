@@ -652,6 +652,26 @@ def test_layers_that_start_anywhere(torch, oracle, bucket, dt):
     full_cycle(torch, oracle, w, W=3, what=f"shifted B={bucket}")
 
 
+@pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("start", [0, 8, 2, 4, 7])
+def test_draws_follow_where_the_tiles_start(torch, oracle, start, bits, dt):
+    """Plans whose quantized tiles all start on a multiple of 8 elements, all on even ones, or some on odd ones take kernels
+    that form their draws differently; chunks and a ragged end of every width, values at both ends of every bucket (the top
+    level is reached exactly, with the largest draws, without a clamp)."""
+    sizes = [start] * (start > 0) + [2048 * 3 + 8 * 5]
+    w = wl.Workload("start", [(s,) for s in sizes], np.array([0] * (start > 0) + [bits], np.uint8), 128, dt, 2, 40 + start,
+                    wl._normal, np.full(len(sizes), 0.3))
+    tiles = cgx.cgx_plan_tiles(cgx.Plan(w.offsets, w.bits, w.bucket, w.dt))
+    quantized = tiles["elem0"][((tiles["info"] >> 4) & 15) != 3]
+    assert ((quantized % 8) == start % 8).any()
+    full_cycle(torch, oracle, w, W=2, seed_shift=start, what=f"start {start} bits {bits}")
+    g = np.where(np.arange(w.n) % 3 == 0, -1.5, 1.5).astype(w.gradient(0).dtype)      # two values per bucket: levels 0 and the top
+    op, om = oracle.quantize(g, w.offsets, w.bits, w.bucket, 3, w.dt)
+    gp, gm = gpu_quantize(torch, g, w.offsets, w.bits, w.bucket, 3, w.dt)
+    assert_same_chunk(gp, gm, op, om, "two values")
+
+
 def test_step_can_be_captured_in_a_graph_and_replayed(torch, oracle):
     """Once a plan's tables exist the entry points only queue kernels, so a step can be captured;
     every replay (with eager work and synchronisations in between) gives the eager result."""

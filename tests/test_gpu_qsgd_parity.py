@@ -223,3 +223,19 @@ def test_layers_that_start_anywhere(torch, oracle, bucket, dt):
     w = wl.Workload("shifted", [(s,) for s in sizes], np.array(bits, np.uint8), bucket, dt, 3, 800 + bucket,
                     wl._normal, np.linspace(0.01, 2.0, len(sizes)))
     full_cycle(torch, oracle, w, W=3, what=f"qsgd shifted B={bucket}")
+
+
+@pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("bits", range(2, 9))
+@pytest.mark.parametrize("start", [0, 2, 4, 7])
+def test_draws_follow_where_the_tiles_start(torch, oracle, start, bits, dt):
+    """Quantized tiles on multiples of 8 elements, on even and on odd ones; both signs of the top level (reached exactly,
+    without a clamp) and zeros of either sign."""
+    sizes = [start] * (start > 0) + [2048 * 3 + 8 * 5]
+    w = wl.Workload("start", [(s,) for s in sizes], np.array([0] * (start > 0) + [bits], np.uint8), 128, dt, 2, 60 + start,
+                    wl._normal, np.full(len(sizes), 0.3))
+    full_cycle(torch, oracle, w, W=2, what=f"start {start} bits {bits}")
+    g = np.array([-1.5, 0.0, 1.5, -0.0], w.gradient(0).dtype)[np.arange(w.n) % 4]
+    op, om = oracle.qsgd_quantize(g, w.offsets, w.bits, w.bucket, 3, w.dt)
+    gp, gm = gpu_quantize(torch, g, w.offsets, w.bits, w.bucket, 3, w.dt)
+    assert_same_chunk(gp, gm, op, om, "top levels and zeros")
