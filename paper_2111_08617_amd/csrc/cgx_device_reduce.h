@@ -29,49 +29,62 @@ __device__ __forceinline__ void bytes_to_float(uint32_t t, float &b0, float &b1,
     b3 = float(t >> 24);
 }
 
-// Levels of one group of 8 codes as floats (kNormSign: signed levels).  Of the signed widths
-// only 4 bits takes the byte-wise form: with 2 and 8 bits as well the reduce kernel needed 129
-// to 131 registers, one wave per SIMD less, when it had 127 of them (it has 100 now; not measured again since).
+// The same for signed bytes: one conversion each (sub-dword operand, sign-extended).
+__device__ __forceinline__ void signed_bytes_to_float(uint32_t t, float &b0, float &b1, float &b2, float &b3)
+{
+    b0 = float(int32_t(int8_t(t)));
+    b1 = float(int32_t(int8_t(t >> 8)));
+    b2 = float(int32_t(int8_t(t >> 16)));
+    b3 = float(int32_t(t) >> 24);
+}
+
+// Levels of one group of 8 codes as floats (kNormSign: signed levels).
+// Bound by the vector ALUs.  Signed codes of 2 and 4 bits become signed bytes first, four at a time: a conversion of a
+// signed byte costs what one of an unsigned byte does.
 template <int SCHEME, int BITS>
 __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
 {
     constexpr bool kSigned = SCHEME == kNormSign;
-    if (BITS == 8 && !kSigned) {
-        bytes_to_float(uint32_t(v), f[0], f[1], f[2], f[3]);
-        bytes_to_float(uint32_t(v >> 32), f[4], f[5], f[6], f[7]);
-    } else if (BITS == 4) {
-        // one code per byte: even codes in one register, odd ones in another.  kSigned: a code is
-        // a two's complement nibble; with its sign bit flipped it reads level + 8 in 1..15
-        constexpr uint32_t kFlip = kSigned ? 0x88888888u : 0u;
-        const uint32_t w = uint32_t(v) ^ kFlip;
-        const uint32_t even = opaque(w & 0x0f0f0f0fu), odd = opaque((w >> 4) & 0x0f0f0f0fu);
-        bytes_to_float(even, f[0], f[2], f[4], f[6]);
-        bytes_to_float(odd, f[1], f[3], f[5], f[7]);
+    const uint32_t w = uint32_t(v);
+    if (BITS == 8) {
         if (kSigned) {
-#pragma unroll
-            for (int j = 0; j < 8; j++) f[j] -= 8.0f;
+            signed_bytes_to_float(w, f[0], f[1], f[2], f[3]);
+            signed_bytes_to_float(uint32_t(v >> 32), f[4], f[5], f[6], f[7]);
+        } else {
+            bytes_to_float(w, f[0], f[1], f[2], f[3]);
+            bytes_to_float(uint32_t(v >> 32), f[4], f[5], f[6], f[7]);
         }
-    } else if (BITS == 2 && !kSigned) {
-        const uint32_t w = uint32_t(v);
-#pragma unroll
-        for (int j = 0; j < 4; j++) {
-            const uint32_t t = opaque((w >> (2 * j)) & 0x0303u);     // codes j and j + 4, one per byte
-            f[j] = float(t & 0xffu);
-            f[4 + j] = float((t >> 8) & 0xffu);
+    } else if (BITS == 4) {
+        // one code per byte: even codes in one register, odd ones in another
+        if (kSigned) {
+            // a nibble with its sign bit flipped is level + 8, and 0x78 more is level + 0x80: no byte carries
+            const uint32_t h = w ^ 0x88888888u;
+            const uint32_t even = ((h & 0x0f0f0f0fu) + 0x78787878u) ^ 0x80808080u;
+            const uint32_t odd = (((h >> 4) & 0x0f0f0f0fu) + 0x78787878u) ^ 0x80808080u;
+            signed_bytes_to_float(opaque(even), f[0], f[2], f[4], f[6]);
+            signed_bytes_to_float(opaque(odd), f[1], f[3], f[5], f[7]);
+        } else {
+            bytes_to_float(opaque(w & 0x0f0f0f0fu), f[0], f[2], f[4], f[6]);
+            bytes_to_float(opaque((w >> 4) & 0x0f0f0f0fu), f[1], f[3], f[5], f[7]);
+        }
+    } else if (BITS == 2) {
+        // four codes per register: the upper half holds the codes that follow those of the lower half
+        const uint32_t x = opaque(((w & 0xffffu) << 14) | (w & 0xffffu));
+        if (kSigned) {
+            // every code selects its level from the four bytes 0, 1, -2, -1
+            constexpr uint32_t kLevels = 0xfffe0100u;
+            const uint32_t lo = __builtin_amdgcn_perm(0u, kLevels, x & 0x03030303u);
+            const uint32_t hi = __builtin_amdgcn_perm(0u, kLevels, (x >> 4) & 0x03030303u);
+            signed_bytes_to_float(opaque(lo), f[0], f[4], f[1], f[5]);
+            signed_bytes_to_float(opaque(hi), f[2], f[6], f[3], f[7]);
+        } else {
+            bytes_to_float(opaque(x & 0x03030303u), f[0], f[4], f[1], f[5]);
+            bytes_to_float(opaque((x >> 4) & 0x03030303u), f[2], f[6], f[3], f[7]);
         }
     } else if (kSigned) {
-        if (BITS == 8) {
-            const uint32_t lo = uint32_t(v), hi = uint32_t(v >> 32);
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                f[j] = float(int32_t(int8_t(lo >> (8 * j))));
-                f[4 + j] = float(int32_t(int8_t(hi >> (8 * j))));
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; j++)      // sign-extending field extract
-                f[j] = float(int32_t(uint32_t(v >> (j * BITS)) << (32 - BITS)) >> (32 - BITS));
-        }
+        for (int j = 0; j < 8; j++)      // sign-extending field extract
+            f[j] = float(int32_t(uint32_t(v >> (j * BITS)) << (32 - BITS)) >> (32 - BITS));
     } else {
         constexpr uint64_t kMask = (1u << BITS) - 1u;
 #pragma unroll

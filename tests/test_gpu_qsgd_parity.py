@@ -239,3 +239,26 @@ def test_draws_follow_where_the_tiles_start(torch, oracle, start, bits, dt):
     op, om = oracle.qsgd_quantize(g, w.offsets, w.bits, w.bucket, 3, w.dt)
     gp, gm = gpu_quantize(torch, g, w.offsets, w.bits, w.bucket, 3, w.dt)
     assert_same_chunk(gp, gm, op, om, "top levels and zeros")
+
+
+@pytest.mark.parametrize("bits", range(2, 9))
+@pytest.mark.parametrize("bucket", [32, 96, 1024])
+def test_units_of_any_size(torch, oracle, bucket, bits):
+    """Chunks with units that a quantizer of another program may write: the smallest, those whose 64th part is no longer
+    exact and the first whose is, the largest, zeros of either sign and values that are not finite; every code occurs."""
+    n, W = 2048 * 2 + 96 * 5, 5
+    off, widths = np.array([0, n], np.int64), np.array([bits], np.uint8)
+    rng = np.random.default_rng(bits * 10000 + bucket)
+    x = rng.standard_normal(n).astype(np.float32)
+    chunk, meta = oracle.qsgd_quantize(x, off, widths, bucket, 1)
+    below, first = np.nextafter(np.float32(2.0 ** -120), np.float32(0)), np.float32(2.0 ** -120)
+    special = np.array([1.4e-45, 1e-40, 1.1754942e-38, below, -below, 0.0, -0.0, first, -first, 1.0, 3e38, np.inf, np.nan],
+                       np.float32)
+    chunks = [rng.integers(0, 256, chunk.size, dtype=np.uint8) for _ in range(W)]
+    for few in (True, False):       # a wave with such units beside ordinary ones, then without any that is not exact
+        units = special if few else special[5:]
+        metas = [rng.choice(units, meta.size).astype(np.float32) for _ in range(W)]
+        ref = oracle.qsgd_dequant_reduce(chunks, metas, off, widths, bucket, wl.F32)["sum32"]
+        got, _ = gpu_reduce(torch, chunks, metas, off, widths, bucket, wl.F32)
+        same = got.view(np.uint32) == ref.view(np.uint32)
+        assert (same | (np.isnan(got) & np.isnan(ref))).all(), f"{bits} bits, buckets of {bucket}: sums differ"
