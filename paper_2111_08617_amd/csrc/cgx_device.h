@@ -91,6 +91,13 @@ typedef uint4v uint4u4 __attribute__((aligned(4)));
 
 // ---------------------------------------------------------------- generator
 
+// Keeps a value opaque to the optimiser at no cost.
+__device__ __forceinline__ uint32_t opaque(uint32_t v)
+{
+    asm("" : "+v"(v));
+    return v;
+}
+
 // 32-bit avalanche finalizer (xor-shift 16, odd multiply, xor-shift 15, odd
 // multiply, xor-shift 16).
 __device__ __forceinline__ uint32_t mix32_head(uint32_t x) { return x ^ (x >> 16); }

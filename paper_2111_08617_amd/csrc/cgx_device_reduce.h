@@ -10,17 +10,9 @@ namespace {
 
 // ---------------------------------------------------------------- dequantize + reduce
 
-// Keeps a value opaque to the optimiser at no cost.  The byte-wise decoders below put one code
-// into every byte of a register and convert the bytes with v_cvt_f32_ubyte0..3; seeing through
-// the mask, the compiler would instead extract every code with a v_bfe_u32 of its own and
-// convert byte 0 (two instructions of the slow issue class per code instead of one).
-__device__ __forceinline__ uint32_t opaque(uint32_t v)
-{
-    asm("" : "+v"(v));
-    return v;
-}
-
-// The four bytes of t as floats.
+// The four bytes of t as floats.  The byte-wise decoders below put one code into every byte of a register and convert
+// the bytes with v_cvt_f32_ubyte0..3; seeing through the mask (hence opaque), the compiler would instead extract every
+// code with a v_bfe_u32 of its own and convert byte 0 (two instructions of the slow issue class per code instead of one).
 __device__ __forceinline__ void bytes_to_float(uint32_t t, float &b0, float &b1, float &b2, float &b3)
 {
     b0 = float(t & 0xffu);

@@ -93,6 +93,22 @@ def test_random_plans_with_a_bucket_size_per_layer(torch, oracle, seed):
     cycle(torch, oracle, w, buckets, f"random plan {seed} (buckets {buckets.tolist()}, bits {w.bits.tolist()})")
 
 
+@pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_ends_within_a_group_where_all_values_have_one_sign(torch, oracle, bits, dt):
+    """Layers of every bucket size that end 1 to 7 elements into a group of 8 and lie below or above zero as a whole."""
+    shifted = lambda rng, n, scale: (scale + 0.7 * rng.standard_normal(n)).astype(np.float32)
+    sizes, buckets = [], []
+    for end in range(1, 8):
+        for bucket in BUCKETS:
+            sizes += [end, bucket + 8 * 3 + end]
+            buckets += [bucket, bucket]
+    for sign in (-3.0, 3.0):
+        w = wl.Workload("one sign", [(s,) for s in sizes], np.full(len(sizes), bits, np.uint8), 128, dt, 2, 60 + bits, shifted,
+                        np.full(len(sizes), sign))
+        cycle(torch, oracle, w, np.array(buckets, np.int32), f"one sign {sign}")
+
+
 def test_equal_sizes_give_the_single_size_bytes(torch, oracle):
     w = wl.tiny_mixed(seed=5, dt=wl.F32, bucket=256)
     g = w.gradient()

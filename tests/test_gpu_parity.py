@@ -672,6 +672,27 @@ def test_draws_follow_where_the_tiles_start(torch, oracle, start, bits, dt):
     assert_same_chunk(gp, gm, op, om, "two values")
 
 
+@pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("bucket", [32, 96, 128, 2048, 2080, 4096])
+def test_ends_within_a_group_where_all_values_have_one_sign(torch, oracle, bucket, bits, dt):
+    """Layers that end 1 to 7 elements into a group of 8, alone and behind whole buckets and chunks, whose values all lie
+    below zero or all above it: what stands in the group's missing elements is no value of their bucket."""
+    shifted = lambda rng, n, scale: (scale + 0.7 * rng.standard_normal(n)).astype(np.float32)
+    for start in (0, 2, 7):          # where the layers start: a kernel of its own per kind of start
+        sizes, scales = [start], [1.0]
+        for end in range(1, 8):
+            for length in (end, 8 * 5 + end, bucket + end, 2048 + bucket + 8 * 3 + end):
+                sizes += [length, -length % 8]
+                scales += [(-3.0, 3.0)[(end + length) % 2], 1.0]
+        widths = np.where(np.arange(len(sizes)) % 2 == 1, bits, 0).astype(np.uint8)
+        w = wl.Workload("one sign", [(s,) for s in sizes], widths, bucket, dt, 2, 60 + bits, shifted, np.array(scales))
+        assert (w.offsets[:-1][widths > 0] % 8 == start).all()
+        full_cycle(torch, oracle, w, W=2, seed_shift=start, what=f"one sign, start {start}")
+        w.scales = -w.scales
+        full_cycle(torch, oracle, w, W=2, seed_shift=start, what=f"the other sign, start {start}")
+
+
 def test_step_can_be_captured_in_a_graph_and_replayed(torch, oracle):
     """Once a plan's tables exist the entry points only queue kernels, so a step can be captured;
     every replay (with eager work and synchronisations in between) gives the eager result."""

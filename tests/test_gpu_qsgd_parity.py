@@ -241,6 +241,18 @@ def test_draws_follow_where_the_tiles_start(torch, oracle, start, bits, dt):
     assert_same_chunk(gp, gm, op, om, "top levels and zeros")
 
 
+@pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("bits", range(2, 9))
+@pytest.mark.parametrize("bucket", [96, 128, 4096])
+def test_ends_within_a_group_where_all_values_have_one_sign(torch, oracle, bucket, bits, dt):
+    """Layers that end 1 to 7 elements into a group of 8, all values negative or all positive."""
+    shifted = lambda rng, n, scale: (scale + 0.7 * rng.standard_normal(n)).astype(np.float32)
+    sizes = [length for end in range(1, 8) for length in (end, 8 * 5 + end, bucket + end, 2048 + bucket + 8 * 3 + end)]
+    w = wl.Workload("one sign", [(s,) for s in sizes], np.full(len(sizes), bits, np.uint8), bucket, dt, 2, 60 + bits, shifted,
+                    np.where(np.arange(len(sizes)) // 2 % 2 == 0, -3.0, 3.0))
+    full_cycle(torch, oracle, w, W=2, what="one sign")
+
+
 @pytest.mark.parametrize("bits", range(2, 9))
 @pytest.mark.parametrize("bucket", [32, 96, 1024])
 def test_units_of_any_size(torch, oracle, bucket, bits):
