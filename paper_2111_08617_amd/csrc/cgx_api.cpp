@@ -407,7 +407,7 @@ int quantize_impl(int scheme, const void *grad, int64_t n, int32_t L, const int6
             cgx::mapping_of(part.bucket, part.chunk) == cgx::kMapWide
                 ? cgx::launch_quantize_wide(scheme, grad, dt, tiles, part.count, draws_of(part), part.longest, seed, packed, meta,
                                             launch_config(), queue)
-                : launch_quantize(scheme, grad, dt, tiles, part.count, draws_of(part), part.aligned, part.bucket, seed, packed, meta,
+                : launch_quantize(scheme, grad, dt, tiles, part.count, draws_of(part), part.through_lds(), part.bucket, seed, packed, meta,
                                   launch_config(), queue);
         if (e != hipSuccess) return CGX_ERR_HIP;
     }

@@ -39,15 +39,14 @@ enum Draws {
     kDrawsOdd = 2        // some on an odd one: these draw across generator words
 };
 
-// aligned_tiles: every vectorised tile starts on a 16-byte boundary of the buffer (its chunks can then be
-// fetched through LDS with whole-line loads).
+// through_lds: TablePart::through_lds().
 // The quantize kernel is built for chunks of 1024 elements (_g2: two groups of 8 per lane) and of 2048
 // (_g4); `tiles` must have been built for that chunk size.
 hipError_t launch_quantize_g2(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, int draws,
-                              bool aligned_tiles, int32_t bucket, uint64_t seed, void *packed, void *meta,
+                              bool through_lds, int32_t bucket, uint64_t seed, void *packed, void *meta,
                               const LaunchConfig &cfg, hipStream_t stream);
 hipError_t launch_quantize_g4(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, int draws,
-                              bool aligned_tiles, int32_t bucket, uint64_t seed, void *packed, void *meta,
+                              bool through_lds, int32_t bucket, uint64_t seed, void *packed, void *meta,
                               const LaunchConfig &cfg, hipStream_t stream);
 // Chunk size of every other kernel (reduce, fused, statistics).
 constexpr int kDefaultChunk = chunk_of(4);

@@ -116,6 +116,10 @@ struct TablePart {
     bool odd = false;            // some quantized tile starts on an odd element index
     bool quads = true;           // every quantized tile starts on a multiple of 8 elements
     bool aligned = true;         // every vectorised quantized tile starts on a 16-byte boundary of the buffer
+
+    // The quantizer fetches the part's chunks through LDS, with whole-line loads.  Short tiles that start elsewhere have no say
+    // in it, but for an odd start, whose draws take a kernel that is not built for both.
+    bool through_lds() const { return aligned && !odd && mapping_of(bucket, chunk) == kMapBuckets; }
 };
 
 // The table of a plan, which all calls with the same chunk and tile lengths share: a program that has run one of them

@@ -6,7 +6,7 @@ namespace {
 
 // DRAWS: where the plan's quantized tiles start (see encode_group).
 // VIA_LDS: every vectorised tile starts on a 16-byte boundary and the bucket-major mapping reads its
-// chunks through LDS (see chunk_through_lds); never with kDrawsOdd, and with kDrawsEven for binary32 only.
+// chunks through LDS (see chunk_through_lds); never with kDrawsOdd.
 template <int SCHEME, int DT, int MAP, int DRAWS, bool VIA_LDS = false>
 __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict__ grad,
                                                            const Tile *__restrict__ tiles, int64_t n_tiles,
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kBlock) void quantize_kernel(const void *__restrict
 
 // This file is compiled once per chunk size (CGX_GROUPS = 2 and 4): launch_quantize_g2, launch_quantize_g4.
 hipError_t CGX_CONCAT(launch_quantize_g, CGX_GROUPS)(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, int draws,
-                           bool aligned_tiles, int32_t bucket, uint64_t seed, void *packed, void *meta,
+                           bool through_lds, int32_t bucket, uint64_t seed, void *packed, void *meta,
                            const LaunchConfig &cfg, hipStream_t stream)
 {
     if (n_tiles == 0) return hipSuccess;
@@ -97,17 +97,16 @@ hipError_t CGX_CONCAT(launch_quantize_g, CGX_GROUPS)(int scheme, const void *gra
                                              CGX_QUANTIZE_SCHEMES(kDrawsOdd)};
 #undef CGX_QUANTIZE_SCHEMES
 #undef CGX_QUANTIZE_MAPS
-    // (a 16-byte boundary is a multiple of 8 elements of binary16)
-    static const Kernel through_lds[2][2][2] = {
-        {{quantize_kernel<kMinMax, CGX_F32, kMapBuckets, kDrawsQuad, true>, quantize_kernel<kMinMax, CGX_F16, kMapBuckets, kDrawsQuad, true>},
-         {quantize_kernel<kNormSign, CGX_F32, kMapBuckets, kDrawsQuad, true>,
-          quantize_kernel<kNormSign, CGX_F16, kMapBuckets, kDrawsQuad, true>}},
-        {{quantize_kernel<kMinMax, CGX_F32, kMapBuckets, kDrawsEven, true>, nullptr},
-         {quantize_kernel<kNormSign, CGX_F32, kMapBuckets, kDrawsEven, true>, nullptr}}};
-    const bool via_lds = aligned_tiles && draws <= (dt == CGX_F32 ? kDrawsEven : kDrawsQuad) &&
-                         mapping_of(bucket, kChunk) == kMapBuckets && cfg.via_lds;
-    const Kernel kernel = via_lds ? through_lds[draws][scheme == kSchemeNormSign][dt == CGX_F16]
-                                  : table[draws][scheme == kSchemeNormSign][dt == CGX_F16][mapping_of(bucket, kChunk)];
+#define CGX_QUANTIZE_LDS(S, O) {quantize_kernel<S, CGX_F32, kMapBuckets, O, true>, quantize_kernel<S, CGX_F16, kMapBuckets, O, true>}
+    // (binary16 with kDrawsEven: whole chunks on 16 bytes, and a layer of less than a chunk that starts on 2, 4 or 6 mod 8.
+    // Quantize of 105 M and 26 M elements beside such a layer, 4 bit, buckets of 128, us through LDS and without: 57 and 61,
+    // 15.9 and 17.5; 105 M at 2 bits 47.5 and 53.5)
+    static const Kernel lds_table[2][2][2] = {{CGX_QUANTIZE_LDS(kMinMax, kDrawsQuad), CGX_QUANTIZE_LDS(kNormSign, kDrawsQuad)},
+                                              {CGX_QUANTIZE_LDS(kMinMax, kDrawsEven), CGX_QUANTIZE_LDS(kNormSign, kDrawsEven)}};
+#undef CGX_QUANTIZE_LDS
+    const Kernel kernel = through_lds && draws != kDrawsOdd && cfg.via_lds
+                              ? lds_table[draws][scheme == kSchemeNormSign][dt == CGX_F16]
+                              : table[draws][scheme == kSchemeNormSign][dt == CGX_F16][mapping_of(bucket, kChunk)];
     hipLaunchKernelGGL(kernel, grid, block, 0, stream, grad, tiles, n_tiles, seed_lo, seed_hi,
                        static_cast<uint8_t *>(packed), static_cast<float *>(meta));
     return hipGetLastError();

@@ -213,6 +213,27 @@ static void check_table(const Plan &p, int bucket, int dt, int chunk, int chunks
     for (int c : covered) CHECK(c == 1);
 }
 
+// Which plans' chunks the quantizer fetches through LDS: all whose whole chunks start on 16 bytes, wherever on an even element
+// their short tiles start.
+static void check_through_lds()
+{
+    using namespace cgx;
+    const struct {
+        std::vector<int64_t> sizes;
+        int dt;
+        bool quads, through_lds;
+    } plans[] = {{{204800, 8, 8, 204800}, CGX_F16, true, true},   {{204800, 4, 12, 204800}, CGX_F16, false, true},
+                 {{204800, 4, 12, 204800}, CGX_F32, false, true}, {{204800, 3, 13, 204800}, CGX_F16, false, false},
+                 {{204800, 4, 204800}, CGX_F16, false, false},    {{204800, 4, 204800}, CGX_F32, false, true}};
+    for (const auto &plan : plans) {
+        std::vector<int64_t> off(1, 0);
+        for (int64_t size : plan.sizes) off.push_back(off.back() + size);
+        const std::vector<uint8_t> bits(plan.sizes.size(), 4);
+        const PlanTable table = build_table(int32_t(bits.size()), off.data(), bits.data(), 128, plan.dt, plan.dt == CGX_F16 ? 2048 : 1024, 1, false);
+        CHECK(table.parts.size() == 1 && table.parts[0].quads == plan.quads && table.parts[0].through_lds() == plan.through_lds);
+    }
+}
+
 static void check_piece_division(std::mt19937 &rng)
 {
     for (uint32_t pieces = 2; pieces <= 8; pieces++)
@@ -301,6 +322,7 @@ int main()
 {
     std::mt19937 rng(12345);
     check_piece_division(rng);
+    check_through_lds();
     const int buckets[] = {32, 64, 96, 128, 512, 1024, 2048, 4096, 8192, 8160};
     int plans = 0;
     for (int bucket : buckets) {

@@ -674,6 +674,17 @@ def test_draws_follow_where_the_tiles_start(torch, oracle, start, bits, dt):
 
 @pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
 @pytest.mark.parametrize("bits", range(1, 9))
+@pytest.mark.parametrize("short", [2, 4, 6])
+def test_aligned_chunks_beside_a_short_layer_that_is_not(torch, oracle, short, bits, dt):
+    """Every whole chunk starts on 16 bytes (and is fetched through LDS), one short layer 2, 4 or 6 elements past them."""
+    sizes = [2048 * 9 + 24, short, 16 - short, 2048 * 6, 128 * 3]
+    w = wl.Workload("beside", [(s,) for s in sizes], np.full(len(sizes), bits, np.uint8), 128, dt, 2, 90 + bits, wl._normal,
+                    np.full(len(sizes), 0.3))
+    full_cycle(torch, oracle, w, W=2, seed_shift=short, what=f"short layer at {short}")
+
+
+@pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("bits", range(1, 9))
 @pytest.mark.parametrize("bucket", [32, 96, 128, 2048, 2080, 4096])
 def test_ends_within_a_group_where_all_values_have_one_sign(torch, oracle, bucket, bits, dt):
     """Layers that end 1 to 7 elements into a group of 8, alone and behind whole buckets and chunks, whose values all lie
