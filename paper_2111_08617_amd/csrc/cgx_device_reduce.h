@@ -31,8 +31,11 @@ __device__ __forceinline__ void signed_bytes_to_float(uint32_t t, float &b0, flo
 }
 
 // Levels of one group of 8 codes as floats (kNormSign: signed levels).
-// Bound by the vector ALUs.  Signed codes of 2 and 4 bits become signed bytes first, four at a time: a conversion of a
-// signed byte costs what one of an unsigned byte does.
+// Bound by the vector ALUs.  Signed 4-bit codes become signed bytes first, four at a time: a conversion of a signed byte
+// costs what one of an unsigned byte does, and no 8.0 has to be subtracted per code (fused step of 8 peers, 14.7 M elements, 24.4 ->
+// 22.1 us, 67 M 87.4 -> 80.7; the reduce is bound by memory: 23.9 both ways).  Signed 2-bit codes are extracted one by one: as bytes
+// that v_perm_b32 selects, four at a time, the same calls take 20.6 us for 19.3 and 76 for 70.5, and the reduce of 14.7 M 20.6 for
+// 17.8 (of 2 peers' 12.4 for 13.0).
 template <int SCHEME, int BITS>
 __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
 {
@@ -59,20 +62,11 @@ __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
             bytes_to_float(opaque(w & 0x0f0f0f0fu), f[0], f[2], f[4], f[6]);
             bytes_to_float(opaque((w >> 4) & 0x0f0f0f0fu), f[1], f[3], f[5], f[7]);
         }
-    } else if (BITS == 2) {
+    } else if (BITS == 2 && !kSigned) {
         // four codes per register: the upper half holds the codes that follow those of the lower half
         const uint32_t x = opaque(((w & 0xffffu) << 14) | (w & 0xffffu));
-        if (kSigned) {
-            // every code selects its level from the four bytes 0, 1, -2, -1
-            constexpr uint32_t kLevels = 0xfffe0100u;
-            const uint32_t lo = __builtin_amdgcn_perm(0u, kLevels, x & 0x03030303u);
-            const uint32_t hi = __builtin_amdgcn_perm(0u, kLevels, (x >> 4) & 0x03030303u);
-            signed_bytes_to_float(opaque(lo), f[0], f[4], f[1], f[5]);
-            signed_bytes_to_float(opaque(hi), f[2], f[6], f[3], f[7]);
-        } else {
-            bytes_to_float(opaque(x & 0x03030303u), f[0], f[4], f[1], f[5]);
-            bytes_to_float(opaque((x >> 4) & 0x03030303u), f[2], f[6], f[3], f[7]);
-        }
+        bytes_to_float(opaque(x & 0x03030303u), f[0], f[4], f[1], f[5]);
+        bytes_to_float(opaque((x >> 4) & 0x03030303u), f[2], f[6], f[3], f[7]);
     } else if (kSigned) {
 #pragma unroll
         for (int j = 0; j < 8; j++)      // sign-extending field extract
