@@ -152,7 +152,7 @@ static void check_table(const Plan &p, int bucket, int dt, int chunk, int chunks
             CHECK(mapping_of(part.bucket, part.chunk) > mapping_of(table.parts[k - 1].bucket, part.chunk));
         if (k > 0) CHECK(part.chunk >= table.parts[k - 1].chunk);
         next += part.count;
-        bool odd = false, aligned = true;
+        bool odd = false, quads = true, aligned = true;
         for (int64_t t = part.first; t < part.first + part.count; t++) {
             const Tile &tile = table.tiles[size_t(t)];
             const size_t l = check_tile(tile, true);
@@ -167,9 +167,10 @@ static void check_table(const Plan &p, int bucket, int dt, int chunk, int chunks
             else CHECK(int(tile.count) <= (tile_kind(tile) == kQuantFast ? chunks_per_tile : 1) * part.chunk);
             if (long_chunk) CHECK((own_bucket(l) > chunk) == (part.chunk == long_chunk));
             odd |= tile.elem0 & 1;
+            quads &= tile.elem0 % 8 == 0;
             if (is_vector_kind(tile_kind(tile))) aligned &= tile.elem0 * (dt == CGX_F16 ? 2 : 4) % 16 == 0;
         }
-        CHECK(odd == part.odd && aligned == part.aligned);
+        CHECK(odd == part.odd && quads == part.quads && aligned == part.aligned);
     }
     CHECK(next == int64_t(table.tiles.size()));
     for (int c : covered) CHECK(c == 1);

@@ -70,6 +70,13 @@ def gpu_fused(torch, chunks, metas, offsets, bits, bucket, dt, seed):
     return p[:pb], m[:mb // 4].reshape(-1, 2)
 
 
+def scale_rounded_up(levels, times):
+    """A binary16 value a for which (levels * 65536) / (times * a) rounds up in binary32."""
+    for a in 1.0 + np.arange(1, 1024) / 1024:
+        if float(np.float32(levels * 65536) / np.float32(times * a)) * (times * a) > levels * 65536:
+            return a
+
+
 def assert_same_chunk(gp, gm, op, om, what=""):
     assert gm.tobytes() == om.tobytes(), f"{what}: meta differs in {int((gm.view(np.uint32) != om.view(np.uint32)).sum())} words"
     if not np.array_equal(gp, op):
@@ -657,16 +664,17 @@ def test_layers_that_start_anywhere(torch, oracle, bucket, dt):
 @pytest.mark.parametrize("start", [0, 8, 2, 4, 7])
 def test_draws_follow_where_the_tiles_start(torch, oracle, start, bits, dt):
     """Plans whose quantized tiles all start on a multiple of 8 elements, all on even ones, or some on odd ones take kernels
-    that form their draws differently; chunks and a ragged end of every width, values at both ends of every bucket (the top
-    level is reached exactly, with the largest draws, without a clamp)."""
-    sizes = [start] * (start > 0) + [2048 * 3 + 8 * 5]
+    that form their draws differently; chunks and an end within a group, of every width; two values per bucket, whose range's
+    scale is rounded up."""
+    sizes = [start] * (start > 0) + [2048 * 3 + 8 * 5 + 3]
     w = wl.Workload("start", [(s,) for s in sizes], np.array([0] * (start > 0) + [bits], np.uint8), 128, dt, 2, 40 + start,
                     wl._normal, np.full(len(sizes), 0.3))
     tiles = cgx.cgx_plan_tiles(cgx.Plan(w.offsets, w.bits, w.bucket, w.dt))
     quantized = tiles["elem0"][((tiles["info"] >> 4) & 15) != 3]
     assert ((quantized % 8) == start % 8).any()
     full_cycle(torch, oracle, w, W=2, seed_shift=start, what=f"start {start} bits {bits}")
-    g = np.where(np.arange(w.n) % 3 == 0, -1.5, 1.5).astype(w.gradient(0).dtype)      # two values per bucket: levels 0 and the top
+    a = scale_rounded_up((1 << bits) - 1, 2)
+    g = np.where(np.arange(w.n) % 3 == 0, -a, a).astype(w.gradient(0).dtype)      # levels 0 and the top
     op, om = oracle.quantize(g, w.offsets, w.bits, w.bucket, 3, w.dt)
     gp, gm = gpu_quantize(torch, g, w.offsets, w.bits, w.bucket, 3, w.dt)
     assert_same_chunk(gp, gm, op, om, "two values")

@@ -229,13 +229,15 @@ def test_layers_that_start_anywhere(torch, oracle, bucket, dt):
 @pytest.mark.parametrize("bits", range(2, 9))
 @pytest.mark.parametrize("start", [0, 2, 4, 7])
 def test_draws_follow_where_the_tiles_start(torch, oracle, start, bits, dt):
-    """Quantized tiles on multiples of 8 elements, on even and on odd ones; both signs of the top level (reached exactly,
-    without a clamp) and zeros of either sign."""
-    sizes = [start] * (start > 0) + [2048 * 3 + 8 * 5]
+    """Quantized tiles on multiples of 8 elements, on even and on odd ones; both signs of the top level (of a norm whose scale
+    is rounded up) and zeros of either sign."""
+    sizes = [start] * (start > 0) + [2048 * 3 + 8 * 5 + 3]
     w = wl.Workload("start", [(s,) for s in sizes], np.array([0] * (start > 0) + [bits], np.uint8), 128, dt, 2, 60 + start,
                     wl._normal, np.full(len(sizes), 0.3))
     full_cycle(torch, oracle, w, W=2, what=f"start {start} bits {bits}")
-    g = np.array([-1.5, 0.0, 1.5, -0.0], w.gradient(0).dtype)[np.arange(w.n) % 4]
+    levels = ((1 << bits - 1) - 1) * 65536
+    a = next(a for a in 1.0 + np.arange(1, 1024) / 1024 if float(np.float32(levels) / np.float32(a)) * a > levels)
+    g = np.array([-a, 0.0, a, -0.0], w.gradient(0).dtype)[np.arange(w.n) % 4]
     op, om = oracle.qsgd_quantize(g, w.offsets, w.bits, w.bucket, 3, w.dt)
     gp, gm = gpu_quantize(torch, g, w.offsets, w.bits, w.bucket, 3, w.dt)
     assert_same_chunk(gp, gm, op, om, "top levels and zeros")
@@ -256,19 +258,18 @@ def test_ends_within_a_group_where_all_values_have_one_sign(torch, oracle, bucke
 @pytest.mark.parametrize("bits", range(2, 9))
 @pytest.mark.parametrize("bucket", [32, 96, 1024])
 def test_units_of_any_size(torch, oracle, bucket, bits):
-    """Chunks with units that a quantizer of another program may write: the smallest, those whose 64th part is no longer
-    exact and the first whose is, the largest, zeros of either sign and values that are not finite; every code occurs."""
+    """Chunks with units that a quantizer of another program may write: the smallest, subnormal and small ones, the
+    largest, zeros of either sign, negative ones and values that are not finite; every code occurs."""
     n, W = 2048 * 2 + 96 * 5, 5
     off, widths = np.array([0, n], np.int64), np.array([bits], np.uint8)
     rng = np.random.default_rng(bits * 10000 + bucket)
     x = rng.standard_normal(n).astype(np.float32)
     chunk, meta = oracle.qsgd_quantize(x, off, widths, bucket, 1)
-    below, first = np.nextafter(np.float32(2.0 ** -120), np.float32(0)), np.float32(2.0 ** -120)
-    special = np.array([1.4e-45, 1e-40, 1.1754942e-38, below, -below, 0.0, -0.0, first, -first, 1.0, 3e38, np.inf, np.nan],
-                       np.float32)
+    small = np.float32(2.0 ** -120)
+    special = np.array([1.4e-45, 1e-40, 1.1754942e-38, np.nextafter(small, np.float32(0)), -small, 0.0, -0.0, small, -1.0, 1.0, 3e38,
+                        np.inf, np.nan], np.float32)
     chunks = [rng.integers(0, 256, chunk.size, dtype=np.uint8) for _ in range(W)]
-    for few in (True, False):       # a wave with such units beside ordinary ones, then without any that is not exact
-        units = special if few else special[5:]
+    for units in (special, special[5:]):       # with subnormal units in a chunk, and without
         metas = [rng.choice(units, meta.size).astype(np.float32) for _ in range(W)]
         ref = oracle.qsgd_dequant_reduce(chunks, metas, off, widths, bucket, wl.F32)["sum32"]
         got, _ = gpu_reduce(torch, chunks, metas, off, widths, bucket, wl.F32)

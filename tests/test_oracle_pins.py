@@ -208,6 +208,21 @@ def test_error_at_most_one_step(oracle, b, dt):
     assert np.allclose(m[:, 0], rng_, rtol=1e-6)
 
 
+@pytest.mark.parametrize("b", range(1, 8))
+def test_no_value_passes_the_top_level_up_to_7_bits(b):
+    """The kernels cut codes of up to 7 bits without a minimum: the largest value's position, trunc(range * inv16) with
+    inv16 = (Lv * 65536) / range rounded up or down, plus the largest draw stays on the top level.  Ranges whose
+    inv16 rounds up are among them, at every scale.  (A position of 8 bits may exceed 255 * 65536.)"""
+    Lv = (1 << b) - 1
+    rng = np.random.default_rng(b)
+    r = np.concatenate([rng.uniform(0.5, 1.0, 400_000), 1.0 - 2.0 ** -24 * np.arange(100_000)]).astype(np.float32)
+    r = np.concatenate([r, r * np.float32(2.0 ** 100), r * np.float32(2.0 ** -80)])
+    inv16 = (np.float32(Lv * 65536) / r).astype(np.float32)
+    assert (inv16.astype(np.float64) * r > Lv * 65536).sum() > 100_000           # exact product of two binary32
+    T = np.trunc(r * inv16).astype(np.int64)
+    assert ((T + 65535) >> 16).max() == Lv
+
+
 @pytest.mark.parametrize("b", [1, 2, 3, 4, 7, 8])
 def test_grid_points_round_trip_exactly(oracle, b):
     """Values already on a power-of-two grid have p = 0: exact for every seed."""
