@@ -41,16 +41,17 @@ __device__ __forceinline__ uint32_t signed_bytes(uint32_t level, uint32_t sign)
 // instruction), or the fold of the 2-bit codes would carry what is above the field down into the codes of elements that are
 // there.  (kNormSign: a missing element's level is 0.)
 //
-// Measured with the draws of kDrawsQuad below, builds in turn on one box, us: binary16 quantize of 355 M elements 156.7 -> 144.9;
-// 25.6 M binary32 elements 20.1 -> 19.9, the fused step of a 13.7 M share of 8 peers 20.2 -> 19.5, norm-and-sign reduce and
-// requantize of it 33.9 -> 32.9.  1.3 G binary32 elements are bound by memory alone and stay at 988.
+// Measured with the draws of kDrawsQuad below, builds in turn on one box, us: binary16 quantize of 355 M elements 155.0 -> 144.0,
+// the fused step of a 13.7 M share of 8 peers 19.4 -> 18.5, norm-and-sign reduce and requantize of it 33.8 -> 32.7.  25.6 M and 1.3 G
+// binary32 elements are bound by memory and stay at 19.8 and 988.
 
 // The 8 codes of one group, packed: element j of the group has buffer index 2 * pair0 + odd + j, key = generator key of
 // the tile.  odd (0 or 1, uniform over a tile: groups start 8 elements apart) tells whether the group starts on the upper
 // half of a generator word; then its 8 draws are the 16-bit halves 1..8 of words pair0 .. pair0 + 4 instead of halves
 // 0..7 of words pair0 .. pair0 + 3.  DRAWS (Draws, cgx_kernels.h; the host picks the instantiation): kDrawsOdd alone pays for
 // the fifth word and the selection, and kDrawsQuad knows that pair0 is a multiple of 4: no carry leaves its two lowest bits,
-// so the words of its four pairs differ in them alone until the first multiplication.
+// so the words of its four pairs differ in them alone until the first multiplication: 3 instructions fewer of 76 (by itself, us:
+// binary16 quantize of 372 M elements 159 -> 155, fused step of 14.7 M elements and 8 peers 20.65 -> 20.4).
 template <int SCHEME, int BITS, int DRAWS>
 __device__ __forceinline__ uint64_t encode_group(const float (&x)[8], const Scale &s, uint32_t pair0, uint32_t key,
                                                  uint32_t odd_start)
