@@ -30,13 +30,34 @@ __device__ __forceinline__ void signed_bytes_to_float(uint32_t t, float &b0, flo
     b3 = float(int32_t(t) >> 24);
 }
 
-// Levels of one group of 8 codes as floats (kNormSign: signed levels).
-// Bound by the vector ALUs.  Signed 4-bit codes become signed bytes first, four at a time: a conversion of a signed byte
-// costs what one of an unsigned byte does, and no 8.0 has to be subtracted per code (fused step of 8 peers, 14.7 M elements, 24.4 ->
-// 22.1 us, 67 M 87.4 -> 80.7; the reduce is bound by memory: 23.9 both ways).  Signed 2-bit codes are extracted one by one: as bytes
-// that v_perm_b32 selects, four at a time, the same calls take 20.6 us for 19.3 and 76 for 70.5, and the reduce of 14.7 M 20.6 for
-// 17.8 (of 2 peers' 12.4 for 13.0).
-template <int SCHEME, int BITS>
+// Two conversions per instruction: v_cvt_scalef32_pk_f32_fp8 / _fp4 turn two bytes, or the two nibbles of a byte, into floats
+// and multiply them by a power of two, at 4.9 cycles of a SIMD where one v_cvt_f32_ubyte takes 4.7.  Codes are small whole
+// numbers, and the subnormals and the first binade of such a format form one linear grid: an E4M3 byte q <= 15 is q / 512, an E2M1
+// nibble q <= 3 is q / 2.  Times 512 (2) that is float(q), exactly.  Builds in turn on one box, us: a 13.7 M share of 8 peers in one
+// fused step (2, 3, 4 and 8 bits) 18.6 -> 17.8, 16.8 M elements of 4 bits 22.3 -> 21.4, of 2 bits 20.6 -> 20.3; the reduce of 34 M at
+// 2 bits 61.0 -> 59.7, of the ResNet-50 plan with its requantize 54.1 -> 53.9.  Not taken where it measured slower: 3-bit
+// codes spread to bytes (fused, 8 peers, 23.7 -> 24.8), signed 2-bit codes as nibbles of sign and magnitude (21.8 -> 22.6), and
+// 2-bit codes of a single peer, bound by what they write (67 M elements in 4 shares 47.5 -> 47.9).
+constexpr float kByteScale = 512.0f, kNibbleScale = 2.0f;
+
+__device__ __forceinline__ void small_bytes_to_float(uint32_t t, float &b0, float &b1, float &b2, float &b3)
+{
+    const auto lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(t, kByteScale, false);
+    const auto hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(t, kByteScale, true);
+    b0 = lo[0], b1 = lo[1], b2 = hi[0], b3 = hi[1];
+}
+
+// Eight nibbles of at most 3, lowest first.
+__device__ __forceinline__ void nibbles_to_float(uint32_t t, float (&f)[8])
+{
+    const auto p0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(t, kNibbleScale, 0), p1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(t, kNibbleScale, 1);
+    const auto p2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(t, kNibbleScale, 2), p3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(t, kNibbleScale, 3);
+    f[0] = p0[0], f[1] = p0[1], f[2] = p1[0], f[3] = p1[1];
+    f[4] = p2[0], f[5] = p2[1], f[6] = p3[0], f[7] = p3[1];
+}
+
+// Levels of one group of 8 codes as floats (kNormSign: signed levels).  SINGLE: of the only peer.
+template <int SCHEME, int BITS, bool SINGLE>
 __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
 {
     constexpr bool kSigned = SCHEME == kNormSign;
@@ -59,14 +80,24 @@ __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
             signed_bytes_to_float(opaque(even), f[0], f[2], f[4], f[6]);
             signed_bytes_to_float(opaque(odd), f[1], f[3], f[5], f[7]);
         } else {
-            bytes_to_float(opaque(w & 0x0f0f0f0fu), f[0], f[2], f[4], f[6]);
-            bytes_to_float(opaque((w >> 4) & 0x0f0f0f0fu), f[1], f[3], f[5], f[7]);
+            small_bytes_to_float(w & 0x0f0f0f0fu, f[0], f[2], f[4], f[6]);
+            small_bytes_to_float((w >> 4) & 0x0f0f0f0fu, f[1], f[3], f[5], f[7]);
         }
-    } else if (BITS == 2 && !kSigned) {
+    } else if (BITS == 2 && !kSigned && SINGLE) {
         // four codes per register: the upper half holds the codes that follow those of the lower half
         const uint32_t x = opaque(((w & 0xffffu) << 14) | (w & 0xffffu));
         bytes_to_float(opaque(x & 0x03030303u), f[0], f[4], f[1], f[5]);
         bytes_to_float(opaque((x >> 4) & 0x03030303u), f[2], f[6], f[3], f[7]);
+    } else if (BITS == 2 && !kSigned) {
+        // a code per nibble: codes 0, 2, 4, 6 in the lower half of the register, the odd ones in the upper half
+        const uint32_t codes = (((w & 0xffffu) << 14) | (w & 0xffffu)) & 0x33333333u;
+        float n[8];
+        nibbles_to_float(codes, n);
+#pragma unroll
+        for (int k = 0; k < 4; k++) {
+            f[2 * k] = n[k];
+            f[2 * k + 1] = n[4 + k];
+        }
     } else if (kSigned) {
 #pragma unroll
         for (int j = 0; j < 8; j++)      // sign-extending field extract
@@ -76,31 +107,6 @@ __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
 #pragma unroll
         for (int j = 0; j < 8; j++) f[j] = float(uint32_t((v >> (j * BITS)) & kMask));
     }
-}
-
-// ---- two conversions per instruction (min/max codes of 4 bits)
-//
-// A code q <= 15 alone in a byte is also the 8-bit float (E4M3) q / 512: the subnormals and the
-// first binade of that format form one linear grid.  v_cvt_pk_f32_fp8 converts two bytes per
-// instruction, exactly, and fma(q / 512, unit * 512, mn) is bit for bit fma(float(q), unit, mn):
-// scaling by a power of two is exact unless unit * 512 overflows, which the caller rules out per
-// peer.  A pair of conversions costs a SIMD little more than one v_cvt_f32_ubyte.
-template <int SCHEME, int BITS>
-constexpr bool kPairedConversion = SCHEME == kMinMax && BITS == 4;
-constexpr float kPairedScale = 512.0f;
-
-// false: unit * 512 would not be finite (or unit is not) and the codes take the plain conversion
-__device__ __forceinline__ bool paired_usable(float2 m) { return __builtin_fabsf(m.x) < 0x1p118f; }
-
-// Levels / 512 of one group of 8 codes of 4 bits.
-__device__ __forceinline__ void codes_to_scaled_float(uint32_t w, float (&f)[8])
-{
-    typedef float float2v __attribute__((ext_vector_type(2)));
-    const uint32_t even = w & 0x0f0f0f0fu, odd = (w >> 4) & 0x0f0f0f0fu;
-    const float2v e0 = __builtin_amdgcn_cvt_pk_f32_fp8(even, false), e1 = __builtin_amdgcn_cvt_pk_f32_fp8(even, true);
-    const float2v o0 = __builtin_amdgcn_cvt_pk_f32_fp8(odd, false), o1 = __builtin_amdgcn_cvt_pk_f32_fp8(odd, true);
-    f[0] = e0.x, f[2] = e0.y, f[4] = e1.x, f[6] = e1.y;
-    f[1] = o0.x, f[3] = o0.y, f[5] = o1.x, f[7] = o1.y;
 }
 
 // The codes of a lane's G groups of a run, group r's 8 in the low 8 * BITS bits of v[r] (bits above are unspecified).
@@ -135,13 +141,11 @@ __device__ __forceinline__ void run_codes(const uint8_t *codes, int lane, uint64
 // cover them are fetched (nvecs of them from the 16-byte boundary at or before in_off: they stay inside the layer's
 // segment, which starts and ends on 16 bytes).  What lies behind the run's end in LDS is stale, and so are the
 // sums of elements past the end: the caller drops them.
-// PAIRED: the two-per-instruction conversion above; the result says whether every peer's unit allowed it:
-// if not, acc holds garbage and the caller forms the sums again without PAIRED.
 template <int BITS>
 constexpr int kRunLead = BITS % 4 == 0 ? 0 : 16;      // bytes between that boundary and the first code, at most 12
 
-template <int SCHEME, int BITS, int WB, bool RUN, bool PAIRED, typename Peers>
-__device__ __forceinline__ bool reduce_peers(Peers &peers, int w0, int64_t in_off, uint32_t g,
+template <int SCHEME, int BITS, int WB, bool RUN, typename Peers>
+__device__ __forceinline__ void reduce_peers(Peers &peers, int w0, int64_t in_off, uint32_t g,
                                              const int (&code_off)[G], float (&acc)[G][8], uint4v *stage,
                                              int lane, int nvecs)
 {
@@ -169,13 +173,8 @@ __device__ __forceinline__ bool reduce_peers(Peers &peers, int w0, int64_t in_of
     wait_vector_memory();
     wave_lds_fence();
     const uint8_t *codes = reinterpret_cast<const uint8_t *>(stage) + lead;
-    bool usable = true;
 #pragma unroll
     for (int i = 0; i < WB; i++) {
-        if constexpr (PAIRED && kPairedConversion<SCHEME, BITS>) {
-            usable = usable && paired_usable(m[i]);
-            m[i].x *= kPairedScale;
-        }
         uint64_t run[G];
         if constexpr (RUN) run_codes<BITS>(codes + i * kBytes, lane, run);
 #pragma unroll
@@ -186,10 +185,7 @@ __device__ __forceinline__ bool reduce_peers(Peers &peers, int w0, int64_t in_of
                 v = run[r];
             else
                 v = staged_codes<BITS>(codes + i * kBytes, code_off[r]);
-            if constexpr (PAIRED && kPairedConversion<SCHEME, BITS>)
-                codes_to_scaled_float(uint32_t(v), f);
-            else
-                codes_to_float<SCHEME, BITS>(v, f);
+            codes_to_float<SCHEME, BITS, WB == 1>(v, f);
 #pragma unroll
             for (int j = 0; j < 8; j++) acc[r][j] = __fadd_rn(acc[r][j], decode<SCHEME>(f[j], m[i]));
         }
@@ -197,7 +193,6 @@ __device__ __forceinline__ bool reduce_peers(Peers &peers, int w0, int64_t in_of
         if (i % 2 == 1) __builtin_amdgcn_sched_barrier(0);
     }
     wave_lds_fence();
-    return __builtin_amdgcn_ballot_w64(!usable) == 0;
 }
 
 // peers staged together: 8 if their packed bytes fit the staging area (one chunk of sums,
@@ -208,9 +203,8 @@ template <int BITS>
 constexpr int kPeerBlock = (kStagedOverRead<BITS> != 0 || 8 * (kChunk * BITS / 8) > kChunk * 4) ? 4 : 8;
 
 // Sum over the W peers of one chunk's dequantized values, added to acc in peer order.
-// PAIRED: as in reduce_peers; false is returned when the sums have to be formed again without it.
-template <int SCHEME, int BITS, bool PAIRED = false, typename Peers>
-__device__ __forceinline__ bool reduce_chunk(Peers &peers, int W, int64_t in_off, uint32_t g,
+template <int SCHEME, int BITS, typename Peers>
+__device__ __forceinline__ void reduce_chunk(Peers &peers, int W, int64_t in_off, uint32_t g,
                                              const LaneMap &map, float (&acc)[G][8], uint4v *stage, int lane)
 {
     constexpr int kBytes = kChunk * BITS / 8;
@@ -218,29 +212,24 @@ __device__ __forceinline__ bool reduce_chunk(Peers &peers, int W, int64_t in_off
     int code_off[G];
 #pragma unroll
     for (int r = 0; r < G; r++) code_off[r] = (map.group(r) >> 3) * BITS;
-    bool good = true;
     for_peer_blocks<kPeerBlock<BITS>>(W, [&](int w0, auto wb) {
-        good &= reduce_peers<SCHEME, BITS, decltype(wb)::value, false, PAIRED>(peers, w0, in_off, g, code_off, acc, stage,
-                                                                              lane, 0);
+        reduce_peers<SCHEME, BITS, decltype(wb)::value, false>(peers, w0, in_off, g, code_off, acc, stage, lane, 0);
     });
-    return good;
 }
 
 // The same for a run whose codes start at byte in_off and whose first bucket is bucket0.
-template <int SCHEME, int BITS, bool PAIRED = false, typename Peers>
-__device__ __forceinline__ bool reduce_run(Peers &peers, int W, int64_t in_off, uint32_t bucket0, const Run &run,
+template <int SCHEME, int BITS, typename Peers>
+__device__ __forceinline__ void reduce_run(Peers &peers, int W, int64_t in_off, uint32_t bucket0, const Run &run,
                                            float (&acc)[G][8], uint4v *stage, int lane)
 {
     constexpr int kBytes = kChunk * BITS / 8 + kRunLead<BITS>;
     static_assert(kPeerBlock<BITS> * kBytes + (G == 4 ? 0 : kStagedOverRead<BITS>) <= kChunk * 4, "staging area too small");
     const int nvecs = (int(in_off & 15) + (run.count * BITS + 7) / 8 + 15) / 16;
     const int unused[G] = {};
-    bool good = true;
     for_peer_blocks<kPeerBlock<BITS>>(W, [&](int w0, auto wb) {
-        good &= reduce_peers<SCHEME, BITS, decltype(wb)::value, true, PAIRED>(peers, w0, in_off, bucket0 + uint32_t(run.bi), unused,
-                                                                             acc, stage, lane, nvecs);
+        reduce_peers<SCHEME, BITS, decltype(wb)::value, true>(peers, w0, in_off, bucket0 + uint32_t(run.bi), unused, acc, stage, lane,
+                                                              nvecs);
     });
-    return good;
 }
 
 // -0 is the identity of binary32 addition for every addend, signed zeros included, so
@@ -253,17 +242,13 @@ __device__ __forceinline__ void clear_sums(float (&acc)[G][8])
         for (int j = 0; j < 8; j++) acc[r][j] = -0.0f;
 }
 
-// acc = the sums of a run over the W peers, with the paired conversion where the units allow it.
+// acc = the sums of a run over the W peers.
 template <int SCHEME, int BITS, typename Peers>
 __device__ __forceinline__ void sum_run(Peers &peers, int W, int64_t in_off, uint32_t bucket0, const Run &run,
                                         float (&acc)[G][8], uint4v *stage, int lane)
 {
     clear_sums(acc);
-    if (!reduce_run<SCHEME, BITS, true>(peers, W, in_off, bucket0, run, acc, stage, lane)) {
-        // a unit of 2^118 or more (or none at all): once more with the plain conversion
-        clear_sums(acc);
-        reduce_run<SCHEME, BITS>(peers, W, in_off, bucket0, run, acc, stage, lane);
-    }
+    reduce_run<SCHEME, BITS>(peers, W, in_off, bucket0, run, acc, stage, lane);
 }
 
 // The sums of a run's missing elements (stale LDS bytes decoded to anything) become 0.
@@ -363,8 +348,6 @@ __device__ __forceinline__ void reduce_fast(Peers &peers, int W, const SumIo &io
         float acc[G][8];
 #pragma unroll
         for (int r = 0; r < G; r++) init8(io, first + map.group(r), acc[r]);
-        // (the plain conversion: this kernel is bound by memory; the paired one cost it 4 registers and a wave per SIMD when
-        // it had 127, and has not been measured at its present 100)
         reduce_chunk<SCHEME, BITS>(peers, W, tile.packed_off + int64_t(c) * (kChunk * BITS / 8),
                                    tile.bucket0 + c * buckets_per_chunk + map.bi, map, acc, stage, lane);
         // the results leave through LDS as well, so that every store instruction writes 1 KB of

@@ -23,11 +23,7 @@ __device__ __forceinline__ void fused_fast(Peers &peers, int W, const Tile &tile
         clear_sums(acc);
         const int64_t in_off = tile.packed_off + int64_t(c) * (kChunk * BITS / 8);
         const uint32_t g = tile.bucket0 + c * buckets_per_chunk + map.bi;
-        if (!reduce_chunk<SCHEME, BITS, true>(peers, W, in_off, g, map, acc, stage, lane)) {
-            // a unit of 2^118 or more (or none at all): once more with the plain conversion
-            clear_sums(acc);
-            reduce_chunk<SCHEME, BITS>(peers, W, in_off, g, map, acc, stage, lane);
-        }
+        reduce_chunk<SCHEME, BITS>(peers, W, in_off, g, map, acc, stage, lane);
         quantize_chunk<SCHEME, BITS, DRAWS>(acc, map, lane, tile.elem0 + int64_t(c) * kChunk, key,
                                      meta_out + kMetaFloats<SCHEME> * (tile.bucket0 + c * buckets_per_chunk),
                                      packed_out + out_off + int64_t(c) * (kChunk * BITS / 8), stage);
