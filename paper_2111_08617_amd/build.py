@@ -11,12 +11,13 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libcgx.so")
 ARGS = os.path.join(HERE, "_cgx_args.so")
 OBJ = os.path.join(HERE, "_build")
-# (source, object name, extra flags): the quantize kernel is built for chunks of 1024 and of 2048 elements
+# (source, object name, extra flags): the quantize, reduce and fused kernels are built for chunks of 1024 and of 2048 elements
 SOURCES = [("cgx_plan.cpp", "cgx_plan", []), ("cgx_api.cpp", "cgx_api", []), ("cgx_adaptive.cpp", "cgx_adaptive", []),
            ("cgx_quantize.hip", "cgx_quantize_g2", ["-DCGX_GROUPS=2"]),
            ("cgx_quantize.hip", "cgx_quantize_g4", ["-DCGX_GROUPS=4"]),
            ("cgx_reduce.hip", "cgx_reduce_g2", ["-DCGX_GROUPS=2"]),
-           ("cgx_reduce.hip", "cgx_reduce_g4", ["-DCGX_GROUPS=4"]), ("cgx_fused.hip", "cgx_fused", []), ("cgx_wide.hip", "cgx_wide", []),
+           ("cgx_reduce.hip", "cgx_reduce_g4", ["-DCGX_GROUPS=4"]), ("cgx_fused.hip", "cgx_fused_g2", ["-DCGX_GROUPS=2"]),
+           ("cgx_fused.hip", "cgx_fused_g4", ["-DCGX_GROUPS=4"]), ("cgx_wide.hip", "cgx_wide", []),
            ("cgx_stats.hip", "cgx_stats", []),
            ("cgx_probe.hip", "cgx_probe", [])]
 

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdlib>
 #include <cstring>
 #include <memory>
@@ -51,6 +52,8 @@ struct CachedPlan {
     uint32_t *d_slots = nullptr;
     int64_t *d_layer_first = nullptr;
     uint64_t last_use = 0;      // cache clock at the latest look-up
+    // a fused call has made sure of the table of kDefaultChunk chunks beside this one, see fused_impl
+    mutable std::atomic<bool> beside_default{false};
     bool pinned = false;        // a stream capture has recorded launches that read these tables: never dropped
 };
 
@@ -488,16 +491,30 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
     return CGX_OK;
 }
 
+// Most elements of a fused call in chunks of 1024 elements: 7 waves on each of 1024 SIMDs.
+constexpr int64_t kMostShortFused = int64_t(7) << 20;
+
 int fused_impl(int scheme, const void *const *packed, const void *const *meta, int32_t W, int64_t n, int32_t L,
                const int64_t *layer_offsets, const uint8_t *bits_per_layer, const Buckets &buckets, int dt,
                uint64_t seed, void *packed_out, void *meta_out, void *stream)
 {
     const hipStream_t queue = static_cast<hipStream_t>(stream);
-    const TableKind kind{cgx::kDefaultChunk, tile_length(kFusedCall, dt, n)};
+    // Chunks of 1024 elements where all their waves are resident at once (7 per SIMD; 4 with chunks of 2048, whose launch would
+    // leave wave slots empty and keep the others twice as long).  us with chunks of 2048 and of 1024, buckets of 512: 8 peers,
+    // 4 bits, 2.1 M elements 8.1 and 7.2, 4.2 M 10.0 and 9.0, 6.3 M 12.0 and 11.0; 16 peers, buckets of 96, 6.3 M 21.5 and 18.8;
+    // 2 peers 6.7 and 6.6.  Beyond, the scales and meta that a wave pays per chunk decide: 8.4 M 13.7 and 13.6 at 4 bits, 13.6
+    // and 14.6 with 2, 3, 4 and 8; 10 M 14.6 and 15.4, 67 M 75.0 and 81.5.  The table is the binary32 quantizer's, and a bucket size
+    // that it lays over chunks of 2048 stays with them here (binary16 chunks too: they would need a table of their own).
+    const TableKind usual{cgx::kDefaultChunk, tile_length(kFusedCall, dt, n)};
+    const bool shorter = dt == CGX_F32 && !buckets.per_layer && n <= kMostShortFused &&
+                         quantize_chunks(dt, buckets, L, layer_offsets, bits_per_layer).chunk == cgx::chunk_of(2);
+    TableKind kind = usual;
+    if (shorter) kind.chunk = cgx::chunk_of(2);
     // tables of the chunks and of the output, which lays out its pass-through layers as binary32
     PlanRef in, out;
     if (plain_chunks(packed, meta, W, CGX_MAX_FUSED_PEERS) && plain(packed_out) && plain(meta_out)) {
         in = known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt, kind);
+        if (shorter && in && !in->beside_default) in = nullptr;
         out = dt == CGX_F32 || !in ? in
                                    : known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, CGX_F32, kind);
     }
@@ -523,19 +540,33 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
     }
     if (!known) {
         int rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, kind, &in);
+        // As for a decompression (reduce_impl): a captured call takes the table of the plan's other calls if its own does not
+        // exist, and a call that is not captured leaves theirs behind, whichever call has built its own.
+        if (rc == CGX_ERR_CAPTURE && shorter) {
+            kind = usual;
+            rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, kind, &in);
+        } else if (rc == CGX_OK && shorter) {
+            PlanRef others;                           // (this call does without it)
+            if (get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, usual, &others) == CGX_OK)
+                in->beside_default = true;
+            else
+                (void)hipGetLastError();
+        }
         if (rc != CGX_OK) return rc;
         rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, CGX_F32, kind, &out);
         if (rc != CGX_OK) return rc;
     }
     if (in->n_tiles != out->n_tiles) return CGX_ERR_SIZE;     // cannot happen: same tiling for both layouts
+    const auto launch_fused = kind.chunk == cgx::kDefaultChunk ? cgx::launch_dequant_reduce_requantize_g4
+                                                                : cgx::launch_dequant_reduce_requantize_g2;
     for (const cgx::TablePart &part : in->parts) {
         const Tile *tiles_in = in->d_tiles + part.first, *tiles_out = out->d_tiles + part.first;
         const hipError_t e =
             cgx::mapping_of(part.bucket, part.chunk) == cgx::kMapWide
                 ? cgx::launch_dequant_reduce_requantize_wide(scheme, peers, W, dt, tiles_in, tiles_out, part.count, draws_of(part),
                                                              part.longest, seed, packed_out, meta_out, launch_config(), queue)
-                : cgx::launch_dequant_reduce_requantize(scheme, peers, W, dt, tiles_in, tiles_out, part.count, draws_of(part), seed,
-                                                        packed_out, meta_out, launch_config(), queue);
+                : launch_fused(scheme, peers, W, dt, tiles_in, tiles_out, part.count, draws_of(part), seed, packed_out, meta_out,
+                               launch_config(), queue);
         if (e != hipSuccess) return CGX_ERR_HIP;
     }
     return CGX_OK;

@@ -98,7 +98,8 @@ __global__ __launch_bounds__(kBlock) void fused_kernel(const Tile *__restrict__ 
 
 }  // namespace
 
-hipError_t launch_dequant_reduce_requantize(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
+// This file is compiled once per chunk size (CGX_GROUPS = 2 and 4): launch_dequant_reduce_requantize_g2, _g4.
+hipError_t CGX_CONCAT(launch_dequant_reduce_requantize_g, CGX_GROUPS)(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
                                             const Tile *tiles_out, int64_t n_tiles, int draws,
                                             uint64_t seed, void *packed_out, void *meta_out,
                                             const LaunchConfig &cfg, hipStream_t stream)

@@ -70,8 +70,12 @@ hipError_t launch_dequant_reduce_g4(int scheme, const PeerPtrs &peers, int W, in
 
 // packed_out / meta_out = quantize(deq_0 + ... + deq_{W-1}) without the binary32 sum ever
 // reaching memory; tiles_in describes the chunks (storage type dt), tiles_out the output
-// (binary32 pass-through); W <= kPeersPerLaunch.
-hipError_t launch_dequant_reduce_requantize(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
+// (binary32 pass-through); W <= kPeersPerLaunch.  (two builds: chunks of 1024 elements and of 2048)
+hipError_t launch_dequant_reduce_requantize_g2(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
+                                            const Tile *tiles_out, int64_t n_tiles, int draws,
+                                            uint64_t seed, void *packed_out, void *meta_out,
+                                            const LaunchConfig &cfg, hipStream_t stream);
+hipError_t launch_dequant_reduce_requantize_g4(int scheme, const PeerPtrs &peers, int W, int dt, const Tile *tiles_in,
                                             const Tile *tiles_out, int64_t n_tiles, int draws,
                                             uint64_t seed, void *packed_out, void *meta_out,
                                             const LaunchConfig &cfg, hipStream_t stream);

@@ -214,6 +214,45 @@ def test_fused_peer_counts(torch, oracle):
         gpu_fused(torch, list(chunks) + [chunks[0]], list(metas) + [metas[0]], w.offsets, w.bits, w.bucket, w.dt, 1)
 
 
+@pytest.mark.parametrize("n", [1, 1024, 1025, 98304, 7 << 20, (7 << 20) + 8])
+@pytest.mark.parametrize("bucket", [64, 512, 672])
+def test_fused_on_either_side_of_the_rule_for_its_chunk(torch, oracle, n, bucket):
+    """Binary32 buffers up to the last that runs in chunks of 1024 elements and one beyond, every width, against the oracle
+    (bit for bit); buckets of 672 stay with chunks of 2048."""
+    L = 1 if n < 4096 else 9
+    off = np.linspace(0, n, L + 1).astype(np.int64)
+    bits = np.array([4] if L == 1 else [1, 2, 3, 4, 5, 6, 7, 8, 0], np.uint8)
+    rng = np.random.default_rng(n + bucket)
+    chunks, metas = zip(*[oracle.quantize(rng.standard_normal(n).astype(np.float32), off, bits, bucket, p, wl.F32) for p in range(3)])
+    ref = oracle.dequant_reduce(list(chunks), list(metas), off, bits, bucket, wl.F32)
+    fp, fm = gpu_fused(torch, chunks, metas, off, bits, bucket, wl.F32, 7)
+    op, om = oracle.quantize(ref["sum32"], off, bits, bucket, 7, wl.F32)
+    assert_same_chunk(fp, fm, op, om, f"n={n} bucket={bucket}")
+
+
+def test_reduce_can_be_captured_after_a_fused_call_whose_table_the_quantizer_built(torch, oracle):
+    """quantize, then fused (which walks the quantizer's table), then a captured reduce: its table exists."""
+    off, bits = np.array([0, 9000, 20480 + 72], np.int64), np.array([4, 3], np.uint8)
+    x = np.random.default_rng(5).standard_normal(int(off[-1])).astype(np.float32)
+    gpu_quantize(torch, x, off, bits, 128, 3, wl.F32)
+    op, om = oracle.quantize(x, off, bits, 128, 3, wl.F32)
+    gpu_fused(torch, [op] * 2, [om] * 2, off, bits, 128, wl.F32, 4)
+    plan, packed, meta = cgx.Plan(off, bits, 128, wl.F32), dev(torch, op), dev(torch, om.reshape(-1))
+    total = torch.zeros(plan.n, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        cgx.cgx_dequant_reduce([packed] * 2, [meta] * 2, plan, total)
+    ref = oracle.dequant_reduce([op] * 2, [om] * 2, off, bits, 128, wl.F32)
+    for replay in range(2):
+        total.fill_(7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_sum_parity(total.cpu().numpy(), ref, f"replay {replay}")
+
+
 @pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
 def test_dequantize_and_local_addend(torch, oracle, dt):
     """cgx_dequantize into binary32 / binary16 and cgx_dequant_reduce_add with a binary32 / binary16
