@@ -85,11 +85,16 @@ __device__ __forceinline__ uint64_t join_halves(uint32_t lo, uint32_t hi)
 // the fused step of a 13.7 M share of 8 peers 19.4 -> 18.5, norm-and-sign reduce and requantize of it 33.8 -> 32.7.  25.6 M and 1.3 G
 // binary32 elements are bound by memory and stay at 19.8 and 988.
 
+// Index of the pair (lower 32 bits) that element `at` (a multiple of 8) behind `first` lies in.  first is uniform over the wave, so
+// this is one vector addition; (first + at) >> 1 in 64 bits was two instructions per group.
+__device__ __forceinline__ uint32_t first_pair(int64_t first, int at) { return uint32_t(uint64_t(first) >> 1) + uint32_t(at >> 1); }
+
 // The 8 codes of one group, packed: element j of the group has buffer index 2 * pair0 + odd + j, key = generator key of
 // the tile.  odd (0 or 1, uniform over a tile: groups start 8 elements apart) tells whether the group starts on the upper
 // half of a generator word; then its 8 draws are the 16-bit halves 1..8 of words pair0 .. pair0 + 4 instead of halves
-// 0..7 of words pair0 .. pair0 + 3.  DRAWS (Draws, cgx_kernels.h; the host picks the instantiation): kDrawsOdd alone pays for
-// the fifth word and the selection, and kDrawsQuad knows that pair0 is a multiple of 4: no carry leaves its two lowest bits,
+// 0..7 of words pair0 .. pair0 + 3.  DRAWS (Draws, cgx_kernels.h; the host picks the instantiation): kDrawsOdd alone has
+// the fifth word and the selection, taken by the tiles that do start on odd elements (20 M ragged binary16 elements in buckets of
+// 160, fused, 4 peers: 25.0 -> 24.25 us, first_pair's share in it included), and kDrawsQuad knows that pair0 is a multiple of 4: no carry leaves its two lowest bits,
 // so the words of its four pairs differ in them alone until the first multiplication: 3 instructions fewer of 76 (by itself, us:
 // binary16 quantize of 372 M elements 159 -> 155, fused step of 14.7 M elements and 8 peers 20.65 -> 20.4).
 template <int SCHEME, int BITS, int DRAWS>
@@ -97,20 +102,25 @@ __device__ __forceinline__ uint64_t encode_group(const float (&x)[8], const Scal
                                                  uint32_t odd_start)
 {
     constexpr uint32_t kLevels = top_level<SCHEME>(BITS);
-    uint32_t word[5];
+    uint32_t word[4];
     if (DRAWS == kDrawsQuad) {
         const uint32_t mixed = mix32_head(pair0 ^ key);
 #pragma unroll
         for (int k = 0; k < 4; k++) word[k] = mix32_tail(mixed ^ uint32_t(k));
     } else {
 #pragma unroll
-        for (int k = 0; k < 4 + int(DRAWS == kDrawsOdd); k++) word[k] = mix32((pair0 + k) ^ key);
+        for (int k = 0; k < 4; k++) word[k] = mix32((pair0 + k) ^ key);
+        if (DRAWS == kDrawsOdd && odd_start) {       // (a branch: half of the tiles of a ragged plan start on even elements)
+            const uint32_t next = mix32((pair0 + 4) ^ key);
+#pragma unroll
+            for (int k = 0; k < 4; k++) word[k] = __builtin_amdgcn_alignbit(k < 3 ? word[k + 1] : next, word[k], 16u);
+        }
     }
     uint32_t sum[8];                                 // position of the element between the levels, plus its draw
 #pragma unroll
     for (int k = 0; k < 4; k++) {
         // the pair's two draws
-        const uint32_t w = DRAWS == kDrawsOdd ? __builtin_amdgcn_alignbit(word[k + 1], word[k], 16u * odd_start) : word[k];
+        const uint32_t w = word[k];
         sum[2 * k] = position_of<SCHEME>(x[2 * k], s) + (w & 0xffffU);
         sum[2 * k + 1] = position_of<SCHEME>(x[2 * k + 1], s) + (w >> 16);
     }
@@ -204,7 +214,7 @@ __device__ __forceinline__ void encode_chunk(const float (&x)[G][8], const Scale
 {
 #pragma unroll
     for (int r = 0; r < G; r++) {
-        const uint32_t pair0 = uint32_t(uint64_t(first + map.group(r)) >> 1);
+        const uint32_t pair0 = first_pair(first, map.group(r));
         stage_codes<BITS>(reinterpret_cast<uint8_t *>(stage) + (map.group(r) >> 3) * BITS,
                           encode_group<SCHEME, BITS, DRAWS>(x[r], s, pair0, key, uint32_t(first) & 1u));
     }
@@ -272,7 +282,7 @@ __device__ __forceinline__ void quantize_chunk_rows(const float (&x)[G][8], int 
         const Scale s = bucket_scale(mn, mx, int(kLevels));
         if ((lane & ((1 << lg) - 1)) == 0) store_meta<SCHEME>(meta_chunk, r * buckets_per_row + (lane >> lg), s);
         const int e = r * kRow + lane * 8;           // the group's first element within the chunk
-        const uint32_t pair0 = uint32_t(uint64_t(first + e) >> 1);
+        const uint32_t pair0 = first_pair(first, e);
         stage_codes<BITS>(reinterpret_cast<uint8_t *>(stage) + (e >> 3) * BITS,
                           encode_group<SCHEME, BITS, DRAWS>(x[r], s, pair0, key, uint32_t(first) & 1u));
     }
@@ -453,7 +463,7 @@ __device__ __forceinline__ void encode_run(const float (&x)[OWN][8], const Run &
     uint64_t codes[OWN];
 #pragma unroll
     for (int r = 0; r < OWN; r++) {
-        const uint32_t pair0 = uint32_t(uint64_t(first + (lane * OWN + r) * 8) >> 1);
+        const uint32_t pair0 = first_pair(first, (lane * OWN + r) * 8);
         codes[r] = encode_group<SCHEME, BITS, DRAWS>(x[r], s, pair0, key, uint32_t(first) & 1u);
         const int v = run.valid(r);
         codes[r] &= v == 8 ? ~uint64_t(0) : (uint64_t(1) << (v * BITS)) - 1u;       // nothing past the end
