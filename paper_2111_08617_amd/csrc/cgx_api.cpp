@@ -491,19 +491,20 @@ int reduce_impl(int scheme, const void *const *packed, const void *const *meta, 
     return CGX_OK;
 }
 
-// Most elements of a fused call in chunks of 1024 elements: 7 waves on each of 1024 SIMDs.
-constexpr int64_t kMostShortFused = int64_t(7) << 20;
+// Most elements of a fused call in chunks of 1024 elements: what chunks of 2048 would give two waves on each of 1024 SIMDs.
+constexpr int64_t kMostShortFused = int64_t(4) << 20;
 
 int fused_impl(int scheme, const void *const *packed, const void *const *meta, int32_t W, int64_t n, int32_t L,
                const int64_t *layer_offsets, const uint8_t *bits_per_layer, const Buckets &buckets, int dt,
                uint64_t seed, void *packed_out, void *meta_out, void *stream)
 {
     const hipStream_t queue = static_cast<hipStream_t>(stream);
-    // Chunks of 1024 elements where all their waves are resident at once (7 per SIMD; 4 with chunks of 2048, whose launch would
-    // leave wave slots empty and keep the others twice as long).  us with chunks of 2048 and of 1024, buckets of 512: 8 peers,
-    // 4 bits, 2.1 M elements 8.1 and 7.2, 4.2 M 10.0 and 9.0, 6.3 M 12.0 and 11.0; 16 peers, buckets of 96, 6.3 M 21.5 and 18.8;
-    // 2 peers 6.7 and 6.6.  Beyond, the scales and meta that a wave pays per chunk decide: 8.4 M 13.7 and 13.6 at 4 bits, 13.6
-    // and 14.6 with 2, 3, 4 and 8; 10 M 14.6 and 15.4, 67 M 75.0 and 81.5.  The table is the binary32 quantizer's, and a bucket size
+    // Chunks of 1024 elements (7 waves per SIMD, 71 registers) where chunks of 2048 (4 waves, 121 registers) would leave half of the
+    // wave slots empty and keep the others twice as long.  us with chunks of 2048 and of 1024: 8 peers, 4 bits, buckets of 512, 2.1 M
+    // elements 8.1 and 7.2, 4.2 M 10.0 and 9.0; 7 peers, 2 bits, buckets of 992, 2.1 M 8.8 and 7.6.  Beyond, it depends on widths and
+    // sizes: 5.2 M, 7 peers, 992, 2 and 8 bits 10.8 and 11.1, 12.0 and 12.4, 4 bits 11.7 and 11.4; 8 peers of 6.3 M at 4 bits 12.0 and
+    // 11.0, 10 M 14.6 and 15.4, 67 M 75.0 and 81.5 (the scales and meta that a wave pays per chunk).
+    // The table is the binary32 quantizer's, and a bucket size
     // that it lays over chunks of 2048 stays with them here (binary16 chunks too: they would need a table of their own).
     const TableKind usual{cgx::kDefaultChunk, tile_length(kFusedCall, dt, n)};
     const bool shorter = dt == CGX_F32 && !buckets.per_layer && n <= kMostShortFused &&

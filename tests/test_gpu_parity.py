@@ -214,7 +214,7 @@ def test_fused_peer_counts(torch, oracle):
         gpu_fused(torch, list(chunks) + [chunks[0]], list(metas) + [metas[0]], w.offsets, w.bits, w.bucket, w.dt, 1)
 
 
-@pytest.mark.parametrize("n", [1, 1024, 1025, 98304, 7 << 20, (7 << 20) + 8])
+@pytest.mark.parametrize("n", [1, 1024, 1025, 98304, 4 << 20, (4 << 20) + 8])
 @pytest.mark.parametrize("bucket", [64, 512, 672])
 def test_fused_on_either_side_of_the_rule_for_its_chunk(torch, oracle, n, bucket):
     """Binary32 buffers up to the last that runs in chunks of 1024 elements and one beyond, every width, against the oracle
