@@ -42,10 +42,27 @@ namespace {
 // the order in which waves finish.  Squares of binary32 values and differences of two
 // binary32 values are exact in binary64; only the additions round.
 
+// v of the partner lane under one of the lane patterns that stay within a row of 16.
+template <int PATTERN>
+__device__ __forceinline__ double row_partner(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(b)), PATTERN, 0xf, 0xf, false));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(b >> 32)), PATTERN, 0xf, 0xf, false));
+    return __builtin_bit_cast(double, uint64_t(hi) << 32 | lo);
+}
+
+// Sum over the wave, in every lane (all lanes take part).  The first four steps stay in the vector ALUs; as shuffles all six went
+// through LDS, a dependent round trip each, which the end of a launch waits for (ResNet-50's adaptive round, two such sums per layer
+// and one per tile, 62.1 -> 60.9 us; 67 M binary16 elements 92.9 -> 89.7).  The additions and their order are the same.
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) v += __shfl_xor(v, m, kWave);
+    v += row_partner<0xb1>(v);      // lane ^ 1
+    v += row_partner<0x4e>(v);      // lane ^ 2
+    v += row_partner<0x141>(v);     // quads are uniform now: row_half_mirror pairs each with its neighbour
+    v += row_partner<0x140>(v);     // row_mirror pairs the halves of a row
+    v += __shfl_xor(v, 16, kWave);
+    v += __shfl_xor(v, 32, kWave);
     return v;
 }
 
