@@ -36,8 +36,9 @@ __device__ __forceinline__ void signed_bytes_to_float(uint32_t t, float &b0, flo
 // nibble q <= 3 is q / 2.  Times 512 (2) that is float(q), exactly.  Builds in turn on one box, us: a 13.7 M share of 8 peers in one
 // fused step (2, 3, 4 and 8 bits) 18.6 -> 17.8, 16.8 M elements of 4 bits 22.3 -> 21.4, of 2 bits 20.6 -> 20.3; the reduce of 34 M at
 // 2 bits 61.0 -> 59.7, of the ResNet-50 plan with its requantize 54.1 -> 53.9.  Not taken where it measured slower: 3-bit
-// codes spread to bytes (fused, 8 peers, 23.7 -> 24.8), signed 2-bit codes as nibbles of sign and magnitude (21.8 -> 22.6), and
-// 2-bit codes of a single peer, bound by what they write (67 M elements in 4 shares 47.5 -> 47.9).
+// codes spread to bytes (fused, 8 peers, 23.7 -> 24.8), signed 2-bit codes as nibbles of sign and magnitude (21.8 -> 22.6), 2-bit
+// codes of a single peer, bound by what they write (67 M elements in 4 shares 47.5 -> 47.9), and 2-bit codes of runs, whose upper
+// bits have to be cleared first (fused, 8 peers, buckets of 992, 24.8 byte by byte, 26.5 as nibbles).
 constexpr float kByteScale = 512.0f, kNibbleScale = 2.0f;
 
 __device__ __forceinline__ void small_bytes_to_float(uint32_t t, float &b0, float &b1, float &b2, float &b3)
@@ -56,8 +57,8 @@ __device__ __forceinline__ void nibbles_to_float(uint32_t t, float (&f)[8])
     f[4] = p2[0], f[5] = p2[1], f[6] = p3[0], f[7] = p3[1];
 }
 
-// Levels of one group of 8 codes as floats (kNormSign: signed levels).  SINGLE: of the only peer.
-template <int SCHEME, int BITS, bool SINGLE>
+// Levels of one group of 8 codes as floats (kNormSign: signed levels).  BYTEWISE: 2-bit codes by v_cvt_f32_ubyte.
+template <int SCHEME, int BITS, bool BYTEWISE>
 __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
 {
     constexpr bool kSigned = SCHEME == kNormSign;
@@ -83,7 +84,7 @@ __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
             small_bytes_to_float(w & 0x0f0f0f0fu, f[0], f[2], f[4], f[6]);
             small_bytes_to_float((w >> 4) & 0x0f0f0f0fu, f[1], f[3], f[5], f[7]);
         }
-    } else if (BITS == 2 && !kSigned && SINGLE) {
+    } else if (BITS == 2 && !kSigned && BYTEWISE) {
         // four codes per register: the upper half holds the codes that follow those of the lower half
         const uint32_t x = opaque(((w & 0xffffu) << 14) | (w & 0xffffu));
         bytes_to_float(opaque(x & 0x03030303u), f[0], f[4], f[1], f[5]);
@@ -185,7 +186,7 @@ __device__ __forceinline__ void reduce_peers(Peers &peers, int w0, int64_t in_of
                 v = run[r];
             else
                 v = staged_codes<BITS>(codes + i * kBytes, code_off[r]);
-            codes_to_float<SCHEME, BITS, WB == 1>(v, f);
+            codes_to_float<SCHEME, BITS, WB == 1 || RUN>(v, f);
 #pragma unroll
             for (int j = 0; j < 8; j++) acc[r][j] = __fadd_rn(acc[r][j], decode<SCHEME>(f[j], m[i]));
         }
