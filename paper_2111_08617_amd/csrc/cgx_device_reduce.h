@@ -57,7 +57,8 @@ __device__ __forceinline__ void nibbles_to_float(uint32_t t, float (&f)[8])
     f[4] = p2[0], f[5] = p2[1], f[6] = p3[0], f[7] = p3[1];
 }
 
-// Levels of one group of 8 codes as floats (kNormSign: signed levels).  BYTEWISE: 2-bit codes by v_cvt_f32_ubyte.
+// Levels of one group of 8 codes as floats (kNormSign: signed levels).  BYTEWISE: 2-bit codes by v_cvt_f32_ubyte.  Signed 2-bit codes
+// are extracted one by one: as bytes that v_perm_b32 selects the fused step of 14.7 M takes 20.6 us for 19.3.
 template <int SCHEME, int BITS, bool BYTEWISE>
 __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
 {
@@ -75,6 +76,8 @@ __device__ __forceinline__ void codes_to_float(uint64_t v, float (&f)[8])
         // one code per byte: even codes in one register, odd ones in another
         if (kSigned) {
             // a nibble with its sign bit flipped is level + 8, and 0x78 more is level + 0x80: no byte carries
+            // (a conversion of a signed byte costs what one of an unsigned byte does, and no 8.0 is subtracted per code: fused step of 8
+            // peers, 14.7 M elements, 24.4 -> 22.1 us)
             const uint32_t h = w ^ 0x88888888u;
             const uint32_t even = ((h & 0x0f0f0f0fu) + 0x78787878u) ^ 0x80808080u;
             const uint32_t odd = (((h >> 4) & 0x0f0f0f0fu) + 0x78787878u) ^ 0x80808080u;

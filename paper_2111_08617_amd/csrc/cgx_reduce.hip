@@ -18,7 +18,7 @@ struct ReduceArguments {
 };
 
 // SINGLE: a decompression (W = 1, no start values) into storage type SINGLE, bound by the eight bytes it writes per byte
-// it reads.  It needs half of the reduction's registers and LDS, and more waves then keep stores in flight (59 instead of 100
+// it reads.  It needs half of the reduction's registers and LDS, and more waves then keep stores in flight (59 instead of 101
 // vector registers at 2048-element chunks, eight waves per SIMD instead of four; 36 instead of 86 at 1024, eight instead of
 // five): 8 shares of 355 M elements to binary16 187 -> 166 us; to binary32, 4 bits, codes from memory, 268 M elements 224 ->
 // 185 us, 67 M 58 -> 49.  (Decompressed again and again from codes that the memory-side cache holds, 162 -> 170 and 43.5 ->
