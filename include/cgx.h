@@ -39,10 +39,11 @@
  *   same plan only queue kernels.  (cgx_quantize on binary32 input and
  *   cgx_requantize, cgx_quantize on binary16 gradients of 2^24 elements or more,
  *   and the fused call on 2^27 or more, keep tables of their own beside the one
- *   the other calls share; the fused call on short binary32 buffers walks that of
- *   cgx_requantize and sees that the shared one exists.)  At most 64 tables are
- *   kept: when a 65th arrives the least recently used one is freed, which waits
- *   for the device; cgx_shutdown() frees them all.
+ *   the other calls share; the fused call on short binary32 buffers sees that the
+ *   shared one exists and walks that of cgx_requantize, if it exists or fits
+ *   beside the others.)  At most 64 tables are kept besides those that captured
+ *   graphs read: when a 65th arrives the least recently used one is freed, which
+ *   waits for the device; cgx_shutdown() frees them all.
  *   A call on a stream that is capturing a graph records its launches into the
  *   graph, and those read the plan's table on every replay.  Therefore:
  *     - the table must exist before the capture: run the same call once, not

@@ -3,7 +3,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
 #include <cstdlib>
 #include <cstring>
 #include <memory>
@@ -52,8 +51,6 @@ struct CachedPlan {
     uint32_t *d_slots = nullptr;
     int64_t *d_layer_first = nullptr;
     uint64_t last_use = 0;      // cache clock at the latest look-up
-    // a fused call has made sure of the table of kDefaultChunk chunks beside this one, see fused_impl
-    mutable std::atomic<bool> beside_default{false};
     bool pinned = false;        // a stream capture has recorded launches that read these tables: never dropped
 };
 
@@ -78,12 +75,13 @@ bool upload(T **dst, const std::vector<T> &src)
 
 std::mutex g_mutex;
 // A caller that keeps changing its plan (new bit widths every so often) must not grow the
-// cache without bound: beyond kMaxPlans entries the least recently used one is dropped.  An
+// cache without bound: beyond kMaxPlans entries (those that captured graphs read are not counted) the least
+// recently used one is dropped.  An
 // entry handed out stays alive while its call uses it (shared ownership); its device tables
 // are released when the last owner lets go, and hipFree waits for launches still reading them.
 // The cache object itself is never destroyed, so nothing is freed during process exit, when
 // the HIP runtime may already be gone.
-constexpr size_t kMaxPlans = 64;
+constexpr int64_t kMaxPlans = 64;
 using PlanRef = std::shared_ptr<const CachedPlan>;
 std::vector<std::shared_ptr<CachedPlan>> &g_plans = *new std::vector<std::shared_ptr<CachedPlan>>();
 uint64_t g_clock = 0;
@@ -245,7 +243,7 @@ struct PlanKey {
 };
 
 // The cached table of a key, or nothing (g_mutex is held).  A table found during a stream capture is pinned, see get_plan.
-PlanRef cached_plan(const PlanKey &k, int device, bool capturing)
+PlanRef cached_plan(const PlanKey &k, int device, bool capturing, bool renew = true)
 {
     for (const auto &p : g_plans) {
         if (p->digest == k.digest && p->device == device && p->bucket == k.bucket && p->dt == k.dt && p->kind == k.kind &&
@@ -254,7 +252,7 @@ PlanRef cached_plan(const PlanKey &k, int device, bool capturing)
              std::memcmp(p->layer_buckets.data(), k.layer_buckets, sizeof(int32_t) * size_t(k.L)) == 0) &&
             std::memcmp(p->bits.data(), k.bits, size_t(k.L)) == 0 &&
             std::memcmp(p->off.data(), k.off, sizeof(int64_t) * (size_t(k.L) + 1)) == 0) {
-            p->last_use = ++g_clock;
+            if (renew) p->last_use = ++g_clock;
             if (capturing) p->pinned = true;
             return p;
         }
@@ -274,8 +272,9 @@ bool is_capturing(hipStream_t stream)
 // such a call needs neither the checks of the layer table nor its sizes again (2 us at 300 layers).  Nothing
 // is found for arguments that those checks would refuse: tables exist for checked plans only, and 1-bit layers
 // are left to them under the norm-and-sign quantizer.
+// instead (may be null): a kind that the call prefers if the plan has both tables (it does not count as used then).
 PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const int64_t *off, const uint8_t *bits,
-                   const Buckets &buckets, int dt, const TableKind &kind)
+                   const Buckets &buckets, int dt, const TableKind &kind, const TableKind *instead = nullptr)
 {
     // (what the checks find out without reading the arrays keeps them unread)
     if (buckets.per_layer || L <= 0 || n <= 0 || !off || !bits || (dt != CGX_F32 && dt != CGX_F16) || buckets.uniform < 32 ||
@@ -283,11 +282,16 @@ PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const i
         return nullptr;
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return nullptr;
-    const PlanKey key{L, off, bits, buckets.uniform, dt, kind, nullptr, plan_digest(L, off, bits, nullptr)};
+    PlanKey key{L, off, bits, buckets.uniform, dt, kind, nullptr, plan_digest(L, off, bits, nullptr)};
     const bool capturing = is_capturing(stream);
     std::lock_guard<std::mutex> lock(g_mutex);
-    const PlanRef plan = cached_plan(key, device, capturing);
-    return plan && scheme == cgx::kSchemeNormSign && plan->one_bit_layers ? nullptr : plan;
+    PlanRef plan = cached_plan(key, device, capturing);
+    if (plan && scheme == cgx::kSchemeNormSign && plan->one_bit_layers) return nullptr;
+    if (plan && instead) {
+        key.kind = *instead;
+        if (PlanRef other = cached_plan(key, device, capturing, false)) return other;
+    }
+    return plan;
 }
 
 // Finds or builds the device-resident tile table of a (valid) plan for a call on `stream`.
@@ -296,8 +300,10 @@ PlanRef known_plan(hipStream_t stream, int scheme, int64_t n, int32_t L, const i
 // and a table that does not exist yet is not built during a capture (that would allocate and copy
 // synchronously in the middle of it): the call fails with CGX_ERR_CAPTURE and records nothing.
 // built (may be null): whether the table is a new one.
+// spare: a table the call can do without.  It is built only where the cache has an entry left (else CGX_ERR_CAPACITY), and
+// until a call looks it up for itself it is the first to be dropped: it never displaces a table in use.
 int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *bits, const Buckets &buckets, int dt,
-             const TableKind &kind, PlanRef *out, bool *built = nullptr)
+             const TableKind &kind, PlanRef *out, bool *built = nullptr, bool spare = false)
 {
     const int32_t bucket = buckets.uniform;
     const int32_t *layer_buckets = buckets.per_layer;
@@ -306,10 +312,12 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) return CGX_ERR_HIP;
     const bool capturing = is_capturing(stream);
-    *out = cached_plan(PlanKey{L, off, bits, bucket, dt, kind, layer_buckets, digest}, device, capturing);
+    *out = cached_plan(PlanKey{L, off, bits, bucket, dt, kind, layer_buckets, digest}, device, capturing, !spare);
     if (built) *built = !*out;
     if (*out) return CGX_OK;
     if (capturing) return CGX_ERR_CAPTURE;
+    const bool full = std::count_if(g_plans.begin(), g_plans.end(), [](const auto &p) { return !p->pinned; }) >= kMaxPlans;
+    if (spare && full) return CGX_ERR_CAPACITY;
     std::shared_ptr<CachedPlan> plan(new CachedPlan, [](CachedPlan *p) {
         free_plan(*p);
         delete p;
@@ -348,9 +356,9 @@ int get_plan(hipStream_t stream, int32_t L, const int64_t *off, const uint8_t *b
     plan->reduce.off_64_bytes[CGX_F32] = 2 * off_grid[2] > off[L];
     plan->reduce.off_64_bytes[CGX_F16] = 2 * off_grid[3] > off[L];
     plan->parts = std::move(table.parts);
-    plan->last_use = ++g_clock;
-    if (g_plans.size() >= kMaxPlans) {
-        // drop the least recently used table that no captured graph reads (if all are pinned the cache grows)
+    plan->last_use = spare ? 0 : ++g_clock;
+    if (full) {
+        // drop the least recently used table that no captured graph reads
         size_t oldest = g_plans.size();
         for (size_t i = 0; i < g_plans.size(); i++)
             if (!g_plans[i]->pinned && (oldest == g_plans.size() || g_plans[i]->last_use < g_plans[oldest]->last_use))
@@ -506,18 +514,18 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
     // 11.0, 10 M 14.6 and 15.4, 67 M 75.0 and 81.5 (the scales and meta that a wave pays per chunk).
     // The table is the binary32 quantizer's, and a bucket size
     // that it lays over chunks of 2048 stays with them here (binary16 chunks too: they would need a table of their own).
-    const TableKind usual{cgx::kDefaultChunk, tile_length(kFusedCall, dt, n)};
+    // The plan's tables stay those of chunks of 2048: they are looked up, built and renewed whichever this call walks, so that a
+    // reduction or a statistic can be captured after it.  The other one is a spare (see get_plan): a program whose plans fill the
+    // cache keeps the tables it would have without it, and its fused calls walk those.
+    const TableKind usual{cgx::kDefaultChunk, tile_length(kFusedCall, dt, n)}, brief{cgx::chunk_of(2), usual.chunks_per_tile};
     const bool shorter = dt == CGX_F32 && !buckets.per_layer && n <= kMostShortFused &&
-                         quantize_chunks(dt, buckets, L, layer_offsets, bits_per_layer).chunk == cgx::chunk_of(2);
-    TableKind kind = usual;
-    if (shorter) kind.chunk = cgx::chunk_of(2);
+                         quantize_chunks(dt, buckets, L, layer_offsets, bits_per_layer).chunk == brief.chunk;
     // tables of the chunks and of the output, which lays out its pass-through layers as binary32
     PlanRef in, out;
     if (plain_chunks(packed, meta, W, CGX_MAX_FUSED_PEERS) && plain(packed_out) && plain(meta_out)) {
-        in = known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt, kind);
-        if (shorter && in && !in->beside_default) in = nullptr;
+        in = known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, dt, usual, shorter ? &brief : nullptr);
         out = dt == CGX_F32 || !in ? in
-                                   : known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, CGX_F32, kind);
+                                   : known_plan(queue, scheme, n, L, layer_offsets, bits_per_layer, buckets, CGX_F32, usual);
     }
     const bool known = in && out;
     if (!known) {
@@ -540,26 +548,24 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
         peers.meta[i] = static_cast<const float *>(meta[i]);
     }
     if (!known) {
-        int rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, kind, &in);
-        // As for a decompression (reduce_impl): a captured call takes the table of the plan's other calls if its own does not
-        // exist, and a call that is not captured leaves theirs behind, whichever call has built its own.
-        if (rc == CGX_ERR_CAPTURE && shorter) {
-            kind = usual;
-            rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, kind, &in);
-        } else if (rc == CGX_OK && shorter) {
-            PlanRef others;                           // (this call does without it)
-            if (get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, usual, &others) == CGX_OK)
-                in->beside_default = true;
-            else
-                (void)hipGetLastError();
+        int rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, usual, &in);
+        if (shorter) {
+            PlanRef other;                            // (a captured call may find the quantizer's table alone)
+            const int spare = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, dt, brief, &other, nullptr, true);
+            if (rc == CGX_ERR_HIP || spare == CGX_ERR_HIP) (void)hipGetLastError();
+            if (spare == CGX_OK) {
+                in = other;
+                rc = CGX_OK;
+            }
         }
         if (rc != CGX_OK) return rc;
-        rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, CGX_F32, kind, &out);
+        out = in;
+        if (dt != CGX_F32) rc = get_plan(queue, L, layer_offsets, bits_per_layer, buckets, CGX_F32, usual, &out);
         if (rc != CGX_OK) return rc;
     }
     if (in->n_tiles != out->n_tiles) return CGX_ERR_SIZE;     // cannot happen: same tiling for both layouts
-    const auto launch_fused = kind.chunk == cgx::kDefaultChunk ? cgx::launch_dequant_reduce_requantize_g4
-                                                                : cgx::launch_dequant_reduce_requantize_g2;
+    const auto launch_fused = in->kind.chunk == cgx::kDefaultChunk ? cgx::launch_dequant_reduce_requantize_g4
+                                                                    : cgx::launch_dequant_reduce_requantize_g2;
     for (const cgx::TablePart &part : in->parts) {
         const Tile *tiles_in = in->d_tiles + part.first, *tiles_out = out->d_tiles + part.first;
         const hipError_t e =

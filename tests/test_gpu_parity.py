@@ -253,6 +253,71 @@ def test_reduce_can_be_captured_after_a_fused_call_whose_table_the_quantizer_bui
         assert_sum_parity(total.cpu().numpy(), ref, f"replay {replay}")
 
 
+def short_fused_plans(oracle, count, first):
+    """(plan, chunk, meta) of `count` binary32 plans, number `first` on, that the fused call runs in chunks of 1024 elements."""
+    x = np.random.default_rng(91).standard_normal(9000).astype(np.float32)
+    for k in range(first, first + count):
+        off, bits = np.array([0, 2048 + 8 * k, 9000], np.int64), np.array([4, 3], np.uint8)
+        yield (cgx.Plan(off, bits, 128), *oracle.quantize(x, off, bits, 128, k, wl.F32))
+
+
+def test_the_fused_call_keeps_its_plans_table_in_use(torch, oracle):
+    """However many plans follow, a plan whose fused call keeps running keeps the table that its other calls walk: a
+    reduce that never ran before can be captured."""
+    ((plan, op, om),) = short_fused_plans(oracle, 1, 500)
+    packed, meta = dev(torch, op), dev(torch, om.reshape(-1))
+    out = torch.zeros(op.size, dtype=torch.uint8, device="cuda"), torch.zeros(om.size, device="cuda")
+    for k in range(70):                                       # more plans than the library keeps
+        cgx.cgx_dequant_reduce_requantize([packed] * 2, [meta] * 2, plan, 4, *out)
+        gpu_quantize(torch, np.ones(9000, np.float32), np.array([0, 1024 + 8 * k, 9000], np.int64), [2, 4], 96, k, wl.F32)
+    total = torch.zeros(plan.n, device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        cgx.cgx_dequant_reduce([packed] * 2, [meta] * 2, plan, total)
+    ref = oracle.dequant_reduce([op] * 2, [om] * 2, plan.offsets, plan.bits, 128, wl.F32)
+    for replay in range(2):
+        total.fill_(7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_sum_parity(total.cpu().numpy(), ref, f"replay {replay}")
+
+
+def test_fused_calls_need_one_table_per_plan(torch, oracle):
+    """As many short plans as the library keeps tables, each with a fused call and a reduce, one plan after the other: every
+    table is still there for a second round (a capture refuses a call that would have to build one)."""
+    cases = []
+    for plan, op, om in short_fused_plans(oracle, 64, 0):
+        cases.append((plan, op, om, dev(torch, op), dev(torch, om.reshape(-1)), torch.zeros(op.size, dtype=torch.uint8, device="cuda"),
+                      torch.zeros(om.size, device="cuda"), torch.zeros(plan.n, device="cuda")))
+
+    def calls():
+        for plan, _, _, packed, meta, packed_out, meta_out, total in cases:
+            cgx.cgx_dequant_reduce_requantize([packed] * 2, [meta] * 2, plan, 4, packed_out, meta_out)
+            cgx.cgx_dequant_reduce([packed] * 2, [meta] * 2, plan, total)
+
+    calls()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        calls()
+    for replay in range(2):
+        for case in cases:
+            for t in case[5:]:
+                t.fill_(7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for plan, op, om, _, _, packed_out, meta_out, total in cases[::9]:
+            ref = oracle.dequant_reduce([op] * 2, [om] * 2, plan.offsets, plan.bits, 128, wl.F32)
+            assert_sum_parity(total.cpu().numpy(), ref, f"replay {replay}")
+            wp, wm = oracle.quantize(ref["sum32"], plan.offsets, plan.bits, 128, 4, wl.F32)
+            assert_same_chunk(packed_out.cpu().numpy(), meta_out.cpu().numpy(), wp, wm, f"replay {replay}")
+
+
 @pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
 def test_dequantize_and_local_addend(torch, oracle, dt):
     """cgx_dequantize into binary32 / binary16 and cgx_dequant_reduce_add with a binary32 / binary16
