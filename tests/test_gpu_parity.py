@@ -55,15 +55,16 @@ def gpu_reduce(torch, chunks, metas, offsets, bits, bucket, dt):
     return out[:plan.n], total
 
 
-def gpu_fused(torch, chunks, metas, offsets, bits, bucket, dt, seed):
-    """cgx_dequant_reduce_requantize on host-made chunks; returns (packed, meta) of the requantized sum."""
-    plan = cgx.Plan(offsets, bits, bucket, dt)
+def gpu_fused(torch, chunks, metas, offsets, bits, bucket, dt, seed, layered=False):
+    """cgx_dequant_reduce_requantize on host-made chunks; returns (packed, meta) of the requantized sum.
+    layered: the same plan with its bucket size given layer by layer, which always runs in chunks of 2048 elements."""
+    plan = cgx.LayeredPlan(offsets, bits, np.full(len(bits), bucket, np.int32), dt) if layered else cgx.Plan(offsets, bits, bucket, dt)
     pb, mb = cgx.cgx_sizes(cgx.Plan(offsets, bits, bucket, wl.F32))
     dp = [dev(torch, c) for c in chunks]
     dm = [dev(torch, m.reshape(-1)) if m.size else torch.zeros(4, device="cuda") for m in metas]
     packed = torch.full((pb + 64,), 0xA5, dtype=torch.uint8, device="cuda")
     meta = torch.full((mb // 4 + 16,), -7.0, dtype=torch.float32, device="cuda")
-    cgx.cgx_dequant_reduce_requantize(dp, dm, plan, seed, packed, meta)
+    (cgx.cgx_layered_dequant_reduce_requantize if layered else cgx.cgx_dequant_reduce_requantize)(dp, dm, plan, seed, packed, meta)
     torch.cuda.synchronize()
     p, m = packed.cpu().numpy(), meta.cpu().numpy()
     assert (p[pb:] == 0xA5).all() and (m[mb // 4:] == -7.0).all(), "wrote past the reported sizes"
@@ -126,6 +127,9 @@ def full_cycle(torch, oracle, w, W, seed_shift=0, what=""):
         fp, fm = gpu_fused(torch, chunks, metas, w.offsets, w.bits, w.bucket, w.dt, 99 + seed_shift)
         op, om = oracle.quantize(ref["sum32"], w.offsets, w.bits, w.bucket, 99 + seed_shift, wl.F32)
         assert_same_chunk(fp, fm, op, om, f"{what} fused reduce+requantize")
+        if w.dt == wl.F32:            # short binary32 buffers run in chunks of 1024 elements; here in chunks of 2048
+            fp, fm = gpu_fused(torch, chunks, metas, w.offsets, w.bits, w.bucket, w.dt, 99 + seed_shift, layered=True)
+            assert_same_chunk(fp, fm, op, om, f"{what} fused reduce+requantize, a bucket size per layer")
 
 
 @pytest.mark.parametrize("dt", [wl.F32, wl.F16], ids=["f32", "f16"])
@@ -201,9 +205,12 @@ def test_many_peers_take_several_launches(torch, oracle):
         assert_sum_parity(got, ref, f"W={W}")
 
 
-def test_fused_peer_counts(torch, oracle):
-    """Every chunk count the fused entry point accepts, on the edge-case plan in binary16 storage."""
-    w = wl.tiny_mixed(seed=91, dt=wl.F16, bucket=64)
+@pytest.mark.parametrize("dt", [wl.F16, wl.F32], ids=["f16", "f32"])
+def test_fused_peer_counts(torch, oracle, dt):
+    """Every chunk count the fused entry point accepts, on the edge-case plan in either storage (binary32: in chunks of 1024
+    elements, whose table the quantizer builds)."""
+    w = wl.tiny_mixed(seed=91, dt=dt, bucket=64)
+    gpu_quantize(torch, w.gradient(0), w.offsets, w.bits, w.bucket, 0, w.dt)
     chunks, metas = zip(*[oracle.quantize(w.gradient(p), w.offsets, w.bits, w.bucket, p, w.dt) for p in range(16)])
     for W in (1, 2, 3, 5, 8, 11, 16):
         ref = oracle.dequant_reduce(list(chunks[:W]), list(metas[:W]), w.offsets, w.bits, w.bucket, w.dt)
@@ -218,13 +225,14 @@ def test_fused_peer_counts(torch, oracle):
 @pytest.mark.parametrize("bucket", [64, 512, 672])
 def test_fused_on_either_side_of_the_rule_for_its_chunk(torch, oracle, n, bucket):
     """Binary32 buffers up to the last that runs in chunks of 1024 elements and one beyond, every width, against the oracle
-    (bit for bit); buckets of 672 stay with chunks of 2048."""
+    (bit for bit); buckets of 672 stay with chunks of 2048.  (The table of the shorter chunks is there: the quantizer's.)"""
     L = 1 if n < 4096 else 9
     off = np.linspace(0, n, L + 1).astype(np.int64)
     bits = np.array([4] if L == 1 else [1, 2, 3, 4, 5, 6, 7, 8, 0], np.uint8)
     rng = np.random.default_rng(n + bucket)
     chunks, metas = zip(*[oracle.quantize(rng.standard_normal(n).astype(np.float32), off, bits, bucket, p, wl.F32) for p in range(3)])
     ref = oracle.dequant_reduce(list(chunks), list(metas), off, bits, bucket, wl.F32)
+    gpu_quantize(torch, np.zeros(n, np.float32), off, bits, bucket, 1, wl.F32)
     fp, fm = gpu_fused(torch, chunks, metas, off, bits, bucket, wl.F32, 7)
     op, om = oracle.quantize(ref["sum32"], off, bits, bucket, 7, wl.F32)
     assert_same_chunk(fp, fm, op, om, f"n={n} bucket={bucket}")
@@ -388,9 +396,9 @@ def test_degenerate_values(torch, oracle):
 
 @pytest.mark.parametrize("b", [2, 4, 8])
 def test_units_at_both_ends_of_the_exponent_range(torch, oracle, b):
-    """Chunks whose buckets' units are huge (on both sides of 2^118, where the fused kernel's scaled unit
-    starts to overflow and it falls back to the plain conversion), tiny (subnormal units) or ordinary, in
-    different peers: the reduce and the fused call, whole chunks and a short end."""
+    """Chunks whose buckets' units are huge (on both sides of 2^118: a decode that scaled the unit by 512 would overflow
+    above it; the conversions scale the code instead), tiny (subnormal units) or ordinary, in different peers: the reduce
+    and the fused call in chunks of 1024 and of 2048 elements, whole chunks and a short end."""
     B, n, W = 256, 2048 * 4 + 1200, 5
     off, bits = np.array([0, n], np.int64), np.array([b], np.uint8)
     rng = np.random.default_rng(100 + b)
@@ -416,9 +424,11 @@ def test_units_at_both_ends_of_the_exponent_range(torch, oracle, b):
     ref = oracle.dequant_reduce(chunks, metas, off, bits, B, wl.F32)
     got, _ = gpu_reduce(torch, chunks, metas, off, bits, B, wl.F32)
     assert np.array_equal(got.view(np.uint32), ref["sum32"].view(np.uint32)), "reduce"
-    fp, fm = gpu_fused(torch, chunks, metas, off, bits, B, wl.F32, 31)
     op, om = oracle.quantize(ref["sum32"], off, bits, B, 31, wl.F32)
-    assert_same_chunk(fp, fm, op, om, "fused")
+    gpu_quantize(torch, ref["sum32"], off, bits, B, 31, wl.F32)            # the table of chunks of 1024 elements exists
+    for layered in (False, True):
+        fp, fm = gpu_fused(torch, chunks, metas, off, bits, B, wl.F32, 31, layered)
+        assert_same_chunk(fp, fm, op, om, f"fused, layered={layered}")
 
 
 def test_repeatable_and_seed_sensitive(torch, oracle):

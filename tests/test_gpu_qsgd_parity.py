@@ -61,13 +61,15 @@ def gpu_reduce(torch, chunks, metas, offsets, bits, bucket, dt):
     return out[:plan.n], total
 
 
-def gpu_fused(torch, chunks, metas, offsets, bits, bucket, dt, seed):
-    plan = cgx.Plan(offsets, bits, bucket, dt)
+def gpu_fused(torch, chunks, metas, offsets, bits, bucket, dt, seed, layered=False):
+    """layered: the same plan with its bucket size given layer by layer, which always runs in chunks of 2048 elements."""
+    plan = cgx.LayeredPlan(offsets, bits, np.full(len(bits), bucket, np.int32), dt) if layered else cgx.Plan(offsets, bits, bucket, dt)
     pb, mb = cgx.cgx_qsgd_sizes(cgx.Plan(offsets, bits, bucket, wl.F32))
     dp, dm = device_chunks(torch, chunks, metas)
     packed = torch.full((pb + 64,), 0xA5, dtype=torch.uint8, device="cuda")
     meta = torch.full((mb // 4 + 16,), -7.0, dtype=torch.float32, device="cuda")
-    cgx.cgx_qsgd_dequant_reduce_requantize(dp, dm, plan, seed, packed, meta)
+    fused = cgx.cgx_qsgd_layered_dequant_reduce_requantize if layered else cgx.cgx_qsgd_dequant_reduce_requantize
+    fused(dp, dm, plan, seed, packed, meta)
     torch.cuda.synchronize()
     p, m = packed.cpu().numpy(), meta.cpu().numpy()
     assert (p[pb:] == 0xA5).all() and (m[mb // 4:] == -7.0).all(), "wrote past the reported sizes"
@@ -109,6 +111,9 @@ def full_cycle(torch, oracle, w, W, what=""):
         fp, fm = gpu_fused(torch, chunks, metas, w.offsets, w.bits, w.bucket, w.dt, 99)
         op, om = oracle.qsgd_quantize(ref["sum32"], w.offsets, w.bits, w.bucket, 99, wl.F32)
         assert_same_chunk(fp, fm, op, om, f"{what} fused reduce+requantize")
+        if w.dt == wl.F32:            # short binary32 buffers run in chunks of 1024 elements; here in chunks of 2048
+            fp, fm = gpu_fused(torch, chunks, metas, w.offsets, w.bits, w.bucket, w.dt, 99, layered=True)
+            assert_same_chunk(fp, fm, op, om, f"{what} fused reduce+requantize, a bucket size per layer")
 
 
 @pytest.mark.parametrize("seed", range(24))
