@@ -75,7 +75,7 @@ __device__ __forceinline__ uint64_t join_halves(uint32_t lo, uint32_t hi)
 // there.  (kNormSign: a missing element's level is 0.)
 //
 // The other widths (3, 5, 6, 7): four levels at a time are summed at their places by v_mad_u32_u16, which picks the upper half of
-// the sum, shifts and adds in one instruction of 4.5 cycles where a shift, a minimum and a shift-or took 12; a missing element's
+// the sum, shifts and adds in one instruction of 4.8 cycles where a shift, a minimum and a shift-or took 12; a missing element's
 // level can only reach upwards, into codes that are missing too.  8-bit levels take their minimum two at a time (v_pk_min_u16).
 // Signed codes of these widths are cut as bytes and the bytes joined.  Builds in turn on one box, us: binary16 quantize of 26 M
 // elements, 3 bits 16.0 -> 15.7, 5 bits 16.4 -> 16.1 (8 bits 16.4 -> 16.5); norm-and-sign of 101 M, 3 bits 48.3 -> 45.0, 8 bits

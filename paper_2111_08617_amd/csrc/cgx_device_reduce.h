@@ -31,7 +31,7 @@ __device__ __forceinline__ void signed_bytes_to_float(uint32_t t, float &b0, flo
 }
 
 // Two conversions per instruction: v_cvt_scalef32_pk_f32_fp8 / _fp4 turn two bytes, or the two nibbles of a byte, into floats
-// and multiply them by a power of two, at 4.9 cycles of a SIMD where one v_cvt_f32_ubyte takes 4.7.  Codes are small whole
+// and multiply them by a power of two, at 5.4 cycles of a SIMD where one v_cvt_f32_ubyte takes 4.7.  Codes are small whole
 // numbers, and the subnormals and the first binade of such a format form one linear grid: an E4M3 byte q <= 15 is q / 512, an E2M1
 // nibble q <= 3 is q / 2.  Times 512 (2) that is float(q), exactly.  Builds in turn on one box, us: a 13.7 M share of 8 peers in one
 // fused step (2, 3, 4 and 8 bits) 18.6 -> 17.8, 16.8 M elements of 4 bits 22.3 -> 21.4, of 2 bits 20.6 -> 20.3; the reduce of 34 M at

@@ -144,9 +144,14 @@ __global__ __launch_bounds__(1024) void stream_probe_kernel(const uint4v *__rest
     X(35, "v_mov_b32_dpp %0, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")                                 \
     X(36, "v_min_f32_dpp %0, %1, %0 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf")                             \
     X(37, "v_fma_mix_f32 %0, %1, %2, %0 op_sel:[0,0,0] op_sel_hi:[1,0,0]")                                       \
-    X(38, "v_rcp_f32 %0, %0")
-// four more forms are written out below: one whose result is a register pair, and three short sequences
+    X(38, "v_rcp_f32 %0, %0")                                                                                    \
+    X(39, "v_mad_u32_u16 %0, %1, 4, %0 op_sel:[1,0,0,0]")                                                        \
+    X(40, "v_mad_u32_u16 %0, %1, %3, %0 op_sel:[1,0,0,0]")                                                       \
+    X(41, "v_pk_min_u16 %0, %1, %0")
+// six more forms are written out below: three whose result is a register pair, and three short sequences
 // that decode a code by lookup (a table in LDS; a table in the lanes of a register, twice)
+#define CGX_ISSUE_FORM_SCALED8 "v_cvt_scalef32_pk_f32_fp8 %0:[2], %0, %1 ; v_xor_b32 %0, %0[0], %0[1] (two results, folded by a v_xor_b32)"
+#define CGX_ISSUE_FORM_SCALED4 "v_cvt_scalef32_pk_f32_fp4 %0:[2], %0, %1 ; v_xor_b32 %0, %0[0], %0[1] (the same)"
 #define CGX_ISSUE_FORM_PAIR "v_cvt_pk_f32_fp8 %0:[2], %0 ; v_xor_b32 %0, %0[0], %0[1] (two results, folded by a v_xor_b32)"
 #define CGX_ISSUE_FORM_TABLE \
     "v_lshrrev_b32 t, 7, %0 ; v_and_b32 t, 60, t ; v_add_u32 t, %1, t ; ds_read_b32 t, t ; v_add_f32 %0, t, %0 (the decode of a code by lookup: 16 entries in LDS, %1 the wave's table)"
@@ -155,7 +160,7 @@ __global__ __launch_bounds__(1024) void stream_probe_kernel(const uint4v *__rest
 #define CGX_ISSUE_FORM_LANES16 \
     "v_lshrrev_b32 t, 8, %0 ; v_and_b32 t, 60, t ; ds_bpermute_b32 t, t, %1 ; v_add_f32 %0, t, %0 (the same, 16 lanes)"
 
-constexpr int kIssueForms = 43;
+constexpr int kIssueForms = 48;
 constexpr int kIssueChains = 16;
 
 template <int FORM>
@@ -170,6 +175,24 @@ struct IssueForm;
     };
 CGX_ISSUE_FORMS(CGX_ISSUE_FORM)
 #undef CGX_ISSUE_FORM
+template <>
+struct IssueForm<kIssueForms - 6> {
+    static __device__ __forceinline__ void step(uint32_t &a, uint32_t b, uint32_t, uint32_t, const uint32_t *)
+    {
+        uint64_t pair;
+        asm volatile("v_cvt_scalef32_pk_f32_fp8 %0, %1, %2" : "=v"(pair) : "v"(a), "v"(b));
+        asm volatile("v_xor_b32 %0, %1, %2" : "=v"(a) : "v"(uint32_t(pair)), "v"(uint32_t(pair >> 32)));
+    }
+};
+template <>
+struct IssueForm<kIssueForms - 5> {
+    static __device__ __forceinline__ void step(uint32_t &a, uint32_t b, uint32_t, uint32_t, const uint32_t *)
+    {
+        uint64_t pair;
+        asm volatile("v_cvt_scalef32_pk_f32_fp4 %0, %1, %2" : "=v"(pair) : "v"(a), "v"(b));
+        asm volatile("v_xor_b32 %0, %1, %2" : "=v"(a) : "v"(uint32_t(pair)), "v"(uint32_t(pair >> 32)));
+    }
+};
 template <>
 struct IssueForm<kIssueForms - 4> {
     static __device__ __forceinline__ void step(uint32_t &a, uint32_t, uint32_t, uint32_t, const uint32_t *)
@@ -252,7 +275,8 @@ const char *issue_probe_form(int form)
 #define CGX_ISSUE_NAME(N, TEXT) TEXT,
         CGX_ISSUE_FORMS(CGX_ISSUE_NAME)
 #undef CGX_ISSUE_NAME
-        CGX_ISSUE_FORM_PAIR, CGX_ISSUE_FORM_TABLE, CGX_ISSUE_FORM_LANES, CGX_ISSUE_FORM_LANES16};
+        CGX_ISSUE_FORM_SCALED8, CGX_ISSUE_FORM_SCALED4, CGX_ISSUE_FORM_PAIR, CGX_ISSUE_FORM_TABLE, CGX_ISSUE_FORM_LANES,
+        CGX_ISSUE_FORM_LANES16};
     return form >= 0 && form < kIssueForms ? names[form] : nullptr;
 }
 
