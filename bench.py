@@ -336,8 +336,8 @@ def measure(name, args, extras=True):
         fused_wall = (time.perf_counter() - t0) * 1e3 / args.steps
         fused_kernel_ms = float(np.mean([a.elapsed_time(b) for a, b in fe]))
         fused_alg = alg["dequant_reduce"] - 4 * m + (alg["requantize"] - 4 * m)
-        # the fused kernel is bound by the vector ALUs, not by HBM: 46 vector instructions per element at 4 bit
-        # and W = 8 (stored: profiles/alu_counters_rocprofv3.md, SQ_INSTS_VALU per wave / elements per wave)
+        # the fused kernel is bound by the vector ALUs, not by HBM: 38 vector instructions per element on the 1.3 B
+        # share, W = 8 (stored: profiles/alu_counters_rocprofv3.md, 2434 per wave of 64 lanes / 4096 elements per wave)
         # against 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 39.3 T lane-instructions/s
         alu_peak = 256 * 4 * 16 * 2.4e9
         fused = {"step": "cgx_quantize(full buffer) + cgx_dequant_reduce_requantize(W chunks)",
@@ -345,8 +345,8 @@ def measure(name, args, extras=True):
                  "dequant_reduce_requantize": dict(rate(fused_alg, fused_kernel_ms),
                                                    raw_gradient_GBps=round(4 * m / fused_kernel_ms / 1e6, 1),
                                                    bound="alu",
-                                                   alu_frac_at_46_instructions_per_element=round(
-                                                       46.0 * m / (fused_kernel_ms * 1e-3) / alu_peak, 4))}
+                                                   alu_frac_at_38_instructions_per_element=round(
+                                                       38.0 * m / (fused_kernel_ms * 1e-3) / alu_peak, 4))}
 
     # the remaining calls of a rank's scatter-reduce / all-gather: decompression of a gathered chunk into the
     # storage type, and the reduce with the rank's own contribution still uncompressed

@@ -42,8 +42,9 @@ int cgx_plan_tiles(int64_t n, int32_t L, const int64_t *layer_offsets, const uin
 /*
  * The same table for kernels whose chunk is chunk_elements (1024 or 2048; CGX_ERR_SIZE otherwise).
  * cgx_plan_tiles gives the table of 2048-element chunks, which the reduce, fused and statistics
- * kernels and the binary16 quantizer walk; cgx_quantize on binary32 input, cgx_requantize and
- * cgx_dequantize to binary32 walk the table of 1024-element chunks, but a call that quantizes takes 2048 where a
+ * kernels and the binary16 quantizer walk; cgx_quantize on binary32 input, cgx_requantize,
+ * cgx_dequantize to binary32 and the fused call on binary32 buffers of up to 4 M elements (if that table exists or
+ * fits the cache) walk the table of 1024-element chunks, but a call that quantizes takes 2048 where a
  * bucket has more than 1024 elements, or where chunks of 1024 would spend a quarter more lanes on the plan's bucket
  * sizes (352, 384, 544 ... 672 and 768).  (In the table of 1024-element chunks buckets of 2048 are one-bucket
  * tiles of kind 4, like those of 4096 and 8192.)
@@ -122,7 +123,8 @@ int cgx_issue_probe(int32_t form, int32_t blocks, int32_t iterations, void *out,
  * CGX_CHUNKS_PER_TILE regroups the binary64 additions of the per-layer errors:
  *   CGX_CHUNKS_PER_TILE=k   every vectorised tile holds up to k chunks (default: chosen per call)
  *   CGX_MAX_BLOCKS=k        persistent grids of at most k blocks (default: one wave per tile)
- *   CGX_QUANTIZE_GROUPS=2|4 chunk size of the quantize calls: 1024 or 2048 elements (default: 2048 for
+ *   CGX_QUANTIZE_GROUPS=2|4 chunk size of the quantize calls, and of the fused call on binary32 buffers of up to
+ *                           4 M elements, which follows it: 1024 or 2048 elements (default: 2048 for
  *                           binary16; for binary32 1024 but for the sizes named at cgx_plan_tiles_chunk).
  *                           With 2, buckets of more than 1024 elements keep chunks of 2048; the other
  *                           layers of such a call, if every layer has its own size, take 1024 on binary32

@@ -129,7 +129,8 @@ enum CallKind { kQuantizeCall, kFusedCall, kOtherCall };
 // elements (4 KB per wave and pass: measured, a streaming kernel sustains about a tenth more with 4 KB
 // per wave than with 8 KB, and the quantizer follows it: 0.74 -> 0.78 of the HBM peak on 1.3 G
 // elements); on binary16 a chunk of 2048 elements is 4 KB already.  The reduce, fused and statistics
-// kernels take 2048 (a peer's codes of a chunk then fill a whole load instruction at 4 bits).
+// kernels take 2048 (a peer's codes of a chunk then fill a whole load instruction at 4 bits), but a decompression to binary32
+// (reduce_impl) and the fused call on short binary32 buffers (fused_impl) 1024.
 // A call with a bucket of more than 1024 elements takes the quantizer of 2048-element chunks also on binary32: such a
 // bucket fits its chunk or a block of its waves (cgx_wide.hip).  The whole call takes it, one launch for all sizes
 // up to 2048 instead of two (ResNet-50 with sizes by layer length, 128 / 512 / 2048: 36 us of quantizing in two launches
@@ -511,7 +512,7 @@ int fused_impl(int scheme, const void *const *packed, const void *const *meta, i
     // wave slots empty and keep the others twice as long.  us with chunks of 2048 and of 1024: 8 peers, 4 bits, buckets of 512, 2.1 M
     // elements 8.1 and 7.2, 4.2 M 10.0 and 9.0; 7 peers, 2 bits, buckets of 992, 2.1 M 8.8 and 7.6.  Beyond, it depends on widths and
     // sizes: 5.2 M, 7 peers, 992, 2 and 8 bits 10.8 and 11.1, 12.0 and 12.4, 4 bits 11.7 and 11.4; 8 peers of 6.3 M at 4 bits 12.0 and
-    // 11.0, 10 M 14.6 and 15.4, 67 M 75.0 and 81.5 (the scales and meta that a wave pays per chunk).
+    // 11.0, 16 peers of 6.3 M in buckets of 96 23.1 and 18.7, 10 M 14.6 and 15.4, 67 M 75.0 and 81.5 (the scales and meta that a wave pays per chunk).
     // The table is the binary32 quantizer's, and a bucket size
     // that it lays over chunks of 2048 stays with them here (binary16 chunks too: they would need a table of their own).
     // The plan's tables stay those of chunks of 2048: they are looked up, built and renewed whichever this call walks, so that a

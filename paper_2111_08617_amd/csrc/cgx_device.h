@@ -11,7 +11,7 @@
 // of 8 consecutive elements, all of the same bucket (a bucket of B elements
 // spans B / (8 kGroups) neighbouring lanes).  kGroups is fixed per translation unit
 // (CGX_GROUPS: 4 unless the build says otherwise, i.e. chunks of 2048 elements; the
-// binary32 quantizer is also built with 2), so
+// quantize, reduce and fused kernels are also built with 2), so
 //   - the bucket minimum / maximum is a lane-local reduction over 32 values
 //     followed by a log2(B/32)-step butterfly across lanes (DPP within a row of
 //     16 lanes, ds_swizzle across rows, a permute across the two halves);

@@ -78,7 +78,8 @@ __device__ __forceinline__ uint64_t join_halves(uint32_t lo, uint32_t hi)
 // the sum, shifts and adds in one instruction of 4.8 cycles where a shift, a minimum and a shift-or took 12; a missing element's
 // level can only reach upwards, into codes that are missing too.  8-bit levels take their minimum two at a time (v_pk_min_u16).
 // Signed codes of these widths are cut as bytes and the bytes joined.  Builds in turn on one box, us: binary16 quantize of 26 M
-// elements, 3 bits 16.0 -> 15.7, 5 bits 16.4 -> 16.1 (8 bits 16.4 -> 16.5); norm-and-sign of 101 M, 3 bits 48.3 -> 45.0, 8 bits
+// elements, 3 bits 15.7 -> 15.4, 5 bits 16.3 -> 15.8, 8 bits 15.4 -> 15.3 (355 M, 128 to a bucket, both builds on the same buffers: 8 bits
+// 168.3 and 168.4, 5 bits 171.5 -> 168.7; buckets of 96, 8 bits, 202.8 -> 196.7); norm-and-sign of 101 M, 3 bits 48.3 -> 45.0, 8 bits
 // 51.5 -> 49.9; fused step of 2 peers, 17 M elements, 3 bits 14.0 -> 13.7, 8 bits 14.3 -> 14.2, norm-and-sign 14.6 -> 13.9.
 //
 // Measured with the draws of kDrawsQuad below, builds in turn on one box, us: binary16 quantize of 355 M elements 155.0 -> 144.0,
@@ -94,7 +95,8 @@ __device__ __forceinline__ uint32_t first_pair(int64_t first, int at) { return u
 // half of a generator word; then its 8 draws are the 16-bit halves 1..8 of words pair0 .. pair0 + 4 instead of halves
 // 0..7 of words pair0 .. pair0 + 3.  DRAWS (Draws, cgx_kernels.h; the host picks the instantiation): kDrawsOdd alone has
 // the fifth word and the selection, taken by the tiles that do start on odd elements (20 M ragged binary16 elements in buckets of
-// 160, fused, 4 peers: 25.0 -> 24.25 us, first_pair's share in it included), and kDrawsQuad knows that pair0 is a multiple of 4: no carry leaves its two lowest bits,
+// 160, fused, 4 peers: 25.0 -> 24.25 us, first_pair's share in it included; where all tiles start odd the branch costs a large
+// binary16 quantize up to half a per cent, 355 M elements of 8 bits 241.1 -> 242.3), and kDrawsQuad knows that pair0 is a multiple of 4: no carry leaves its two lowest bits,
 // so the words of its four pairs differ in them alone until the first multiplication: 3 instructions fewer of 76 (by itself, us:
 // binary16 quantize of 372 M elements 159 -> 155, fused step of 14.7 M elements and 8 peers 20.65 -> 20.4).
 template <int SCHEME, int BITS, int DRAWS>

@@ -34,8 +34,10 @@ __device__ __forceinline__ void signed_bytes_to_float(uint32_t t, float &b0, flo
 // and multiply them by a power of two, at 5.4 cycles of a SIMD where one v_cvt_f32_ubyte takes 4.7.  Codes are small whole
 // numbers, and the subnormals and the first binade of such a format form one linear grid: an E4M3 byte q <= 15 is q / 512, an E2M1
 // nibble q <= 3 is q / 2.  Times 512 (2) that is float(q), exactly.  Builds in turn on one box, us: a 13.7 M share of 8 peers in one
-// fused step (2, 3, 4 and 8 bits) 18.6 -> 17.8, 16.8 M elements of 4 bits 22.3 -> 21.4, of 2 bits 20.6 -> 20.3; the reduce of 34 M at
-// 2 bits 61.0 -> 59.7, of the ResNet-50 plan with its requantize 54.1 -> 53.9.  Not taken where it measured slower: 3-bit
+// fused step (2, 3, 4 and 8 bits) 20.1 -> 19.4, 16.8 M elements of 4 bits 22.7 -> 21.7, the 1.3 B share 187.2 -> 185.4; the
+// reduce of 34 M at 2 bits 63.1 -> 60.9, at 4 bits 72.2 -> 70.5.  Nibbles against bytes for the 2-bit codes, everything else alike: that
+// reduce 60.9 and 63.5, that share 19.4 and 19.7, but fused steps of 2 bits alone 20.9 and 20.5 (16.8 M; 67 M 64.8 and 63.6).
+// Not taken where it measured slower: 3-bit
 // codes spread to bytes (fused, 8 peers, 23.7 -> 24.8), signed 2-bit codes as nibbles of sign and magnitude (21.8 -> 22.6), 2-bit
 // codes of a single peer, bound by what they write (67 M elements in 4 shares 47.5 -> 47.9), and 2-bit codes of runs, whose upper
 // bits have to be cleared first (fused, 8 peers, buckets of 992, 24.8 byte by byte, 26.5 as nibbles).

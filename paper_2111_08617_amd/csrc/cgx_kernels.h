@@ -25,7 +25,7 @@ struct LaunchConfig {
     int chunks_per_tile = 0;   // fast-tile length in chunks of kChunk elements; 0: chosen per call
     int max_blocks = 0;        // 0: one wave per tile; >0: persistent grid of at most this many blocks
     int via_lds = 1;           // quantize and squared errors: fetch aligned chunks of the buffer through LDS
-    int quantize_groups = 0;   // 2 or 4: chunk size of every quantize call; 0: chosen per call
+    int quantize_groups = 0;   // 2 or 4: chunk size of every quantize call, and of the fused calls that follow it; 0: chosen per call
     long keep_sums_max_bytes = 128l << 20;   // reduce: results up to this size are kept in the memory-side cache
     int dequantize_through = 1;              // cgx_dequantize: stores written through at system scope
     int reduce_groups = 0;                   // 2 or 4: chunk size of every reduce call (0: chosen per call)
@@ -48,7 +48,7 @@ hipError_t launch_quantize_g2(int scheme, const void *grad, int dt, const Tile *
 hipError_t launch_quantize_g4(int scheme, const void *grad, int dt, const Tile *tiles, int64_t n_tiles, int draws,
                               bool through_lds, int32_t bucket, uint64_t seed, void *packed, void *meta,
                               const LaunchConfig &cfg, hipStream_t stream);
-// Chunk size of every other kernel (reduce, fused, statistics).
+// Chunk size of the other kernels (reduce and fused: where nothing else is chosen per call; statistics).
 constexpr int kDefaultChunk = chunk_of(4);
 
 // How a reduce writes its result (see flush_stage_to_elements in cgx_device.h).
